@@ -151,7 +151,7 @@ int apo_analyze_batch_dev(apo_ctx *ctx, const uint64_t *d_tokens, const uint64_t
                           uint32_t num_windows, uint32_t min_len, apo_candidate *d_out,
                           uint64_t out_cap, uint64_t *h_out_offsets, void *hip_stream);
 
-/* Batches are split into `lanes` (1..4, default 3) groups of consecutive
+/* Batches with a window of more than 8192 tokens are split into `lanes` (1..4, default 3) groups of consecutive
  * windows with about equal token counts, analysed concurrently on separate
  * streams, workspaces and host threads (lane 0 uses the caller's stream),
  * each lane host-driven (launches sized from device counts read between
@@ -204,17 +204,19 @@ int apo_interval_counts_dev(apo_ctx *ctx, const uint32_t *d_len, const uint32_t 
                             uint32_t m, uint32_t *d_next, uint32_t *d_count, uint32_t *d_tmp, void *hip_stream);
 
 /* Per-stage device times of the last analysis (ms): token ranks, suffix
- * array, LCP, candidates, candidate sort, selection, output.  Returns the
- * number of stages written (<= nstages). */
+ * array, LCP, candidates, candidate sort, selection, output.  For a batch whose
+ * windows are all short (at most 8192 tokens, one workgroup each) the longest
+ * any window took in that stage.  Returns the number of stages written
+ * (<= nstages). */
 int apo_last_stage_ms(apo_ctx *ctx, double *stage_ms, int nstages);
 
 /* Counters of the last analysis, in this order: rounds of doubling (the
  * first-token sort included), candidates generated, candidates after dedup,
  * selection rounds, accepted occurrences, rows, sum over rounds of active
  * suffixes (the first-token sort counts every suffix), distinct tokens (for
- * a batch: summed over its windows, except that the windows with more than
- * 4096 distinct tokens, ranked through one shared table, count their union
- * once), 1 if the selection finished with the sequential completion (else
+ * a batch: summed over its windows, except that in a batch with a window of
+ * more than 8192 tokens the windows with more than 4096 distinct tokens, ranked
+ * through one shared table, count their union once), 1 if the selection finished with the sequential completion (else
  * 0), the candidates the exact prefix walk decided before the rounds (0: none),
  * and the windows whose first two doubling rounds were taken window by
  * window from ranks of their adjacent token pairs (host-driven batches whose
@@ -245,8 +247,10 @@ int apo_inject_device_error(apo_ctx *ctx, int after_syncs);
  * (default) windows of at most 2^17 tokens in a batch, and single windows of
  * at most 2^15 tokens, are decided by one wavefront per window walking the
  * window's candidates in priority order over an on-chip bitmap; longer
- * windows use the round-based evaluation.  on = 0 sends every analysis
- * through the rounds.  Results are identical either way.  APO_EINVAL
+ * windows use the round-based evaluation.  Windows of at most 8192 tokens
+ * (alone, or in a batch of such windows) go through all stages in one
+ * workgroup each.  on = 0 sends every analysis stage by stage through the
+ * rounds.  Results are identical either way.  APO_EINVAL
  * unless on is 0 or 1. */
 int apo_set_window_greedy(apo_ctx *ctx, int on);
 

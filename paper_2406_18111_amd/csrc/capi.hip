@@ -3,6 +3,7 @@
 #include "apo.h"
 #include "pipeline.h"
 #include "stages.h"
+#include "winfused.h"
 #include <algorithm>
 #include <atomic>
 #include <cstdio>
@@ -155,6 +156,12 @@ struct apo_ctx {
     uint32_t W, rows;
   };
   std::vector<LaneOut> louts;
+  // pinned memory of the one-workgroup analyses: what they report, and the
+  // tokens, rows and occurrences of host callers
+  apo::FusedInfo *finfo = nullptr;
+  uint64_t *ftok = nullptr;
+  apo_candidate *frows = nullptr;
+  apo_occurrence *focc = nullptr;
 };
 
 namespace apo {
@@ -221,6 +228,7 @@ extern "C" int apo_destroy(apo_ctx *ctx) {
     (void)hipStreamDestroy(st);
   }
   if (ctx->lane_ready) (void)hipEventDestroy(ctx->lane_ready);
+  if (ctx->finfo) (void)hipHostFree(ctx->finfo);
   (void)hipStreamDestroy(ctx->stream);
   delete ctx;
   return APO_OK;
@@ -271,12 +279,52 @@ static int run_ctx(apo_ctx *c, const void *d_tok, int bits, uint32_t n, uint32_t
   c->ws.sel_cap = c->sel_cap;
   c->ws.sel_prefix = c->sel_prefix;
   c->ws.win_greedy = c->win_greedy;
+  c->ws.fuse_one = false;
   const uint64_t off[2] = {0, n};
   int tl, db;
   c->tune.pick(n, tl, db);
   c->ws.eng.set_params(tl, db);
   rc = run_pipeline(c->ws, d_tok, bits, n, off, 1, min_len, stop, s, c->info);
   return map_rc(rc);
+}
+
+// Whether a lone window of n tokens is analysed by one workgroup.  Kernel
+// timing and the injected errors are those of the stage-by-stage analysis.
+static bool fused_one(const apo_ctx *c, uint32_t n) {
+  return n <= kFusedMax && c->win_greedy && c->ws.ktag == KT_NONE && c->ws.fail_after < 0;
+}
+
+// That analysis on stream s, through the pinned report; tokens and outputs in
+// device or pinned host memory.  Fills ctx->info; outputs are written only if
+// both fit.
+static int run_fused(apo_ctx *c, const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows,
+                     uint32_t row_cap, void *occ, uint32_t occ_cap, hipStream_t s) {
+  const int rc = ctx_ensure(c, c->ws, n, 1);
+  if (rc) return map_rc(rc);
+  fused_window(tok, bits, n, min_len, rows, row_cap, occ, occ_cap, c->finfo, s);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+    (void)hipGetLastError();
+    return APO_EDEVICE;
+  }
+  fused_read(*c->finfo, n, c->ws, c->info);
+  return APO_OK;
+}
+
+static int fused_buffers(apo_ctx *c) {
+  if (c->finfo) return APO_OK;
+  const size_t info = (sizeof(FusedInfo) + 255) & ~(size_t)255, tok = (size_t)kFusedMax * 8,
+               out = (size_t)kFusedMax * sizeof(apo_candidate);
+  void *p = nullptr;
+  if (hipHostMalloc(&p, info + tok + 2 * out, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return APO_EDEVICE;
+  }
+  char *m = static_cast<char *>(p);
+  c->finfo = reinterpret_cast<FusedInfo *>(m);
+  c->ftok = reinterpret_cast<uint64_t *>(m + info);
+  c->frows = reinterpret_cast<apo_candidate *>(m + info + tok);
+  c->focc = reinterpret_cast<apo_occurrence *>(m + info + tok + out);
+  return APO_OK;
 }
 
 static int analyze_host(apo_ctx *ctx, const void *tokens, int bits, uint32_t n, uint32_t min_len,
@@ -289,9 +337,25 @@ static int analyze_host(apo_ctx *ctx, const void *tokens, int bits, uint32_t n, 
   if (occ_n) *occ_n = 0;
   ctx->info = RunInfo{};
   if (n < 2) return APO_OK;
+  const size_t bytes = (size_t)n * (bits / 8);
+  if (fused_one(ctx, n)) {
+    // the kernel reads the tokens from pinned memory and writes its rows there
+    int rc = fused_buffers(ctx);
+    if (rc) return rc;
+    memcpy(ctx->ftok, tokens, bytes);
+    rc = run_fused(ctx, ctx->ftok, bits, n, min_len, ctx->frows, out_cap, occ ? ctx->focc : nullptr, occ_cap,
+                   ctx->stream);
+    if (rc) return rc;
+    const uint32_t rows = ctx->info.rows, acc = ctx->info.accepted;
+    *out_n = rows;
+    if (occ_n) *occ_n = acc;
+    if (rows > out_cap || (occ && acc > occ_cap)) return APO_ERANGE;
+    if (rows) memcpy(out, ctx->frows, (size_t)rows * sizeof(apo_candidate));
+    if (occ && acc) memcpy(occ, ctx->focc, (size_t)acc * sizeof(apo_occurrence));
+    return APO_OK;
+  }
   int rc = ctx_ensure(ctx, ctx->ws, n, 1);
   if (rc) return map_rc(rc);
-  const size_t bytes = (size_t)n * (bits / 8);
   if (hipMemcpyAsync(ctx->ws.tok64, tokens, bytes, hipMemcpyHostToDevice, ctx->stream) != hipSuccess) {
     (void)hipGetLastError();
     return APO_EDEVICE;
@@ -336,6 +400,14 @@ extern "C" int apo_analyze_window_dev(apo_ctx *ctx, const void *d_tokens, int to
   ctx->info = RunInfo{};
   if (n < 2) return APO_OK;
   hipStream_t s = pick_stream(ctx, stream);
+  if (fused_one(ctx, n)) {
+    int rc = fused_buffers(ctx);
+    if (!rc) rc = run_fused(ctx, d_tokens, token_bits, n, min_len, d_out, out_cap, d_occ, occ_cap, s);
+    if (rc) return rc;
+    *h_out_n = ctx->info.rows;
+    if (h_occ_n) *h_occ_n = ctx->info.accepted;
+    return ctx->info.rows > out_cap || (d_occ && ctx->info.accepted > occ_cap) ? APO_ERANGE : APO_OK;
+  }
   int rc = run_ctx(ctx, d_tokens, token_bits, n, min_len, Stop::FULL, s);
   if (rc) return rc;
   const uint32_t rows = ctx->info.rows, acc = ctx->info.accepted;
@@ -498,6 +570,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
     ln.ws->sel_cap = ctx->sel_cap;
     ln.ws->sel_prefix = ctx->sel_prefix;
     ln.ws->win_greedy = ctx->win_greedy;
+    ln.ws->fuse_one = true;
     if (ln.st != s && hipStreamWaitEvent(ln.st, ctx->lane_ready, 0) != hipSuccess) return APO_EDEVICE;
     lanes.push_back(std::move(ln));
   }
@@ -629,6 +702,13 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
 static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off, uint32_t W, uint32_t min_len,
                         hipStream_t s, uint64_t total) {
   int L = std::min<int>(ctx->lanes, (int)(W / 2));
+  // a batch of short windows is one launch with a workgroup per window, which
+  // lanes have nothing to add to
+  uint64_t longest = 0;
+  for (uint32_t w = 0; w < W; w++) longest = std::max<uint64_t>(longest, off[w + 1] - off[w]);
+  if (longest <= kFusedMax && ctx->win_greedy && ctx->ws.ktag == KT_NONE &&
+      (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx)))
+    L = 1;
   if (ctx->budget && L >= 2) {
     // fewer lanes when their workspaces would not fit the budget; lane
     // workspaces left idle by the smaller count give their memory back
@@ -660,6 +740,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   w.sel_prefix = ctx->sel_prefix;
   if (w.win_greedy != ctx->win_greedy) ctx->gc.reset();  // a captured sequence holds the other selection path
   w.win_greedy = ctx->win_greedy;
+  w.fuse_one = true;
   // Timed kernel launches are bracketed by events on the stream, which is
   // only reliable outside captured graphs: profiling runs the same sync-free
   // sequence without capture.
@@ -1041,6 +1122,7 @@ extern "C" int apo_tune(apo_ctx *ctx, const void *d_tokens, int token_bits, uint
   reps = std::max(1, std::min(reps, 50));
   int rc = ctx_ensure(ctx, ctx->ws, n, 1);
   if (rc) return map_rc(rc);
+  ctx->ws.fuse_one = false;  // the parameters are those of the stage-by-stage analysis
   const uint64_t off[2] = {0, n};
   double best = 1e30;
   int bt = kDefaultTileLog, bd = kDefaultDigitBits;
@@ -1223,6 +1305,7 @@ static void slot_loop(Server *S, Slot *sl) {
         int tl, db;
         S->tune.pick(total, tl, db);
         sl->ws.eng.set_params(tl, db);
+        sl->ws.fuse_one = true;
         rc = map_rc(run_pipeline(sl->ws, sl->ws.tok64, 64, total, off.data(), W, batch[0]->min_len, Stop::FULL,
                                  sl->stream, info));
       }

@@ -6,6 +6,7 @@
 #include "apo.h"
 #include "pipeline.h"
 #include "stages.h"
+#include "winfused.h"
 #include <cstdio>
 #include <mutex>
 
@@ -23,6 +24,7 @@ struct NoAllocDevice {
   int rc = APO_EDEVICE;     // outcome of the set-up on this device
   void *ptr = nullptr;      // this device's copy of `scratch`
   Workspace ws;             // laid out over ptr
+  FusedInfo *finfo = nullptr;  // pinned report of the one-workgroup analysis
   std::mutex mu;            // one analysis at a time per device
 };
 static NoAllocDevice g_noalloc[kNoAllocDevices];
@@ -49,6 +51,10 @@ int noalloc_setup(int device) {
       D.rc = rc == -2 ? APO_ENOMEM : APO_EDEVICE;
       return;
     }
+    if (hipHostMalloc((void **)&D.finfo, sizeof(FusedInfo), hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      D.finfo = nullptr;  // short windows then take the stage-by-stage analysis too
+    }
     D.rc = APO_OK;
   });
   return D.rc;
@@ -63,6 +69,17 @@ int noalloc_run(int device, hipStream_t s, int tile_log, int digit_bits, const v
   if (n > APO_NOALLOC_MAX_N) return APO_ENOMEM;
   std::lock_guard<std::mutex> lk(D.mu);
   Workspace &w = D.ws;
+  if (D.finfo && n <= kFusedMax) {
+    fused_window(d_tok, bits, n, min_len, d_out, out_cap, d_occ, occ_cap, D.finfo, s);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+      (void)hipGetLastError();
+      return APO_EDEVICE;
+    }
+    fused_read(*D.finfo, n, w, info);
+    *h_out_n = info.rows;
+    if (h_occ_n) *h_occ_n = info.accepted;
+    return info.rows > out_cap || (d_occ && info.accepted > occ_cap) ? APO_ERANGE : APO_OK;
+  }
   // The array keeps the previous call's contents: clear what the stages
   // expect to find zeroed (device counters, the sort engine's histograms and
   // counters), with fill kernels.

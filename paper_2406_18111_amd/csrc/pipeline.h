@@ -31,6 +31,7 @@ enum Cnt {
   CNT_PNEXT = 21,  // batches: next window for the per-window pair ranks
   CNT_PFLAG = 22,  // batches: windows whose pairs the per-window ranking left alone
   CNT_A1 = 23,     // batches: the first doubling round's active count, from the pair ranking
+  CNT_STAGE = 24,  // batches of short windows: longest stage times (kStages words, 10 ns)
   CNT_COUNT = 32
 };
 
@@ -118,6 +119,7 @@ struct Workspace {
   int sel_prefix = -1;             // exact prefix walk before the rounds: -1 automatic, 0 never, k > 0 k candidates
   uint32_t pair_w = 0;             // windows of the run when it ranked their token pairs (else 0)
   int fail_after = -1;             // test hook: host syncs before one reports a device error (-1: never)
+  bool fuse_one = false;           // a lone short window takes the one-workgroup analysis in run_pipeline too
   bool win_greedy = true;          // one-wavefront-per-window greedy where windows are short enough
 
   // device bytes a workspace of capacity (N, W) holds (exact)

@@ -1,6 +1,7 @@
 // Stage sequence of one analysis (Section 4.2, Algorithm 2), host side.
 #include "pipeline.h"
 #include "stages.h"
+#include "winfused.h"
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -298,6 +299,22 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   const bool host = mode == Mode::HOST;
   const bool stamps = mode != Mode::CAPTURE;
   uint32_t *dc = w.dcnt;
+  uint64_t maxwin = 0;
+  for (uint32_t k = 0; k < W; k++) maxwin = std::max<uint64_t>(maxwin, h_off[k + 1] - h_off[k]);
+  // Short windows: the whole analysis of each by one workgroup.
+  if (stop == Stop::FULL && (W > 1 || w.fuse_one) && maxwin <= kFusedMax && bits == 64 && w.win_greedy &&
+      w.ktag == KT_NONE && w.fail_after < 0) {
+    if (mode != Mode::CAPTURE)
+      if ((rc = upload_windows(w, h_off, W, s, true))) return rc;
+    w.pair_w = W > 1 ? W : 0;
+    w.kev_n = 0;
+    E.reset_counters(s);
+    fused_batch(w, d_tok, W, (uint32_t)maxwin, min_len, s);
+    if (mode == Mode::CAPTURE) return 0;
+    rc = finish_run(w, N, N, 1, info, s, false);
+    for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;
+    return rc;
+  }
   stamp(w, 0, s, stamps);
   if (mode != Mode::CAPTURE)  // a captured sequence expects d_off (and the order) to be uploaded already
     if ((rc = upload_windows(w, h_off, W, s, !host))) return rc;
@@ -310,8 +327,6 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     wend = w.wend;
     wid = w.wid;
   }
-  uint64_t maxwin = 0;
-  for (uint32_t k = 0; k < W; k++) maxwin = std::max<uint64_t>(maxwin, h_off[k + 1] - h_off[k]);
   fill_u32(dc, CNT_RANGE, 0, s);
   fill_u32(dc + CNT_NDSUM, 8, 0, s);
   fill_u32(dc + CNT_SNAPS, 1, 0, s);
