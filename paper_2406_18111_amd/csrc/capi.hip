@@ -301,7 +301,7 @@ static int run_fused(apo_ctx *c, const void *tok, int bits, uint32_t n, uint32_t
                      uint32_t row_cap, void *occ, uint32_t occ_cap, hipStream_t s) {
   const int rc = ctx_ensure(c, c->ws, n, 1);
   if (rc) return map_rc(rc);
-  fused_window(tok, bits, n, min_len, rows, row_cap, occ, occ_cap, c->finfo, s);
+  fused_window(tok, bits, n, min_len, rows, row_cap, occ, occ_cap, c->ws.crec, c->finfo, s);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     (void)hipGetLastError();
     return APO_EDEVICE;

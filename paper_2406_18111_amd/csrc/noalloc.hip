@@ -70,7 +70,7 @@ int noalloc_run(int device, hipStream_t s, int tile_log, int digit_bits, const v
   std::lock_guard<std::mutex> lk(D.mu);
   Workspace &w = D.ws;
   if (D.finfo && n <= kFusedMax) {
-    fused_window(d_tok, bits, n, min_len, d_out, out_cap, d_occ, occ_cap, D.finfo, s);
+    fused_window(d_tok, bits, n, min_len, d_out, out_cap, d_occ, occ_cap, w.crec, D.finfo, s);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
       (void)hipGetLastError();
       return APO_EDEVICE;

@@ -18,9 +18,10 @@ struct FusedInfo {
 
 // One window of n tokens (2 <= n <= kFusedMax, `bits` 32 or 64; device memory
 // or pinned host memory).  Rows and occurrences are written only when both
-// fit (row_cap; occ_cap unless occ is null); `info` always is.
+// fit (row_cap; occ_cap unless occ is null); `info` always is.  spill: device
+// scratch of 16 bytes per token.
 void fused_window(const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows, uint32_t row_cap, void *occ,
-                  uint32_t occ_cap, FusedInfo *info, hipStream_t s);
+                  uint32_t occ_cap, void *spill, FusedInfo *info, hipStream_t s);
 
 // Copies what `info` reports into the run's info and the host mirrors of the
 // per-round counts.

@@ -6,11 +6,12 @@
 // and 7 host synchronisations around a few microseconds of work each.  Here it
 // is one launch: the window's tokens are read once and its rows written once,
 // and the steps in between are separated by workgroup barriers.  Measured on
-// MI355X, whole calls: 250 tokens 753 -> 57 us, 4096 tokens 913 -> 211 us, 5000
-// tokens with occurrences 1165 -> 261 us, a batch of 64 windows of 250 to 5000
-// tokens 3973 -> 391 us.  What bounds it now is the issue rate and LDS rate of
-// one compute unit (4096 tokens: suffix sort 72 us of 162, the candidates, their
-// sort and the greedy 20 to 30 us each).
+// MI355X, whole calls: 250 tokens 748 -> 48 us, 4096 tokens 976 -> 190 us, 5000
+// tokens with occurrences 1191 -> 227 us, a batch of 64 windows of 250 to 5000
+// tokens 4.0 ms -> 329 us.  What bounds it now is the issue rate of one compute
+// unit (64 lanes per cycle): 4096 tokens take 138 us of kernel time, the token
+// ranks 11, the suffix sort 55, LCP 9, candidates 12, their sort 24, the greedy
+// 25.  A first form, radix passes over every suffix in every round, took 162.
 #include "winfused.h"
 #include "device_util.h"
 #include "stages.h"
@@ -35,6 +36,16 @@ __device__ __forceinline__ uint32_t lane_incl_sum(uint32_t v) {
   v += dpp0<0x143, 0xc>(v);
   return v;
 }
+// Maximum over the lanes, in lane 63.
+__device__ __forceinline__ uint32_t lane_max(uint32_t v) {
+  v = max(v, dpp0<0x111, 0xf>(v));
+  v = max(v, dpp0<0x112, 0xf>(v));
+  v = max(v, dpp0<0x114, 0xf>(v));
+  v = max(v, dpp0<0x118, 0xf>(v));
+  v = max(v, dpp0<0x142, 0xa>(v));
+  v = max(v, dpp0<0x143, 0xc>(v));
+  return v;
+}
 // Value of the lane before (lane 0: 0).
 __device__ __forceinline__ uint32_t lane_prev(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, false);
@@ -44,87 +55,212 @@ __device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_A
 
 constexpr uint32_t kOwnRanks = 4096;     // most distinct values the stage-by-stage batch ranks per window
 constexpr int kFusedRounds = 15;         // doubling rounds of a window of up to kFusedMax tokens
-static_assert((1u << (kFusedRounds - 2)) >= kFusedMax, "round r groups by 2^r tokens");
+static_assert((1u << (kFusedRounds - 2)) >= kFusedMax, "the last round leaves nothing grouped");
+constexpr int kPosBits = 13;             // a suffix's position in its sort key
+static_assert((1u << kPosBits) >= kFusedMax, "positions");
+constexpr uint32_t kPackMost = 16;       // tokens in a sort key
 constexpr int kMaxDigit = 7;             // radix digit bits
 constexpr int kDigits = 1 << kMaxDigit;  // counter stride per wavefront
 
-// Stable positions of m items by one digit.  Item i of a lane is number
-// wave * 64 * ipt + 64 * i + lane; pos[i] receives its place in the digit's
-// order.  Each wavefront counts its items digit by digit (lanes of equal digit
-// found by ballots), then adds up the digits below and the wavefronts before
-// it.  One barrier inside; the caller puts one after its stores.
-template <int NT, int MAXI, int DB>
-__device__ __forceinline__ void digit_places(const uint32_t (&dg)[MAXI], int ipt, uint32_t m, uint16_t *cnt,
-                                             uint32_t (&pos)[MAXI]) {
+// The wavefront's number as a scalar, so that branches on it are scalar too.
+__device__ __forceinline__ uint32_t wave_id() {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+// The first `c` lanes (all from 64 on).
+__device__ __forceinline__ uint64_t first_lanes(uint32_t c) { return c >= 64 ? ~0ull : (1ull << c) - 1ull; }
+
+// Bits of a mask below the calling lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// One stable pass of a radix sort of m items in LDS, in place, by the digit
+// digit(item) < 2^kMaxDigit.  Wavefront w holds items [w * 64 * ipt, ...).  It
+// ranks its items digit by digit, 64 at a time (lanes of equal digit found by
+// one ballot per bit, running counts in its row of cnt), and parks each rank
+// beside the item; the digit's first place for the wavefront follows from all
+// rows; then every item is read, and after a barrier written to its place.
+// Only the last step, which holds MAXI items per lane in registers, is unrolled;
+// with the whole pass unrolled the kernel took 97 to 128 registers instead of 79
+// to 95, in the same time.
+template <int NT, int MAXI, class T, class Digit, class Park, class Parked>
+__device__ __forceinline__ void radix_pass(T *it, uint32_t m, int ipt, uint16_t *cnt, uint16_t *row0, Digit digit,
+                                           Park park, Parked parked) {
   constexpr int NW = NT / 64;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t below = (1ull << lane) - 1ull;
-  uint16_t *my = cnt + wv * kDigits;
-#pragma unroll
-  for (int d = 0; d < (1 << DB); d += 64) my[d + lane] = 0;
+  const uint32_t lane = threadIdx.x & 63, wv = wave_id(), base = wv * 64 * ipt;
+  uint16_t *my = cnt + wv * kDigits, *row = row0 + wv * kDigits;
+  my[lane] = 0;
+  my[64 + lane] = 0;
   wave_order();
-  const uint32_t base = (uint32_t)(wv * 64 * ipt);
+#pragma unroll 1
+  for (uint32_t q0 = base; q0 < base + 64 * ipt && q0 < m; q0 += 64) {  // scalar
+    const uint32_t k = min(q0 + lane, m - 1);
+    const uint32_t d = digit(it[k]);
+    const uint64_t in = first_lanes(m - q0);
+    uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
 #pragma unroll
-  for (int i = 0; i < MAXI; i++) {
-    if (i >= ipt || base + 64 * i >= m) continue;  // uniform
-    const bool valid = base + 64 * i + lane < m;
-    const uint32_t d = dg[i];
-    uint64_t same = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < DB; b++) {
-      const uint64_t one = __ballot((d >> b) & 1u);
-      same &= ((d >> b) & 1u) ? one : ~one;
+    for (int b = 0; b < kMaxDigit; b++) {
+      const int t = __builtin_amdgcn_sbfe((int)d, b, 1);  // 0 or -1
+      const uint64_t one = __builtin_amdgcn_ballot_w64(t != 0);
+      lo &= ~((uint32_t)one ^ (uint32_t)t);
+      hi &= ~((uint32_t)(one >> 32) ^ (uint32_t)t);
     }
-    const uint32_t before = (uint32_t)__popcll(same & below);
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
     const uint32_t prev = my[d];
     wave_order();  // every lane has read before the first one of each digit writes
-    if (valid && before == 0) my[d] = (uint16_t)(prev + (uint32_t)__popcll(same));
-    pos[i] = prev + before;
+    if (q0 + lane < m) {
+      if (before == 0) my[d] = (uint16_t)(prev + (uint32_t)__popc(lo) + (uint32_t)__popc(hi));
+      park(k, prev + before);
+    }
     wave_order();
   }
   __syncthreads();
-  uint32_t tot[DB == 7 ? 2 : 1] = {0}, bef[DB == 7 ? 2 : 1] = {0};
-#pragma unroll
+  uint32_t t0 = 0, t1 = 0, b0 = 0, b1 = 0;
+#pragma unroll 4
   for (int w = 0; w < NW; w++) {
+    const uint32_t c = cnt[w * kDigits + lane], e = cnt[w * kDigits + 64 + lane];
+    t0 += c;
+    t1 += e;
+    b0 += w < (int)wv ? c : 0u;
+    b1 += w < (int)wv ? e : 0u;
+  }
+  const uint32_t i0 = lane_incl_sum(t0), i1 = lane_incl_sum(t1);
+  row[lane] = (uint16_t)(i0 - t0 + b0);
+  row[64 + lane] = (uint16_t)((uint32_t)__builtin_amdgcn_readlane((int)i0, 63) + i1 - t1 + b1);
+  wave_order();
+  T v[MAXI];
+  uint32_t pos[MAXI];
 #pragma unroll
-    for (int q = 0; q < (DB == 7 ? 2 : 1); q++) {
-      const uint32_t c = cnt[w * kDigits + 64 * q + lane];
-      tot[q] += c;
-      bef[q] += w < wv ? c : 0u;
+  for (int i = 0; i < MAXI; i++)
+    if (i < ipt && base + 64 * i < m) {  // scalar
+      const uint32_t k = min(base + 64 * i + lane, m - 1);
+      v[i] = it[k];
+      pos[i] = parked(v[i], k) + row[digit(v[i])];
     }
-  }
-  const uint32_t inc0 = lane_incl_sum(tot[0]);
-  const uint32_t b0 = inc0 - tot[0] + bef[0];
-  uint32_t b1 = 0;
-  if (DB == 7) {
-    const uint32_t all0 = (uint32_t)__builtin_amdgcn_readlane((int)inc0, 63);
-    b1 = all0 + lane_incl_sum(tot[DB == 7 ? 1 : 0]) - tot[DB == 7 ? 1 : 0] + bef[DB == 7 ? 1 : 0];
-  }
+  __syncthreads();
 #pragma unroll
-  for (int i = 0; i < MAXI; i++) {
-    if (i >= ipt || base + 64 * i >= m) continue;
-    uint32_t at = (uint32_t)__shfl((int)b0, (int)(dg[i] & 63u), 64);
-    if (DB == 7) {
-      const uint32_t hi = (uint32_t)__shfl((int)b1, (int)(dg[i] & 63u), 64);
-      at = (dg[i] & 64u) ? hi : at;
-    }
-    pos[i] += at;
-  }
+  for (int i = 0; i < MAXI; i++)
+    if (i < ipt && base + 64 * i + lane < m) it[pos[i]] = v[i];
+  __syncthreads();
 }
 
-// The same for bits [shift, shift + nb) of key (nb <= 7, uniform).
-template <int NT, int MAXI>
-__device__ __forceinline__ void key_places(const uint32_t (&key)[MAXI], int shift, int nb, int ipt, uint32_t m,
-                                           uint16_t *cnt, uint32_t (&pos)[MAXI]) {
-  uint32_t dg[MAXI];
-  const uint32_t msk = (1u << nb) - 1u;
+// Place of element i of a key array that threads store IPT consecutive elements
+// of: exchanging elements within a block of IPT so that 32 neighbouring threads
+// storing their i-th element use 32 different banks (64-bit words); in order, a
+// stride of IPT words put 4 to 8 of them on one bank, and the stores of 4096
+// keys took as long as the searches (7.5 and 9.2 us in all).
+template <int IPT>
+__device__ __forceinline__ uint32_t spread(uint32_t i) {
+  return i ^ ((i >> 5) & (IPT - 1));
+}
+
+// Sorts m distinct 64-bit keys (at most NT * IPT; ~0 pads) held IPT per
+// thread into LDS (element i at spread(i)): the thread's own run by a network
+// over its registers, then runs merged pairwise, each thread producing IPT
+// consecutive outputs.
+template <int NT, int IPT>
+__device__ __forceinline__ void merge_sort(uint64_t (&x)[IPT], uint64_t *keys, uint32_t m) {
 #pragma unroll
-  for (int i = 0; i < MAXI; i++) dg[i] = (key[i] >> shift) & msk;
-  if (nb <= 6) digit_places<NT, MAXI, 6>(dg, ipt, m, cnt, pos);
-  else digit_places<NT, MAXI, 7>(dg, ipt, m, cnt, pos);
+  for (int k = 2; k <= IPT; k <<= 1)
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1)
+#pragma unroll
+      for (int i = 0; i < IPT; i++)
+        if ((i & j) == 0) {
+          const uint64_t u = x[i], v = x[i | j];
+          const bool swap = ((i & k) == 0 || k == IPT) == (v < u);
+          x[i] = swap ? v : u;
+          x[i | j] = swap ? u : v;
+        }
+  const uint32_t o0 = threadIdx.x * IPT;
+#pragma unroll 1
+  for (uint32_t L = IPT;; L <<= 1) {  // uniform
+#pragma unroll
+    for (int i = 0; i < IPT; i++)
+      if (o0 + i < m) keys[spread<IPT>(o0 + i)] = x[i];
+    __syncthreads();
+    if (L >= m) break;
+    if (o0 < m) {
+      // outputs o0 .. o0 + IPT - 1 of the pair of runs A (from `base`) and B:
+      // where the first of them splits the runs by binary search, then a merge
+      const uint32_t base = o0 & ~(2 * L - 1), d = o0 - base;
+      const uint32_t la = min(L, m - base), lb = min(L, m - base - la);
+      auto at = [=](uint32_t i) { return keys[spread<IPT>(base + i)]; };  // A, then B from la on
+      uint32_t lo = d > lb ? d - lb : 0, hi = min(d, la);
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (at(mid) < at(la + d - 1 - mid)) lo = mid + 1;
+        else hi = mid;
+      }
+      uint32_t ia = lo, ib = d - lo;
+      uint64_t u = ia < la ? at(ia) : ~0ull, v = ib < lb ? at(la + ib) : ~0ull;
+#pragma unroll
+      for (int i = 0; i < IPT; i++) {
+        // equal only when one run is used up and the other's is ~0
+        const bool fa = u < v || ib >= lb;
+        x[i] = fa ? u : v;
+        ia += fa ? 1u : 0u;
+        ib += fa ? 0u : 1u;
+        const uint64_t nx = (fa ? ia < la : ib < lb) ? at(fa ? ia : la + ib) : ~0ull;
+        u = fa ? nx : u;
+        v = fa ? v : nx;
+      }
+    }
+    __syncthreads();
+  }
 }
 
 __device__ __forceinline__ int bits_of(uint32_t x) { return x ? 32 - __clz((int)x) : 0; }
+
+// Minimum of 8 words, and the last of the first `c` (1 to 8) that is below l
+// (-1: none); p is 16-byte aligned.
+__device__ __forceinline__ uint32_t min8(const uint16_t *p) {
+  const uint4 v = *reinterpret_cast<const uint4 *>(p);
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t mn = 0xFFFFu;
+#pragma unroll
+  for (int q = 0; q < 4; q++) mn = min(mn, min(w[q] & 0xFFFFu, w[q] >> 16));
+  return mn;
+}
+__device__ __forceinline__ int below8(const uint16_t *p, uint32_t c, uint32_t l) {
+  const uint4 v = *reinterpret_cast<const uint4 *>(p);
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t f = 0;
+#pragma unroll
+  for (int q = 0; q < 8; q++) f |= ((w[q >> 1] >> (16 * (q & 1))) & 0xFFFFu) < l ? 1u << q : 0u;
+  f &= (1u << c) - 1u;
+  return f ? 31 - __clz((int)f) : -1;
+}
+
+// Last i < k with lcp[i] < l, or -1: climbs the levels of minima of 8 until a
+// block left of k holds one, then descends to it.
+__device__ __forceinline__ uint32_t last_smaller(const uint16_t *l0, const uint16_t *l1, const uint16_t *l2,
+                                                 const uint16_t *l3, uint32_t k, uint32_t l) {
+  uint32_t pos = k;
+  int lev = 0, f;
+  for (;;) {
+    if (pos == 0) return kNone;
+    const uint32_t lo = (pos - 1) & ~7u;
+    const uint16_t *p = lev == 0 ? l0 : lev == 1 ? l1 : lev == 2 ? l2 : l3;
+    f = below8(p + lo, pos - lo, l);
+    if (f >= 0) {
+      f += (int)lo;
+      break;
+    }
+    pos = lo;  // level 3 goes on down itself: 16 words at most
+    if (lev < 3) {
+      pos >>= 3;
+      lev++;
+    }
+  }
+  while (lev > 0) {
+    lev--;
+    const uint16_t *p = lev == 0 ? l0 : lev == 1 ? l1 : l2;
+    f = 8 * f + below8(p + 8 * f, 8, l);
+  }
+  return (uint32_t)f;
+}
 
 struct Row { uint32_t start, length, count; };
 struct Occ { uint32_t start, length, cand; };
@@ -138,6 +274,7 @@ struct FusedArgs {
   Row *rows;               // one window: final; batch: window w's rows start at off[w] / min_len
   Occ *occ;
   uint32_t row_cap, occ_cap;
+  uint64_t *spill;         // two words per token: records that find no room in LDS yet
   FusedInfo *info;         // one window
   uint32_t *dcnt, *rhist, *win_rows;  // batch: counters added up over the windows
 };
@@ -147,21 +284,22 @@ template <int NT, int IPT>
 __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
   constexpr int NW = NT / 64;
   constexpr uint32_t CAP = NT * IPT, SLOTS = 2 * CAP;
-  constexpr int CI = 2 * IPT;  // candidates per thread at most
-  static_assert(CAP <= kFusedMax, "16 bytes of LDS per token, and positions and ranks in 14 bits");
-  // ra, rb (8 bytes per token each) hold, one phase after the other:
-  //   ranking: the tokens; the hash table, later the ranks by slot
-  //   suffix sort: token ranks, suffix ranks, suffix order, LCP; the exchange buffer
-  //   candidate sort: start | ID << 16; length
-  __shared__ __align__(16) unsigned char ra[CAP * 8 + 64], rb[CAP * 8];
-  __shared__ uint16_t rc[CAP];               // slots of the distinct values; later the accepted candidates
-  __shared__ uint16_t cnt[NW * kDigits];     // radix counters; later LCP minima, surviving candidates
-  __shared__ uint32_t bitmap[CAP / 32];
+  constexpr uint32_t EARLY = CAP + CAP / 2 + 8;  // candidate records that fit before sa
+  static_assert(CAP <= kFusedMax, "16 bytes of LDS per token, and positions and ranks in 13 bits");
+  // lds holds, one phase after the other:
+  //   ranking: the tokens; the hash table, later the sorted distinct values
+  //   suffix sort: sort keys, later the list being sorted and its parked ranks;
+  //     token ranks (32 zero words past the end), suffix ranks, suffix order, LCP
+  //   candidates: records start | ID << 16 | length << 32 | parked rank << 48
+  __shared__ __align__(16) unsigned char lds[CAP * 16 + 64];
+  __shared__ __align__(16) uint16_t rc[CAP > NW * kDigits ? CAP : NW * kDigits];  // distinct values' tokens; radix rows; accepted candidates
+  __shared__ __align__(16) uint16_t cnt[NW * kDigits];  // radix counters; LCP minima; surviving candidates
+  __shared__ uint32_t bitmap[CAP / 32 + 2];  // slots that open a group; accepted positions; row openings
   __shared__ uint32_t wsum[NW], wsum2[NW];
-  __shared__ uint32_t s_nd, s_top, s_zero, s_single, s_max, s_skip, s_acc, s_dup;
+  __shared__ uint32_t s_nd, s_top, s_zero, s_active, s_large, s_max, s_skip, s_c, s_acc, s_dup;
   __shared__ uint32_t s_hist[kFusedRounds];
   __shared__ uint64_t s_stamp[kStages + 1];
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wv = wave_id();
   const uint64_t below = (1ull << lane) - 1ull;
 
   uint32_t win = 0, n = a.n;
@@ -183,262 +321,353 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
   };
   stamp(0);
 
-  // ---- order-preserving token ranks: distinct values through an LDS hash
-  // table (a slot holds the number of the token that claimed it), sorted, and
-  // every token's rank read from its slot
-  uint64_t *tokl = reinterpret_cast<uint64_t *>(ra);
-  uint32_t *tab = reinterpret_cast<uint32_t *>(rb);
-  uint64_t tk[IPT];
+  // ---- order-preserving token ranks.  Distinct values through an LDS hash
+  // table (a slot holds the number of the token that claimed it, every other
+  // token's entry becomes that number); the claimants' values sorted; each
+  // claimant's entry becomes its rank, found by binary search.
+  uint64_t *tokl = reinterpret_cast<uint64_t *>(lds);
+  {
+    uint32_t *tab = reinterpret_cast<uint32_t *>(lds + CAP * 8);
+    if (a.bits == 64) {
+      const uint64_t *t = static_cast<const uint64_t *>(a.tok) + tb;
+      uint64_t v[IPT];
 #pragma unroll
-  for (int i = 0; i < IPT; i++) {
-    const uint32_t k = i * NT + tid;
-    tk[i] = 0;
-    if (k < n)
-      tk[i] = a.bits == 64 ? static_cast<const uint64_t *>(a.tok)[tb + k]
-                           : (uint64_t) static_cast<const uint32_t *>(a.tok)[tb + k];
-  }
-  if (tid == 0) {
-    s_nd = 0;
-    s_top = 0;
-    s_skip = 0;
-    s_max = 0;
-    s_acc = 0;
-    s_dup = 0;
-  }
-  for (uint32_t k = tid; k < SLOTS; k += NT) tab[k] = kNone;
+      for (int i = 0; i < IPT; i++) v[i] = t[min(i * NT + tid, n - 1)];
 #pragma unroll
-  for (int i = 0; i < IPT; i++)
-    if (i * NT + tid < n) tokl[i * NT + tid] = tk[i];
-  __syncthreads();
-  uint16_t slot[IPT];
+      for (int i = 0; i < IPT; i++)
+        if (i * NT + tid < n) tokl[i * NT + tid] = v[i];
+    } else {
+      const uint32_t *t = static_cast<const uint32_t *>(a.tok) + tb;
+      uint32_t v[IPT];
 #pragma unroll
-  for (int i = 0; i < IPT; i++) {
-    const uint32_t k = i * NT + tid;
-    slot[i] = 0;
-    if (k >= n) continue;
-    uint32_t h = (uint32_t)(mix64(tk[i]) >> 40) & (SLOTS - 1);
-    for (;;) {  // n <= SLOTS / 2 values: a free slot is always found
-      uint32_t cur = tab[h];
-      if (cur == kNone) {
-        cur = atomicCAS(&tab[h], kNone, k);
+      for (int i = 0; i < IPT; i++) v[i] = t[min(i * NT + tid, n - 1)];
+#pragma unroll
+      for (int i = 0; i < IPT; i++)
+        if (i * NT + tid < n) tokl[i * NT + tid] = v[i];
+    }
+    if (tid == 0) {
+      s_nd = 0;
+      s_top = 0;
+      s_skip = 0;
+      s_max = 0;
+      s_c = 0;
+      s_acc = 0;
+      s_dup = 0;
+    }
+    if (tid < kFusedRounds) s_hist[tid] = 0;
+    for (uint32_t k = 4 * tid; k < SLOTS; k += 4 * NT)
+      *reinterpret_cast<uint4 *>(tab + k) = make_uint4(kNone, kNone, kNone, kNone);
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t k = tid; k < n; k += NT) {
+      const uint64_t key = tokl[k];
+      uint32_t at = (uint32_t)(mix64(key) >> 40) & (SLOTS - 1);
+      for (;;) {  // n <= SLOTS / 2 values: a free slot is always found
+        uint32_t cur = tab[at];
         if (cur == kNone) {
-          rc[atomicAdd(&s_nd, 1u)] = (uint16_t)h;
-          if (tk[i] == ~0ull) s_top = 1;
+          cur = atomicCAS(&tab[at], kNone, k);
+          if (cur == kNone) {
+            rc[atomicAdd(&s_nd, 1u)] = (uint16_t)k;
+            if (key == ~0ull) s_top = 1;
+            break;
+          }
+        }
+        if (tokl[cur] == key) {
+          tokl[k] = cur;  // nobody reads this token's value: it is in no slot
           break;
         }
+        at = (at + 1) & (SLOTS - 1);
       }
-      if (tokl[cur] == tk[i]) break;
-      h = (h + 1) & (SLOTS - 1);
-    }
-    slot[i] = (uint16_t)h;
-  }
-  __syncthreads();
-  const uint32_t D = s_nd;
-  {
-    // the distinct values in runs of 64, one per lane, sorted by a bitonic
-    // network over lane moves; then runs merged pairwise, each value finding
-    // its place by a binary search in the other run (pads: the largest value,
-    // kept apart by place)
-    uint32_t P = 64;
-    while (P < D) P <<= 1;
-    uint64_t v[IPT];
-    uint32_t vs[IPT], pos[IPT];
-    // register r of a thread holds value r * NT + tid while P >= NT; wavefronts
-    // past P hold nothing
-    const bool holds = tid < P;
-    const int R = (int)((P + NT - 1) / NT);
-#pragma unroll
-    for (int r = 0; r < IPT; r++) {
-      const uint32_t q = r * NT + tid;
-      vs[r] = kNone;
-      v[r] = ~0ull;
-      if (r < R && q < D) {
-        vs[r] = rc[q];
-        v[r] = tokl[tab[vs[r]]];
-      }
-    }
-#pragma unroll
-    for (uint32_t k = 2; k <= 64; k <<= 1)
-#pragma unroll
-      for (uint32_t j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-        for (int r = 0; r < IPT; r++) {
-          if (r >= R || !holds) continue;
-          const uint64_t o = ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(v[r] >> 32), (int)j, 64) << 32) |
-                             (uint32_t)__shfl_xor((int)(uint32_t)v[r], (int)j, 64);
-          const uint32_t os = (uint32_t)__shfl_xor((int)vs[r], (int)j, 64);
-          const bool lower = (lane & j) == 0, asc = (lane & k) == 0 || k == 64;
-          // pads order after every value, so equal pairs are pads and a value
-          // equal to a pad (the largest token) goes first
-          const bool mine_less = v[r] < o || (v[r] == o && vs[r] < os);
-          const bool keep = (lower == asc) == mine_less || (v[r] == o && vs[r] == os);
-          v[r] = keep ? v[r] : o;
-          vs[r] = keep ? vs[r] : os;
-        }
-    __syncthreads();  // tokens and table read
-    uint64_t *buf[2] = {reinterpret_cast<uint64_t *>(ra), reinterpret_cast<uint64_t *>(rb)};
-#pragma unroll
-    for (int r = 0; r < IPT; r++) {
-      pos[r] = r * NT + tid;
-      if (r < R && holds) buf[0][pos[r]] = v[r];
     }
     __syncthreads();
-    int cb = 0;
-    for (uint32_t L = 64; L < P; L <<= 1) {
-      const uint64_t *src = cb ? buf[1] : buf[0];
-      uint64_t *dst = cb ? buf[0] : buf[1];
-#pragma unroll
-      for (int r = 0; r < IPT; r++) {
-        if (r >= R || !holds) continue;
-        const uint32_t i = pos[r], base = i & ~(2 * L - 1), right = i & L;
-        const bool rt = right != 0;
-        const uint64_t x = v[r];
-        const uint64_t *o = src + (right ? base : base + L);
-        uint32_t c = 0;
-        for (uint32_t step = L >> 1; step > 0; step >>= 1) {  // branch-free steps
-          const uint64_t y = o[c + step - 1];
-          c += ((y < x) | ((y == x) & rt)) ? step : 0u;
-        }
-        c += ((o[c] < x) | ((o[c] == x) & rt)) ? 1u : 0u;  // c <= L - 1 before this step
-        pos[r] = base + (i - base - right) + c;
-        dst[pos[r]] = x;
-      }
-      __syncthreads();
-      cb ^= 1;
-    }
-    // ranks by slot (rb: its last use as a merge buffer is over, or it is the
-    // merged list, which nothing reads)
-    uint16_t *srank = reinterpret_cast<uint16_t *>(rb);
-#pragma unroll
-    for (int r = 0; r < IPT; r++)
-      if (r < R && vs[r] != kNone) srank[vs[r]] = (uint16_t)(pos[r] + 1);
   }
-  __syncthreads();
-  uint16_t *txt = reinterpret_cast<uint16_t *>(ra);  // token ranks 1..D, 32 words past the end readable
-  uint16_t *rank = txt + CAP + 32, *sa = rank + CAP, *lcp = sa + CAP;
-  uint32_t *exch = reinterpret_cast<uint32_t *>(rb);
+  const uint32_t D = s_nd;
   {
-    const uint16_t *srank = reinterpret_cast<const uint16_t *>(rb);
+    uint64_t *sorted = reinterpret_cast<uint64_t *>(lds + CAP * 8);
+    uint64_t x[IPT];
 #pragma unroll
-    for (int i = 0; i < IPT; i++)
-      if (i * NT + tid < n) txt[i * NT + tid] = srank[slot[i]];
-    if (tid < 32) txt[n + tid] = 0;
+    for (int i = 0; i < IPT; i++) {
+      const uint32_t q = tid * IPT + i;
+      x[i] = q < D ? tokl[rc[min(q, D - 1)]] : ~0ull;
+    }
+    merge_sort<NT, IPT>(x, sorted, D);  // the table's last reads are a barrier behind
+#pragma unroll 1
+    for (uint32_t q = tid; q < D; q += NT) {
+      const uint32_t k = rc[q];
+      const uint64_t key = tokl[k];
+      uint32_t lo = 0, hi = D - 1;  // sorted[lo .. hi] holds it
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (sorted[spread<IPT>(mid)] < key) lo = mid + 1;
+        else hi = mid;
+      }
+      tokl[k] = (1ull << 63) | (lo + 1);
+    }
+    __syncthreads();
   }
+  uint16_t *txt = reinterpret_cast<uint16_t *>(lds + CAP * 8);  // token ranks 1..D
+  uint16_t *rank = txt + CAP + 32, *sa = rank + CAP, *lcp = sa + CAP;
+  uint32_t *exch = reinterpret_cast<uint32_t *>(lds);
+  uint16_t *rel = reinterpret_cast<uint16_t *>(lds + CAP * 4);
+#pragma unroll 1
+  for (uint32_t k = tid; k < n; k += NT) {
+    const uint64_t e = tokl[k];
+    txt[k] = (uint16_t)((e >> 63) ? e : tokl[e]);
+  }
+  if (tid < 32) txt[n + tid] = 0;
   __syncthreads();
   stamp(1);
 
-  // ---- suffix array by prefix doubling.  A round lists the suffixes j in the
-  // order of their second halves (j = SA[k] - h) and sorts that list stably by
-  // the group of the first half.  The h shortest suffixes, whose second half is
-  // empty, wrap around (j = SA[k] - h + n): the one of h tokens (SA[k] = 0) is
-  // put first, the shorter ones may stand anywhere, each alone in its group.
+  // ---- suffix array.  First every suffix sorted by as many tokens as fit in a
+  // 64-bit word above its position (3 at least, kPackMost at most).
   const int ipt = (int)((n + NT - 1) / NT);
-  const uint32_t kb = wv * 64 * ipt + lane;  // item i of this lane: kb + 64 * i
-  uint32_t nhist = 0;
+  const int tbits = bits_of(D);
+  uint32_t h = min((uint32_t)((64 - kPosBits) / tbits), kPackMost);
   {
-    uint32_t j[IPT], key[IPT], pos[IPT];
-    int kbits = bits_of(D - 1);
-    uint32_t h = 0;
+    uint64_t x[IPT];
+#pragma unroll
+    for (int i = 0; i < IPT; i++) x[i] = 0;
+#pragma unroll 1
+    for (uint32_t q = 0; q < h; q++)  // zeros past the end: h <= 32
+#pragma unroll
+      for (int i = 0; i < IPT; i++) x[i] = (x[i] << tbits) | txt[min(tid * IPT + i, n - 1) + q];
 #pragma unroll
     for (int i = 0; i < IPT; i++) {
-      j[i] = kb + 64 * i;
-      key[i] = (i < ipt && j[i] < n) ? txt[j[i]] - 1u : 0u;
+      const uint32_t j = tid * IPT + i;
+      x[i] = j < n ? (x[i] << kPosBits) | j : ~0ull;
     }
-    for (uint32_t round = 0;; round++) {
-      if (round) {
-        const uint32_t first = s_zero;
+    merge_sort<NT, IPT>(x, reinterpret_cast<uint64_t *>(lds), n);
+  }
+  // Groups of equal h-token prefixes: a bitmap of the slots that open one (slot
+  // n counts as one), and rank[j] = the first slot of j's group.
+  const uint32_t wbase = wv * 64 * ipt, wtop = min(wbase + 64 * ipt, n);  // the wavefront's slots
+  {
+    const uint64_t *keys = reinterpret_cast<const uint64_t *>(lds);
+#pragma unroll 1
+    for (uint32_t k0 = wbase; k0 < wtop; k0 += 64) {  // scalar
+      const uint32_t k = min(k0 + lane, n - 1);
+      const uint64_t key = keys[spread<IPT>(k)], prev = keys[spread<IPT>(k ? k - 1 : 0)];
+      const uint32_t j = (uint32_t)key & ((1u << kPosBits) - 1u);
+      sa[k] = (uint16_t)j;
+      if (j == 0) s_zero = k;
+      const uint64_t hd = __ballot(k0 + lane == 0 || k0 + lane >= n || (prev >> kPosBits) != (key >> kPosBits));
+      if (lane == 0) {
+        bitmap[k0 >> 5] = (uint32_t)hd;
+        bitmap[(k0 >> 5) + 1] = (uint32_t)(hd >> 32);
+      }
+    }
+    if (tid == 0 && n % 64 == 0) bitmap[n >> 5] = 1;
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t k = tid; k < n; k += NT) {
+      uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
+      while (!w) w = bitmap[--x];  // slot 0 opens a group
+      rank[sa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
+    }
+  }
+  // Suffixes still grouped, and whether some group is large (96 slots or more;
+  // up to 158 may pass): counting costs a group's size per member, the radix
+  // passes about as much as a group of 100 (5000 tokens of a nested loop: 16 us a
+  // round by counting, 17 to 20 by radix passes).
+  uint32_t active;
+  bool large;
+  auto survey = [&] {
+    if (tid == 0) s_active = s_large = 0;
+    __syncthreads();
+    if (2048 * wv < n) {  // scalar: one word per lane
+      uint32_t more = 0;
+      if (32 * tid < n) {
+        const uint32_t w = bitmap[tid], up = 32 * tid + 32 <= n ? bitmap[tid + 1] : kNone;
+        more = (uint32_t)__popc(~(w & ((w >> 1) | (up << 31))) & (uint32_t)first_lanes(n - 32 * tid));
+        if (!(w | up) && 32 * tid + 64 <= n && !bitmap[tid + 2]) s_large = 1;  // 96 slots without an opening
+      }
+      more = lane_incl_sum(more);
+      if (lane == 63 && more) atomicAdd(&s_active, more);
+    }
+    __syncthreads();
+    active = s_active;
+    large = s_large != 0;
+  };
+  survey();
+  // Then prefix doubling of the suffixes still grouped.  While no group is
+  // large a suffix finds its new group by counting its group's members with a
+  // smaller second half, whose group numbers lie side by side (eight per LDS
+  // read); its place in the new group is taken from a counter, any order doing.
+  // Otherwise a round lists them in the order of their second halves (j = SA[k] - h over all slots k) and sorts
+  // that list stably by the group of the first half.  The h shortest suffixes,
+  // whose second half is empty, wrap around (j = SA[k] - h + n): the one of h
+  // tokens (SA[k] = 0) is put first, the shorter ones are alone in their groups.
+  uint16_t *sah = sa;  // where the suffix order is now
+  while (active) {  // uniform
+    const uint32_t m = active;
+    if (!large) {
+      uint32_t *ctr = reinterpret_cast<uint32_t *>(lds);
+      uint16_t *half = reinterpret_cast<uint16_t *>(lds + CAP * 4);
+      uint16_t *san = sah == sa ? half + CAP : sa;
+#pragma unroll 1
+      for (uint32_t k = tid; k < n; k += NT) {
+        const uint32_t s = sah[k] + h;
+        const uint32_t r = rank[min(s, n - 1)];
+        half[k] = (uint16_t)(s < n ? r + 1 : 0);
+        ctr[k] = 0;
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (uint32_t k = tid; k < n; k += NT) {
+        const uint32_t j = sah[k], g = rank[j];
+        if ((bitmap[(g + 1) >> 5] >> ((g + 1) & 31)) & 1u) {
+          san[k] = (uint16_t)j;
+          continue;
+        }
+        uint32_t x = (k + 1) >> 5, w = bitmap[x] & (kNone << ((k + 1) & 31));
+        while (!w) w = bitmap[++x];
+        const uint32_t e = 32 * x + (uint32_t)__ffs((int)w) - 1u;  // the group: slots [g, e)
+        typedef short pair __attribute__((ext_vector_type(2)));
+        const short me = (short)half[k];
+        const pair mine = {me, me};
+        uint32_t less = 0;
+        for (uint32_t b = g & ~7u; b < e; b += 8) {
+          const uint4 v = *reinterpret_cast<const uint4 *>(half + b);
+          uint32_t sg[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int i = 0; i < IPT; i++) {
-          const uint32_t k = kb + 64 * i;
-          if (i >= ipt || k >= n) continue;
-          const uint32_t s = sa[k == 0 ? first : k <= first ? k - 1 : k];
-          j[i] = s >= h ? s - h : s + n - h;
-          key[i] = rank[j[i]];
+          for (int q = 0; q < 4; q++)  // sign bits: below mine (values of at most 14 bits)
+            sg[q] = __builtin_bit_cast(uint32_t, (pair)(__builtin_bit_cast(pair, sg[q]) - mine)) & 0x80008000u;
+          if (b < g || b + 8 > e) {
+            const uint32_t ok = (b < g ? 0xFFu << (g - b) : 0xFFu) & (b + 8 > e ? (1u << (e - b)) - 1u : 0xFFu);
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+              sg[q] &= ((ok >> (2 * q)) & 1u ? 0x8000u : 0u) | ((ok >> (2 * q + 1)) & 1u ? 0x80000000u : 0u);
+          }
+          less += (uint32_t)(__popc(sg[0]) + __popc(sg[1]) + __popc(sg[2]) + __popc(sg[3]));
+        }
+        rank[j] = (uint16_t)(g + less);  // this suffix's old group number was this thread's alone to read
+        san[g + less + atomicAdd(&ctr[g + less], 1u)] = (uint16_t)j;
+      }
+      __syncthreads();
+#pragma unroll 1
+      for (uint32_t k0 = wbase; k0 < wtop; k0 += 64) {  // scalar
+        const uint32_t k = min(k0 + lane, n - 1), j = san[k];
+        if (j == 0) s_zero = k;
+        const uint64_t hd = __ballot(k0 + lane >= n || rank[j] == k);
+        if (lane == 0) {
+          bitmap[k0 >> 5] = (uint32_t)hd;
+          bitmap[(k0 >> 5) + 1] = (uint32_t)(hd >> 32);
         }
       }
-      const int lo = kbits > kMaxDigit ? (kbits + 1) / 2 : kbits;
-      if (lo < kbits) {
-        key_places<NT, IPT>(key, 0, lo, ipt, n, cnt, pos);
-#pragma unroll
-        for (int i = 0; i < IPT; i++)
-          if (i < ipt && kb + 64 * i < n) exch[pos[i]] = j[i] | (key[i] << 16);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < IPT; i++)
-          if (i < ipt && kb + 64 * i < n) {
-            const uint32_t e = exch[kb + 64 * i];
-            j[i] = e & 0xFFFFu;
-            key[i] = e >> 16;
-          }
-        key_places<NT, IPT>(key, lo, kbits - lo, ipt, n, cnt, pos);
-      } else {
-        key_places<NT, IPT>(key, 0, lo, ipt, n, cnt, pos);
-      }
-#pragma unroll
-      for (int i = 0; i < IPT; i++)
-        if (i < ipt && kb + 64 * i < n) sa[pos[i]] = (uint16_t)j[i];
+      sah = san;
+      h *= 2;
+      survey();
+      continue;
+    }
+    if (sah != sa) {  // uniform
+      for (uint32_t k = tid; k < n; k += NT) sa[k] = sah[k];
+      sah = sa;
       __syncthreads();
-      // group heads: (first half's group, second half's) differs from the slot before
-      uint64_t head[IPT];
-      uint32_t last = kNone;  // the wavefront's last head
+    }
+    {
+      const uint32_t first = s_zero;
+      uint32_t e[IPT];
+      uint64_t mk[IPT];
+      uint32_t run = 0;
 #pragma unroll
       for (int i = 0; i < IPT; i++) {
-        head[i] = ~0ull;
-        const uint32_t k0 = wv * 64 * ipt + 64 * i;
+        mk[i] = 0;
+        const uint32_t k0 = wv * 64 * ipt + 64 * i, k = min(k0 + lane, n - 1);
         if (i >= ipt || k0 >= n) continue;  // uniform
-        const uint32_t k = k0 + lane;
-        bool hd = true;
-        uint32_t c = 0;
-        if (k < n) {
-          const uint32_t s = sa[k];
-          j[i] = s;
-          if (s == 0) s_zero = k;
-          if (round == 0) c = txt[s];
-          else c = ((uint32_t)rank[s] << 16) | (s + h < n ? rank[s + h] : 0xFFFFu);
-        }
+        const uint32_t s = sa[k == 0 ? first : k <= first ? k - 1 : k];
+        const uint32_t j = s >= h ? s - h : s + n - h;
+        const uint32_t g = rank[j];
+        e[i] = j | (g << 16);
+        mk[i] = __ballot(!((bitmap[(g + 1) >> 5] >> ((g + 1) & 31)) & 1u)) & first_lanes(n - k0);
+        run += (uint32_t)__popcll(mk[i]);
+      }
+      if (lane == 0) wsum[wv] = run;
+      __syncthreads();
+      uint32_t off = 0;
+#pragma unroll
+      for (int w = 0; w < NW; w++) off += w < (int)wv ? wsum[w] : 0u;
+#pragma unroll
+      for (int i = 0; i < IPT; i++) {
+        if ((mk[i] >> lane) & 1ull) exch[off + lanes_below(mk[i])] = e[i];
+        off += (uint32_t)__popcll(mk[i]);
+      }
+      __syncthreads();
+    }
+    const int mpt = (int)((m + NT - 1) / NT);
+    {
+      const int gbits = bits_of(n - 1), low = gbits > kMaxDigit ? gbits / 2 : gbits;
+#pragma unroll 1
+      for (int shift = 0; shift < gbits; shift += low) {
+        const uint32_t msk = shift ? kNone : (1u << low) - 1u;  // the upper digit takes what is left
+        radix_pass<NT, IPT>(
+            exch, m, mpt, cnt, rc, [=](uint32_t e) { return (e >> (16 + shift)) & msk; },
+            [=](uint32_t k, uint32_t r) { rel[k] = (uint16_t)r; }, [=](uint32_t, uint32_t k) { return (uint32_t)rel[k]; });
+        if (shift) break;
+      }
+    }
+    {
+      // new groups: entry q opens one when its first or second half's group
+      // differs from the entry before; its slot is its distance into the old
+      // group past that group's first slot
+      uint64_t og[IPT], ng[IPT];
+      uint32_t e[IPT];
+      uint32_t lo = kNone, ln = kNone;  // the wavefront's last old and new group openings
+#pragma unroll
+      for (int i = 0; i < IPT; i++) {
+        og[i] = ng[i] = ~0ull;
+        const uint32_t q0 = wv * 64 * mpt + 64 * i, q = q0 + lane;
+        if (i >= mpt || q0 >= m) continue;  // uniform
+        e[i] = exch[min(q, m - 1)];
+        const uint32_t s = (e[i] & 0xFFFFu) + h;
+        const uint32_t r = rank[min(s, n - 1)];
+        const uint32_t c = (e[i] & 0xFFFF0000u) | (s < n ? r : 0xFFFFu);
         uint32_t p = lane_prev(c);
-        if (lane == 0 && k) {
-          const uint32_t s = sa[k - 1];
-          if (round == 0) p = txt[s];
-          else p = ((uint32_t)rank[s] << 16) | (s + h < n ? rank[s + h] : 0xFFFFu);
+        if (lane == 0 && q) {
+          const uint32_t b = exch[q - 1], s = (b & 0xFFFFu) + h;
+          p = (b & 0xFFFF0000u) | (s < n ? rank[s] : 0xFFFFu);
         }
-        if (k && k < n) hd = c != p;
-        head[i] = __ballot(hd);
-        const uint64_t in = n - k0 >= 64 ? ~0ull : (1ull << (n - k0)) - 1ull;
-        if (head[i] & in) last = k0 + 63u - (uint32_t)__clzll((long long)(head[i] & in));
+        og[i] = __ballot(q == 0 || q >= m || (c >> 16) != (p >> 16));
+        ng[i] = __ballot(q == 0 || q >= m || c != p);
+        const uint64_t in = first_lanes(m - q0);
+        if (og[i] & in) lo = q0 + 63u - (uint32_t)__clzll((long long)(og[i] & in));
+        if (ng[i] & in) ln = q0 + 63u - (uint32_t)__clzll((long long)(ng[i] & in));
       }
       if (lane == 0) {
-        wsum[wv] = last;
-        wsum2[wv] = (uint32_t)(head[0] & 1ull);
+        wsum[wv] = lo;
+        wsum2[wv] = ln;
       }
-      if (tid == 0) s_single = 0;
       __syncthreads();
-      uint32_t carry = 0;
+      uint32_t co = 0, cn = 0;
 #pragma unroll
-      for (int w = 0; w < NW; w++)
-        if (w < (int)wv && wsum[w] != kNone) carry = wsum[w];
-      const uint64_t next_first = wv + 1 < NW ? wsum2[wv + 1 < NW ? wv + 1 : 0] : 1u;
-      uint32_t singles = 0;
+      for (int w = 0; w < NW; w++) {
+        if (w < (int)wv && wsum[w] != kNone) co = wsum[w];
+        if (w < (int)wv && wsum2[w] != kNone) cn = wsum2[w];
+      }
 #pragma unroll
       for (int i = 0; i < IPT; i++) {
-        const uint32_t k0 = wv * 64 * ipt + 64 * i;
-        if (i >= ipt || k0 >= n) continue;
-        const uint64_t in = n - k0 >= 64 ? ~0ull : (1ull << (n - k0)) - 1ull;
-        const uint64_t up = i + 1 < ipt ? head[i + 1 < IPT ? i + 1 : i] & 1ull : next_first;
-        singles += (uint32_t)__popcll(head[i] & in & ((head[i] >> 1) | (up << 63)));
-        const uint64_t upto = head[i] & in & (below | (1ull << lane));
-        if (k0 + lane < n) rank[j[i]] = (uint16_t)(upto ? k0 + 63u - (uint32_t)__clzll((long long)upto) : carry);
-        if (head[i] & in) carry = k0 + 63u - (uint32_t)__clzll((long long)(head[i] & in));
+        const uint32_t q0 = wv * 64 * mpt + 64 * i;
+        if (i >= mpt || q0 >= m) continue;
+        const uint64_t in = first_lanes(m - q0);
+        const uint64_t upto = in & (below | (1ull << lane)), uo = og[i] & upto, un = ng[i] & upto;
+        if (q0 + lane < m) {
+          const uint32_t ob = uo ? q0 + 63u - (uint32_t)__clzll((long long)uo) : co;
+          const uint32_t nb = un ? q0 + 63u - (uint32_t)__clzll((long long)un) : cn;
+          const uint32_t j = e[i] & 0xFFFFu, g = e[i] >> 16, slot = g + (q0 + lane - ob);
+          sa[slot] = (uint16_t)j;
+          rank[j] = (uint16_t)(g + (nb - ob));
+          if (nb == q0 + lane) atomicOr(&bitmap[slot >> 5], 1u << (slot & 31));
+          if (j == 0) s_zero = slot;
+        }
+        if (og[i] & in) co = q0 + 63u - (uint32_t)__clzll((long long)(og[i] & in));
+        if (ng[i] & in) cn = q0 + 63u - (uint32_t)__clzll((long long)(ng[i] & in));
       }
-      if (lane == 0 && singles) atomicAdd(&s_single, singles);
-      __syncthreads();
-      const uint32_t active = n - s_single;
-      if (tid == 0) s_hist[round] = active;  // at most kFusedRounds: 2^(round - 1) < n
-      nhist = round + 1;
-      if (active == 0) break;  // uniform
-      h = h ? 2 * h : 1;
-      kbits = bits_of(n - 1);
+      h *= 2;
+      survey();  // its first barrier ends the writes above
     }
+  }
+  if (sah != sa) {  // uniform
+    for (uint32_t k = tid; k < n; k += NT) sa[k] = sah[k];
+    __syncthreads();
   }
   stamp(2);
 
@@ -473,158 +702,113 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
       h = h ? h - 1 : 0;
     }
     if (tid == 0) lcp[n - 1] = 0;
+    if (tid < 8 && n + tid < ((n + 7) & ~7u)) lcp[n + tid] = 0xFFFF;
   }
+  // minima of 8, 64 and 512 LCP values for the ID's previous-smaller-value
+  // queries (0xFFFF past the end)
+  uint16_t *min1 = cnt, *min2 = min1 + CAP / 8, *min3 = min2 + CAP / 64;
+  static_assert(CAP / 8 + CAP / 64 + CAP / 64 <= NW * kDigits, "minima fit the radix counters");
+  for (uint32_t b = tid; b < CAP / 8 + CAP / 64 + CAP / 64; b += NT) cnt[b] = 0xFFFF;
   __syncthreads();
   stamp(3);
 
-  // ---- candidates of every adjacent pair in suffix-array order.  The minima
-  // of 16 and 256 LCP values serve the ID's previous-smaller-value queries.
-  uint16_t *min1 = cnt, *min2 = cnt + CAP / 16;
-  static_assert(CAP / 16 + CAP / 256 <= NW * kDigits, "minima fit the radix counters");
-  for (uint32_t b = tid; b < (n + 15) / 16; b += NT) {
-    uint32_t mn = 0xFFFFu;
-    for (uint32_t q = 0; q < 16 && b * 16 + q < n; q++) mn = min(mn, (uint32_t)lcp[b * 16 + q]);
-    min1[b] = (uint16_t)mn;
-  }
+  // ---- candidates of every adjacent pair in suffix-array order
+  for (uint32_t b = tid; b < (n + 7) / 8; b += NT) min1[b] = (uint16_t)min8(lcp + 8 * b);
   __syncthreads();
-  for (uint32_t b = tid; b < (n + 255) / 256; b += NT) {
-    uint32_t mn = 0xFFFFu;
-    for (uint32_t q = 0; q < 16 && b * 16 + q < (n + 15) / 16; q++) mn = min(mn, (uint32_t)min1[b * 16 + q]);
-    min2[b] = (uint16_t)mn;
-  }
+  for (uint32_t b = tid; b < (n + 63) / 64; b += NT) min2[b] = (uint16_t)min8(min1 + 8 * b);
   __syncthreads();
-  uint32_t C = 0, maxl = 0;
+  for (uint32_t b = tid; b < (n + 511) / 512; b += NT) min3[b] = (uint16_t)min8(min2 + 8 * b);
+  __syncthreads();
+  uint64_t *rec = reinterpret_cast<uint64_t *>(lds);
   {
-    uint32_t w0[CI], w1[CI], at[CI];
-    uint32_t run = 0, mx = 0, skipped = 0;
-#pragma unroll
-    for (int i = 0; i < IPT; i++) {
-      at[2 * i] = at[2 * i + 1] = kNone;
-      w0[2 * i] = w0[2 * i + 1] = w1[2 * i] = w1[2 * i + 1] = 0;
-      const uint32_t k0 = wv * 64 * ipt + 64 * i, k = k0 + lane;
-      if (i >= ipt || k0 >= n) continue;  // uniform
-      uint32_t l = 0, s1 = 0, s2 = 0;
-      bool disj = false;
-      if (k + 1 < n) {
-        const uint32_t x = sa[k], y = sa[k + 1], p = lcp[k];
+    uint32_t mx = 0;
+#pragma unroll 1
+    for (uint32_t k0 = wv * 64 * ipt; k0 < wv * 64 * ipt + 64 * ipt && k0 < n; k0 += 64) {  // scalar
+      const uint32_t k = k0 + lane;
+      uint32_t l = 0, s1 = 0, s2 = 0, both = 0;
+      bool rep = false;
+      if (k < n) {
+        const uint32_t x = sa[k], y = k + 1 < n ? sa[k + 1] : x, p = lcp[k];
+        const uint32_t w = k ? sa[k - 1] : x, pp = k ? lcp[k - 1] : 0u;
+        both = max(p, pp);
         const uint32_t lo = min(x, y), d = max(x, y) - lo;
-        if (p <= d) {
+        const bool disj = p <= d;
+        if (disj) {
           l = p;
           s1 = x;
           s2 = y;
-          disj = true;
         } else {
           l = (p + d) / 2;
           l -= l % d;
           s1 = lo;
           s2 = lo + l;
         }
-        if (l < a.min_len) l = 0;
+        if (l < a.min_len || k + 1 == n) l = 0;
+        // pair k - 1 disjoint too and of equal length: its second candidate is
+        // this pair's first
+        rep = l && disj && k && pp == l && pp <= max(x, w) - min(x, w);
       }
-      // pair k - 1's length when it is disjoint too (equal lengths: its second
-      // candidate is this pair's first)
-      bool rep = false;
-      if (l && disj && k) {
-        const uint32_t x = sa[k - 1], y = sa[k], p = lcp[k - 1];
-        rep = p == l && p <= max(x, y) - min(x, y);
-      }
-      uint32_t id = 0;
-      if (l) {  // 1 + the last pair before k whose LCP is below l
-        int f = (int)k - 1;
-        while (f >= 0 && (f & 15) != 15 && lcp[f] >= l) f--;
-        if (f >= 0 && (f & 15) == 15) {
-          int b = f >> 4;
-          while (b >= 0 && (b & 15) != 15 && min1[b] >= l) b--;
-          if (b >= 0 && (b & 15) == 15) {
-            int c = b >> 4;
-            while (c >= 0 && min2[c] >= l) c--;
-            b = c < 0 ? -1 : (c << 4) + 15;
-            while (b >= 0 && min1[b] >= l) b--;
-          }
-          f = b < 0 ? -1 : (b << 4) + 15;
-          while (f >= 0 && lcp[f] >= l) f--;
-        }
-        id = (uint32_t)(f + 1);
+      // a suffix shares 2^r tokens with a neighbour: still grouped after round r
+#pragma unroll 1
+      for (int r = 0; r < kFusedRounds; r++) {
+        const uint64_t g = __ballot(both >> r);
+        if (!g) break;  // scalar
+        if (lane == 0) atomicAdd(&s_hist[r], (uint32_t)__popcll(g));
       }
       const uint64_t m2 = __ballot(l != 0), m1 = __ballot(l != 0 && !rep);
-      uint32_t q = run + (uint32_t)__popcll(m1 & below) + (uint32_t)__popcll(m2 & below);
-      if (l) {
-        if (!rep) {
-          at[2 * i] = q++;
-          w0[2 * i] = s1 | (id << 16);
-          w1[2 * i] = l;
-        }
-        at[2 * i + 1] = q;
-        w0[2 * i + 1] = s2 | (id << 16);
-        w1[2 * i + 1] = l;
+      if (!m2) continue;  // scalar
+      const uint64_t id = l ? 1u + last_smaller(lcp, min1, min2, min3, k, l) : 0u;
+      // records in any order: the sort's key tells all but duplicates apart
+      uint32_t q = 0;
+      if (lane == 0) {
+        q = atomicAdd(&s_c, (uint32_t)(__popcll(m1) + __popcll(m2)));
+        atomicAdd(&s_skip, (uint32_t)(__popcll(m2) - __popcll(m1)));
       }
-      run += (uint32_t)(__popcll(m1) + __popcll(m2));
-      skipped += (uint32_t)(__popcll(m2) - __popcll(m1));
+      q = (uint32_t)__builtin_amdgcn_readfirstlane((int)q) + lanes_below(m1) + lanes_below(m2);
+      if (l) {
+        const uint64_t head = (id << 16) | ((uint64_t)l << 32);
+        if (!rep) {
+          if (q < EARLY) rec[q] = head | s1;
+          else a.spill[2 * tb + q] = head | s1;
+          q++;
+        }
+        if (q < EARLY) rec[q] = head | s2;
+        else a.spill[2 * tb + q] = head | s2;
+      }
       mx = max(mx, l);
     }
-    if (mx) atomicMax(&s_max, mx);
-    if (lane == 0) {
-      wsum[wv] = run;
-      if (skipped) atomicAdd(&s_skip, skipped);
-    }
-    __syncthreads();  // suffix order, ranks, LCP and minima read
-    uint32_t off = 0;
-#pragma unroll
-    for (int w = 0; w < NW; w++) {
-      const uint32_t c = wsum[w];
-      off += w < (int)wv ? c : 0u;
-      C += c;
-    }
-    maxl = s_max;
-    uint32_t *o0 = reinterpret_cast<uint32_t *>(ra);
-    uint16_t *o1 = reinterpret_cast<uint16_t *>(rb);
-#pragma unroll
-    for (int i = 0; i < CI; i++)
-      if (at[i] != kNone) {
-        o0[off + at[i]] = w0[i];
-        o1[off + at[i]] = (uint16_t)w1[i];
-      }
+    mx = lane_max(mx);
+    if (lane == 63 && mx) atomicMax(&s_max, mx);
   }
+  __syncthreads();  // suffix order, LCP and minima read, records written
+  const uint32_t C = s_c, maxl = s_max;
+  for (uint32_t k = EARLY + tid; k < C; k += NT) rec[k] = a.spill[2 * tb + k];
   for (uint32_t k = tid; k < (n + 31) / 32; k += NT) bitmap[k] = 0;
   __syncthreads();
   stamp(4);
 
-  // ---- priority order (length desc, ID asc, start asc): a stable sort by
-  // start, then ID, then length, 7 bits or fewer at a time
-  uint32_t *c0 = reinterpret_cast<uint32_t *>(ra);   // start | ID << 16
-  uint16_t *c1 = reinterpret_cast<uint16_t *>(rb);   // length
+  // ---- priority order (length desc, ID asc, start asc): a radix sort of the
+  // three fields as one key
   if (C) {  // uniform
-    const int cpt = (int)((C + NT - 1) / NT);
-    const uint32_t cb = wv * 64 * cpt + lane;
-    const int pb = bits_of(n - 1), lb = bits_of(maxl - a.min_len);
-    for (int field = 0; field < 3; field++) {
-      const int fb = field == 2 ? lb : pb;
-      const int np = (fb + kMaxDigit - 1) / kMaxDigit;
-      int shift = 0;
-      for (int p = 0; p < np; p++) {
-        const int nb = (fb - shift + (np - p) - 1) / (np - p);
-        uint32_t w0[CI], w1[CI], key[CI], pos[CI];
-#pragma unroll
-        for (int i = 0; i < CI; i++) {
-          w0[i] = w1[i] = key[i] = 0;
-          if (i < cpt && cb + 64 * i < C) {
-            w0[i] = c0[cb + 64 * i];
-            w1[i] = c1[cb + 64 * i];
-            key[i] = field == 0 ? w0[i] & 0xFFFFu : field == 1 ? w0[i] >> 16 : maxl - w1[i];
-          }
-        }
-        key_places<NT, CI>(key, shift, nb, cpt, C, cnt, pos);
-#pragma unroll
-        for (int i = 0; i < CI; i++)
-          if (i < cpt && cb + 64 * i < C) {
-            c0[pos[i]] = w0[i];
-            c1[pos[i]] = (uint16_t)w1[i];
-          }
-        __syncthreads();
-        shift += nb;
-      }
-    }
+    const int pb = bits_of(n - 1), bits = bits_of(maxl - a.min_len) + 2 * pb;
+    const int np = (bits + kMaxDigit - 1) / kMaxDigit;
+#pragma unroll 1
+    for (int p = 0; p < np; p++)
+      radix_pass<NT, 2 * IPT>(
+          rec, C, (int)((C + NT - 1) / NT), cnt, rc,
+          [=](uint64_t v) {
+            const uint64_t key = ((uint64_t)(maxl - ((uint32_t)(v >> 32) & 0xFFFFu)) << (2 * pb)) |
+                                 ((uint64_t)((uint32_t)v >> 16) << pb) | ((uint32_t)v & 0xFFFFu);
+            return (uint32_t)(key >> (p * kMaxDigit)) & (kDigits - 1u);
+          },
+          [=](uint32_t k, uint32_t r) { reinterpret_cast<uint16_t *>(rec)[4 * k + 3] = (uint16_t)r; },
+          [=](uint64_t v, uint32_t) { return (uint32_t)(v >> 48); });
   }
+  auto rstart = [=](uint32_t k) { return (uint32_t)reinterpret_cast<const uint16_t *>(rec)[4 * k]; };
+  auto rlen = [=](uint32_t k) { return (uint32_t)reinterpret_cast<const uint16_t *>(rec)[4 * k + 2]; };
+  auto same_row = [=](uint32_t k, uint32_t q) {  // equal length and ID
+    return (((rec[k] ^ rec[q]) >> 16) & 0xFFFFFFFFull) == 0;
+  };
   stamp(5);
 
   // ---- greedy selection in priority order over a bitmap of accepted
@@ -638,13 +822,14 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
   static_assert(NT <= NW * kDigits, "a chunk's survivors fit the radix counters");
   {
     uint32_t chunk = 64;
+#pragma unroll 1
     for (uint32_t p0 = 0; p0 < C; p0 += chunk, chunk = min(2 * chunk, (uint32_t)NT)) {
       const uint32_t k = p0 + tid;
       bool ok = false, dup = false;
       if (tid < chunk && k < C) {
-        const uint32_t w = c0[k], l = c1[k];
-        dup = k && c0[k - 1] == w && c1[k - 1] == l;
-        const uint32_t s = w & 0xFFFFu, e = s + l - 1u;
+        const uint64_t v = rec[k];
+        dup = k && ((rec[k - 1] ^ v) << 16) == 0;
+        const uint32_t s = (uint32_t)v & 0xFFFFu, e = s + ((uint32_t)(v >> 32) & 0xFFFFu) - 1u;
         ok = !dup && !((bitmap[s >> 5] >> (s & 31)) & 1u) && !((bitmap[e >> 5] >> (e & 31)) & 1u);
       }
       const uint64_t m = __ballot(ok), md = __ballot(dup);
@@ -654,21 +839,21 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
       }
       __syncthreads();
       uint32_t before = 0, tot = 0;
-#pragma unroll
+#pragma unroll 4
       for (int w = 0; w < NW; w++) {
         const uint32_t c = wsum[w];
         before += w < (int)wv ? c : 0u;
         tot += c;
       }
-      if (ok) surv[before + (uint32_t)__popcll(m & below)] = (uint16_t)(k - p0);
+      if (ok) surv[before + lanes_below(m)] = (uint16_t)(k - p0);
       __syncthreads();
       if (wv == 0 && tot) {
         uint32_t na = s_acc;
+#pragma unroll 1
         for (uint32_t q0 = 0; q0 < tot; q0 += 64) {
           const bool valid = q0 + lane < tot;
-          const uint32_t kk = p0 + (valid ? surv[q0 + lane] : 0u);
-          const uint32_t w = c0[kk], l = c1[kk];
-          const uint32_t s = w & 0xFFFFu, e = s + l - 1u;
+          const uint32_t kk = p0 + surv[min(q0 + lane, tot - 1)];
+          const uint32_t s = rstart(kk), e = s + rlen(kk) - 1u;
           const uint32_t ws = bitmap[s >> 5], we = bitmap[e >> 5];
           uint64_t pass = __ballot(valid && !((ws >> (s & 31)) & 1u) && !((we >> (e & 31)) & 1u));
           uint64_t take = 0;
@@ -703,7 +888,7 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
               atomicOr(&bitmap[x], msk);
             }
           }
-          if (mine) acc[na + (uint32_t)__popcll(take & below)] = (uint16_t)kk;
+          if (mine) acc[na + lanes_below(take)] = (uint16_t)kk;
           na += (uint32_t)__popcll(take);
           wave_order();
         }
@@ -713,55 +898,52 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
     }
   }
   const uint32_t A = s_acc, M = C - s_dup;
+  uint32_t nhist = 1;  // doubling rounds: up to the first that leaves nothing grouped
+  while (s_hist[nhist - 1]) nhist++;
   stamp(6);
 
   // ---- rows: occurrence o opens one when its length or ID differs from the
-  // one before; its count is the distance to the next row's first occurrence
-  uint16_t *first = reinterpret_cast<uint16_t *>(rb) + 2 * CAP;  // above the lengths
+  // one before; its count is the distance to the next opening
   uint32_t nrows = 0;
-  for (uint32_t o0 = 0; o0 < A; o0 += NT) {  // row count first
+#pragma unroll 1
+  for (uint32_t o0 = 0; o0 < A; o0 += NT) {
     const uint32_t o = o0 + tid;
-    bool nr = false;
-    if (o < A) {
-      const uint32_t k = acc[o];
-      nr = o == 0;
-      if (o) {
-        const uint32_t kp = acc[o - 1];
-        nr = c1[k] != c1[kp] || (c0[k] >> 16) != (c0[kp] >> 16);
+    const bool open = o < A && (o == 0 || !same_row(acc[o], acc[o - 1]));
+    const uint64_t m = __ballot(open);
+    if (lane == 0) {
+      if (o0 + 64 * wv < A) {
+        bitmap[(o0 >> 5) + 2 * wv] = (uint32_t)m;
+        bitmap[(o0 >> 5) + 2 * wv + 1] = (uint32_t)(m >> 32);
       }
+      atomicAdd(&s_nd, (uint32_t)__popcll(m));  // holds D until here, which all have read
     }
-    const uint64_t m = __ballot(nr);
-    if (lane == 0) wsum[wv] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t before = nrows, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NW; w++) {
-      const uint32_t c = wsum[w];
-      before += w < (int)wv ? c : 0u;
-      tot += c;
-    }
-    if (nr) first[before + (uint32_t)__popcll(m & below)] = (uint16_t)o;
-    nrows += tot;
-    __syncthreads();
   }
-  const bool fits = nrows <= a.row_cap && (!a.occ || A <= a.occ_cap);
-  if (fits) {
+  __syncthreads();
+  nrows = s_nd - D;
+  if (nrows <= a.row_cap && (!a.occ || A <= a.occ_cap)) {
     Row *rows = a.rows + (a.off ? tb / a.min_len : 0);
-    for (uint32_t r = tid; r < nrows; r += NT) {
-      const uint32_t o = first[r], k = acc[o];
-      rows[r] = Row{c0[k] & 0xFFFFu, c1[k], (r + 1 < nrows ? first[r + 1] : A) - o};
-    }
-    if (a.occ)
-      for (uint32_t o = tid; o < A; o += NT) {
-        uint32_t lo = 0, hi = nrows;  // the last row starting at or before o
-        while (hi - lo > 1) {
-          const uint32_t mid = (lo + hi) / 2;
-          if (first[mid] <= o) lo = mid;
-          else hi = mid;
-        }
-        const uint32_t k = acc[o];
-        a.occ[o] = Occ{c0[k] & 0xFFFFu, c1[k], lo};
+    uint32_t done = 0;  // openings in the words before
+#pragma unroll 1
+    for (uint32_t o0 = 0; o0 < A; o0 += NT) {
+      const uint32_t o = o0 + tid;
+      // openings up to o's word: the words of this pass below it
+      uint32_t pre = done, tot = 0;
+      for (uint32_t w = 0; w < 2 * NW && o0 + 32 * w < A; w++) {  // scalar
+        const uint32_t c = (uint32_t)__popc(bitmap[(o0 >> 5) + w]);
+        pre += w < (tid >> 5) ? c : 0u;
+        tot += c;
       }
+      done += tot;
+      if (o >= A) continue;
+      const uint32_t word = bitmap[o >> 5], k = acc[o];
+      const uint32_t r = pre + (uint32_t)__popc(word & (2u << (o & 31)) - 1u) - 1u;
+      if ((word >> (o & 31)) & 1u) {
+        uint32_t next = word & ~((2u << (o & 31)) - 1u), x = o >> 5;
+        while (!next && 32 * (x + 1) < A) next = bitmap[++x];
+        rows[r] = Row{rstart(k), rlen(k), (next ? 32 * x + (uint32_t)__ffs((int)next) - 1u : A) - o};
+      }
+      if (a.occ) a.occ[o] = Occ{rstart(k), rlen(k), r};
+    }
   }
   if (tid == 0) {
     stamp(7);
@@ -824,7 +1006,7 @@ void launch(const FusedArgs &a, uint32_t blocks, uint32_t longest, hipStream_t s
 }  // namespace
 
 void fused_window(const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows, uint32_t row_cap, void *occ,
-                  uint32_t occ_cap, FusedInfo *info, hipStream_t s) {
+                  uint32_t occ_cap, void *spill, FusedInfo *info, hipStream_t s) {
   FusedArgs a{};
   a.tok = tok;
   a.bits = bits;
@@ -834,6 +1016,7 @@ void fused_window(const void *tok, int bits, uint32_t n, uint32_t min_len, void 
   a.row_cap = row_cap;
   a.occ = static_cast<Occ *>(occ);
   a.occ_cap = occ_cap;
+  a.spill = static_cast<uint64_t *>(spill);
   a.info = info;
   launch(a, 1, n, s);
 }
@@ -870,6 +1053,7 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint32_t maxwin, uin
   a.min_len = min_len;
   a.rows = static_cast<Row *>(w.occ);  // a batch reports no occurrences: their array stages the rows
   a.row_cap = kNone;
+  a.spill = reinterpret_cast<uint64_t *>(w.crec);
   a.dcnt = w.dcnt;
   a.rhist = w.rhist;
   a.win_rows = w.win_rows;
