@@ -205,8 +205,8 @@ int apo_interval_counts_dev(apo_ctx *ctx, const uint32_t *d_len, const uint32_t 
 
 /* Per-stage device times of the last analysis (ms): token ranks, suffix
  * array, LCP, candidates, candidate sort, selection, output.  For a batch whose
- * windows are all short (at most 8192 tokens, one workgroup each) the longest
- * any window took in that stage.  Returns the number of stages written
+ * windows have a workgroup each (see apo_set_window_greedy) the longest any
+ * window took in that stage.  Returns the number of stages written
  * (<= nstages). */
 int apo_last_stage_ms(apo_ctx *ctx, double *stage_ms, int nstages);
 
@@ -214,13 +214,13 @@ int apo_last_stage_ms(apo_ctx *ctx, double *stage_ms, int nstages);
  * first-token sort included), candidates generated, candidates after dedup,
  * selection rounds, accepted occurrences, rows, sum over rounds of active
  * suffixes (the first-token sort counts every suffix), distinct tokens (for
- * a batch: summed over its windows, except that in a batch with a window of
- * more than 8192 tokens the windows with more than 4096 distinct tokens, ranked
- * through one shared table, count their union once), 1 if the selection finished with the sequential completion (else
+ * a batch: summed over its windows, except that in a batch analysed stage by
+ * stage the windows with more than 4096 distinct tokens, ranked through one
+ * shared table, count their union once), 1 if the selection finished with the sequential completion (else
  * 0), the candidates the exact prefix walk decided before the rounds (0: none),
- * and the windows whose first two doubling rounds were taken window by
- * window from ranks of their adjacent token pairs (host-driven batches whose
- * windows all have at most 4096 distinct tokens and 8192 distinct pairs).
+ * and the windows of batches (per lane) in which every window has at most 4096
+ * distinct tokens and 8192 distinct adjacent pairs, which need no doubling
+ * round over the whole batch for their first two tokens.
  * Writes min(nvals, 11) values and returns that number. */
 int apo_last_counters(apo_ctx *ctx, uint64_t *vals, int nvals);
 
@@ -247,9 +247,11 @@ int apo_inject_device_error(apo_ctx *ctx, int after_syncs);
  * (default) windows of at most 2^17 tokens in a batch, and single windows of
  * at most 2^15 tokens, are decided by one wavefront per window walking the
  * window's candidates in priority order over an on-chip bitmap; longer
- * windows use the round-based evaluation.  Windows of at most 8192 tokens
- * (alone, or in a batch of such windows) go through all stages in one
- * workgroup each.  on = 0 sends every analysis stage by stage through the
+ * windows use the round-based evaluation.  Such single windows, and batches
+ * whose windows all have at most 2^16 tokens, go through all stages in one
+ * workgroup per window, unless a window over 8192 tokens has more than 8192
+ * distinct ones, a kernel is being timed (apo_profile_kernel) or an error is to
+ * be injected.  on = 0 sends every analysis stage by stage through the
  * rounds.  Results are identical either way.  APO_EINVAL
  * unless on is 0 or 1. */
 int apo_set_window_greedy(apo_ctx *ctx, int on);

@@ -32,6 +32,7 @@ enum Cnt {
   CNT_PFLAG = 22,  // batches: windows whose pairs the per-window ranking left alone
   CNT_A1 = 23,     // batches: the first doubling round's active count, from the pair ranking
   CNT_STAGE = 24,  // batches of short windows: longest stage times (kStages words, 10 ns)
+  CNT_FUSED = 31,  // 1: the run took the one-workgroup analyses
   CNT_COUNT = 32
 };
 
@@ -158,8 +159,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
 int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t *wid, const uint32_t *wbeg,
                 uint64_t m_bound, bool host, hipStream_t s, bool window_major);
 // sel_launched: selection rounds enqueued by a sync-free run (-1: host-driven).
-// Returns 1 when a sync-free run left candidates undecided (the caller then
-// reruns host-driven).
+// Returns 1 when a sync-free run left candidates undecided, or one-workgroup
+// analyses left windows out (the caller then reruns host-driven).
 int finish_run(Workspace &w, uint64_t N, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
                bool stamps);
 

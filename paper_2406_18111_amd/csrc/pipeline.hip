@@ -276,15 +276,19 @@ static void fill_info(Workspace &w, uint64_t N, RunInfo &info) {
 int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t s, bool order) {
   APO_HIP_TRY(hipMemcpyAsync(w.d_off, h_off, (W + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
   if (!order || !W) return 0;
-  // longest first, in buckets of equal bit length (a counting sort): a long
+  // longest first, in buckets of sizes up to the same power of two (a counting sort): a long
   // window taken last would hold one workgroup while the others are idle
   // (host-driven lanes keep the given order: there other lanes fill the
   // idle compute units, and the step measured slower with it)
   uint32_t cnt[66] = {0};
-  for (uint32_t k = 0; k < W; k++) cnt[64 - bit_length_u64(h_off[k + 1] - h_off[k]) + 1]++;
+  auto bucket = [&](uint32_t k) {
+    const uint64_t n = h_off[k + 1] - h_off[k];
+    return 64 - bit_length_u64(n ? n - 1 : 0);
+  };
+  for (uint32_t k = 0; k < W; k++) cnt[bucket(k) + 1]++;
   for (int b = 1; b < 66; b++) cnt[b] += cnt[b - 1];
   w.h_order.resize(W + 1);
-  for (uint32_t k = 0; k < W; k++) w.h_order[cnt[64 - bit_length_u64(h_off[k + 1] - h_off[k])]++] = k;
+  for (uint32_t k = 0; k < W; k++) w.h_order[cnt[bucket(k)]++] = k;
   APO_HIP_TRY(hipMemcpyAsync(w.d_order, w.h_order.data(), W * sizeof(uint32_t), hipMemcpyHostToDevice, s));
   return 0;
 }
@@ -301,19 +305,24 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   uint32_t *dc = w.dcnt;
   uint64_t maxwin = 0;
   for (uint32_t k = 0; k < W; k++) maxwin = std::max<uint64_t>(maxwin, h_off[k + 1] - h_off[k]);
-  // Short windows: the whole analysis of each by one workgroup.
-  if (stop == Stop::FULL && (W > 1 || w.fuse_one) && maxwin <= kFusedMax && bits == 64 && w.win_greedy &&
+  // The whole analysis of each window by one workgroup, where every window is
+  // short enough; if some hold too many distinct tokens for that, stage by stage
+  // after all.
+  if (stop == Stop::FULL && (W > 1 || w.fuse_one) && maxwin <= kFusedLongMax && bits == 64 && w.win_greedy &&
       w.ktag == KT_NONE && w.fail_after < 0) {
     if (mode != Mode::CAPTURE)
       if ((rc = upload_windows(w, h_off, W, s, true))) return rc;
     w.pair_w = W > 1 ? W : 0;
     w.kev_n = 0;
     E.reset_counters(s);
-    fused_batch(w, d_tok, W, (uint32_t)maxwin, min_len, s);
+    fused_batch(w, static_cast<const uint64_t *>(d_tok), h_off, W, min_len, mode == Mode::CAPTURE, s);
     if (mode == Mode::CAPTURE) return 0;
     rc = finish_run(w, N, N, 1, info, s, false);
-    for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;
-    return rc;
+    if (rc != 1) {
+      for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;
+      return rc;
+    }
+    info = RunInfo{};
   }
   stamp(w, 0, s, stamps);
   if (mode != Mode::CAPTURE)  // a captured sequence expects d_off (and the order) to be uploaded already
@@ -330,6 +339,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   fill_u32(dc, CNT_RANGE, 0, s);
   fill_u32(dc + CNT_NDSUM, 8, 0, s);
   fill_u32(dc + CNT_SNAPS, 1, 0, s);
+  fill_u32(dc + CNT_FUSED, 1, 0, s);
   fill_u32(w.rhist, 4 * (uint64_t)w.nsnap, 0, s);
 
   // ---- order-preserving token ranks
@@ -687,6 +697,7 @@ int finish_run(Workspace &w, uint64_t N, uint64_t m_bound, int sel_launched, Run
   APO_HIP_TRY(hipMemcpyAsync(w.hsel, w.selcnt, 2 * (kSelRoundCap + 2) * 4, hipMemcpyDeviceToHost, s));
   if ((rc = read_counters(w, s))) return rc;
   fill_info(w, N, info);
+  if (w.hcnt[CNT_FUSED] && w.hcnt[CNT_WFLAG]) return 1;
   info.sel_rounds = 0;
   const int qmax = sel_launched < 0 ? kSelRoundCap : sel_launched;
   for (int q = 0; q < qmax; q++)

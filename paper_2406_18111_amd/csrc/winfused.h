@@ -8,28 +8,34 @@ namespace apo {
 // ranks, suffix ranks and suffix order in LDS, and its candidate sort up to two
 // records per token (16 bytes of LDS per token in all, of the 160 KB).
 constexpr uint32_t kFusedMax = 8192;
+// Longest window one workgroup takes with its arrays in the workspace (positions
+// and ranks in 16 bits, one array of them in LDS at a time).
+constexpr uint32_t kFusedLongMax = 65536;
 
 // What one window's analysis reports to the host (pinned memory).
 struct FusedInfo {
   uint32_t sigma, cands, maxl, m, accepted, rows, nhist;
+  uint32_t over;              // 1: too many distinct tokens for one workgroup, nothing else is set
   uint32_t hist[kMaxRounds];  // suffixes still grouped after each doubling round
   uint64_t stamp[kStages + 1];
 };
 
-// One window of n tokens (2 <= n <= kFusedMax, `bits` 32 or 64; device memory
-// or pinned host memory).  Rows and occurrences are written only when both
-// fit (row_cap; occ_cap unless occ is null); `info` always is.  spill: device
-// scratch of 16 bytes per token.
-void fused_window(const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows, uint32_t row_cap, void *occ,
-                  uint32_t occ_cap, void *spill, FusedInfo *info, hipStream_t s);
+// One window of n tokens (2 <= n <= kFusedLongMax, `bits` 32 or 64; device
+// memory or pinned host memory).  Rows and occurrences are written only when
+// both fit (row_cap; occ_cap unless occ is null); `info` always is.  w: scratch
+// arrays for n tokens.
+void fused_window(const Workspace &w, const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows,
+                  uint32_t row_cap, void *occ, uint32_t occ_cap, FusedInfo *info, hipStream_t s);
 
 // Copies what `info` reports into the run's info and the host mirrors of the
 // per-round counts.
 void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info);
 
-// Batch of windows of at most kFusedMax 64-bit tokens each (offsets and order in
-// w.d_off and w.d_order): rows of all windows packed in window order into
-// w.rows, counts into w.win_rows, counters where finish_run reads them.
-void fused_batch(Workspace &w, const void *tok, uint32_t W, uint32_t maxwin, uint32_t min_len, hipStream_t s);
+// Batch of windows of at most kFusedLongMax 64-bit tokens each (offsets and
+// order in w.d_off and w.d_order): rows of all windows packed in window order
+// into w.rows, counts into w.win_rows, counters where finish_run reads them.
+// Windows with too many distinct tokens are left out and counted in CNT_WFLAG.
+void fused_batch(Workspace &w, const void *tok, const uint64_t *h_off, uint32_t W, uint32_t min_len, bool capture,
+                 hipStream_t s);
 
 }  // namespace apo

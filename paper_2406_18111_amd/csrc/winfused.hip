@@ -54,6 +54,10 @@ __device__ __forceinline__ uint32_t lane_prev(uint32_t v) {
 __device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 constexpr uint32_t kOwnRanks = 4096;     // most distinct values the stage-by-stage batch ranks per window
+constexpr uint32_t kOwnPairs = 8192;     // and most distinct adjacent pairs
+constexpr int kLongRounds = 18;          // the same for windows of up to kFusedLongMax tokens
+static_assert((1u << (kLongRounds - 2)) >= kFusedLongMax && kLongRounds <= kMaxRounds, "the last round leaves nothing grouped");
+constexpr uint32_t kLongPack = 8;        // tokens in a sort key there
 constexpr int kFusedRounds = 15;         // doubling rounds of a window of up to kFusedMax tokens
 static_assert((1u << (kFusedRounds - 2)) >= kFusedMax, "the last round leaves nothing grouped");
 constexpr int kPosBits = 13;             // a suffix's position in its sort key
@@ -234,7 +238,8 @@ __device__ __forceinline__ int below8(const uint16_t *p, uint32_t c, uint32_t l)
 }
 
 // Last i < k with lcp[i] < l, or -1: climbs the levels of minima of 8 until a
-// block left of k holds one, then descends to it.
+// block left of k holds one, then descends to it.  Windows of up to CAP tokens.
+template <uint32_t CAP>
 __device__ __forceinline__ uint32_t last_smaller(const uint16_t *l0, const uint16_t *l1, const uint16_t *l2,
                                                  const uint16_t *l3, uint32_t k, uint32_t l) {
   uint32_t pos = k;
@@ -248,7 +253,7 @@ __device__ __forceinline__ uint32_t last_smaller(const uint16_t *l0, const uint1
       f += (int)lo;
       break;
     }
-    pos = lo;  // level 3 goes on down itself: 16 words at most
+    pos = lo;  // level 3 goes on down itself: CAP / 512 words at most
     if (lev < 3) {
       pos >>= 3;
       lev++;
@@ -262,6 +267,60 @@ __device__ __forceinline__ uint32_t last_smaller(const uint16_t *l0, const uint1
   return (uint32_t)f;
 }
 
+// The sequential greedy over `tot` candidates in priority order, by one
+// wavefront, 64 at a time (item(q): start | length << 16): the lowest lane with
+// no marked end is accepted and knocks out the later lanes that overlap it; the
+// accepted intervals are then marked in the bitmap.  keep(o, q): candidate q is
+// accepted occurrence o; returns the number accepted, `na` before.
+template <class Item, class Keep>
+__device__ __forceinline__ uint32_t greedy_walk(uint32_t *bitmap, uint32_t tot, uint32_t na, Item item, Keep keep) {
+  const uint32_t lane = threadIdx.x & 63;
+#pragma unroll 1
+  for (uint32_t q0 = 0; q0 < tot; q0 += 64) {
+    const bool valid = q0 + lane < tot;
+    const uint32_t v = item(min(q0 + lane, tot - 1));
+    const uint32_t s = v & 0xFFFFu, e = s + (v >> 16) - 1u;
+    const uint32_t ws = bitmap[s >> 5], we = bitmap[e >> 5];
+    uint64_t pass = __ballot(valid && !((ws >> (s & 31)) & 1u) && !((we >> (e & 31)) & 1u));
+    uint64_t take = 0;
+    while (pass) {
+      const int t = __ffsll((unsigned long long)pass) - 1;
+      const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)s, t),
+                     et = (uint32_t)__builtin_amdgcn_readlane((int)e, t);  // t is uniform
+      take |= 1ull << t;
+      pass &= ~__ballot(valid && s <= et && e >= st);
+    }
+    // intervals of a few bitmap words are painted by their own lane, longer
+    // ones by the whole wavefront
+    const bool mine = (take >> lane) & 1ull;
+    const bool own = mine && (e >> 5) - (s >> 5) < 4u;
+    if (own)
+      for (uint32_t x = s >> 5; x <= (e >> 5); x++) {
+        uint32_t msk = kNone;
+        if (x == (s >> 5)) msk &= kNone << (s & 31);
+        if (x == (e >> 5)) msk &= kNone >> (31 - (e & 31));
+        atomicOr(&bitmap[x], msk);
+      }
+    uint64_t todo = take & ~__ballot(own);
+    while (todo) {
+      const int t = __ffsll((unsigned long long)todo) - 1;
+      todo &= todo - 1;
+      const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)s, t),
+                     et = (uint32_t)__builtin_amdgcn_readlane((int)e, t);
+      for (uint32_t x = (st >> 5) + lane; x <= (et >> 5); x += 64) {
+        uint32_t msk = kNone;
+        if (x == (st >> 5)) msk &= kNone << (st & 31);
+        if (x == (et >> 5)) msk &= kNone >> (31 - (et & 31));
+        atomicOr(&bitmap[x], msk);
+      }
+    }
+    if (mine) keep(na + lanes_below(take), q0 + lane);
+    na += (uint32_t)__popcll(take);
+    wave_order();
+  }
+  return na;
+}
+
 struct Row { uint32_t start, length, count; };
 struct Occ { uint32_t start, length, cand; };
 
@@ -269,7 +328,8 @@ struct FusedArgs {
   const void *tok;
   int bits;
   const uint64_t *off;     // batch: window offsets; null: one window of n tokens
-  const uint32_t *order;   // batch: block b takes window order[b]
+  const uint32_t *order;   // batch: block b takes window order[b] if it has over `above` and up to `most` tokens
+  uint32_t above, most;
   uint32_t n, min_len;
   Row *rows;               // one window: final; batch: window w's rows start at off[w] / min_len
   Occ *occ;
@@ -278,6 +338,42 @@ struct FusedArgs {
   FusedInfo *info;         // one window
   uint32_t *dcnt, *rhist, *win_rows;  // batch: counters added up over the windows
 };
+
+// What a window's analysis found, to the host (one window) or added to the
+// batch's counters.  own: distinct tokens without the largest value.
+struct Report { uint32_t sigma, own, cands, skipped, maxl, m, accepted, rows, pairs, nhist; };
+
+__device__ __forceinline__ void report(const FusedArgs &a, uint32_t win, const Report &r, const uint32_t *hist,
+                                       const uint64_t *stamp) {
+  if (a.info) {
+    FusedInfo &f = *a.info;
+    f.sigma = a.bits == 64 ? r.sigma : 0u;
+    f.cands = r.cands + r.skipped;
+    f.maxl = r.maxl;
+    f.m = r.m;
+    f.accepted = r.accepted;
+    f.rows = r.rows;
+    f.nhist = r.nhist;
+    f.over = 0;
+    for (uint32_t k = 0; k < r.nhist; k++) f.hist[k] = hist[k];
+    for (int k = 0; k <= kStages; k++) f.stamp[k] = stamp[k];
+    return;
+  }
+  a.win_rows[win] = r.rows;
+  atomicAdd(&a.dcnt[CNT_NDSUM], r.sigma);
+  atomicMax(&a.dcnt[CNT_NDMAX], r.sigma);
+  atomicAdd(&a.dcnt[CNT_C], r.cands);
+  atomicAdd(&a.dcnt[CNT_CSKIP], r.skipped);
+  atomicMax(&a.dcnt[CNT_MAXL], r.maxl);
+  atomicAdd(&a.dcnt[CNT_M], r.m);
+  atomicAdd(&a.dcnt[CNT_A], r.accepted);
+  atomicAdd(&a.dcnt[CNT_NROWS], r.rows);
+  // past the bounds of the stage-by-stage batch's per-window ranks and pair ranks
+  if (r.own > kOwnRanks || r.pairs > kOwnPairs) atomicAdd(&a.dcnt[CNT_PFLAG], 1u);
+  for (uint32_t k = 0; k < r.nhist; k++)
+    if (hist[k]) atomicAdd(&a.rhist[4 * k], hist[k]);
+  for (int k = 0; k < kStages; k++) atomicMax(&a.dcnt[CNT_STAGE + k], (uint32_t)(stamp[k + 1] - stamp[k]));
+}
 
 // NT threads, up to NT * IPT tokens.
 template <int NT, int IPT>
@@ -308,13 +404,14 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
     win = a.order[blockIdx.x];
     tb = a.off[win] - a.off[0];
     n = (uint32_t)(a.off[win + 1] - a.off[win]);
-    if (n < 2) {  // uniform
+    if (n < 2 && a.above == 0) {  // uniform
       if (tid == 0) {
         a.win_rows[win] = 0;
         atomicAdd(&a.dcnt[CNT_NDSUM], n);
       }
       return;
     }
+    if (n <= a.above || n > a.most) return;  // another launch's
   }
   auto stamp = [&](int k) {
     if (tid == 0) s_stamp[k] = wall_clock64();
@@ -757,7 +854,7 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
       }
       const uint64_t m2 = __ballot(l != 0), m1 = __ballot(l != 0 && !rep);
       if (!m2) continue;  // scalar
-      const uint64_t id = l ? 1u + last_smaller(lcp, min1, min2, min3, k, l) : 0u;
+      const uint64_t id = l ? 1u + last_smaller<CAP>(lcp, min1, min2, min3, k, l) : 0u;
       // records in any order: the sort's key tells all but duplicates apart
       uint32_t q = 0;
       if (lane == 0) {
@@ -848,50 +945,13 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
       if (ok) surv[before + lanes_below(m)] = (uint16_t)(k - p0);
       __syncthreads();
       if (wv == 0 && tot) {
-        uint32_t na = s_acc;
-#pragma unroll 1
-        for (uint32_t q0 = 0; q0 < tot; q0 += 64) {
-          const bool valid = q0 + lane < tot;
-          const uint32_t kk = p0 + surv[min(q0 + lane, tot - 1)];
-          const uint32_t s = rstart(kk), e = s + rlen(kk) - 1u;
-          const uint32_t ws = bitmap[s >> 5], we = bitmap[e >> 5];
-          uint64_t pass = __ballot(valid && !((ws >> (s & 31)) & 1u) && !((we >> (e & 31)) & 1u));
-          uint64_t take = 0;
-          while (pass) {
-            const int t = __ffsll((unsigned long long)pass) - 1;
-            const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)s, t),
-                           et = (uint32_t)__builtin_amdgcn_readlane((int)e, t);  // t is uniform
-            take |= 1ull << t;
-            pass &= ~__ballot(valid && s <= et && e >= st);
-          }
-          // intervals of a few bitmap words are painted by their own lane,
-          // longer ones by the whole wavefront
-          const bool mine = (take >> lane) & 1ull;
-          const bool own = mine && (e >> 5) - (s >> 5) < 4u;
-          if (own)
-            for (uint32_t x = s >> 5; x <= (e >> 5); x++) {
-              uint32_t msk = kNone;
-              if (x == (s >> 5)) msk &= kNone << (s & 31);
-              if (x == (e >> 5)) msk &= kNone >> (31 - (e & 31));
-              atomicOr(&bitmap[x], msk);
-            }
-          uint64_t todo = take & ~__ballot(own);
-          while (todo) {
-            const int t = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1;
-            const uint32_t st = (uint32_t)__builtin_amdgcn_readlane((int)s, t),
-                           et = (uint32_t)__builtin_amdgcn_readlane((int)e, t);
-            for (uint32_t x = (st >> 5) + lane; x <= (et >> 5); x += 64) {
-              uint32_t msk = kNone;
-              if (x == (st >> 5)) msk &= kNone << (st & 31);
-              if (x == (et >> 5)) msk &= kNone >> (31 - (et & 31));
-              atomicOr(&bitmap[x], msk);
-            }
-          }
-          if (mine) acc[na + lanes_below(take)] = (uint16_t)kk;
-          na += (uint32_t)__popcll(take);
-          wave_order();
-        }
+        const uint32_t na = greedy_walk(
+            bitmap, tot, s_acc,
+            [=](uint32_t q) {
+              const uint32_t k = p0 + surv[q];
+              return rstart(k) | (rlen(k) << 16);
+            },
+            [=](uint32_t o, uint32_t q) { acc[o] = (uint16_t)(p0 + surv[q]); });
         if (lane == 0) s_acc = na;
       }
       __syncthreads();
@@ -947,34 +1007,670 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
   }
   if (tid == 0) {
     stamp(7);
-    if (a.info) {
-      FusedInfo &f = *a.info;
-      f.sigma = a.bits == 64 ? D : 0u;
-      f.cands = C + s_skip;
-      f.maxl = maxl;
-      f.m = M;
-      f.accepted = A;
-      f.rows = nrows;
-      f.nhist = nhist;
-      for (uint32_t r = 0; r < nhist; r++) f.hist[r] = s_hist[r];
-      for (int k = 0; k <= kStages; k++) f.stamp[k] = s_stamp[k];
-    } else {
-      a.win_rows[win] = nrows;
-      atomicAdd(&a.dcnt[CNT_NDSUM], D);
-      atomicMax(&a.dcnt[CNT_NDMAX], D);
-      atomicAdd(&a.dcnt[CNT_C], C);
-      atomicAdd(&a.dcnt[CNT_CSKIP], s_skip);
-      atomicMax(&a.dcnt[CNT_MAXL], maxl);
-      atomicAdd(&a.dcnt[CNT_M], M);
-      atomicAdd(&a.dcnt[CNT_A], A);
-      atomicAdd(&a.dcnt[CNT_NROWS], nrows);
-      // a window whose ranks the stage-by-stage batch takes from the shared table
-      if (D - s_top > kOwnRanks) atomicAdd(&a.dcnt[CNT_PFLAG], 1u);
-      for (uint32_t r = 0; r < nhist; r++)
-        if (s_hist[r]) atomicAdd(&a.rhist[4 * r], s_hist[r]);
-      for (int k = 0; k < kStages; k++)
-        atomicMax(&a.dcnt[CNT_STAGE + k], (uint32_t)(s_stamp[k + 1] - s_stamp[k]));
+    // at most 8192 distinct pairs in a window of 8192 tokens
+    report(a, win, Report{D, D - s_top, C, s_skip, maxl, M, A, nrows, 0, nhist}, s_hist, s_stamp);
+  }
+}
+
+// ------------------------------------------------------------ longer windows
+// The same analysis by one workgroup for windows of up to kFusedLongMax tokens:
+// LDS holds the one array that a stage reads at random (token ranks, suffix
+// ranks or LCP values, two bytes per token), the others pass through the
+// window's share of the workspace, in order or scattered within it, which one
+// L2 holds.
+constexpr int kLongNT = 1024, kLongNW = kLongNT / 64;
+constexpr int kByte = 256;                    // radix digits of 8 bits
+constexpr uint32_t kLongSlots = 16384;        // hash table of the distinct tokens
+constexpr uint32_t kLongDistinct = 8192;      // most distinct tokens (the largest value aside)
+constexpr uint64_t kFree = ~0ull;
+
+struct LongArgs {
+  FusedArgs f;
+  uint16_t *txt, *sa, *rank, *lcp;  // two bytes per token, four bytes apart per window: base + 2 * offset
+  uint64_t *e0, *e1;                // two words per token
+  uint64_t *flags;                  // one word per token (n / 32 of them used)
+};
+
+// Counts of a wavefront's items [beg, end) by digit, into its row of ctr.
+template <class Get, class Digit>
+__device__ __forceinline__ void byte_count(uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit) {
+  const uint32_t lane = threadIdx.x & 63;
+#pragma unroll 1
+  for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
+    decltype(get(0u)) v[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) v[u] = get(min(q0 + 64 * u + lane, end - 1));
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      if (q0 + 64 * u + lane < end) atomicAdd(&my[digit(v[u])], 1u);
+  }
+}
+
+// Rows of counts into first places: digit by digit, wavefront by wavefront.
+__device__ __forceinline__ void byte_scan(uint32_t *ctr, uint32_t *wsum) {
+  const uint32_t tid = threadIdx.x, wv = wave_id();
+  __syncthreads();
+  uint32_t tot = 0, inc = 0;
+  if (wv < kByte / 64) {
+#pragma unroll 4
+    for (int w = 0; w < kLongNW; w++) tot += ctr[w * kByte + tid];
+    inc = lane_incl_sum(tot);
+    if ((tid & 63) == 63) wsum[wv] = inc;
+  }
+  __syncthreads();
+  if (wv < kByte / 64) {
+    uint32_t base = inc - tot;
+    for (uint32_t w = 0; w < wv; w++) base += wsum[w];
+#pragma unroll 4
+    for (int w = 0; w < kLongNW; w++) {
+      const uint32_t c = ctr[w * kByte + tid];
+      ctr[w * kByte + tid] = base;
+      base += c;
     }
+  }
+  __syncthreads();
+}
+
+// Stable scatter of a wavefront's items by digit: put(place, item).
+template <class Get, class Digit, class Put>
+__device__ __forceinline__ void byte_scatter(uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit, Put put) {
+  const uint32_t lane = threadIdx.x & 63;
+#pragma unroll 1
+  for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
+    decltype(get(0u)) v[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) v[u] = get(min(q0 + 64 * u + lane, end - 1));
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const uint32_t q = q0 + 64 * u;
+      if (q >= end) continue;  // scalar
+      const uint32_t d = digit(v[u]);
+      const uint64_t in = first_lanes(end - q);
+      uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
+#pragma unroll
+      for (int b = 0; b < 8; b++) {
+        const int t = __builtin_amdgcn_sbfe((int)d, b, 1);  // 0 or -1
+        const uint64_t one = __builtin_amdgcn_ballot_w64(t != 0);
+        lo &= ~((uint32_t)one ^ (uint32_t)t);
+        hi &= ~((uint32_t)(one >> 32) ^ (uint32_t)t);
+      }
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+      const uint32_t prev = my[d];
+      wave_order();  // every lane has read before the first one of each digit writes
+      if (q + lane < end) {
+        if (before == 0) my[d] = prev + (uint32_t)__popc(lo) + (uint32_t)__popc(hi);
+        put(prev + before, v[u]);
+      }
+      wave_order();
+    }
+  }
+}
+
+__global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
+  constexpr int NT = kLongNT, NW = kLongNW;
+  constexpr uint32_t CAP = kFusedLongMax;
+  const FusedArgs &a = la.f;
+  // one after the other: the distinct tokens' table, their sorted list (64 KB)
+  // and ranks by slot; token ranks; suffix ranks; token ranks; LCP values; the
+  // survivors of a chunk of candidates
+  __shared__ __align__(16) unsigned char big[CAP * 2];
+  __shared__ __align__(16) uint32_t ctr[NW * kByte];   // radix counters; LCP minima of 8
+  __shared__ __align__(16) uint32_t bitmap[CAP / 32 + 2];  // as in k_window; LCP minima of 64 and 512
+  __shared__ uint32_t wsum[NW], wsum2[NW];
+  __shared__ uint32_t s_nd, s_top, s_over, s_zero, s_active, s_max, s_skip, s_c, s_acc, s_dup, s_pairs;
+  __shared__ uint32_t s_hist[kLongRounds];
+  __shared__ uint64_t s_stamp[kStages + 1];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wv = wave_id();
+  const uint64_t below = (1ull << lane) - 1ull;
+
+  uint32_t win = 0, n = a.n;
+  uint64_t tb = 0;
+  if (a.off) {
+    win = a.order[blockIdx.x];
+    tb = a.off[win] - a.off[0];
+    n = (uint32_t)(a.off[win + 1] - a.off[win]);
+    if (n <= a.above || n > a.most) return;  // uniform: another launch's
+  }
+  uint16_t *const gtxt = la.txt + 2 * tb, *const gsa = la.sa + 2 * tb, *const grank = la.rank + 2 * tb,
+                 *const glcp = la.lcp + 2 * tb;
+  uint64_t *const e0 = la.e0 + 2 * tb, *const e1 = la.e1 + 2 * tb, *const fl = la.flags + tb;
+  auto stamp = [&](int k) {
+    if (tid == 0) s_stamp[k] = wall_clock64();
+  };
+  stamp(0);
+  // a wavefront's share of m items, in order
+  auto seg = [](uint32_t m) { return ((m + 64 * kLongNW - 1) / (64 * kLongNW)) * 64; };
+  uint32_t *const my = ctr + wv * kByte;
+  auto clear_row = [&] {
+    *reinterpret_cast<uint4 *>(my + 4 * lane) = make_uint4(0, 0, 0, 0);
+    wave_order();
+  };
+
+  // ---- token ranks: distinct values through an LDS hash table of the values
+  // (the largest one, which marks free slots, aside), sorted in LDS
+  {
+    unsigned long long *tab = reinterpret_cast<unsigned long long *>(big);
+    uint16_t *const slot = reinterpret_cast<uint16_t *>(e0);      // of every token
+    uint16_t *const dslot = reinterpret_cast<uint16_t *>(e1 + n);  // of every distinct value
+    if (tid == 0) s_nd = s_top = s_over = s_skip = s_max = s_c = s_acc = s_dup = s_pairs = 0;
+    if (tid < kLongRounds) s_hist[tid] = 0;
+    for (uint32_t k = 2 * tid; k < kLongSlots; k += 2 * NT) *reinterpret_cast<ulonglong2 *>(tab + k) = make_ulonglong2(kFree, kFree);
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t k0 = tid; k0 < n; k0 += 8 * NT) {
+      uint64_t v[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const uint64_t k = tb + min(k0 + u * NT, n - 1);
+        v[u] = a.bits == 64 ? static_cast<const uint64_t *>(a.tok)[k] : (uint64_t) static_cast<const uint32_t *>(a.tok)[k];
+      }
+      if (*(volatile uint32_t *)&s_over) break;  // this window is not for this kernel
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        if (k0 + u * NT >= n) break;
+        const uint64_t key = v[u];
+        uint32_t at = (uint32_t)(mix64(key) >> 40) & (kLongSlots - 1);
+        if (key == kFree) {
+          s_top = 1;
+          at = kLongSlots;
+        } else {
+          for (int probe = 0;; probe++) {
+            if (probe == (int)kLongSlots) {  // full (only past the limit)
+              s_over = 1;
+              break;
+            }
+            unsigned long long cur = tab[at];
+            if (cur == kFree) {
+              cur = atomicCAS(&tab[at], (unsigned long long)kFree, (unsigned long long)key);
+              if (cur == kFree) {
+                const uint32_t q = atomicAdd(&s_nd, 1u);
+                if (q < kLongDistinct) {
+                  e1[q] = key;
+                  dslot[q] = (uint16_t)at;
+                } else {
+                  s_over = 1;
+                }
+                break;
+              }
+            }
+            if (cur == key) break;
+            at = (at + 1) & (kLongSlots - 1);
+          }
+        }
+        slot[k0 + u * NT] = (uint16_t)at;
+      }
+    }
+    __syncthreads();
+    if (s_over) {  // uniform: left to the stage-by-stage analysis
+      if (tid == 0) {
+        if (a.info) a.info->over = 1;
+        else {
+          a.win_rows[win] = 0;
+          atomicAdd(&a.dcnt[CNT_WFLAG], 1u);
+        }
+      }
+      return;
+    }
+  }
+  const uint32_t nd = s_nd, top = s_top, D = nd + top;
+  {
+    uint64_t *sorted = reinterpret_cast<uint64_t *>(big);
+    uint16_t *srank = reinterpret_cast<uint16_t *>(big + kLongDistinct * 8);  // by slot
+    uint16_t *const slot = reinterpret_cast<uint16_t *>(e0), *const dslot = reinterpret_cast<uint16_t *>(e1 + n);
+    constexpr int R = kLongDistinct / NT;
+    uint64_t x[R];
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      const uint32_t q = tid * R + i;
+      x[i] = q < nd ? e1[q] : ~0ull;
+    }
+    merge_sort<NT, R>(x, sorted, nd);  // the table's last reads are a barrier behind
+#pragma unroll 1
+    for (uint32_t q = tid; q < nd; q += NT) {
+      const uint64_t key = e1[q];
+      uint32_t lo = 0, hi = nd - 1;  // sorted[lo .. hi] holds it
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (sorted[spread<R>(mid)] < key) lo = mid + 1;
+        else hi = mid;
+      }
+      srank[dslot[q]] = (uint16_t)(lo + 1);
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (uint32_t k = tid; k < n; k += NT) {
+      const uint32_t at = slot[k];
+      gtxt[k] = (uint16_t)(at == kLongSlots ? D : srank[at]);
+    }
+    __syncthreads();
+  }
+  auto load_lds = [&](const uint16_t *from) {  // n words, four a lane (windows start 4-byte aligned: two 4-byte loads)
+    uint32_t *to = reinterpret_cast<uint32_t *>(big);
+    const uint32_t *g = reinterpret_cast<const uint32_t *>(from);
+#pragma unroll 4
+    for (uint32_t k = tid; k < (n + 1) / 2; k += NT) to[k] = g[k];
+    __syncthreads();
+  };
+  uint16_t *const txt = reinterpret_cast<uint16_t *>(big);
+  load_lds(gtxt);
+  stamp(1);
+
+  // ---- suffix array: every suffix sorted by its first h tokens, as many as fit
+  // above its position in a 64-bit word (kLongPack at most), by a radix sort
+  const int tbits = bits_of(D);
+  uint32_t h = min((uint32_t)(48 / tbits), kLongPack);
+  const uint32_t wbeg = min(wv * seg(n), n), wtop = min(wbeg + seg(n), n);  // the wavefront's tokens and slots
+  {
+    auto key_of = [&](uint32_t j) {
+      uint64_t key = 0;
+#pragma unroll 1
+      for (uint32_t q = 0; q < h; q++) key = (key << tbits) | (j + q < n ? txt[j + q] : 0u);
+      return (key << 16) | j;
+    };
+    const int np = ((int)h * tbits + 7) / 8;
+    uint64_t *src = e0, *dst = e1;
+    for (uint32_t k = wbeg + lane; k < wtop; k += 64) src[k] = key_of(k);  // read back by the same wavefront
+#pragma unroll 1
+    for (int p = 0; p < np; p++) {
+      const int sh = 16 + 8 * p;
+      auto get = [=](uint32_t k) { return src[k]; };
+      auto dig = [=](uint64_t v) { return (uint32_t)(v >> sh) & 255u; };
+      clear_row();
+      byte_count(my, wbeg, wtop, get, dig);
+      byte_scan(ctr, wsum);
+      uint64_t *to = dst;
+      byte_scatter(my, wbeg, wtop, get, dig, [=](uint32_t at, uint64_t v) { to[at] = v; });
+      __syncthreads();
+      dst = src;
+      src = to;
+    }
+    // groups: a bitmap of the slots that open one (slot n counts as one)
+#pragma unroll 1
+    for (uint32_t k0 = wbeg; k0 < wtop; k0 += 64) {  // scalar
+      const uint32_t k = min(k0 + lane, n - 1);
+      const uint64_t key = src[k], prev = src[k ? k - 1 : 0];
+      const uint32_t j = (uint32_t)key & 0xFFFFu;
+      if (k0 + lane < n) gsa[k] = (uint16_t)j;
+      if (j == 0) s_zero = k;
+      const uint64_t hd = __ballot(k0 + lane == 0 || k0 + lane >= n || (prev >> 16) != (key >> 16));
+      if (lane == 0) {
+        bitmap[k0 >> 5] = (uint32_t)hd;
+        bitmap[(k0 >> 5) + 1] = (uint32_t)(hd >> 32);
+      }
+    }
+    if (tid == 0 && n % 64 == 0) bitmap[n >> 5] = 1;
+    __syncthreads();
+  }
+  uint16_t *const rank = reinterpret_cast<uint16_t *>(big);  // rank[j]: the first slot of j's group
+#pragma unroll 4
+  for (uint32_t k = tid; k < n; k += NT) {
+    uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
+    while (!w) w = bitmap[--x];  // slot 0 opens a group
+    rank[gsa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
+  }
+  uint32_t active;
+  auto survey = [&] {
+    if (tid == 0) s_active = 0;
+    __syncthreads();
+    uint32_t more = 0;
+    for (uint32_t x = tid; 32 * x < n; x += NT) {
+      const uint32_t w = bitmap[x], up = 32 * x + 32 <= n ? bitmap[x + 1] : kNone;
+      more += (uint32_t)__popc(~(w & ((w >> 1) | (up << 31))) & (uint32_t)first_lanes(n - 32 * x));
+    }
+    more = lane_incl_sum(more);
+    if (lane == 63 && more) atomicAdd(&s_active, more);
+    __syncthreads();
+    active = s_active;
+  };
+  survey();
+
+  // Prefix doubling of the suffixes still grouped, listed in the order of their
+  // second halves and sorted stably by the group of the first half (k_window's
+  // second form): j | group << 16
+  {
+    uint32_t *const l0 = reinterpret_cast<uint32_t *>(e0), *const l1 = reinterpret_cast<uint32_t *>(e1);
+#pragma unroll 1
+    while (active) {  // uniform
+      const uint32_t first = s_zero, m = active;
+      uint32_t mine = 0;
+      clear_row();
+#pragma unroll 1
+      for (uint32_t k0 = wbeg; k0 < wtop; k0 += 256) {  // scalar
+        uint32_t s[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+          const uint32_t k = min(k0 + 64 * u + lane, n - 1);
+          s[u] = gsa[k == 0 ? first : k <= first ? k - 1 : k];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+          if (k0 + 64 * u >= wtop) continue;  // scalar
+          const uint32_t j = s[u] >= h ? s[u] - h : s[u] + n - h;
+          const uint32_t g = rank[j];
+          const uint64_t mk =
+              __ballot(!((bitmap[(g + 1) >> 5] >> ((g + 1) & 31)) & 1u)) & first_lanes(wtop - k0 - 64 * u);
+          if ((mk >> lane) & 1ull) {
+            l0[wbeg + mine + lanes_below(mk)] = j | (g << 16);
+            atomicAdd(&my[g & 255u], 1u);
+          }
+          mine += (uint32_t)__popcll(mk);
+        }
+      }
+      byte_scan(ctr, wsum);
+      byte_scatter(
+          my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, [](uint32_t e) { return (e >> 16) & 255u; },
+          [=](uint32_t at, uint32_t e) { l1[at] = e; });
+      __syncthreads();
+      const uint32_t qbeg = min(wv * seg(m), m), qtop = min(qbeg + seg(m), m);
+      auto get = [=](uint32_t q) { return l1[q]; };
+      auto dig = [](uint32_t e) { return e >> 24; };
+      clear_row();
+      byte_count(my, qbeg, qtop, get, dig);
+      byte_scan(ctr, wsum);
+      byte_scatter(my, qbeg, qtop, get, dig, [=](uint32_t at, uint32_t e) { l0[at] = e; });
+      __syncthreads();
+      // openings of old and new groups among the sorted entries
+      uint32_t lo = kNone, ln = kNone;
+#pragma unroll 1
+      for (uint32_t q0 = qbeg; q0 < qtop; q0 += 256) {  // scalar
+        uint32_t e[4], p[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+          const uint32_t q = min(q0 + 64 * u + lane, m - 1);
+          e[u] = l0[q];
+          p[u] = l0[q ? q - 1 : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+          const uint32_t c0 = q0 + 64 * u, q = c0 + lane;
+          if (c0 >= qtop) continue;  // scalar
+          const uint32_t s = (e[u] & 0xFFFFu) + h, t = (p[u] & 0xFFFFu) + h;
+          const uint32_t r = rank[min(s, n - 1)], z = rank[min(t, n - 1)];
+          const bool og = q == 0 || q >= m || (e[u] >> 16) != (p[u] >> 16);
+          // the empty second half (one past the end) sorts first and alone
+          const bool ng = og || (s < n) != (t < n) || (s < n && r != z);
+          const uint64_t mo = __ballot(og), mn = __ballot(ng), in = first_lanes(qtop - c0);
+          if (lane == 0) {
+            fl[2 * (c0 >> 6)] = mo;
+            fl[2 * (c0 >> 6) + 1] = mn;
+          }
+          if (mo & in) lo = c0 + 63u - (uint32_t)__clzll((long long)(mo & in));
+          if (mn & in) ln = c0 + 63u - (uint32_t)__clzll((long long)(mn & in));
+        }
+      }
+      if (lane == 0) {
+        wsum[wv] = lo;
+        wsum2[wv] = ln;
+      }
+      __syncthreads();
+      uint32_t co = 0, cn = 0;
+      for (uint32_t w = 0; w < wv; w++) {
+        if (wsum[w] != kNone) co = wsum[w];
+        if (wsum2[w] != kNone) cn = wsum2[w];
+      }
+#pragma unroll 1
+      for (uint32_t q0 = qbeg; q0 < qtop; q0 += 64) {  // scalar
+        const uint32_t q = q0 + lane, e = l0[min(q, m - 1)];
+        const uint64_t in = first_lanes(qtop - q0);
+        const uint64_t og = fl[2 * (q0 >> 6)] & in, ng = fl[2 * (q0 >> 6) + 1] & in, upto = below | (1ull << lane);
+        if (q < qtop) {
+          const uint64_t uo = og & upto, un = ng & upto;
+          const uint32_t ob = uo ? q0 + 63u - (uint32_t)__clzll((long long)uo) : co;
+          const uint32_t nb = un ? q0 + 63u - (uint32_t)__clzll((long long)un) : cn;
+          const uint32_t j = e & 0xFFFFu, g = e >> 16, slot = g + (q - ob);
+          gsa[slot] = (uint16_t)j;
+          rank[j] = (uint16_t)(g + (nb - ob));
+          if (nb == q) atomicOr(&bitmap[slot >> 5], 1u << (slot & 31));
+          if (j == 0) s_zero = slot;
+        }
+        if (og) co = q0 + 63u - (uint32_t)__clzll((long long)og);
+        if (ng) cn = q0 + 63u - (uint32_t)__clzll((long long)ng);
+      }
+      h *= 2;
+      survey();  // its first barrier ends the writes above
+    }
+  }
+  {
+    const uint32_t *from = reinterpret_cast<const uint32_t *>(big);
+    uint32_t *g = reinterpret_cast<uint32_t *>(grank);
+    for (uint32_t k = tid; k < (n + 1) / 2; k += NT) g[k] = from[k];
+    __syncthreads();
+  }
+  stamp(2);
+
+  // ---- LCP: Kasai's walk as in k_window, over the token ranks
+  load_lds(gtxt);
+  {
+    const uint32_t per = (n + NT - 1) / NT;
+    uint32_t l = 0;
+#pragma unroll 1
+    for (uint32_t x = tid * per; x < tid * per + per && x < n; x++) {
+      const uint32_t r = grank[x];
+      if (r == 0) {
+        l = 0;
+        continue;
+      }
+      const uint32_t y = gsa[r - 1], lim = n - (x > y ? x : y);
+      while (l + 8 <= lim) {
+        uint64_t p0, p1, q0, q1;
+        __builtin_memcpy(&p0, txt + x + l, 8);
+        __builtin_memcpy(&q0, txt + y + l, 8);
+        __builtin_memcpy(&p1, txt + x + l + 4, 8);
+        __builtin_memcpy(&q1, txt + y + l + 4, 8);
+        const uint64_t d0 = p0 ^ q0, d1 = p1 ^ q1;
+        if (d0 | d1) break;
+        l += 8;
+      }
+      while (l < lim && txt[x + l] == txt[y + l]) l++;  // at most 7 equal ones
+      glcp[r - 1] = (uint16_t)l;
+      l = l ? l - 1 : 0;
+    }
+    if (tid == 0) glcp[n - 1] = 0;
+  }
+  __syncthreads();
+  uint16_t *const lcp = reinterpret_cast<uint16_t *>(big);
+  load_lds(glcp);
+  uint16_t *const min1 = reinterpret_cast<uint16_t *>(ctr), *const min2 = reinterpret_cast<uint16_t *>(bitmap),
+                 *const min3 = min2 + CAP / 64;
+  static_assert(CAP / 8 * 2 <= sizeof(ctr) && (CAP / 64 + CAP / 64) * 2 <= sizeof(bitmap), "minima fit");
+  if (tid < 8 && n + tid < ((n + 7) & ~7u)) lcp[n + tid] = 0xFFFF;
+  for (uint32_t b = tid; b < CAP / 8; b += NT) min1[b] = 0xFFFF;
+  for (uint32_t b = tid; b < CAP / 32; b += NT) min2[b] = 0xFFFF;
+  __syncthreads();
+  stamp(3);
+
+  // ---- candidates, as in k_window
+  for (uint32_t b = tid; b < (n + 7) / 8; b += NT) min1[b] = (uint16_t)min8(lcp + 8 * b);
+  __syncthreads();
+  for (uint32_t b = tid; b < (n + 63) / 64; b += NT) min2[b] = (uint16_t)min8(min1 + 8 * b);
+  __syncthreads();
+  for (uint32_t b = tid; b < (n + 511) / 512; b += NT) min3[b] = (uint16_t)min8(min2 + 8 * b);
+  __syncthreads();
+  {
+    uint32_t mx = 0, pairs = 0;
+#pragma unroll 1
+    for (uint32_t k0 = wbeg; k0 < wtop; k0 += 64) {  // scalar
+      const uint32_t k = k0 + lane;
+      uint32_t l = 0, s1 = 0, s2 = 0, both = 0, pp = 0;
+      bool rep = false;
+      if (k < n) {
+        const uint32_t x = gsa[k], y = k + 1 < n ? gsa[k + 1] : x, p = lcp[k], w = k ? gsa[k - 1] : x;
+        pp = k ? lcp[k - 1] : 0u;
+        both = max(p, pp);
+        const uint32_t lo = min(x, y), d = max(x, y) - lo;
+        const bool disj = p <= d;
+        if (disj) {
+          l = p;
+          s1 = x;
+          s2 = y;
+        } else {
+          l = (p + d) / 2;
+          l -= l % d;
+          s1 = lo;
+          s2 = lo + l;
+        }
+        if (l < a.min_len || k + 1 == n) l = 0;
+        rep = l && disj && k && pp == l && pp <= max(x, w) - min(x, w);
+      }
+#pragma unroll 1
+      for (int r = 0; r < kLongRounds; r++) {
+        const uint64_t g = __ballot(both >> r);
+        if (!g) break;  // scalar
+        if (lane == 0) atomicAdd(&s_hist[r], (uint32_t)__popcll(g));
+      }
+      pairs += (uint32_t)__popcll(__ballot(k < n && pp < 2));  // first of its two-token prefix
+      const uint64_t m2 = __ballot(l != 0), m1 = __ballot(l != 0 && !rep);
+      if (!m2) continue;  // scalar
+      const uint64_t id = l ? 1u + last_smaller<CAP>(lcp, min1, min2, min3, k, l) : 0u;
+      uint32_t q = 0;
+      if (lane == 0) {
+        q = atomicAdd(&s_c, (uint32_t)(__popcll(m1) + __popcll(m2)));
+        atomicAdd(&s_skip, (uint32_t)(__popcll(m2) - __popcll(m1)));
+      }
+      q = (uint32_t)__builtin_amdgcn_readfirstlane((int)q) + lanes_below(m1) + lanes_below(m2);
+      if (l) {
+        const uint64_t head = (id << 16) | ((uint64_t)l << 32);
+        if (!rep) e0[q++] = head | s1;
+        e0[q] = head | s2;
+      }
+      mx = max(mx, l);
+    }
+    mx = lane_max(mx);
+    if (lane == 63 && mx) atomicMax(&s_max, mx);
+    if (lane == 0) atomicAdd(&s_pairs, pairs);
+  }
+  __syncthreads();
+  const uint32_t C = s_c, maxl = s_max;
+  stamp(4);
+
+  // ---- priority order: radix sort by (maxl - length, ID, start)
+  const uint64_t *rec = e0;
+  uint64_t *accs = e1;  // accepted records
+  if (C) {  // uniform
+    const int pb = bits_of(n - 1), bits = bits_of(maxl - a.min_len) + 2 * pb, np = (bits + 7) / 8;
+    const uint32_t cbeg = min(wv * seg(C), C), ctop = min(cbeg + seg(C), C);
+    uint64_t *src = e0, *dst = e1;
+#pragma unroll 1
+    for (int p = 0; p < np; p++) {
+      auto get = [=](uint32_t k) { return src[k]; };
+      auto dig = [=](uint64_t v) {
+        const uint64_t key = ((uint64_t)(maxl - (uint32_t)(v >> 32)) << (2 * pb)) |
+                             ((uint64_t)((uint32_t)v >> 16) << pb) | ((uint32_t)v & 0xFFFFu);
+        return (uint32_t)(key >> (8 * p)) & 255u;
+      };
+      clear_row();
+      byte_count(my, cbeg, ctop, get, dig);
+      byte_scan(ctr, wsum);
+      uint64_t *to = dst;
+      byte_scatter(my, cbeg, ctop, get, dig, [=](uint32_t at, uint64_t v) { to[at] = v; });
+      __syncthreads();
+      dst = src;
+      src = to;
+    }
+    rec = src;
+    accs = dst;
+  }
+  for (uint32_t k = tid; k < (n + 31) / 32; k += NT) bitmap[k] = 0;
+  __syncthreads();
+  stamp(5);
+
+  // ---- greedy selection, as in k_window; the survivors' intervals and numbers
+  // go to LDS
+  {
+    uint32_t *const item = reinterpret_cast<uint32_t *>(big), *const num = item + NT;
+    uint32_t chunk = 64;
+    uint64_t v = rec[min(tid, C ? C - 1 : 0)], pv = tid ? rec[min(tid, C) - (C ? 1 : 0)] : 0;
+#pragma unroll 1
+    for (uint32_t p0 = 0; p0 < C; p0 += chunk, chunk = min(2 * chunk, (uint32_t)NT)) {
+      const uint32_t k = p0 + tid, nx = min(p0 + chunk + tid, C - 1);
+      const uint64_t nv = rec[nx], npv = rec[nx ? nx - 1 : 0];  // the next chunk's, ahead
+      bool ok = false, dup = false;
+      const uint32_t s = (uint32_t)v & 0xFFFFu, l = (uint32_t)(v >> 32), e = s + l - 1u;
+      if (tid < chunk && k < C) {
+        dup = k && pv == v;
+        ok = !dup && !((bitmap[s >> 5] >> (s & 31)) & 1u) && !((bitmap[e >> 5] >> (e & 31)) & 1u);
+      }
+      const uint64_t m = __ballot(ok), md = __ballot(dup);
+      if (lane == 0) {
+        wsum[wv] = (uint32_t)__popcll(m);
+        if (md) atomicAdd(&s_dup, (uint32_t)__popcll(md));
+      }
+      __syncthreads();
+      uint32_t before = 0, tot = 0;
+#pragma unroll 4
+      for (int w = 0; w < NW; w++) {
+        const uint32_t c = wsum[w];
+        before += w < (int)wv ? c : 0u;
+        tot += c;
+      }
+      if (ok) {
+        const uint32_t q = before + lanes_below(m);
+        item[q] = s | (l << 16);
+        num[q] = k;
+      }
+      __syncthreads();
+      if (wv == 0 && tot) {
+        const uint32_t na = greedy_walk(
+            bitmap, tot, s_acc, [=](uint32_t q) { return item[q]; },
+            [=](uint32_t o, uint32_t q) { accs[o] = rec[num[q]]; });
+        if (lane == 0) s_acc = na;
+      }
+      __syncthreads();
+      v = nv;
+      pv = npv;
+    }
+  }
+  const uint32_t A = s_acc, M = C - s_dup;
+  uint32_t nhist = 1;
+  while (s_hist[nhist - 1]) nhist++;
+  stamp(6);
+
+  // ---- rows
+  auto rstart = [=](uint64_t v) { return (uint32_t)v & 0xFFFFu; };
+  auto rlen = [=](uint64_t v) { return (uint32_t)(v >> 32); };
+#pragma unroll 1
+  for (uint32_t o0 = 0; o0 < A; o0 += NT) {
+    const uint32_t o = o0 + tid;
+    const bool open = o < A && (o == 0 || (accs[o] >> 16) != (accs[o - 1] >> 16));
+    const uint64_t m = __ballot(open);
+    if (lane == 0) {
+      if (o0 + 64 * wv < A) {
+        bitmap[(o0 >> 5) + 2 * wv] = (uint32_t)m;
+        bitmap[(o0 >> 5) + 2 * wv + 1] = (uint32_t)(m >> 32);
+      }
+      atomicAdd(&s_nd, (uint32_t)__popcll(m));  // holds nd until here, which all have read
+    }
+  }
+  __syncthreads();
+  const uint32_t nrows = s_nd - nd;
+  if (nrows <= a.row_cap && (!a.occ || A <= a.occ_cap)) {
+    Row *rows = a.rows + (a.off ? tb / a.min_len : 0);
+    uint32_t done = 0;
+#pragma unroll 1
+    for (uint32_t o0 = 0; o0 < A; o0 += NT) {
+      const uint32_t o = o0 + tid;
+      uint32_t pre = done, tot = 0;
+      for (uint32_t w = 0; w < 2 * NW && o0 + 32 * w < A; w++) {  // scalar
+        const uint32_t c = (uint32_t)__popc(bitmap[(o0 >> 5) + w]);
+        pre += w < (tid >> 5) ? c : 0u;
+        tot += c;
+      }
+      done += tot;
+      if (o >= A) continue;
+      const uint64_t v = accs[o];
+      const uint32_t word = bitmap[o >> 5];
+      const uint32_t r = pre + (uint32_t)__popc(word & ((2u << (o & 31)) - 1u)) - 1u;
+      if ((word >> (o & 31)) & 1u) {
+        uint32_t next = word & ~((2u << (o & 31)) - 1u), x = o >> 5;
+        while (!next && 32 * (x + 1) < A) next = bitmap[++x];
+        rows[r] = Row{rstart(v), rlen(v), (next ? 32 * x + (uint32_t)__ffs((int)next) - 1u : A) - o};
+      }
+      if (a.occ) a.occ[o] = Occ{rstart(v), rlen(v), r};
+    }
+  }
+  if (tid == 0) {
+    stamp(7);
+    report(a, win, Report{D, nd, C, s_skip, maxl, M, A, nrows, s_pairs, nhist}, s_hist, s_stamp);
   }
 }
 
@@ -994,20 +1690,48 @@ __global__ __launch_bounds__(256) void k_pack_rows(const Row *src, const uint64_
   for (uint32_t r = threadIdx.x; r < c; r += 256) dst[base + r] = from[r];
 }
 
-void launch(const FusedArgs &a, uint32_t blocks, uint32_t longest, hipStream_t s) {
-  // the smallest workgroup that holds the longest window: fewer wavefronts
-  // per barrier, and more windows per compute unit
-  if (longest <= 1024) hipLaunchKernelGGL((k_window<256, 4>), dim3(blocks), dim3(256), 0, s, a);
-  else if (longest <= 2048) hipLaunchKernelGGL((k_window<512, 4>), dim3(blocks), dim3(512), 0, s, a);
-  else if (longest <= 4096) hipLaunchKernelGGL((k_window<1024, 4>), dim3(blocks), dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a);
+// Window sizes up to which each workgroup size is used: the smallest one that
+// holds a window means fewer wavefronts per barrier, and more windows per
+// compute unit.
+constexpr uint32_t kClassMost[] = {1024, 2048, 4096, kFusedMax, kFusedLongMax};
+constexpr int kFusedClasses = 5;
+
+void launch(const LongArgs &la, int cls, uint32_t blocks, hipStream_t s) {
+  const FusedArgs &a = la.f;
+  switch (cls) {
+    case 0: hipLaunchKernelGGL((k_window<256, 4>), dim3(blocks), dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_window<512, 4>), dim3(blocks), dim3(512), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_window<1024, 4>), dim3(blocks), dim3(1024), 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a); break;
+    default: hipLaunchKernelGGL(k_window_long, dim3(blocks), dim3(kLongNT), 0, s, la);
+  }
+}
+
+LongArgs args_of(const Workspace &w) {
+  LongArgs la{};
+  la.f.spill = reinterpret_cast<uint64_t *>(w.crec);
+  la.txt = reinterpret_cast<uint16_t *>(w.tokrank);
+  la.sa = reinterpret_cast<uint16_t *>(w.sa);
+  la.rank = reinterpret_cast<uint16_t *>(w.rank);
+  la.lcp = reinterpret_cast<uint16_t *>(w.lcp);
+  la.e0 = reinterpret_cast<uint64_t *>(w.T);  // at least four words of 64 bits per token
+  la.e1 = la.e0 + 2 * w.capN;
+  la.flags = reinterpret_cast<uint64_t *>(w.tmp_a);
+  return la;
+}
+
+int class_of_window(uint64_t n) {
+  int c = 0;
+  while (n > kClassMost[c]) c++;
+  return c;
 }
 
 }  // namespace
 
-void fused_window(const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows, uint32_t row_cap, void *occ,
-                  uint32_t occ_cap, void *spill, FusedInfo *info, hipStream_t s) {
-  FusedArgs a{};
+void fused_window(const Workspace &w, const void *tok, int bits, uint32_t n, uint32_t min_len, void *rows,
+                  uint32_t row_cap, void *occ, uint32_t occ_cap, FusedInfo *info, hipStream_t s) {
+  LongArgs la = args_of(w);
+  FusedArgs &a = la.f;
   a.tok = tok;
   a.bits = bits;
   a.n = n;
@@ -1016,9 +1740,8 @@ void fused_window(const void *tok, int bits, uint32_t n, uint32_t min_len, void 
   a.row_cap = row_cap;
   a.occ = static_cast<Occ *>(occ);
   a.occ_cap = occ_cap;
-  a.spill = static_cast<uint64_t *>(spill);
   a.info = info;
-  launch(a, 1, n, s);
+  launch(la, class_of_window(n), 1, s);
 }
 
 void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
@@ -1041,23 +1764,40 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
   for (int k = 0; k < kStages; k++) info.stage_ms[k] = (double)(f.stamp[k + 1] - f.stamp[k]) * 1e-5;  // 100 MHz
 }
 
-void fused_batch(Workspace &w, const void *tok, uint32_t W, uint32_t maxwin, uint32_t min_len, hipStream_t s) {
+void fused_batch(Workspace &w, const void *tok, const uint64_t *h_off, uint32_t W, uint32_t min_len, bool capture,
+                 hipStream_t s) {
   fill_u32(w.dcnt, CNT_COUNT, 0, s);
+  fill_u32(w.dcnt + CNT_FUSED, 1, 1, s);
   fill_u32(w.rhist, 4 * (uint64_t)w.nsnap, 0, s);
   fill_u32(w.selcnt, 3 * (kSelRoundCap + 2), 0, s);
-  FusedArgs a{};
+  LongArgs la = args_of(w);
+  FusedArgs &a = la.f;
   a.tok = tok;
   a.bits = 64;
   a.off = w.d_off;
-  a.order = w.d_order;
   a.min_len = min_len;
   a.rows = static_cast<Row *>(w.occ);  // a batch reports no occurrences: their array stages the rows
   a.row_cap = kNone;
-  a.spill = reinterpret_cast<uint64_t *>(w.crec);
   a.dcnt = w.dcnt;
   a.rhist = w.rhist;
   a.win_rows = w.win_rows;
-  launch(a, W, maxwin, s);
+  // The windows come longest first.  A captured sequence may be replayed with
+  // other windows of the same total, number and longest length: there every
+  // launch looks at every window.
+  uint32_t count[kFusedClasses] = {0}, longest = 0;
+  for (uint32_t k = 0; k < W; k++) {
+    const uint64_t n = h_off[k + 1] - h_off[k];
+    count[class_of_window(n)]++;
+    longest = std::max<uint32_t>(longest, (uint32_t)n);
+  }
+  uint32_t at = 0;
+  for (int c = class_of_window(longest); c >= 0; c--) {
+    a.above = c ? kClassMost[c - 1] : 0;
+    a.most = kClassMost[c];
+    a.order = w.d_order + (capture ? 0 : at);
+    if (capture || count[c]) launch(la, c, capture ? W : count[c], s);
+    at += count[c];
+  }
   hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, W,
                      min_len, static_cast<Row *>(w.rows));
   copy_u32(w.selcnt, w.dcnt + CNT_M, s);

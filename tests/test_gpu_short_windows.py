@@ -1,7 +1,8 @@
-"""Short windows (at most 8192 tokens), analysed by one workgroup each: rows,
-occurrences and counters against the oracle and against the stage-by-stage
-analysis (set_window_greedy(False)), at the edges of the workgroup sizes (256,
-512 and 1024 threads with 4 or 8 tokens each)."""
+"""Windows analysed by one workgroup each (alone up to 32768 tokens, in batches
+up to 65536): rows, occurrences and counters against the oracle and against the
+stage-by-stage analysis (set_window_greedy(False)), at the edges of the
+workgroup sizes (256, 512 and 1024 threads with 4 or 8 tokens each, then arrays
+in the workspace)."""
 import ctypes
 
 import numpy as np
@@ -13,7 +14,7 @@ from paper_2406_18111_amd import _lib, synth
 pytestmark = pytest.mark.gpu
 
 TOP = np.uint64(np.iinfo(np.uint64).max)
-EDGES = (2, 3, 63, 64, 65, 255, 257, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 5000, 8191, 8192, 8193)
+EDGES = (2, 3, 63, 64, 65, 255, 257, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 5000, 8191, 8192, 8193, 12345, 32767, 32768)
 
 
 def _streams(n):
@@ -47,7 +48,7 @@ def ctx():
 def test_short_window(ctx, n):
     import torch
     for name, t in _streams(n).items():
-        for m in (1, 5):
+        for m in ((1, 5) if n <= 8193 else (2,)):
             print("n", n, name, "min_len", m, flush=True)
             ref = oracle.find_repeats(t, m)
             occ_ref = np.stack([ref["occ_start"], ref["occ_len"], ref["occ_row"]], 1).astype(np.int64).reshape(-1, 3)
@@ -67,7 +68,7 @@ def test_short_window(ctx, n):
             assert sum(r["sa_active"]) == c["active_sum"]
 
 
-@pytest.mark.parametrize("n", (5, 1000, 3001, 8192))
+@pytest.mark.parametrize("n", (5, 1000, 3001, 8192, 9001, 32768))
 def test_short_window_u32(ctx, n):
     import torch
     t = np.random.default_rng(n).integers(0, 4, n).astype(np.uint32) * np.uint32(0x3FFFFFFF)
@@ -126,3 +127,43 @@ def test_short_window_batch(ctx, longest):
             finally:
                 ctx.set_lanes(3)
                 ctx.set_graphs(True)
+
+
+def test_long_window_batch(ctx):
+    """Windows of up to 65536 tokens beside short ones, at the largest sizes
+    and the least and most repetitive inputs; then with a window over the
+    distinct-token limit (8192, the largest value aside), which sends the batch
+    through the stage-by-stage analysis."""
+    rng = np.random.default_rng(7)
+    many = synth.loop_stream(5, 20000, 300, 4096, 0.05)
+    at = np.concatenate([rng.permutation(8192).astype(np.uint64), rng.integers(0, 8192, 3000).astype(np.uint64), [TOP]])
+    over = np.concatenate([at, np.array([8192], np.uint64)])
+    base = [synth.loop_stream(3, 65536, 211, 4096, 0.05), np.full(65536, 7, np.uint64), many, at,
+            np.tile(np.arange(3, dtype=np.uint64), 22000)[:65535], rng.integers(0, 2, 40001).astype(np.uint64),
+            synth.loop_stream(4, 3000, 40, 64, 0.05), np.zeros(0, np.uint64), synth.loop_stream(6, 8192, 40, 64, 0.05)]
+    for wins, lanes in ((base, 3), (base, 1), (base[::-1] + [over], 3)):
+        toks = np.concatenate(wins).astype(np.uint64)
+        off = np.zeros(len(wins) + 1, dtype=np.uint64)
+        off[1:] = np.cumsum([len(w) for w in wins])
+        refs = [_rows(oracle.find_repeats(w, 4)) for w in wins]
+        act = sum(int(oracle.suffix_array(w, return_active=True)[1].sum()) for w in wins if len(w) > 1)
+        for graphs in (True, False):
+            print("windows", [len(w) for w in wins], "lanes", lanes, "graphs", graphs, flush=True)
+            try:
+                ctx.set_lanes(lanes)
+                ctx.set_graphs(graphs)
+                for rep in range(2):
+                    rows, oo = ctx.analyze_batch(toks, off, 4)
+                    for w in range(len(wins)):
+                        assert np.array_equal(_as3(rows[int(oo[w]):int(oo[w + 1])]), refs[w]), (rep, w, len(wins[w]))
+                    assert ctx.counters()["active_sum"] - len(toks) == act
+            finally:
+                ctx.set_lanes(3)
+                ctx.set_graphs(True)
+
+
+def test_window_over_the_distinct_limit(ctx):
+    """A lone window of more than 8192 distinct tokens is analysed stage by stage."""
+    t = np.concatenate([np.arange(8193, dtype=np.uint64) << np.uint64(33)] * 2)
+    rows, occ = ctx.analyze(t, 3, occurrences=True)
+    assert np.array_equal(_as3(rows), _rows(oracle.find_repeats(t, 3))) and len(occ) == 2
