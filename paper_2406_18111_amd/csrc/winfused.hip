@@ -53,6 +53,24 @@ __device__ __forceinline__ uint32_t lane_prev(uint32_t v) {
 
 __device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
+// The lanes of `in` whose d agrees with this lane's in its low BITS bits: one
+// ballot per bit.  Each step keeps a lane's bit of the mask where the ballot
+// agrees with the lane's own bit (a & ~(b ^ c) in one instruction; written out,
+// the compiler makes 6 instructions of a bit instead of 4).
+template <int BITS>
+__device__ __forceinline__ uint64_t equal_lanes(uint32_t d, uint64_t in) {
+  uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
+#pragma unroll
+  for (int b = 0; b < BITS; b++) {
+    int t = __builtin_amdgcn_sbfe((int)d, b, 1);  // 0 or -1
+    asm("" : "+v"(t));  // nothing is known of t: it is compared as it is
+    const uint64_t one = __builtin_amdgcn_ballot_w64(t != 0);
+    lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)one, (uint32_t)t, 0x90);
+    hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(one >> 32), (uint32_t)t, 0x90);
+  }
+  return ((uint64_t)hi << 32) | lo;
+}
+
 constexpr uint32_t kOwnRanks = 4096;     // most distinct values the stage-by-stage batch ranks per window
 constexpr uint32_t kOwnPairs = 8192;     // and most distinct adjacent pairs
 constexpr int kLongRounds = 18;          // the same for windows of up to kFusedLongMax tokens
@@ -102,19 +120,12 @@ __device__ __forceinline__ void radix_pass(T *it, uint32_t m, int ipt, uint16_t 
     const uint32_t k = min(q0 + lane, m - 1);
     const uint32_t d = digit(it[k]);
     const uint64_t in = first_lanes(m - q0);
-    uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
-#pragma unroll
-    for (int b = 0; b < kMaxDigit; b++) {
-      const int t = __builtin_amdgcn_sbfe((int)d, b, 1);  // 0 or -1
-      const uint64_t one = __builtin_amdgcn_ballot_w64(t != 0);
-      lo &= ~((uint32_t)one ^ (uint32_t)t);
-      hi &= ~((uint32_t)(one >> 32) ^ (uint32_t)t);
-    }
-    const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    const uint64_t same = equal_lanes<kMaxDigit>(d, in);
+    const uint32_t before = lanes_below(same);
     const uint32_t prev = my[d];
     wave_order();  // every lane has read before the first one of each digit writes
     if (q0 + lane < m) {
-      if (before == 0) my[d] = (uint16_t)(prev + (uint32_t)__popc(lo) + (uint32_t)__popc(hi));
+      if (before == 0) my[d] = (uint16_t)(prev + (uint32_t)__popcll(same));
       park(k, prev + before);
     }
     wave_order();
@@ -595,7 +606,7 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
   // whose second half is empty, wrap around (j = SA[k] - h + n): the one of h
   // tokens (SA[k] = 0) is put first, the shorter ones are alone in their groups.
   uint16_t *sah = sa;  // where the suffix order is now
-  while (active) {  // uniform
+  while (active && h < n) {  // uniform (from n tokens on nothing can be grouped)
     const uint32_t m = active;
     if (!large) {
       uint32_t *ctr = reinterpret_cast<uint32_t *>(lds);
@@ -1031,9 +1042,25 @@ struct LongArgs {
   uint64_t *flags;                  // one word per token (n / 32 of them used)
 };
 
-// Counts of a wavefront's items [beg, end) by digit, into its row of ctr.
-template <class Get, class Digit>
-__device__ __forceinline__ void byte_count(uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit) {
+// Rank of each lane among the items of its digit d < 256 that the wavefront has
+// met, `my` counting them (in: the lanes that hold an item).
+__device__ __forceinline__ uint32_t rank_lanes(uint32_t *my, uint32_t d, uint64_t in) {
+  const uint64_t same = equal_lanes<8>(d, in);
+  const uint32_t before = lanes_below(same);
+  const uint32_t prev = my[d];
+  wave_order();  // every lane has read before the first one of each digit writes
+  if (before == 0 && ((in >> (threadIdx.x & 63)) & 1ull)) my[d] = prev + (uint32_t)__popcll(same);
+  wave_order();
+  return prev + before;
+}
+
+// Ranks a wavefront's items [beg, end) among its items of equal digit, in order
+// (lanes of equal digit found by one ballot per bit, running counts in the
+// wavefront's row of ctr): park(k, rank).  One LDS atomic per item took longer
+// than this, 22 us against 10 for 30011 items, since most lanes meet on a few
+// digits of a repetitive window.
+template <class Get, class Digit, class Park>
+__device__ __forceinline__ void byte_rank(uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit, Park park) {
   const uint32_t lane = threadIdx.x & 63;
 #pragma unroll 1
   for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
@@ -1041,8 +1068,12 @@ __device__ __forceinline__ void byte_count(uint32_t *my, uint32_t beg, uint32_t 
 #pragma unroll
     for (int u = 0; u < 4; u++) v[u] = get(min(q0 + 64 * u + lane, end - 1));
 #pragma unroll
-    for (int u = 0; u < 4; u++)
-      if (q0 + 64 * u + lane < end) atomicAdd(&my[digit(v[u])], 1u);
+    for (int u = 0; u < 4; u++) {
+      const uint32_t q = q0 + 64 * u;
+      if (q >= end) continue;  // scalar
+      const uint32_t r = rank_lanes(my, digit(v[u]), first_lanes(end - q));
+      if (q + lane < end) park(q + lane, r);
+    }
   }
 }
 
@@ -1071,38 +1102,24 @@ __device__ __forceinline__ void byte_scan(uint32_t *ctr, uint32_t *wsum) {
   __syncthreads();
 }
 
-// Stable scatter of a wavefront's items by digit: put(place, item).
-template <class Get, class Digit, class Put>
-__device__ __forceinline__ void byte_scatter(uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit, Put put) {
+// Moves a wavefront's items to their places: put(place, item).
+template <class Get, class Digit, class Parked, class Put>
+__device__ __forceinline__ void byte_move(const uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit,
+                                          Parked parked, Put put) {
   const uint32_t lane = threadIdx.x & 63;
 #pragma unroll 1
   for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
     decltype(get(0u)) v[4];
-#pragma unroll
-    for (int u = 0; u < 4; u++) v[u] = get(min(q0 + 64 * u + lane, end - 1));
+    uint32_t r[4];
 #pragma unroll
     for (int u = 0; u < 4; u++) {
-      const uint32_t q = q0 + 64 * u;
-      if (q >= end) continue;  // scalar
-      const uint32_t d = digit(v[u]);
-      const uint64_t in = first_lanes(end - q);
-      uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
-#pragma unroll
-      for (int b = 0; b < 8; b++) {
-        const int t = __builtin_amdgcn_sbfe((int)d, b, 1);  // 0 or -1
-        const uint64_t one = __builtin_amdgcn_ballot_w64(t != 0);
-        lo &= ~((uint32_t)one ^ (uint32_t)t);
-        hi &= ~((uint32_t)(one >> 32) ^ (uint32_t)t);
-      }
-      const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-      const uint32_t prev = my[d];
-      wave_order();  // every lane has read before the first one of each digit writes
-      if (q + lane < end) {
-        if (before == 0) my[d] = prev + (uint32_t)__popc(lo) + (uint32_t)__popc(hi);
-        put(prev + before, v[u]);
-      }
-      wave_order();
+      const uint32_t k = min(q0 + 64 * u + lane, end - 1);
+      v[u] = get(k);
+      r[u] = parked(k);
     }
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      if (q0 + 64 * u + lane < end) put(my[digit(v[u])] + r[u], v[u]);
   }
 }
 
@@ -1141,6 +1158,11 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
   // a wavefront's share of m items, in order
   auto seg = [](uint32_t m) { return ((m + 64 * kLongNW - 1) / (64 * kLongNW)) * 64; };
   uint32_t *const my = ctr + wv * kByte;
+  // ranks parked between the two halves of a radix pass (the LCP values come
+  // later, and are in LDS when the candidates are sorted)
+  uint16_t *const rel = glcp;
+  auto park = [=](uint32_t k, uint32_t r) { rel[k] = (uint16_t)r; };
+  auto parked = [=](uint32_t k) { return (uint32_t)rel[k]; };
   auto clear_row = [&] {
     *reinterpret_cast<uint4 *>(my + 4 * lane) = make_uint4(0, 0, 0, 0);
     wave_order();
@@ -1276,10 +1298,10 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
       auto get = [=](uint32_t k) { return src[k]; };
       auto dig = [=](uint64_t v) { return (uint32_t)(v >> sh) & 255u; };
       clear_row();
-      byte_count(my, wbeg, wtop, get, dig);
+      byte_rank(my, wbeg, wtop, get, dig, park);
       byte_scan(ctr, wsum);
       uint64_t *to = dst;
-      byte_scatter(my, wbeg, wtop, get, dig, [=](uint32_t at, uint64_t v) { to[at] = v; });
+      byte_move(my, wbeg, wtop, get, dig, parked, [=](uint32_t at, uint64_t v) { to[at] = v; });
       __syncthreads();
       dst = src;
       src = to;
@@ -1330,10 +1352,9 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
   {
     uint32_t *const l0 = reinterpret_cast<uint32_t *>(e0), *const l1 = reinterpret_cast<uint32_t *>(e1);
 #pragma unroll 1
-    while (active) {  // uniform
+    while (active && h < n) {  // uniform
       const uint32_t first = s_zero, m = active;
       uint32_t mine = 0;
-      clear_row();
 #pragma unroll 1
       for (uint32_t k0 = wbeg; k0 < wtop; k0 += 256) {  // scalar
         uint32_t s[4];
@@ -1349,46 +1370,50 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
           const uint32_t g = rank[j];
           const uint64_t mk =
               __ballot(!((bitmap[(g + 1) >> 5] >> ((g + 1) & 31)) & 1u)) & first_lanes(wtop - k0 - 64 * u);
-          if ((mk >> lane) & 1ull) {
-            l0[wbeg + mine + lanes_below(mk)] = j | (g << 16);
-            atomicAdd(&my[g & 255u], 1u);
-          }
+          if ((mk >> lane) & 1ull) l0[wbeg + mine + lanes_below(mk)] = j | (g << 16);
           mine += (uint32_t)__popcll(mk);
         }
       }
+      // the wavefront's own entries first, then an even share of them all
+      auto low = [](uint32_t e) { return (e >> 16) & 255u; };
+      clear_row();
+      byte_rank(my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, low, park);
       byte_scan(ctr, wsum);
-      byte_scatter(
-          my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, [](uint32_t e) { return (e >> 16) & 255u; },
+      byte_move(
+          my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, low, parked,
           [=](uint32_t at, uint32_t e) { l1[at] = e; });
       __syncthreads();
       const uint32_t qbeg = min(wv * seg(m), m), qtop = min(qbeg + seg(m), m);
       auto get = [=](uint32_t q) { return l1[q]; };
       auto dig = [](uint32_t e) { return e >> 24; };
       clear_row();
-      byte_count(my, qbeg, qtop, get, dig);
+      byte_rank(my, qbeg, qtop, get, dig, park);
       byte_scan(ctr, wsum);
-      byte_scatter(my, qbeg, qtop, get, dig, [=](uint32_t at, uint32_t e) { l0[at] = e; });
+      byte_move(my, qbeg, qtop, get, dig, parked, [=](uint32_t at, uint32_t e) { l0[at] = e; });
       __syncthreads();
       // openings of old and new groups among the sorted entries
       uint32_t lo = kNone, ln = kNone;
 #pragma unroll 1
       for (uint32_t q0 = qbeg; q0 < qtop; q0 += 256) {  // scalar
-        uint32_t e[4], p[4];
+        uint32_t e[4];
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-          const uint32_t q = min(q0 + 64 * u + lane, m - 1);
-          e[u] = l0[q];
-          p[u] = l0[q ? q - 1 : 0];
-        }
+        for (int u = 0; u < 4; u++) e[u] = l0[min(q0 + 64 * u + lane, m - 1)];
 #pragma unroll
         for (int u = 0; u < 4; u++) {
           const uint32_t c0 = q0 + 64 * u, q = c0 + lane;
           if (c0 >= qtop) continue;  // scalar
-          const uint32_t s = (e[u] & 0xFFFFu) + h, t = (p[u] & 0xFFFFu) + h;
-          const uint32_t r = rank[min(s, n - 1)], z = rank[min(t, n - 1)];
-          const bool og = q == 0 || q >= m || (e[u] >> 16) != (p[u] >> 16);
-          // the empty second half (one past the end) sorts first and alone
-          const bool ng = og || (s < n) != (t < n) || (s < n && r != z);
+          auto half = [&](uint32_t e) {  // the second half's group, 0 for the empty one (one past the end)
+            const uint32_t s = (e & 0xFFFFu) + h, r = rank[min(s, n - 1)];
+            return s < n ? r + 1 : 0u;
+          };
+          const uint32_t c = half(e[u]);
+          uint32_t pe = lane_prev(e[u]), pc = lane_prev(c);
+          if (lane == 0 && q) {
+            pe = l0[q - 1];
+            pc = half(pe);
+          }
+          const bool og = q == 0 || q >= m || (e[u] >> 16) != (pe >> 16);
+          const bool ng = og || c != pc;
           const uint64_t mo = __ballot(og), mn = __ballot(ng), in = first_lanes(qtop - c0);
           if (lane == 0) {
             fl[2 * (c0 >> 6)] = mo;
@@ -1486,8 +1511,9 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
   __syncthreads();
   for (uint32_t b = tid; b < (n + 511) / 512; b += NT) min3[b] = (uint16_t)min8(min2 + 8 * b);
   __syncthreads();
+  uint32_t mine = 0;  // the wavefront's records, in suffix-array order from 2 * wbeg on
   {
-    uint32_t mx = 0, pairs = 0;
+    uint32_t mx = 0, pairs = 0, skipped = 0;
 #pragma unroll 1
     for (uint32_t k0 = wbeg; k0 < wtop; k0 += 64) {  // scalar
       const uint32_t k = k0 + lane;
@@ -1522,50 +1548,107 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
       const uint64_t m2 = __ballot(l != 0), m1 = __ballot(l != 0 && !rep);
       if (!m2) continue;  // scalar
       const uint64_t id = l ? 1u + last_smaller<CAP>(lcp, min1, min2, min3, k, l) : 0u;
-      uint32_t q = 0;
-      if (lane == 0) {
-        q = atomicAdd(&s_c, (uint32_t)(__popcll(m1) + __popcll(m2)));
-        atomicAdd(&s_skip, (uint32_t)(__popcll(m2) - __popcll(m1)));
-      }
-      q = (uint32_t)__builtin_amdgcn_readfirstlane((int)q) + lanes_below(m1) + lanes_below(m2);
+      uint32_t q = 2 * wbeg + mine + lanes_below(m1) + lanes_below(m2);
       if (l) {
         const uint64_t head = (id << 16) | ((uint64_t)l << 32);
         if (!rep) e0[q++] = head | s1;
         e0[q] = head | s2;
       }
+      mine += (uint32_t)(__popcll(m1) + __popcll(m2));
+      skipped += (uint32_t)(__popcll(m2) - __popcll(m1));
       mx = max(mx, l);
     }
     mx = lane_max(mx);
     if (lane == 63 && mx) atomicMax(&s_max, mx);
-    if (lane == 0) atomicAdd(&s_pairs, pairs);
+    if (lane == 0) {
+      atomicAdd(&s_pairs, pairs);
+      atomicAdd(&s_skip, skipped);
+      atomicAdd(&s_c, mine);
+    }
   }
   __syncthreads();
   const uint32_t C = s_c, maxl = s_max;
   stamp(4);
 
-  // ---- priority order: radix sort by (maxl - length, ID, start)
+  // ---- priority order (length desc, ID asc, start asc).  For one length the
+  // ID never decreases along the suffix array, so a stable radix sort by length
+  // leaves (length, ID) in order, and each run of equal ones is put in order of
+  // the starts: a record's place is the number of its run's records that start
+  // before it.  With a long run (128 records or more; up to 190 may pass) the
+  // three fields are sorted as one key instead.
   const uint64_t *rec = e0;
   uint64_t *accs = e1;  // accepted records
   if (C) {  // uniform
-    const int pb = bits_of(n - 1), bits = bits_of(maxl - a.min_len) + 2 * pb, np = (bits + 7) / 8;
+    const int pb = bits_of(n - 1), lb = bits_of(maxl - a.min_len);
     const uint32_t cbeg = min(wv * seg(C), C), ctop = min(cbeg + seg(C), C);
     uint64_t *src = e0, *dst = e1;
-#pragma unroll 1
-    for (int p = 0; p < np; p++) {
-      auto get = [=](uint32_t k) { return src[k]; };
-      auto dig = [=](uint64_t v) {
-        const uint64_t key = ((uint64_t)(maxl - (uint32_t)(v >> 32)) << (2 * pb)) |
-                             ((uint64_t)((uint32_t)v >> 16) << pb) | ((uint32_t)v & 0xFFFFu);
-        return (uint32_t)(key >> (8 * p)) & 255u;
-      };
-      clear_row();
-      byte_count(my, cbeg, ctop, get, dig);
-      byte_scan(ctr, wsum);
+    auto pass = [&](uint32_t beg, uint32_t end, auto dig) {
+      const uint64_t *from = src;
       uint64_t *to = dst;
-      byte_scatter(my, cbeg, ctop, get, dig, [=](uint32_t at, uint64_t v) { to[at] = v; });
+      auto get = [=](uint32_t k) { return from[k]; };
+      clear_row();
+      byte_rank(my, beg, end, get, dig, park);
+      byte_scan(ctr, wsum);
+      byte_move(my, beg, end, get, dig, parked, [=](uint32_t at, uint64_t v) { to[at] = v; });
       __syncthreads();
       dst = src;
       src = to;
+    };
+#pragma unroll 1
+    for (int sh = 0; sh == 0 || sh < lb; sh += 8)
+      pass(sh ? cbeg : 2 * wbeg, sh ? ctop : 2 * wbeg + mine,
+           [=](uint64_t v) { return ((maxl - (uint32_t)(v >> 32)) >> sh) & 255u; });
+    // a bitmap of the records that open a run
+    if (tid == 0) s_active = 0;
+#pragma unroll 1
+    for (uint32_t q0 = cbeg; q0 < ctop; q0 += 64) {  // scalar
+      const uint32_t k = min(q0 + lane, C - 1);
+      const uint64_t open = __ballot(q0 + lane == 0 || q0 + lane >= C || (src[k] >> 16) != (src[k ? k - 1 : 0] >> 16));
+      if (lane == 0) {
+        ctr[q0 >> 5] = (uint32_t)open;
+        ctr[(q0 >> 5) + 1] = (uint32_t)(open >> 32);
+      }
+    }
+    __syncthreads();
+    for (uint32_t x = tid; 32 * x + 128 <= C; x += NT)
+      if (!(ctr[x] | ctr[x + 1] | ctr[x + 2] | ctr[x + 3])) s_active = 1;  // 128 records without an opening
+    __syncthreads();
+    if (s_active) {  // uniform
+      __syncthreads();  // ... before the counters are used again
+      const int bits = lb + 2 * pb;
+#pragma unroll 1
+      for (int sh = 0; sh < bits; sh += 8)
+        pass(cbeg, ctop, [=](uint64_t v) {
+          const uint64_t key = ((uint64_t)(maxl - (uint32_t)(v >> 32)) << (2 * pb)) |
+                               ((uint64_t)((uint32_t)v >> 16) << pb) | ((uint32_t)v & 0xFFFFu);
+          return (uint32_t)(key >> sh) & 255u;
+        });
+    } else {
+      const uint64_t *from = src;
+#pragma unroll 1
+      for (uint32_t k = cbeg + lane; k < ctop; k += 64) {
+        const uint64_t v = from[k];
+        const uint32_t s = (uint32_t)v & 0xFFFFu;
+        uint32_t x = k >> 5, w = ctr[x] & ((2u << (k & 31)) - 1u);
+        while (!w) w = ctr[--x];  // record 0 opens a run
+        const uint32_t b = 32 * x + 31u - (uint32_t)__clz((int)w);
+        x = k >> 5;
+        w = ctr[x] & ~((2u << (k & 31)) - 1u);
+        while (!w && 32 * (x + 1) < C) w = ctr[++x];
+        const uint32_t e = w ? min(32 * x + (uint32_t)__ffs((int)w) - 1u, C) : C;
+        uint32_t at = b;
+        if (e - b > 1)
+#pragma unroll 4
+          for (uint32_t q = b; q < e; q++) {
+            const uint32_t t = (uint32_t)from[q] & 0xFFFFu;
+            at += (t < s || (t == s && q < k)) ? 1u : 0u;
+          }
+        dst[at] = v;
+      }
+      __syncthreads();
+      uint64_t *t = src;
+      src = dst;
+      dst = t;
     }
     rec = src;
     accs = dst;
