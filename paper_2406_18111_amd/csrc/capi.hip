@@ -660,7 +660,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
       for (Lane &ln : lanes) {
         ln.info = RunInfo{};
         ln.ws->kev_n = 0;
-        int rc = finish_run(*ln.ws, ln.total, 2 * ln.total, kSelFreeRounds, ln.info, s, false);
+        int rc = finish_run(*ln.ws, ln.total, ln.W, 2 * ln.total, kSelFreeRounds, ln.info, s, false);
         if (rc == 1)  // greedy rounds left candidates undecided: this lane again, host-driven
           rc = run_pipeline(*ln.ws, d_tok + ln.tok0, 64, ln.total, ln.norm.data(), ln.W, min_len, Stop::FULL, s,
                             ln.info, Mode::HOST);
@@ -759,7 +759,14 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   GraphCache &G = ctx->gc;
   const bool hit = G.exec && G.tok == d_tok && G.total == total && G.W == W && G.maxwin == maxwin &&
                    G.min_len == min_len && G.tile == tl && G.digit == db && G.mem == w.mem && G.stream == s;
-  if (upload_windows(w, norm.data(), W, s, true) || hipStreamSynchronize(s) != hipSuccess) return APO_EDEVICE;
+  if (upload_windows(w, norm.data(), W, s, true)) return APO_EDEVICE;
+  // Windows with a workgroup each: the first run of a shape is enqueued right
+  // away, and its few launches are recorded while it is on the GPU.
+  const bool ahead = !hit && maxwin <= kFusedLongMax && w.win_greedy;
+  if (ahead) {
+    rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::CAPTURE);
+    if (rc) return map_rc(rc);
+  }
   if (!hit) {
     G.reset();
     bool ok = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess;
@@ -798,9 +805,9 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
     ctx->graph_replays++;
   }
   w.kev_n = 0;
-  if (hipGraphLaunch(G.exec, s) != hipSuccess) return APO_EDEVICE;
+  if (!ahead && hipGraphLaunch(G.exec, s) != hipSuccess) return APO_EDEVICE;
   ctx->info = RunInfo{};
-  rc = finish_run(w, total, 2 * total, kSelFreeRounds, ctx->info, s, false);
+  rc = finish_run(w, total, W, 2 * total, kSelFreeRounds, ctx->info, s, false);
   if (rc == 1) rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::HOST);
   return map_rc(rc);
 }
@@ -809,13 +816,8 @@ static int batch_offsets(apo_ctx *ctx, uint32_t W, uint64_t *out_offsets, uint64
   std::vector<uint32_t> cnt;
   cnt.reserve(W);
   for (const auto &lo : ctx->louts) {
-    std::vector<uint32_t> c(lo.W, 0);
-    if (lo.W > 1 && lo.rows) {
-      if (hipMemcpy(c.data(), lo.ws->win_rows, lo.W * 4, hipMemcpyDeviceToHost) != hipSuccess) return APO_EDEVICE;
-    } else if (lo.W == 1) {
-      c[0] = lo.rows;
-    }
-    cnt.insert(cnt.end(), c.begin(), c.end());
+    if (lo.W > 1 && lo.rows) cnt.insert(cnt.end(), lo.ws->hwin, lo.ws->hwin + lo.W);
+    else cnt.insert(cnt.end(), lo.W, lo.W == 1 ? lo.rows : 0u);
   }
   if (cnt.size() != W) return APO_EDEVICE;
   out_offsets[0] = 0;
@@ -1317,13 +1319,8 @@ static void slot_loop(Server *S, Slot *sl) {
                                  sl->stream, info));
       }
       if (!rc) {
-        std::vector<uint32_t> cnt(W, 0);
-        if (W > 1 && info.rows) {
-          if (hipMemcpy(cnt.data(), sl->ws.win_rows, W * 4, hipMemcpyDeviceToHost) != hipSuccess) rc = APO_EDEVICE;
-        } else if (W == 1) {
-          cnt[0] = info.rows;
-        }
-        for (uint32_t w = 0; w < W; w++) outoff[w + 1] = outoff[w] + cnt[w];
+        for (uint32_t w = 0; w < W; w++)
+          outoff[w + 1] = outoff[w] + (W == 1 ? info.rows : info.rows ? sl->ws.hwin[w] : 0u);
         rows.resize(info.rows);
         if (!rc && info.rows &&
             hipMemcpy(rows.data(), sl->ws.rows, (size_t)info.rows * sizeof(apo_candidate), hipMemcpyDeviceToHost) !=

@@ -87,7 +87,8 @@ struct Workspace {
   uint32_t *dhi = nullptr, *dlo = nullptr;
   uint64_t *d_off = nullptr;
   uint32_t *d_order = nullptr;  // windows longest first (per-window kernels of sync-free runs take them so)
-  std::vector<uint32_t> h_order;  // its host copy, kept alive for the upload
+  uint64_t *hoff = nullptr;        // pinned copies of both and of win_rows, one allocation
+  uint32_t *horder = nullptr, *hwin = nullptr;
   uint32_t *wbeg = nullptr, *wend = nullptr, *wid = nullptr, *win_rows = nullptr;
   uint32_t *rank = nullptr, *snap = nullptr, *sa = nullptr;
   uint32_t *lcp = nullptr;
@@ -109,7 +110,7 @@ struct Workspace {
   uint32_t *hrhist = nullptr;      // pinned host mirror of rhist
   uint32_t *selcnt = nullptr;      // selection rounds: live counts, undecided counts
   uint32_t *hsel = nullptr;        // pinned host mirror of selcnt
-  uint32_t *hcnt = nullptr;        // pinned host mirror of dcnt
+  uint32_t *hcnt = nullptr;        // pinned host mirror of dcnt; rhist and selcnt follow it here and on the device
   SortCounters *hctr = nullptr;    // pinned host mirror of engine counters
   hipEvent_t ev[kStages + 1] = {};
   int ktag = KT_NONE;              // kernel family timed with events around each launch
@@ -158,10 +159,11 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
 // already ordered window by window.
 int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t *wid, const uint32_t *wbeg,
                 uint64_t m_bound, bool host, hipStream_t s, bool window_major);
+// W > 1: the windows' row counts arrive in w.hwin.
 // sel_launched: selection rounds enqueued by a sync-free run (-1: host-driven).
 // Returns 1 when a sync-free run left candidates undecided, or one-workgroup
 // analyses left windows out (the caller then reruns host-driven).
-int finish_run(Workspace &w, uint64_t N, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
+int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
                bool stamps);
 
 }  // namespace apo

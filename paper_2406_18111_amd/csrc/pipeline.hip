@@ -53,14 +53,13 @@ void Workspace::release() {
   if (mem && !external) (void)hipFree(mem);
   mem = nullptr;
   external = false;
-  if (hcnt) (void)hipHostFree(hcnt);
-  hcnt = nullptr;
+  if (hcnt) (void)hipHostFree(hcnt);  // holds hrhist and hsel too
+  hcnt = hrhist = hsel = nullptr;
   if (hctr) (void)hipHostFree(hctr);
   hctr = nullptr;
-  if (hrhist) (void)hipHostFree(hrhist);
-  hrhist = nullptr;
-  if (hsel) (void)hipHostFree(hsel);
-  hsel = nullptr;
+  if (hoff) (void)hipHostFree(hoff);  // holds horder and hwin too
+  hoff = nullptr;
+  horder = hwin = nullptr;
   for (auto &e : ev)
     if (e) { (void)hipEventDestroy(e); e = nullptr; }
   for (auto &e : kev)
@@ -192,10 +191,14 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
   selcnt = (uint32_t *)(m + o_sc);
   int rc = eng.alloc(C2, nullptr, ext ? static_cast<char *>(ext) + L.total : nullptr);
   if (rc) { release(); return rc; }
-  APO_HIP_TRY(hipHostMalloc((void **)&hcnt, CNT_COUNT * 4, hipHostMallocDefault));
+  // the mirrors of dcnt, rhist and selcnt lie as those do, so that one copy takes all three
+  APO_HIP_TRY(hipHostMalloc((void **)&hcnt, o_sc + 2 * (kSelRoundCap + 2) * 4 - o_cnt, hipHostMallocDefault));
+  hrhist = hcnt + (o_rh - o_cnt) / 4;
+  hsel = hcnt + (o_sc - o_cnt) / 4;
   APO_HIP_TRY(hipHostMalloc((void **)&hctr, sizeof(SortCounters), hipHostMallocDefault));
-  APO_HIP_TRY(hipHostMalloc((void **)&hrhist, 4 * 64 * 4, hipHostMallocDefault));
-  APO_HIP_TRY(hipHostMalloc((void **)&hsel, 2 * (kSelRoundCap + 2) * 4, hipHostMallocDefault));
+  APO_HIP_TRY(hipHostMalloc((void **)&hoff, (size_t)(wantW + 1) * 16, hipHostMallocDefault));
+  horder = reinterpret_cast<uint32_t *>(hoff + wantW + 1);
+  hwin = horder + wantW + 1;
   for (auto &ev_ : ev) APO_HIP_TRY(hipEventCreate(&ev_));
   for (auto &ev_ : kev) APO_HIP_TRY(hipEventCreate(&ev_));
   APO_HIP_TRY(hipMemset(dcnt, 0, CNT_COUNT * 4));
@@ -205,8 +208,10 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
 }
 
 // ------------------------------------------------------------- helpers
-static int read_counters(Workspace &w, hipStream_t s) {
-  APO_HIP_TRY(hipMemcpyAsync(w.hcnt, w.dcnt, CNT_COUNT * 4, hipMemcpyDeviceToHost, s));
+static int read_counters(Workspace &w, hipStream_t s, bool rounds = false) {
+  // rounds: the per-round counts behind the counters too
+  const size_t bytes = rounds ? (size_t)(w.hsel + 2 * (kSelRoundCap + 2) - w.hcnt) * 4 : CNT_COUNT * 4;
+  APO_HIP_TRY(hipMemcpyAsync(w.hcnt, w.dcnt, bytes, hipMemcpyDeviceToHost, s));
   APO_HIP_TRY(hipMemcpyAsync(w.hctr, w.eng.bufs().ctr, sizeof(SortCounters), hipMemcpyDeviceToHost, s));
   APO_HIP_TRY(hipStreamSynchronize(s));
   if (w.fail_after >= 0 && w.fail_after-- == 0) {  // test hook: this sync reports a device error
@@ -274,7 +279,10 @@ static void fill_info(Workspace &w, uint64_t N, RunInfo &info) {
 }
 
 int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t s, bool order) {
-  APO_HIP_TRY(hipMemcpyAsync(w.d_off, h_off, (W + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
+  // through pinned memory (pageable copies wait for themselves); the run that
+  // reads them ends before the next upload
+  memcpy(w.hoff, h_off, (W + 1) * sizeof(uint64_t));
+  APO_HIP_TRY(hipMemcpyAsync(w.d_off, w.hoff, (W + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
   if (!order || !W) return 0;
   // longest first, in buckets of sizes up to the same power of two (a counting sort): a long
   // window taken last would hold one workgroup while the others are idle
@@ -287,9 +295,8 @@ int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t 
   };
   for (uint32_t k = 0; k < W; k++) cnt[bucket(k) + 1]++;
   for (int b = 1; b < 66; b++) cnt[b] += cnt[b - 1];
-  w.h_order.resize(W + 1);
-  for (uint32_t k = 0; k < W; k++) w.h_order[cnt[bucket(k)]++] = k;
-  APO_HIP_TRY(hipMemcpyAsync(w.d_order, w.h_order.data(), W * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+  for (uint32_t k = 0; k < W; k++) w.horder[cnt[bucket(k)]++] = k;
+  APO_HIP_TRY(hipMemcpyAsync(w.d_order, w.horder, W * sizeof(uint32_t), hipMemcpyHostToDevice, s));
   return 0;
 }
 
@@ -315,9 +322,9 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     w.pair_w = W > 1 ? W : 0;
     w.kev_n = 0;
     E.reset_counters(s);
-    fused_batch(w, static_cast<const uint64_t *>(d_tok), h_off, W, min_len, mode == Mode::CAPTURE, s);
+    fused_batch(w, d_tok, W, maxwin, min_len, s);
     if (mode == Mode::CAPTURE) return 0;
-    rc = finish_run(w, N, N, 1, info, s, false);
+    rc = finish_run(w, N, W, N, 1, info, s, false);
     if (rc != 1) {
       for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;
       return rc;
@@ -644,7 +651,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   if (orc) return orc;
   stamp(w, 7, s, stamps);
   if (mode == Mode::CAPTURE) return 0;
-  rc = finish_run(w, N, m_bound, host ? -1 : sel_launched, info, s, stamps);
+  rc = finish_run(w, N, W, m_bound, host ? -1 : sel_launched, info, s, stamps);
   if (host && sel_done < 0 && m_bound > 0) {
     info.sel_rounds = (uint32_t)sel_launched;
     info.sel_sequential = 1;
@@ -690,12 +697,11 @@ int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t
 
 // Final synchronisation of a run (or of a replayed graph): counters, the
 // rare selection completion for sync-free runs, stage and kernel timings.
-int finish_run(Workspace &w, uint64_t N, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
+int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
                bool stamps) {
   int rc;
-  APO_HIP_TRY(hipMemcpyAsync(w.hrhist, w.rhist, 4 * w.nsnap * 4, hipMemcpyDeviceToHost, s));
-  APO_HIP_TRY(hipMemcpyAsync(w.hsel, w.selcnt, 2 * (kSelRoundCap + 2) * 4, hipMemcpyDeviceToHost, s));
-  if ((rc = read_counters(w, s))) return rc;
+  if (W > 1) APO_HIP_TRY(hipMemcpyAsync(w.hwin, w.win_rows, W * 4, hipMemcpyDeviceToHost, s));
+  if ((rc = read_counters(w, s, true))) return rc;
   fill_info(w, N, info);
   if (w.hcnt[CNT_FUSED] && w.hcnt[CNT_WFLAG]) return 1;
   info.sel_rounds = 0;

@@ -35,7 +35,6 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info);
 // order in w.d_off and w.d_order): rows of all windows packed in window order
 // into w.rows, counts into w.win_rows, counters where finish_run reads them.
 // Windows with too many distinct tokens are left out and counted in CNT_WFLAG.
-void fused_batch(Workspace &w, const void *tok, const uint64_t *h_off, uint32_t W, uint32_t min_len, bool capture,
-                 hipStream_t s);
+void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, uint32_t min_len, hipStream_t s);
 
 }  // namespace apo

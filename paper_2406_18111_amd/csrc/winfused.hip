@@ -89,6 +89,25 @@ __device__ __forceinline__ uint32_t wave_id() {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 }
 
+// Sum of the wavefronts' words before wavefront wv, and of all N (at most 64):
+// one word per lane and a scan (adding up 16 words in every lane of every
+// wavefront took most of the time of a step that has little else to do).
+template <int N>
+__device__ __forceinline__ uint32_t words_before(const uint32_t *w, uint32_t wv, uint32_t &all) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t inc = lane_incl_sum(lane < N ? w[lane] : 0u);
+  all = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  return wv ? (uint32_t)__builtin_amdgcn_readlane((int)inc, (int)wv - 1) : 0u;
+}
+
+// The last word before wavefront wv's that is not kNone (0: none).
+__device__ __forceinline__ uint32_t last_word(const uint32_t *w, uint32_t wv) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t v = lane < wv ? w[lane] : kNone;
+  const uint64_t m = __ballot(v != kNone);
+  return m ? (uint32_t)__builtin_amdgcn_readlane((int)v, 63 - __clzll((long long)m)) : 0u;
+}
+
 // The first `c` lanes (all from 64 on).
 __device__ __forceinline__ uint64_t first_lanes(uint32_t c) { return c >= 64 ? ~0ull : (1ull << c) - 1ull; }
 
@@ -111,7 +130,8 @@ __device__ __forceinline__ void radix_pass(T *it, uint32_t m, int ipt, uint16_t 
                                            Park park, Parked parked) {
   constexpr int NW = NT / 64;
   const uint32_t lane = threadIdx.x & 63, wv = wave_id(), base = wv * 64 * ipt;
-  uint16_t *my = cnt + wv * kDigits, *row = row0 + wv * kDigits;
+  uint16_t *my = cnt + wv * kDigits;
+  const uint16_t *row = row0 + wv * kDigits;
   my[lane] = 0;
   my[64 + lane] = 0;
   wave_order();
@@ -131,19 +151,30 @@ __device__ __forceinline__ void radix_pass(T *it, uint32_t m, int ipt, uint16_t 
     wave_order();
   }
   __syncthreads();
-  uint32_t t0 = 0, t1 = 0, b0 = 0, b1 = 0;
-#pragma unroll 4
-  for (int w = 0; w < NW; w++) {
-    const uint32_t c = cnt[w * kDigits + lane], e = cnt[w * kDigits + 64 + lane];
-    t0 += c;
-    t1 += e;
-    b0 += w < (int)wv ? c : 0u;
-    b1 += w < (int)wv ? e : 0u;
+  // one digit per lane of two wavefronts: counts into first places, digit by
+  // digit and wavefront by wavefront
+  if (wv < 2) {  // scalar
+    uint32_t c[NW], tot = 0;
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      c[w] = cnt[w * kDigits + threadIdx.x];
+      tot += c[w];
+    }
+    const uint32_t inc = lane_incl_sum(tot);
+    uint32_t at = inc - tot;
+    if (wv == 1) {  // the lower digits' total: one word per lane again
+      uint32_t low = 0;
+#pragma unroll
+      for (int w = 0; w < NW; w++) low += cnt[w * kDigits + lane];
+      at += (uint32_t)__builtin_amdgcn_readlane((int)lane_incl_sum(low), 63);
+    }
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      row0[w * kDigits + threadIdx.x] = (uint16_t)at;
+      at += c[w];
+    }
   }
-  const uint32_t i0 = lane_incl_sum(t0), i1 = lane_incl_sum(t1);
-  row[lane] = (uint16_t)(i0 - t0 + b0);
-  row[64 + lane] = (uint16_t)((uint32_t)__builtin_amdgcn_readlane((int)i0, 63) + i1 - t1 + b1);
-  wave_order();
+  __syncthreads();
   T v[MAXI];
   uint32_t pos[MAXI];
 #pragma unroll
@@ -339,8 +370,7 @@ struct FusedArgs {
   const void *tok;
   int bits;
   const uint64_t *off;     // batch: window offsets; null: one window of n tokens
-  const uint32_t *order;   // batch: block b takes window order[b] if it has over `above` and up to `most` tokens
-  uint32_t above, most;
+  const uint32_t *order;   // batch: block b takes window order[b]
   uint32_t n, min_len;
   Row *rows;               // one window: final; batch: window w's rows start at off[w] / min_len
   Occ *occ;
@@ -386,44 +416,44 @@ __device__ __forceinline__ void report(const FusedArgs &a, uint32_t win, const R
   for (int k = 0; k < kStages; k++) atomicMax(&a.dcnt[CNT_STAGE + k], (uint32_t)(stamp[k + 1] - stamp[k]));
 }
 
-// NT threads, up to NT * IPT tokens.
+// LDS of a window of up to NT * IPT tokens.  lds holds, one phase after the other:
+//   ranking: the tokens; the hash table, later the sorted distinct values
+//   suffix sort: sort keys, later the list being sorted and its parked ranks;
+//     token ranks (32 zero words past the end), suffix ranks, suffix order, LCP
+//   candidates: records start | ID << 16 | length << 32 | parked rank << 48
 template <int NT, int IPT>
-__global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
+struct ShortLds {
+  static constexpr uint32_t CAP = NT * IPT, ROWS = NT / 64 * kDigits;
+  alignas(16) unsigned char lds[CAP * 16 + 64];
+  alignas(16) uint16_t rc[CAP > ROWS ? CAP : ROWS];  // distinct values' tokens; radix rows; accepted candidates
+  alignas(16) uint16_t cnt[ROWS];  // radix counters; LCP minima; surviving candidates
+  uint32_t bitmap[CAP / 32 + 2];   // slots that open a group; accepted positions; row openings
+  uint32_t wsum[NT / 64], wsum2[NT / 64];
+  uint32_t s_nd, s_top, s_zero, s_active, s_large, s_max, s_skip, s_c, s_acc, s_dup;
+  uint32_t s_hist[kFusedRounds];
+  uint64_t s_stamp[kStages + 1];
+};
+
+// The analysis of window `win` (n tokens from token tb on) by NT threads.
+template <int NT, int IPT>
+__device__ __forceinline__ void window_short(const FusedArgs &a, ShortLds<NT, IPT> &L, uint32_t win, uint64_t tb,
+                                             uint32_t n) {
   constexpr int NW = NT / 64;
   constexpr uint32_t CAP = NT * IPT, SLOTS = 2 * CAP;
   constexpr uint32_t EARLY = CAP + CAP / 2 + 8;  // candidate records that fit before sa
   static_assert(CAP <= kFusedMax, "16 bytes of LDS per token, and positions and ranks in 13 bits");
-  // lds holds, one phase after the other:
-  //   ranking: the tokens; the hash table, later the sorted distinct values
-  //   suffix sort: sort keys, later the list being sorted and its parked ranks;
-  //     token ranks (32 zero words past the end), suffix ranks, suffix order, LCP
-  //   candidates: records start | ID << 16 | length << 32 | parked rank << 48
-  __shared__ __align__(16) unsigned char lds[CAP * 16 + 64];
-  __shared__ __align__(16) uint16_t rc[CAP > NW * kDigits ? CAP : NW * kDigits];  // distinct values' tokens; radix rows; accepted candidates
-  __shared__ __align__(16) uint16_t cnt[NW * kDigits];  // radix counters; LCP minima; surviving candidates
-  __shared__ uint32_t bitmap[CAP / 32 + 2];  // slots that open a group; accepted positions; row openings
-  __shared__ uint32_t wsum[NW], wsum2[NW];
-  __shared__ uint32_t s_nd, s_top, s_zero, s_active, s_large, s_max, s_skip, s_c, s_acc, s_dup;
-  __shared__ uint32_t s_hist[kFusedRounds];
-  __shared__ uint64_t s_stamp[kStages + 1];
+  auto &lds = L.lds;
+  auto &rc = L.rc;
+  auto &cnt = L.cnt;
+  auto &bitmap = L.bitmap;
+  auto &wsum = L.wsum;
+  auto &wsum2 = L.wsum2;
+  auto &s_nd = L.s_nd, &s_top = L.s_top, &s_zero = L.s_zero, &s_active = L.s_active, &s_large = L.s_large;
+  auto &s_max = L.s_max, &s_skip = L.s_skip, &s_c = L.s_c, &s_acc = L.s_acc, &s_dup = L.s_dup;
+  auto &s_hist = L.s_hist;
+  auto &s_stamp = L.s_stamp;
   const uint32_t tid = threadIdx.x, lane = tid & 63, wv = wave_id();
   const uint64_t below = (1ull << lane) - 1ull;
-
-  uint32_t win = 0, n = a.n;
-  uint64_t tb = 0;
-  if (a.off) {
-    win = a.order[blockIdx.x];
-    tb = a.off[win] - a.off[0];
-    n = (uint32_t)(a.off[win + 1] - a.off[win]);
-    if (n < 2 && a.above == 0) {  // uniform
-      if (tid == 0) {
-        a.win_rows[win] = 0;
-        atomicAdd(&a.dcnt[CNT_NDSUM], n);
-      }
-      return;
-    }
-    if (n <= a.above || n > a.most) return;  // another launch's
-  }
   auto stamp = [&](int k) {
     if (tid == 0) s_stamp[k] = wall_clock64();
   };
@@ -691,9 +721,7 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
       }
       if (lane == 0) wsum[wv] = run;
       __syncthreads();
-      uint32_t off = 0;
-#pragma unroll
-      for (int w = 0; w < NW; w++) off += w < (int)wv ? wsum[w] : 0u;
+      uint32_t all, off = words_before<NW>(wsum, wv, all);
 #pragma unroll
       for (int i = 0; i < IPT; i++) {
         if ((mk[i] >> lane) & 1ull) exch[off + lanes_below(mk[i])] = e[i];
@@ -745,12 +773,7 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
         wsum2[wv] = ln;
       }
       __syncthreads();
-      uint32_t co = 0, cn = 0;
-#pragma unroll
-      for (int w = 0; w < NW; w++) {
-        if (w < (int)wv && wsum[w] != kNone) co = wsum[w];
-        if (w < (int)wv && wsum2[w] != kNone) cn = wsum2[w];
-      }
+      uint32_t co = last_word(wsum, wv), cn = last_word(wsum2, wv);
 #pragma unroll
       for (int i = 0; i < IPT; i++) {
         const uint32_t q0 = wv * 64 * mpt + 64 * i;
@@ -946,13 +969,8 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
         if (md) atomicAdd(&s_dup, (uint32_t)__popcll(md));
       }
       __syncthreads();
-      uint32_t before = 0, tot = 0;
-#pragma unroll 4
-      for (int w = 0; w < NW; w++) {
-        const uint32_t c = wsum[w];
-        before += w < (int)wv ? c : 0u;
-        tot += c;
-      }
+      uint32_t tot;
+      const uint32_t before = words_before<NW>(wsum, wv, tot);
       if (ok) surv[before + lanes_below(m)] = (uint16_t)(k - p0);
       __syncthreads();
       if (wv == 0 && tot) {
@@ -1123,31 +1141,34 @@ __device__ __forceinline__ void byte_move(const uint32_t *my, uint32_t beg, uint
   }
 }
 
-__global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
+// LDS of a longer window.  big holds, one after the other: the distinct tokens'
+// table, their sorted list (64 KB) and ranks by slot; token ranks; suffix ranks;
+// token ranks; LCP values; the survivors of a chunk of candidates.
+struct LongLds {
+  alignas(16) unsigned char big[kFusedLongMax * 2];
+  alignas(16) uint32_t ctr[kLongNW * kByte];                // radix counters; LCP minima of 8; run openings
+  alignas(16) uint32_t bitmap[kFusedLongMax / 32 + 2];      // as in ShortLds; LCP minima of 64 and 512
+  uint32_t wsum[kLongNW], wsum2[kLongNW];
+  uint32_t s_nd, s_top, s_over, s_zero, s_active, s_max, s_skip, s_c, s_acc, s_dup, s_pairs;
+  uint32_t s_hist[kLongRounds];
+  uint64_t s_stamp[kStages + 1];
+};
+
+__device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint32_t win, uint64_t tb, uint32_t n) {
   constexpr int NT = kLongNT, NW = kLongNW;
   constexpr uint32_t CAP = kFusedLongMax;
   const FusedArgs &a = la.f;
-  // one after the other: the distinct tokens' table, their sorted list (64 KB)
-  // and ranks by slot; token ranks; suffix ranks; token ranks; LCP values; the
-  // survivors of a chunk of candidates
-  __shared__ __align__(16) unsigned char big[CAP * 2];
-  __shared__ __align__(16) uint32_t ctr[NW * kByte];   // radix counters; LCP minima of 8
-  __shared__ __align__(16) uint32_t bitmap[CAP / 32 + 2];  // as in k_window; LCP minima of 64 and 512
-  __shared__ uint32_t wsum[NW], wsum2[NW];
-  __shared__ uint32_t s_nd, s_top, s_over, s_zero, s_active, s_max, s_skip, s_c, s_acc, s_dup, s_pairs;
-  __shared__ uint32_t s_hist[kLongRounds];
-  __shared__ uint64_t s_stamp[kStages + 1];
+  auto &big = L.big;
+  auto &ctr = L.ctr;
+  auto &bitmap = L.bitmap;
+  auto &wsum = L.wsum;
+  auto &wsum2 = L.wsum2;
+  auto &s_nd = L.s_nd, &s_top = L.s_top, &s_over = L.s_over, &s_zero = L.s_zero, &s_active = L.s_active;
+  auto &s_max = L.s_max, &s_skip = L.s_skip, &s_c = L.s_c, &s_acc = L.s_acc, &s_dup = L.s_dup, &s_pairs = L.s_pairs;
+  auto &s_hist = L.s_hist;
+  auto &s_stamp = L.s_stamp;
   const uint32_t tid = threadIdx.x, lane = tid & 63, wv = wave_id();
   const uint64_t below = (1ull << lane) - 1ull;
-
-  uint32_t win = 0, n = a.n;
-  uint64_t tb = 0;
-  if (a.off) {
-    win = a.order[blockIdx.x];
-    tb = a.off[win] - a.off[0];
-    n = (uint32_t)(a.off[win + 1] - a.off[win]);
-    if (n <= a.above || n > a.most) return;  // uniform: another launch's
-  }
   uint16_t *const gtxt = la.txt + 2 * tb, *const gsa = la.sa + 2 * tb, *const grank = la.rank + 2 * tb,
                  *const glcp = la.lcp + 2 * tb;
   uint64_t *const e0 = la.e0 + 2 * tb, *const e1 = la.e1 + 2 * tb, *const fl = la.flags + tb;
@@ -1428,11 +1449,7 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
         wsum2[wv] = ln;
       }
       __syncthreads();
-      uint32_t co = 0, cn = 0;
-      for (uint32_t w = 0; w < wv; w++) {
-        if (wsum[w] != kNone) co = wsum[w];
-        if (wsum2[w] != kNone) cn = wsum2[w];
-      }
+      uint32_t co = last_word(wsum, wv), cn = last_word(wsum2, wv);
 #pragma unroll 1
       for (uint32_t q0 = qbeg; q0 < qtop; q0 += 64) {  // scalar
         const uint32_t q = q0 + lane, e = l0[min(q, m - 1)];
@@ -1679,13 +1696,8 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
         if (md) atomicAdd(&s_dup, (uint32_t)__popcll(md));
       }
       __syncthreads();
-      uint32_t before = 0, tot = 0;
-#pragma unroll 4
-      for (int w = 0; w < NW; w++) {
-        const uint32_t c = wsum[w];
-        before += w < (int)wv ? c : 0u;
-        tot += c;
-      }
+      uint32_t tot;
+      const uint32_t before = words_before<NW>(wsum, wv, tot);
       if (ok) {
         const uint32_t q = before + lanes_below(m);
         item[q] = s | (l << 16);
@@ -1757,6 +1769,44 @@ __global__ __launch_bounds__(kLongNT) void k_window_long(LongArgs la) {
   }
 }
 
+// The window of a workgroup: the lone one, or the next longest of the batch.
+__device__ __forceinline__ uint32_t window_of(const FusedArgs &a, uint32_t &win, uint64_t &tb) {
+  win = 0;
+  tb = 0;
+  if (!a.off) return a.n;
+  win = a.order[blockIdx.x];
+  tb = a.off[win] - a.off[0];
+  const uint32_t n = (uint32_t)(a.off[win + 1] - a.off[win]);
+  if (n < 2 && threadIdx.x == 0) {
+    a.win_rows[win] = 0;
+    atomicAdd(&a.dcnt[CNT_NDSUM], n);
+  }
+  return n;
+}
+
+template <int NT, int IPT>
+__global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
+  __shared__ ShortLds<NT, IPT> L;
+  uint32_t win;
+  uint64_t tb;
+  const uint32_t n = window_of(a, win, tb);
+  if (n >= 2) window_short<NT, IPT>(a, L, win, tb, n);  // uniform
+}
+
+// Windows of any length up to kFusedLongMax in one launch: in launches of their
+// own the short windows of a batch would wait for its last long one.
+__global__ __launch_bounds__(kLongNT) void k_window_any(LongArgs la) {
+  __shared__ union Lds {
+    ShortLds<kLongNT, kFusedMax / kLongNT> s;
+    LongLds l;
+  } L;
+  uint32_t win;
+  uint64_t tb;
+  const uint32_t n = window_of(la.f, win, tb);
+  if (n > kFusedMax) window_long(la, L.l, win, tb, n);  // uniform
+  else if (n >= 2) window_short<kLongNT, kFusedMax / kLongNT>(la.f, L.s, win, tb, n);
+}
+
 // Packs the windows' rows, each window's at row off[w] / min_len of `src`,
 // into dst in window order: window w's go to the sum of the counts before it,
 // which its workgroup adds up itself (a few thousand words at most).
@@ -1773,21 +1823,15 @@ __global__ __launch_bounds__(256) void k_pack_rows(const Row *src, const uint64_
   for (uint32_t r = threadIdx.x; r < c; r += 256) dst[base + r] = from[r];
 }
 
-// Window sizes up to which each workgroup size is used: the smallest one that
-// holds a window means fewer wavefronts per barrier, and more windows per
-// compute unit.
-constexpr uint32_t kClassMost[] = {1024, 2048, 4096, kFusedMax, kFusedLongMax};
-constexpr int kFusedClasses = 5;
-
-void launch(const LongArgs &la, int cls, uint32_t blocks, hipStream_t s) {
+void launch(const LongArgs &la, uint32_t blocks, uint64_t longest, hipStream_t s) {
+  // the smallest workgroup that holds the longest window: fewer wavefronts per
+  // barrier, and more windows per compute unit
   const FusedArgs &a = la.f;
-  switch (cls) {
-    case 0: hipLaunchKernelGGL((k_window<256, 4>), dim3(blocks), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL((k_window<512, 4>), dim3(blocks), dim3(512), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_window<1024, 4>), dim3(blocks), dim3(1024), 0, s, a); break;
-    case 3: hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a); break;
-    default: hipLaunchKernelGGL(k_window_long, dim3(blocks), dim3(kLongNT), 0, s, la);
-  }
+  if (longest <= 1024) hipLaunchKernelGGL((k_window<256, 4>), dim3(blocks), dim3(256), 0, s, a);
+  else if (longest <= 2048) hipLaunchKernelGGL((k_window<512, 4>), dim3(blocks), dim3(512), 0, s, a);
+  else if (longest <= 4096) hipLaunchKernelGGL((k_window<1024, 4>), dim3(blocks), dim3(1024), 0, s, a);
+  else if (longest <= kFusedMax) hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a);
+  else hipLaunchKernelGGL(k_window_any, dim3(blocks), dim3(kLongNT), 0, s, la);
 }
 
 LongArgs args_of(const Workspace &w) {
@@ -1801,12 +1845,6 @@ LongArgs args_of(const Workspace &w) {
   la.e1 = la.e0 + 2 * w.capN;
   la.flags = reinterpret_cast<uint64_t *>(w.tmp_a);
   return la;
-}
-
-int class_of_window(uint64_t n) {
-  int c = 0;
-  while (n > kClassMost[c]) c++;
-  return c;
 }
 
 }  // namespace
@@ -1824,7 +1862,7 @@ void fused_window(const Workspace &w, const void *tok, int bits, uint32_t n, uin
   a.occ = static_cast<Occ *>(occ);
   a.occ_cap = occ_cap;
   a.info = info;
-  launch(la, class_of_window(n), 1, s);
+  launch(la, 1, n, s);
 }
 
 void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
@@ -1847,8 +1885,7 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
   for (int k = 0; k < kStages; k++) info.stage_ms[k] = (double)(f.stamp[k + 1] - f.stamp[k]) * 1e-5;  // 100 MHz
 }
 
-void fused_batch(Workspace &w, const void *tok, const uint64_t *h_off, uint32_t W, uint32_t min_len, bool capture,
-                 hipStream_t s) {
+void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, uint32_t min_len, hipStream_t s) {
   fill_u32(w.dcnt, CNT_COUNT, 0, s);
   fill_u32(w.dcnt + CNT_FUSED, 1, 1, s);
   fill_u32(w.rhist, 4 * (uint64_t)w.nsnap, 0, s);
@@ -1858,29 +1895,14 @@ void fused_batch(Workspace &w, const void *tok, const uint64_t *h_off, uint32_t 
   a.tok = tok;
   a.bits = 64;
   a.off = w.d_off;
+  a.order = w.d_order;
   a.min_len = min_len;
   a.rows = static_cast<Row *>(w.occ);  // a batch reports no occurrences: their array stages the rows
   a.row_cap = kNone;
   a.dcnt = w.dcnt;
   a.rhist = w.rhist;
   a.win_rows = w.win_rows;
-  // The windows come longest first.  A captured sequence may be replayed with
-  // other windows of the same total, number and longest length: there every
-  // launch looks at every window.
-  uint32_t count[kFusedClasses] = {0}, longest = 0;
-  for (uint32_t k = 0; k < W; k++) {
-    const uint64_t n = h_off[k + 1] - h_off[k];
-    count[class_of_window(n)]++;
-    longest = std::max<uint32_t>(longest, (uint32_t)n);
-  }
-  uint32_t at = 0;
-  for (int c = class_of_window(longest); c >= 0; c--) {
-    a.above = c ? kClassMost[c - 1] : 0;
-    a.most = kClassMost[c];
-    a.order = w.d_order + (capture ? 0 : at);
-    if (capture || count[c]) launch(la, c, capture ? W : count[c], s);
-    at += count[c];
-  }
+  launch(la, W, longest, s);
   hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, W,
                      min_len, static_cast<Row *>(w.rows));
   copy_u32(w.selcnt, w.dcnt + CNT_M, s);
