@@ -24,7 +24,7 @@ enum Cnt {
   CNT_AUX = 14,    // scratch count of a stage (tile counts, histogram size, runs)
   CNT_SNAPS = 15,  // 1 + last doubling round with a rank snapshot (0: none)
   CNT_NDSUM = 16,  // batches: distinct tokens summed over the windows ranked on their own
-  CNT_NDMAX = 17,  // batches: most distinct tokens of one such window
+  CNT_NDMAX = 17,  // batches: most distinct tokens of one such window (one window of 32-bit tokens: the largest token)
   CNT_WFLAG = 18,  // batches: windows ranked through the shared table instead
   CNT_WNEXT = 19,  // batches: next window for the per-window ranking
   CNT_WNEXT2 = 20, // batches: next window for the per-window first doubling round
@@ -111,7 +111,9 @@ struct Workspace {
   uint32_t *selcnt = nullptr;      // selection rounds: live counts, undecided counts
   uint32_t *hsel = nullptr;        // pinned host mirror of selcnt
   uint32_t *hcnt = nullptr;        // pinned host mirror of dcnt; rhist and selcnt follow it here and on the device
-  SortCounters *hctr = nullptr;    // pinned host mirror of engine counters
+  SortCounters *hctr = nullptr;    // pinned: the engine counters' error word
+  uint32_t *hflag = nullptr;       // pinned: report_seq of the last report that is there
+  uint32_t report_seq = 0;         // reports asked for
   hipEvent_t ev[kStages + 1] = {};
   int ktag = KT_NONE;              // kernel family timed with events around each launch
   hipEvent_t kev[2 * kMaxTimed] = {};

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <thread>
 
 namespace apo {
 
@@ -53,9 +54,8 @@ void Workspace::release() {
   if (mem && !external) (void)hipFree(mem);
   mem = nullptr;
   external = false;
-  if (hcnt) (void)hipHostFree(hcnt);  // holds hrhist and hsel too
-  hcnt = hrhist = hsel = nullptr;
-  if (hctr) (void)hipHostFree(hctr);
+  if (hcnt) (void)hipHostFree(hcnt);  // holds hrhist, hsel, hflag and hctr too
+  hcnt = hrhist = hsel = hflag = nullptr;
   hctr = nullptr;
   if (hoff) (void)hipHostFree(hoff);  // holds horder and hwin too
   hoff = nullptr;
@@ -191,11 +191,14 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
   selcnt = (uint32_t *)(m + o_sc);
   int rc = eng.alloc(C2, nullptr, ext ? static_cast<char *>(ext) + L.total : nullptr);
   if (rc) { release(); return rc; }
-  // the mirrors of dcnt, rhist and selcnt lie as those do, so that one copy takes all three
-  APO_HIP_TRY(hipHostMalloc((void **)&hcnt, o_sc + 2 * (kSelRoundCap + 2) * 4 - o_cnt, hipHostMallocDefault));
+  // the mirrors of dcnt, rhist and selcnt lie as those do, so that one pass takes all three
+  const size_t mirror = o_sc + 2 * (kSelRoundCap + 2) * 4 - o_cnt;
+  APO_HIP_TRY(hipHostMalloc((void **)&hcnt, mirror + 64 + sizeof(SortCounters), hipHostMallocCoherent));
+  memset(hcnt, 0, mirror + 64 + sizeof(SortCounters));
   hrhist = hcnt + (o_rh - o_cnt) / 4;
   hsel = hcnt + (o_sc - o_cnt) / 4;
-  APO_HIP_TRY(hipHostMalloc((void **)&hctr, sizeof(SortCounters), hipHostMallocDefault));
+  hflag = hcnt + mirror / 4;
+  hctr = reinterpret_cast<SortCounters *>(reinterpret_cast<char *>(hcnt) + mirror + 64);
   APO_HIP_TRY(hipHostMalloc((void **)&hoff, (size_t)(wantW + 1) * 16, hipHostMallocDefault));
   horder = reinterpret_cast<uint32_t *>(hoff + wantW + 1);
   hwin = horder + wantW + 1;
@@ -208,12 +211,45 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
 }
 
 // ------------------------------------------------------------- helpers
-static int read_counters(Workspace &w, hipStream_t s, bool rounds = false) {
-  // rounds: the per-round counts behind the counters too
-  const size_t bytes = rounds ? (size_t)(w.hsel + 2 * (kSelRoundCap + 2) - w.hcnt) * 4 : CNT_COUNT * 4;
-  APO_HIP_TRY(hipMemcpyAsync(w.hcnt, w.dcnt, bytes, hipMemcpyDeviceToHost, s));
-  APO_HIP_TRY(hipMemcpyAsync(w.hctr, w.eng.bufs().ctr, sizeof(SortCounters), hipMemcpyDeviceToHost, s));
-  APO_HIP_TRY(hipStreamSynchronize(s));
+// The counters, and the round counts behind them, straight into the pinned
+// mirror, with a flag the host polls: a copy of each block and a stream wait
+// held the stream some 35 us, this some 15.
+__global__ void k_report(const uint32_t *cnt, uint32_t words, const SortCounters *ctr, uint32_t *out,
+                         SortCounters *out_ctr, uint32_t *flag, uint32_t seq) {
+  for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) out[i] = cnt[i];
+  if (threadIdx.x == 0) out_ctr->err = ctr->err;
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Waits until there() holds, which the device's stores to pinned memory make
+// so.  The stream is queried now and then: one that has ended, or failed, makes
+// no more of them.
+template <typename F>
+static int wait_report(F there, hipStream_t s) {
+  for (uint32_t i = 1;; i++) {
+    if (there()) return 0;
+    if (i % 1024 == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipSuccess) return there() ? 0 : -4;
+      (void)hipGetLastError();
+      if (e != hipErrorNotReady) APO_HIP_TRY(e);
+      std::this_thread::yield();
+    } else {
+      __builtin_ia32_pause();
+    }
+  }
+}
+
+// drain: the stream too (its copies to pinned memory)
+static int read_counters(Workspace &w, hipStream_t s, bool drain = false) {
+  int rc;
+  const uint32_t words = (uint32_t)(w.hsel + 2 * (kSelRoundCap + 2) - w.hcnt);
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, s, w.dcnt, words, w.eng.bufs().ctr, w.hcnt, w.hctr, w.hflag,
+                     ++w.report_seq);
+  if (drain) APO_HIP_TRY(hipStreamSynchronize(s));
+  else if ((rc = wait_report([&] { return __atomic_load_n(w.hflag, __ATOMIC_ACQUIRE) == w.report_seq; }, s))) return rc;
   if (w.fail_after >= 0 && w.fail_after-- == 0) {  // test hook: this sync reports a device error
     fprintf(stderr, "[apo] injected device error\n");
     return -4;
@@ -352,6 +388,11 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   // ---- order-preserving token ranks
   const uint32_t *key0;
   uint32_t bits0;
+  // One window, host-driven: the first sort takes 2^pack tokens at once, as many
+  // as fit the 32-bit key (at most 16, the prefix of the first rank snapshot).
+  int pack = 0;
+  uint64_t vals = 0;  // key digits 1..vals (0: not known)
+  const bool packs = host && !batch && stop != Stop::SA && N > 0;
   // batches of 64-bit tokens: the windows ranked on their own also get their
   // first doubling round from a per-window kernel; the engine's first round
   // then only sorts the flagged windows (and is skipped by host-driven runs
@@ -411,6 +452,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     } else {
       nd_bound = 0;
     }
+    vals = nd_bound;
     win_r0 = batch;
     skip0 = batch && !shared;
     key0 = w.tokrank;
@@ -418,12 +460,27 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   } else {
     key0 = static_cast<const uint32_t *>(d_tok);
     bits0 = 32;
+    if (packs) {
+      max_token(key0, N, dc + CNT_NDMAX, s);
+      if ((rc = read_counters(w, s))) return rc;
+      vals = (uint64_t)w.hcnt[CNT_NDMAX] + 1;
+      bits0 = std::max<uint32_t>(bit_length_u64(w.hcnt[CNT_NDMAX]), 1);
+    }
+  }
+  if (packs && vals > 0) {
+    const int b = bit_length_u64(vals);
+    while (pack < kSnapFrom && (b << (pack + 1)) <= 32 && (1ull << (pack + 1)) <= maxwin) pack++;
+    if (pack) bits0 = (uint32_t)b << pack;
   }
   stamp(w, 1, s, stamps);
 
   // ---- suffix array by prefix doubling
-  // Host-driven: rounds are launched `spec` at a time and the host reads their
-  // outcomes once per batch.  Otherwise every round up to the bound for the
+  // Host-driven: each round's outcome goes to pinned memory as the next round's
+  // gather closes it, and the host, polling, launches the round after that
+  // while the GPU is busy with the next one: the stream never waits, and one
+  // round is launched in vain (rounds launched four at a time and read with a
+  // stream wait: 12 launched where 10 were needed at n = 131071).  Otherwise every
+  // round up to the bound for the
   // longest window is launched.  A round launched after the last active suffix
   // became unique finds empty lists everywhere and changes nothing, so extra
   // rounds never alter the result.  Large units only arise from large units
@@ -450,17 +507,20 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       win_round0(B, w.d_off, worder, W, w.wflag, key0, w.rank, w.aflag, rel_bits, dc + CNT_WNEXT2, false, pflag, nullptr,
                  nullptr, s);
   } else {
-    E.gather_identity(key0, (uint32_t)N, s);
+    if (pack)
+      E.gather_packed(key0, (uint32_t)N, bits == 64 ? 0u : 1u, 1 << pack, (int)bits0 >> pack, w.rhist, pack, s);
+    else
+      E.gather_identity(key0, (uint32_t)N, s);
     E.init_units(cur, w.d_off, W, 0, bits0, s);
   }
   bool big = maxwin > (1ull << E.tile_log());
   uint64_t act = N;
-  int r = pair0 ? 2 : 0, synced = r, done_round = -1;
+  int r = pair0 ? 2 : pack, done_round = -1;
   w.kev_n = 0;
-  const int spec = host ? 4 : r_max;
-  while (done_round < 0) {
-    if (r >= w.nsnap) return -4;
-    if (r > 0) E.gather_sa(cur, w.rank, w.aflag, wend, (uint32_t)N, 1u << (r - 1), w.rhist, r, s);
+  const uint32_t seq = ++w.report_seq;
+  auto round = [&]() -> int {  // launches round r
+    if (r > pack) E.gather_sa(cur, w.rank, w.aflag, wend, (uint32_t)N, 1u << (r - 1), w.rhist, r, s, host ? w.hrhist : nullptr,
+                               seq);
     // sync-free runs with pair ranks: the second round's state from them,
     // after that round's gather (which found nothing grouped and cleared
     // the lists it fills), so the round's sort launches find no work
@@ -469,7 +529,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
                  dc + CNT_A1, w.rhist, s);
     RankOut R{w.rank, (uint32_t)r, w.aflag};
     if (r > 0 || !skip0) {
-      if (big) E.msd(cur, act, r == 0 ? (int)bits0 : (int)rel_bits, s, r == 0 ? nullptr : wbeg);
+      const bool first = r == pack;  // keys are tokens, not ranks
+      if (big) E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg);
       const bool timed = w.ktag == KT_LDS_SA && w.kev_n < kMaxTimed;
       if (timed) APO_HIP_TRY(hipEventRecord(w.kev[2 * w.kev_n], s));
       E.lds_sa(cur, R, rel_bits, act, s);
@@ -483,31 +544,39 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     if (r >= kSnapFrom) snapshot_ranks(w.rank, w.snap + (size_t)r * N, N, w.rhist + 4 * (r - 1), dc + CNT_SNAPS, r, s);
     cur ^= 1;
     r++;
-    if (!host) {
-      if (r >= r_max) {
-        E.round_end(cur ^ 1, r - 1, w.rhist, s);
-        done_round = r - 1;  // an upper bound of the last round that did work
-      }
-      continue;
+    return 0;
+  };
+  if (!host) {
+    while (r < r_max) {
+      if (r >= w.nsnap) return -4;
+      if ((rc = round())) return rc;
     }
-    if (r - synced >= spec || r >= w.nsnap) {
-      E.round_end(cur ^ 1, r - 1, w.rhist, s);
-      APO_HIP_TRY(hipMemcpyAsync(w.hrhist, w.rhist, 4 * w.nsnap * 4, hipMemcpyDeviceToHost, s));
-      if ((rc = read_counters(w, s))) return rc;
-      for (int k = synced; k < r; k++)
-        if (w.hrhist[4 * k] == 0) { done_round = k; break; }
-      if (done_round < 0) {
-        act = w.hrhist[4 * (r - 1)];
-        big = w.hrhist[4 * (r - 1) + 1] > 0;
-        synced = r;
-      }
-    }
+    E.round_end(cur ^ 1, r - 1, w.rhist, s);
+    done_round = r - 1;  // an upper bound of the last round that did work
+  }
+  for (int k = r; done_round < 0; k++) {  // k: the round whose outcome is next
+    while (r <= k + 1 && r < w.nsnap)
+      if ((rc = round())) return rc;
+    if (k >= w.nsnap) return -4;
+    if (r == k + 1) E.round_end(cur ^ 1, k, w.rhist, s, w.hrhist, seq);  // no round is left to close it
+    uint64_t got = 0;
+    auto there = [&] {
+      got = __atomic_load_n(reinterpret_cast<const uint64_t *>(w.hrhist + 4 * k), __ATOMIC_ACQUIRE);
+      return got >> 33 == (seq & 0x7FFFFFFFu);
+    };
+    if ((rc = wait_report(there, s))) return rc;
+    act = got & 0xFFFFFFFFu;
+    big = (got >> 32) & 1u;
+    if (act == 0) done_round = k;
+  }
+  if (w.fail_after >= 0 && w.fail_after-- == 0) {  // test hook, as in read_counters
+    fprintf(stderr, "[apo] injected device error\n");
+    return -4;
   }
   r = done_round;
   APO_HIP_TRY(hipMemcpyAsync(w.sa, B.val[0], N * 4, hipMemcpyDeviceToDevice, s));
   stamp(w, 2, s, stamps);
   if (stop == Stop::SA) {
-    APO_HIP_TRY(hipMemcpyAsync(w.hrhist, w.rhist, 4 * w.nsnap * 4, hipMemcpyDeviceToHost, s));
     if ((rc = read_counters(w, s))) return rc;
     fill_info(w, N, info);
     return 0;
@@ -516,6 +585,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   // ---- LCP via Phi / PLCP (lifting over the snapshots of the rounds that
   // sorted something, at most r-1)
   build_lcp(w.sa, w.rank, N, wbeg, wend, w.snap, dc + CNT_SNAPS, key0, r - 1, w.lcp, s);
+  if (pack) short_rounds(w.lcp, N, pack, w.rhist, s);
   stamp(w, 3, s, stamps);
   if (stop == Stop::LCP) return read_counters(w, s);
 
@@ -633,7 +703,6 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       q0 = hi;
       sel_launched = hi;
       if (!host) break;  // checked after the output stage
-      APO_HIP_TRY(hipMemcpyAsync(w.hsel, w.selcnt, 2 * (kSelRoundCap + 2) * 4, hipMemcpyDeviceToHost, s));
       if ((rc = read_counters(w, s))) return rc;
       for (int q = lo; q < hi; q++)
         if (w.hsel[q + 1] == 0) { sel_done = q; break; }  // nlive[q + 1]: undecided after round q

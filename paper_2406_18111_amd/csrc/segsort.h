@@ -23,7 +23,8 @@ class SortEngine {
   int tile_log() const { return (int)b_.tile_log; }
   int digit_bits() const { return (int)b_.digit_bits; }
   void round_begin(int cur, hipStream_t s);
-  void round_end(int cur, int r, uint32_t *hist, hipStream_t s);
+  // mirror (nullable, pinned, 8-byte words): at word 2 r the active slots, above them 2 * seq + (large units left)
+  void round_end(int cur, int r, uint32_t *hist, hipStream_t s, uint32_t *mirror = nullptr, uint32_t seq = 0);
   // only (nullable): just the ranges w with only[w] != 0
   void init_units(int cur, const uint64_t *d_off, uint32_t nranges, uint32_t base, uint32_t key_bits,
                   hipStream_t s, const uint8_t *only = nullptr);
@@ -34,8 +35,11 @@ class SortEngine {
   // only (nullable): just the slots p with only[wid[p]] != 0, and nothing unless *gate > 0 (gate nullable)
   void gather_identity(const uint32_t *src, uint32_t n, hipStream_t s, const uint32_t *wid = nullptr,
                        const uint8_t *only = nullptr, const uint32_t *gate = nullptr);
+  // keys of k tokens of one window (src + add in 1 .. 2^b - 1, k * b <= 32); hist: the replaced rounds' counts, set to n
+  void gather_packed(const uint32_t *src, uint32_t n, uint32_t add, int k, int b, uint32_t *hist, int skipped,
+                     hipStream_t s);
   void gather_sa(int cur, const uint32_t *rank, const uint8_t *aflag, const uint32_t *slot_wend, uint32_t n,
-                 uint32_t h, uint32_t *hist, int r, hipStream_t s);
+                 uint32_t h, uint32_t *hist, int r, hipStream_t s, uint32_t *mirror = nullptr, uint32_t seq = 0);
   void gather_field(int cur, const uint32_t *field, int stride, const uint32_t *all_dev, int sub,
                     const uint32_t *c_dev, uint32_t c, uint64_t bound, hipStream_t s);
   void iota_val(const uint32_t *n_dev, uint64_t bound, hipStream_t s);

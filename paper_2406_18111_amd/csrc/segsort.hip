@@ -45,15 +45,24 @@ __global__ void k_round_begin(SortCounters *c, int cur) {
   }
 }
 
-// Records the outcome of round `r` (active slots and large units handed to
-// the next round, entries sorted in LDS) so the host can read several rounds
-// at once.
-__global__ void k_round_end(const SortCounters *c, int cur, int r, uint32_t *hist) {
-  if (threadIdx.x == 0) {
-    hist[4 * r] = c->act_cnt[cur ^ 1];
-    hist[4 * r + 1] = (uint32_t)(c->big_pk[cur ^ 1][0] >> 32);
-    hist[4 * r + 2] = c->lds_elems;
-  }
+// Records the outcome of round r - active slots and large units handed to
+// the next round, entries sorted in LDS - in hist and, for a host that polls,
+// the first two in its pinned mirror: one 64-bit store (nothing to order) of the
+// active slots below 2 * seq + (large units left).
+__device__ __forceinline__ void record_round(const SortCounters *c, int nxt, int r, uint32_t *hist, uint32_t *mirror,
+                                             uint32_t seq) {
+  const uint32_t act = c->act_cnt[nxt], big = (uint32_t)(c->big_pk[nxt][0] >> 32);
+  hist[4 * r] = act;
+  hist[4 * r + 1] = big;
+  hist[4 * r + 2] = c->lds_elems;
+  if (mirror)
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(mirror + 4 * r),
+                       ((unsigned long long)(2 * seq + (big ? 1u : 0u)) << 32) | act, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ void k_round_end(const SortCounters *c, int cur, int r, uint32_t *hist, uint32_t *mirror, uint32_t seq) {
+  if (threadIdx.x == 0) record_round(c, cur ^ 1, r, hist, mirror, seq);
 }
 
 __device__ __forceinline__ uint32_t chunks_of(uint32_t len, uint32_t chunk_log) {
@@ -191,6 +200,22 @@ __global__ void k_gather_identity(SortBufs B, const uint32_t *src, uint32_t n, c
   }
 }
 
+// The first sort of one window by its first k tokens at once: slot p holds
+// suffix p, keyed by tokens p .. p + k - 1 (value + add, in 1 .. 2^b - 1, k * b <= 32;
+// 0 past the end), which replaces the rounds of 1, 2, .., k / 2 tokens.  A thread's k reads overlap its neighbours': one pass over the
+// tokens from HBM, the rest from L1.  The replaced rounds' counts are set to n
+// here (work was done) and counted from the LCP array later.
+__global__ void k_gather_packed(SortBufs B, const uint32_t *src, uint32_t n, uint32_t add, uint32_t k, uint32_t b,
+                                uint32_t *hist, uint32_t skipped) {
+  if (blockIdx.x == 0 && threadIdx.x < skipped) hist[4 * threadIdx.x] = n;
+  for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x) {
+    uint32_t key = 0;
+    for (uint32_t q = 0; q < k; q++) key = (key << b) | (q < n - p ? src[p + q] + add : 0u);
+    B.key[0][p] = key;
+    B.val[0][p] = p;
+  }
+}
+
 // Doubling round with offset h: key = rank of the suffix h positions later,
 // 0 when that lies past the end of the suffix's window.
 // Block 0 also closes the previous round (records its outcome in hist[r-1])
@@ -200,13 +225,12 @@ __global__ void k_gather_identity(SortBufs B, const uint32_t *src, uint32_t n, c
 // 2^(r-1) positions later (0 past the window end).  A dense pass over the
 // slots (the grouped-slot flags are sequential) instead of an active list.
 __global__ void k_gather_sa(SortBufs B, int cur, const uint32_t *rank, const uint8_t *aflag,
-                            const uint32_t *slot_wend, uint32_t n, uint32_t h, uint32_t *hist, int r) {
+                            const uint32_t *slot_wend, uint32_t n, uint32_t h, uint32_t *hist, int r,
+                            uint32_t *mirror, uint32_t seq) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     SortCounters *c = B.ctr;
     const int nxt = cur ^ 1;
-    hist[4 * (r - 1)] = c->act_cnt[cur];
-    hist[4 * (r - 1) + 1] = (uint32_t)(c->big_pk[cur][0] >> 32);
-    hist[4 * (r - 1) + 2] = c->lds_elems;
+    record_round(c, cur, r - 1, hist, mirror, seq);
     for (int t = 0; t < kClasses; t++) c->cls_cnt[nxt][t] = 0;
     for (int t = 1; t < kMsdLists; t++) c->big_pk[cur][t] = 0;
     c->big_pk[nxt][0] = 0;
@@ -1269,8 +1293,8 @@ void SortEngine::round_begin(int cur, hipStream_t s) {
   hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(64), 0, s, b_.ctr, cur);
 }
 
-void SortEngine::round_end(int cur, int r, uint32_t *hist, hipStream_t s) {
-  hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, s, b_.ctr, cur, r, hist);
+void SortEngine::round_end(int cur, int r, uint32_t *hist, hipStream_t s, uint32_t *mirror, uint32_t seq) {
+  hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, s, b_.ctr, cur, r, hist, mirror, seq);
 }
 
 void SortEngine::init_units(int cur, const uint64_t *d_off, uint32_t nranges, uint32_t base,
@@ -1290,9 +1314,17 @@ void SortEngine::gather_identity(const uint32_t *src, uint32_t n, hipStream_t s,
   hipLaunchKernelGGL(k_gather_identity, grid_for(n, 256, 4096), dim3(256), 0, s, b_, src, n, wid, only, gate);
 }
 
+void SortEngine::gather_packed(const uint32_t *src, uint32_t n, uint32_t add, int k, int b, uint32_t *hist,
+                               int skipped, hipStream_t s) {
+  hipLaunchKernelGGL(k_gather_packed, grid_for(n, 256, 8192), dim3(256), 0, s, b_, src, n, add, (uint32_t)k,
+                     (uint32_t)b, hist, (uint32_t)skipped);
+}
+
 void SortEngine::gather_sa(int cur, const uint32_t *rank, const uint8_t *aflag, const uint32_t *slot_wend,
-                           uint32_t n, uint32_t h, uint32_t *hist, int r, hipStream_t s) {
-  hipLaunchKernelGGL(k_gather_sa, dim3(4096), dim3(256), 0, s, b_, cur, rank, aflag, slot_wend, n, h, hist, r);
+                           uint32_t n, uint32_t h, uint32_t *hist, int r, hipStream_t s, uint32_t *mirror,
+                           uint32_t seq) {
+  hipLaunchKernelGGL(k_gather_sa, dim3(4096), dim3(256), 0, s, b_, cur, rank, aflag, slot_wend, n, h, hist, r, mirror,
+                     seq);
 }
 
 void SortEngine::gather_field(int cur, const uint32_t *field, int stride, const uint32_t *all_dev, int sub,

@@ -75,6 +75,10 @@ void snapshot_ranks(const uint32_t *rank, uint32_t *snap_r, uint64_t n, const ui
                     int r, hipStream_t s);
 // LCP of adjacent suffixes.  rank: final ranks of the suffix sort (1 + slot);
 // snap: level j at snap + j * n for kSnapFrom <= j < *snaps (and j <= top).
+// *out = max(*out, largest of the n tokens)
+void max_token(const uint32_t *tok, uint64_t n, uint32_t *out, hipStream_t s);
+// hist[4 r] = slots whose suffix shares its first 2^r tokens with a neighbour (r < rounds <= 4)
+void short_rounds(const uint32_t *lcp, uint64_t n, int rounds, uint32_t *hist, hipStream_t s);
 void build_lcp(const uint32_t *sa, const uint32_t *rank, uint64_t n, const uint32_t *wbeg, const uint32_t *wend,
                const uint32_t *snap, const uint32_t *snaps, const uint32_t *key0, int top, uint32_t *lcp,
                hipStream_t s);

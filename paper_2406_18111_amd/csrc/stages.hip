@@ -1273,6 +1273,47 @@ void build_lcp(const uint32_t *sa, const uint32_t *rank, uint64_t n, const uint3
                      sa, rank, n, wbeg, wend, snap, snaps, key0, top, lcp);
 }
 
+__global__ __launch_bounds__(256) void k_max_token(const uint32_t *tok, uint64_t n, uint32_t *out) {
+  __shared__ uint32_t sh[4];
+  uint32_t m = 0;
+  GRID_STRIDE(i, n) m = max(m, tok[i]);
+  m = wave_incl_max(m);
+  if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicMax(out, max(max(sh[0], sh[1]), max(sh[2], sh[3])));
+}
+
+void max_token(const uint32_t *tok, uint64_t n, uint32_t *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_max_token, grid_for(n, 256, 1024), dim3(256), 0, s, tok, n, out);
+}
+
+// What the doubling rounds that a packed first key replaced would have left
+// grouped: a suffix is grouped after round r iff it shares 2^r tokens with one
+// of its neighbours in the suffix array.
+__global__ __launch_bounds__(256) void k_short_rounds(const uint32_t *lcp, uint64_t n, int rounds, uint32_t *hist) {
+  __shared__ uint32_t sh[4];
+  if (threadIdx.x < 4) sh[threadIdx.x] = 0;
+  __syncthreads();
+  uint32_t cnt[4] = {0, 0, 0, 0};
+  GRID_STRIDE(i, n) {
+    const uint32_t m = max(i ? lcp[i - 1] : 0u, lcp[i]);
+#pragma unroll
+    for (int r = 0; r < 4; r++) cnt[r] += m >= (1u << r) ? 1u : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const uint32_t c = wave_incl_sum(cnt[r]);
+    if ((threadIdx.x & 63) == 63) atomicAdd(&sh[r], c);
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < rounds) atomicAdd(&hist[4 * threadIdx.x], sh[threadIdx.x]);
+}
+
+void short_rounds(const uint32_t *lcp, uint64_t n, int rounds, uint32_t *hist, hipStream_t s) {
+  fill_u32(hist, 4 * (uint64_t)rounds, 0, s);
+  hipLaunchKernelGGL(k_short_rounds, grid_for(n, 256, 1024), dim3(256), 0, s, lcp, n, rounds, hist);
+}
+
 // ------------------------------------------------------------ candidates
 // Block minima of LCP (kMinFan-ary levels) for previous-smaller-value queries.
 // Full blocks are read with four 16-byte loads (levels are 16-entry aligned).
