@@ -1,6 +1,7 @@
 // Small device helpers (wave64 scans, hashing) shared by the HIP kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <type_traits>
 #include <stdint.h>
 
 namespace apo {
@@ -49,6 +50,43 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t x) {
     if (lane >= o) x = x > y ? x : y;
   }
   return x;
+}
+
+// The value of lane (lane ^ M): register moves between lanes, no LDS access (a
+// ds_bpermute costs its latency, some 130 cycles, at every step of a network).
+// Every lane has to be active.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "one lane bit");
+  auto dpp = [](uint32_t x, auto ctrl) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, decltype(ctrl)::value, 0xF, 0xF, true);
+  };
+  if constexpr (M == 1) return dpp(v, std::integral_constant<int, 0xB1>{});   // quad_perm 1,0,3,2
+  if constexpr (M == 2) return dpp(v, std::integral_constant<int, 0x4E>{});   // quad_perm 2,3,0,1
+  if constexpr (M == 4)  // half-row mirror (xor 7), then quad_perm 3,2,1,0 (xor 3)
+    return dpp(dpp(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+  if constexpr (M == 8) return dpp(v, std::integral_constant<int, 0x128>{});  // row_ror 8
+  const bool up = (threadIdx.x & M) != 0;
+  if constexpr (M == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);  // rows 0 0 2 2 / 1 1 3 3
+    return up ? r[0] : r[1];
+  }
+  if constexpr (M == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);  // halves 0 0 / 1 1
+    return up ? r[0] : r[1];
+  }
+}
+template <int M>
+__device__ __forceinline__ uint64_t lane_xor64(uint64_t v) {
+  return ((uint64_t)lane_xor<M>((uint32_t)(v >> 32)) << 32) | lane_xor<M>((uint32_t)v);
+}
+
+// One step of a bitonic network over lanes: keeps the smaller (low) or the
+// larger of this lane's value and that of lane ^ M.
+template <int M>
+__device__ __forceinline__ uint64_t lane_step(uint64_t v, bool low) {
+  const uint64_t o = lane_xor64<M>(v);
+  return (o < v) == low ? o : v;
 }
 
 // Block-wide exclusive sum over NT threads.  `sh` needs NT/64 words.  Returns

@@ -283,8 +283,7 @@ static void sort_plain(Workspace &w, const uint32_t *count_dev, uint64_t bound, 
     const int last = (L == nlevels - 1);
     const uint32_t nb = last ? 0u : (uint32_t)bits[L + 1];
     if (bound > (1u << E.tile_log())) E.msd(cur, bound, bits[L], s);
-    E.lds_plain(cur, nb, last, keep ? keep : w.keep, bound, s);
-    E.bulk_plain(cur, nb, last, keep ? keep : w.keep, bound, s);
+    E.units_plain(cur, nb, last, keep ? keep : w.keep, bound, s);
     if (!last) {
       cur ^= 1;
       E.round_begin(cur, s);
@@ -533,12 +532,11 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       if (big) E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg);
       const bool timed = w.ktag == KT_LDS_SA && w.kev_n < kMaxTimed;
       if (timed) APO_HIP_TRY(hipEventRecord(w.kev[2 * w.kev_n], s));
-      E.lds_sa(cur, R, rel_bits, act, s);
+      E.units_sa(cur, R, rel_bits, act, s);
       if (timed) {
         APO_HIP_TRY(hipEventRecord(w.kev[2 * w.kev_n + 1], s));
         w.kround[w.kev_n++] = r;
       }
-      E.bulk_sa(cur, R, rel_bits, act, s);
     }
     // rounds >= kSnapFrom: the rank array after the round, for the LCP walk
     if (r >= kSnapFrom) snapshot_ranks(w.rank, w.snap + (size_t)r * N, N, w.rhist + 4 * (r - 1), dc + CNT_SNAPS, r, s);
@@ -637,8 +635,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     E.init_runs(0, w.tmp_d, dc + CNT_AUX, dc + CNT_C, c_bound, rank_bits, s);
     fill_u8_dev(w.keep, dc + CNT_C, c_bound, 1, s);
     if (c_bound > (1ull << E.tile_log())) E.msd(0, c_bound, (int)rank_bits, s);
-    E.lds_plain(0, 0, 1, w.keep, c_bound, s);
-    E.bulk_plain(0, 0, 1, w.keep, c_bound, s);
+    E.units_plain(0, 0, 1, w.keep, c_bound, s);
     compact_sorted_runs(B.val[0], w.keep, dc + CNT_C, c_bound, w.tmp_a, w.tmp_b, w.tmp_c, dc + CNT_MAXL, w.s_len,
                         w.s_start, w.s_id, w.tile_tmp, dc + CNT_M, s,
                         wkey ? (uint32_t)((1ull << lbits) - 1) : 0xFFFFFFFFu);

@@ -47,12 +47,9 @@ class SortEngine {
   // stays 0), so keys that are ranks inside a window need only the window's
   // bits; max_bits counts those bits.
   void msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base = nullptr);
-  void lds_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s);
-  void lds_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep, uint64_t work_hint,
-                 hipStream_t s);
-  void bulk_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s);
-  void bulk_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep, uint64_t work_hint,
-                  hipStream_t s);
+  // sorts and regroups the units the msd passes (or the list itself) left: rows, tiles, one-group chunks
+  void units_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s);
+  void units_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep, uint64_t work_hint, hipStream_t s);
 
  private:
   SortBufs b_{};

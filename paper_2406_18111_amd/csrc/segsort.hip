@@ -501,208 +501,244 @@ __global__ __launch_bounds__(kLdsThreads) void k_lds_sort(SortBufs B, int cur, R
 // ---------------------------------------------- wavefront sort (tiny units)
 // Units of at most 64 entries (classes 1..6) are sorted inside one wavefront:
 // a 64-lane row holds 64/2^c units of class c, bitonic stages are cross-lane
-// exchanges, group heads come from a wave-wide max-scan, and appends are
-// aggregated per wavefront with ballots.  No LDS, no barriers.
-__device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int m) {
-  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
-  const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
-  return ((uint64_t)hi << 32) | lo;
+// exchanges, group heads come from a ballot, and appends are
+// aggregated per workgroup with ballots.  No LDS traffic but the list bases.
+constexpr int kWaveMaxCi = 6;  // classes 1..6 (0-based 0..5)
+constexpr int kWaveCtrs = kWaveMaxCi + 2;  // new units per class, active entries, sorted entries
+// Threads that hold a workgroup's counts nobody needs the position of (the
+// active count of SA rounds, which keep flags instead of a list, and the
+// statistics) until its last item, when they are added once.
+constexpr int kActThread = kWaveMaxCi, kElemThread = kWaveMaxCi + 1;
+
+// Adds a workgroup's deferred counts (see kActThread).
+__device__ __forceinline__ void flush_counts(const SortBufs &B, int nxt, uint32_t deferred) {
+  if (threadIdx.x == kActThread && deferred) atomicAdd(&B.ctr->act_cnt[nxt], deferred);
+  if (threadIdx.x == kElemThread && deferred) atomicAdd(&B.ctr->lds_elems, deferred);
 }
 
-constexpr int kWaveMaxCi = 6;  // classes 1..6 (0-based 0..5)
-constexpr int kWaveItems = 8;  // items per wavefront per block batch
-constexpr int kWaveCtrs = kWaveMaxCi + 2;  // new units per class, active entries, sorted entries
-
-// Units of <= 64 entries, several per wavefront (2^(6-c) units of class c
-// side by side), sorted by a bitonic network over lane shuffles.  A block
-// takes a batch of 4 x kWaveItems items; the slots its new active entries
-// and units need are reserved with one atomic per counter per batch (the
-// per-item counts are wave ballots), so the hot list counters see few
-// atomics.  The batch loop is uniform across the block.
-template <int MODE>
-__global__ __launch_bounds__(256, 5) void k_wave_sort(SortBufs B, int cur, RankOut R, int last_level, uint8_t *keep) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int nxt = cur ^ 1;
-  __shared__ uint32_t wtot[4][kWaveCtrs];
-  __shared__ uint32_t wbase[4][kWaveCtrs];
+// Rows of the unit classes of a list: item i is row i of class ci, first_item[ci] <= i.
+struct WaveList {
   uint32_t cnt[kWaveMaxCi], first_item[kWaveMaxCi + 1];
-  first_item[0] = 0;
+  __device__ __forceinline__ uint32_t total() const { return first_item[kWaveMaxCi]; }
+};
+__device__ __forceinline__ WaveList wave_list(const SortBufs &B, int cur) {
+  WaveList w;
+  w.first_item[0] = 0;
 #pragma unroll
   for (int ci = 0; ci < kWaveMaxCi; ci++) {
-    cnt[ci] = B.ctr->cls_cnt[cur][ci];
+    w.cnt[ci] = B.ctr->cls_cnt[cur][ci];
     const uint32_t per = 64u >> (ci + 1);
-    first_item[ci + 1] = first_item[ci] + (cnt[ci] + per - 1) / per;
+    w.first_item[ci + 1] = w.first_item[ci] + (w.cnt[ci] + per - 1) / per;
   }
-  const uint32_t total = first_item[kWaveMaxCi];
+  return w;
+}
+
+// The rows' 2^c-lane segments sorted, each ascending, for c = 1..C.
+template <int K, int J>
+__device__ __forceinline__ uint64_t row_merge(uint64_t v, int c) {
+  const int lane = threadIdx.x & 63;
+  // ascending everywhere in the segment's last merge
+  const bool asc = (lane & K) == 0 || (1 << c) == K;
+  v = lane_step<J>(v, ((lane & J) == 0) == asc);
+  if constexpr (J > 1) v = row_merge<K, J / 2>(v, c);
+  return v;
+}
+__device__ __forceinline__ uint64_t row_sort(uint64_t v, int c) {  // c is uniform
+  v = row_merge<2, 1>(v, c);
+  if (c >= 2) v = row_merge<4, 2>(v, c);
+  if (c >= 3) v = row_merge<8, 4>(v, c);
+  if (c >= 4) v = row_merge<16, 8>(v, c);
+  if (c >= 5) v = row_merge<32, 16>(v, c);
+  if (c >= 6) v = row_merge<64, 32>(v, c);
+  return v;
+}
+
+template <int NT>
+struct WaveLds {
+  uint32_t wtot[NT / 64][kWaveCtrs], wbase[NT / 64][kWaveCtrs];
+};
+
+// Rows b0 .. b0 + (NT / 64) * ITEMS - 1 by one workgroup, ITEMS a wavefront.
+// The slots its new active entries and units need are reserved with one atomic
+// per counter (the per-item counts are wave ballots), so the hot list counters
+// see few atomics.
+template <int MODE, int NT, int ITEMS>
+__device__ __forceinline__ void wave_rows(const SortBufs &B, int cur, const RankOut &R, int last_level, uint8_t *keep,
+                                          const WaveList &W, uint32_t b0, WaveLds<NT> &S, uint32_t &deferred) {
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nxt = cur ^ 1;
+  const uint32_t total = W.total();
   const uint64_t lanes_lt = (1ull << lane) - 1ull;
-  constexpr uint32_t kBatch = 4 * kWaveItems;
-  uint32_t deferred = 0;  // threads kWaveMaxCi (SA active count) and kWaveMaxCi + 1 (sorted entries)
-  for (uint64_t b0 = (uint64_t)blockIdx.x * kBatch; b0 < total; b0 += (uint64_t)gridDim.x * kBatch) {
-    // per item and lane: slot of an entry that stays active, and a new unit
-    uint32_t act_p[kWaveItems], unit_pos[kWaveItems], unit_code[kWaveItems];
-    uint32_t tot[kWaveCtrs];
+  // per item and lane: slot of an entry that stays active, and a new unit
+  uint32_t act_p[ITEMS], unit_pos[ITEMS], unit_code[ITEMS];
+  uint32_t tot[kWaveCtrs];
 #pragma unroll
-    for (int q = 0; q < kWaveCtrs; q++) tot[q] = 0;
-    // the batch's global loads first (unit descriptors, then entries), so
-    // that their latencies overlap instead of adding up item by item
-    int ck[kWaveItems];
-    uint32_t nbk[kWaveItems];
-    Unit uk[kWaveItems];
-    uint64_t vk[kWaveItems];
+  for (int q = 0; q < kWaveCtrs; q++) tot[q] = 0;
+  // the batch's global loads first (unit descriptors, then entries), so
+  // that their latencies overlap instead of adding up item by item
+  int ck[ITEMS];
+  uint32_t nbk[ITEMS];
+  Unit uk[ITEMS];
+  uint64_t vk[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kWaveItems; k++) {
-      ck[k] = 0;
-      nbk[k] = 0;
-      uk[k] = Unit{0, 0};
-      const uint64_t item = b0 + (uint64_t)wid * kWaveItems + k;
-      if (item >= total) continue;  // wave-uniform
-      int ci = 0;
+  for (int k = 0; k < ITEMS; k++) {
+    ck[k] = 0;
+    nbk[k] = 0;
+    uk[k] = Unit{0, 0};
+    const uint64_t item = b0 + (uint64_t)wid * ITEMS + k;
+    if (item >= total) continue;  // wave-uniform
+    int ci = 0;
 #pragma unroll
-      for (int q = 1; q < kWaveMaxCi; q++) ci += item >= first_item[q] ? 1 : 0;
-      uint32_t cnt_ci = 0, off_ci = 0;
+    for (int q = 1; q < kWaveMaxCi; q++) ci += item >= W.first_item[q] ? 1 : 0;
+    uint32_t cnt_ci = 0, off_ci = 0;
 #pragma unroll
-      for (int q = 0; q < kWaveMaxCi; q++)
-        if (q == ci) { cnt_ci = cnt[q]; off_ci = first_item[q]; }
-      const uint32_t per = 64u >> (ci + 1);
-      const uint32_t first = (uint32_t)(item - off_ci) * per;
-      const uint32_t nb = min(per, cnt_ci - first);
-      const uint32_t j = (uint32_t)lane >> (ci + 1);
-      ck[k] = ci;
-      nbk[k] = nb;
-      if (j < nb) uk[k] = B.cls[cur][B.cls_off[ci] + first + j];
-    }
-#pragma unroll
-    for (int k = 0; k < kWaveItems; k++) {
-      vk[k] = ~0ull;
-      const int c = ck[k] + 1;
-      const uint32_t j = (uint32_t)lane >> c, idx = (uint32_t)lane & ((1u << c) - 1);
-      const Unit u = uk[k];
-      if (j < nbk[k] && idx < (u.len & kLenMask)) {
-        const int bb = (u.len & kBufBit) ? 1 : 0;
-        const uint32_t p = u.start + idx;
-        vk[k] = ((uint64_t)key_buf(B, bb)[p] << 32) | val_buf(B, bb)[p];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kWaveItems; k++) {
-      act_p[k] = kNone;
-      unit_code[k] = 0;
-      unit_pos[k] = 0;
-      const uint64_t item = b0 + (uint64_t)wid * kWaveItems + k;
-      if (item >= total) continue;  // wave-uniform
-      const int c = ck[k] + 1;
-      const uint32_t sub = 1u << c;
-      const uint32_t nb = nbk[k];
-      const uint32_t j = (uint32_t)lane >> c, idx = (uint32_t)lane & (sub - 1);
-      const Unit u = uk[k];
-      const uint32_t len = u.len & kLenMask;
-      const bool valid = j < nb && idx < len;
-      uint64_t v = vk[k];
-      for (uint32_t kk = 2; kk <= sub; kk <<= 1) {
-        for (uint32_t jj = kk >> 1; jj > 0; jj >>= 1) {
-          const uint64_t o = shfl_xor64(v, (int)jj);
-          const bool asc = (kk == sub) || (((uint32_t)lane & kk) == 0);
-          const bool lower = ((uint32_t)lane & jj) == 0;
-          v = (lower == asc) ? (v < o ? v : o) : (v > o ? v : o);
-        }
-      }
-      const uint32_t key = (uint32_t)(v >> 32);
-      const uint32_t prevkey = (uint32_t)__shfl_up((int)key, 1, 64);
-      const uint32_t nextkey = (uint32_t)__shfl_down((int)key, 1, 64);
-      const bool bnd = valid && (idx == 0 || key != prevkey);
-      const bool last = valid && (idx + 1 == len || nextkey != key);
-      const uint32_t hs = wave_incl_max(bnd ? (uint32_t)lane : 0u);  // head lane of this lane's group
-      const bool single = bnd && last;
-      const uint32_t p = u.start + idx;
-      const uint32_t gpos = u.start + (hs - (j << c));
-      if (valid) {
-        const uint32_t val = (uint32_t)v;
-        B.val[0][p] = val;
-        if (MODE == MODE_SA) {
-          if (!((u.len & kHeadBit) && gpos == u.start)) R.rank[val] = gpos + 1;  // else unchanged
-        }
-        if (last_level) keep[p] = bnd ? 1 : 0;
-      }
-      tot[kWaveMaxCi + 1] += (uint32_t)__popcll(__ballot(valid));
-      if (!last_level) {
-        const bool stay = valid && !single;
-        tot[kWaveMaxCi] += (uint32_t)__popcll(__ballot(stay));
-        if (R.aflag) {
-          if (valid) R.aflag[p] = stay ? 1 : 0;
-        } else if (stay) {
-          act_p[k] = p;
-        }
-        // new units: groups of size >= 2, emitted by their last lane
-        const bool emit = last && !bnd;
-        const uint32_t size = (uint32_t)lane - hs + 1;
-        const int mycc = emit ? class_of(size) : -1;
-#pragma unroll
-        for (int cc = 0; cc < kWaveMaxCi; cc++) tot[cc] += (uint32_t)__popcll(__ballot(mycc == cc));
-        if (emit) {
-          unit_pos[k] = gpos;
-          unit_code[k] = (size << 8) | (uint32_t)(mycc + 1);
-        }
-      }
-    }
-    // reserve list slots: one atomic per counter per block batch
-    if (lane == 0) {
-#pragma unroll
-      for (int q = 0; q < kWaveCtrs; q++) wtot[wid][q] = tot[q];
-    }
-    __syncthreads();
-    if (threadIdx.x < kWaveCtrs) {
-      const int q = threadIdx.x;
-      uint32_t sum = 0;
-      for (int w = 0; w < 4; w++) sum += wtot[w][q];
-      uint32_t base = 0;
-      if (sum) {
-        // counts whose positions nobody needs (the active count of SA rounds,
-        // which keep flags instead of a list, and the statistics) are added
-        // once per workgroup at the end
-        if (q < kWaveMaxCi) base = atomicAdd(&B.ctr->cls_cnt[nxt][q], sum);
-        else if (q == kWaveMaxCi && !R.aflag) base = atomicAdd(&B.ctr->act_cnt[nxt], sum);
-        else deferred += sum;
-      }
-      for (int w = 0; w < 4; w++) {
-        wbase[w][q] = base;
-        base += wtot[w][q];
-      }
-    }
-    __syncthreads();
-    if (!last_level) {
-      uint32_t abase = wbase[wid][kWaveMaxCi];
-      uint32_t cbase[kWaveMaxCi];
-#pragma unroll
-      for (int cc = 0; cc < kWaveMaxCi; cc++) cbase[cc] = wbase[wid][cc];
-#pragma unroll
-      for (int k = 0; k < kWaveItems; k++) {
-        const bool stay = act_p[k] != kNone;
-        const uint64_t am = __ballot(stay);
-        if (stay) {
-          const uint32_t w = abase + (uint32_t)__popcll(am & lanes_lt);
-          if (w < B.cap) B.act[nxt][w] = act_p[k];
-          else atomicOr(&B.ctr->err, 4u);
-        }
-        abase += (uint32_t)__popcll(am);
-        const int mycc = (int)(unit_code[k] & 0xFF) - 1;
-#pragma unroll
-        for (int cc = 0; cc < kWaveMaxCi; cc++) {
-          const uint64_t m = __ballot(mycc == cc);
-          if (mycc == cc) {
-            const uint32_t kk = cbase[cc] + (uint32_t)__popcll(m & lanes_lt);
-            const uint32_t capc = B.cls_off[cc + 1] - B.cls_off[cc];
-            if (kk < capc)
-              B.cls[nxt][B.cls_off[cc] + kk] = Unit{unit_pos[k], (unit_code[k] >> 8) | (MODE == MODE_SA ? kHeadBit : 0u)};
-            else atomicOr(&B.ctr->err, 8u);
-          }
-          cbase[cc] += (uint32_t)__popcll(m);
-        }
-      }
-    }
-    __syncthreads();  // wtot/wbase are reused by the next batch
+    for (int q = 0; q < kWaveMaxCi; q++)
+      if (q == ci) { cnt_ci = W.cnt[q]; off_ci = W.first_item[q]; }
+    const uint32_t per = 64u >> (ci + 1);
+    const uint32_t first = (uint32_t)(item - off_ci) * per;
+    const uint32_t nb = min(per, cnt_ci - first);
+    const uint32_t j = (uint32_t)lane >> (ci + 1);
+    ck[k] = ci;
+    nbk[k] = nb;
+    if (j < nb) uk[k] = B.cls[cur][B.cls_off[ci] + first + j];
   }
-  if (threadIdx.x == kWaveMaxCi && deferred) atomicAdd(&B.ctr->act_cnt[nxt], deferred);
-  if (threadIdx.x == kWaveMaxCi + 1 && deferred) atomicAdd(&B.ctr->lds_elems, deferred);
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    vk[k] = ~0ull;
+    const int c = ck[k] + 1;
+    const uint32_t j = (uint32_t)lane >> c, idx = (uint32_t)lane & ((1u << c) - 1);
+    const Unit u = uk[k];
+    if (j < nbk[k] && idx < (u.len & kLenMask)) {
+      const int bb = (u.len & kBufBit) ? 1 : 0;
+      const uint32_t p = u.start + idx;
+      vk[k] = ((uint64_t)key_buf(B, bb)[p] << 32) | val_buf(B, bb)[p];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) {
+    act_p[k] = kNone;
+    unit_code[k] = 0;
+    unit_pos[k] = 0;
+    const uint64_t item = b0 + (uint64_t)wid * ITEMS + k;
+    if (item >= total) continue;  // wave-uniform
+    const int c = ck[k] + 1;
+    const uint32_t sub = 1u << c;
+    const uint32_t nb = nbk[k];
+    const uint32_t j = (uint32_t)lane >> c, idx = (uint32_t)lane & (sub - 1);
+    const Unit u = uk[k];
+    const uint32_t len = u.len & kLenMask;
+    const bool valid = j < nb && idx < len;
+    const uint64_t v = row_sort(vk[k], c);
+    const uint32_t key = (uint32_t)(v >> 32);
+    // the neighbours' keys (wave_shr 1, wave_shl 1)
+    const uint32_t prevkey = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x138, 0xF, 0xF, false);
+    const uint32_t nextkey = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x130, 0xF, 0xF, false);
+    const bool bnd = valid && (idx == 0 || key != prevkey);
+    const bool last = valid && (idx + 1 == len || nextkey != key);
+    // head lane of this lane's group (lanes without an entry: any)
+    const uint32_t hs = 63u - (uint32_t)__clzll((long long)((__ballot(bnd) & (lanes_lt * 2 + 1)) | 1ull));
+    const bool single = bnd && last;
+    const uint32_t p = u.start + idx;
+    const uint32_t gpos = u.start + (hs - (j << c));
+    if (valid) {
+      const uint32_t val = (uint32_t)v;
+      B.val[0][p] = val;
+      if (MODE == MODE_SA) {
+        if (!((u.len & kHeadBit) && gpos == u.start)) R.rank[val] = gpos + 1;  // else unchanged
+      }
+      if (last_level) keep[p] = bnd ? 1 : 0;
+    }
+    tot[kWaveMaxCi + 1] += (uint32_t)__popcll(__ballot(valid));
+    if (!last_level) {
+      const bool stay = valid && !single;
+      tot[kWaveMaxCi] += (uint32_t)__popcll(__ballot(stay));
+      if (R.aflag) {
+        if (valid) R.aflag[p] = stay ? 1 : 0;
+      } else if (stay) {
+        act_p[k] = p;
+      }
+      // new units: groups of size >= 2, emitted by their last lane
+      const bool emit = last && !bnd;
+      const uint32_t size = (uint32_t)lane - hs + 1;
+      const int mycc = emit ? class_of(size) : -1;
+#pragma unroll
+      for (int cc = 0; cc < kWaveMaxCi; cc++) tot[cc] += (uint32_t)__popcll(__ballot(mycc == cc));
+      if (emit) {
+        unit_pos[k] = gpos;
+        unit_code[k] = (size << 8) | (uint32_t)(mycc + 1);
+      }
+    }
+  }
+  // reserve list slots: one atomic per counter per block batch
+  if (lane == 0) {
+#pragma unroll
+    for (int q = 0; q < kWaveCtrs; q++) S.wtot[wid][q] = tot[q];
+  }
+  __syncthreads();
+  if (threadIdx.x < kWaveCtrs) {
+    const int q = threadIdx.x;
+    uint32_t sum = 0;
+    for (int w = 0; w < NT / 64; w++) sum += S.wtot[w][q];
+    uint32_t base = 0;
+    if (sum) {
+      // counts whose positions nobody needs (the active count of SA rounds,
+      // which keep flags instead of a list, and the statistics) are added
+      // once per workgroup at the end
+      if (q < kWaveMaxCi) base = atomicAdd(&B.ctr->cls_cnt[nxt][q], sum);
+      else if (q == kWaveMaxCi && !R.aflag) base = atomicAdd(&B.ctr->act_cnt[nxt], sum);
+      else deferred += sum;
+    }
+    for (int w = 0; w < NT / 64; w++) {
+      S.wbase[w][q] = base;
+      base += S.wtot[w][q];
+    }
+  }
+  __syncthreads();
+  if (!last_level) {
+    uint32_t abase = S.wbase[wid][kWaveMaxCi];
+    uint32_t cbase[kWaveMaxCi];
+#pragma unroll
+    for (int cc = 0; cc < kWaveMaxCi; cc++) cbase[cc] = S.wbase[wid][cc];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+      const bool stay = act_p[k] != kNone;
+      const uint64_t am = __ballot(stay);
+      if (stay) {
+        const uint32_t w = abase + (uint32_t)__popcll(am & lanes_lt);
+        if (w < B.cap) B.act[nxt][w] = act_p[k];
+        else atomicOr(&B.ctr->err, 4u);
+      }
+      abase += (uint32_t)__popcll(am);
+      const int mycc = (int)(unit_code[k] & 0xFF) - 1;
+#pragma unroll
+      for (int cc = 0; cc < kWaveMaxCi; cc++) {
+        const uint64_t m = __ballot(mycc == cc);
+        if (mycc == cc) {
+          const uint32_t kk = cbase[cc] + (uint32_t)__popcll(m & lanes_lt);
+          const uint32_t capc = B.cls_off[cc + 1] - B.cls_off[cc];
+          if (kk < capc)
+            B.cls[nxt][B.cls_off[cc] + kk] = Unit{unit_pos[k], (unit_code[k] >> 8) | (MODE == MODE_SA ? kHeadBit : 0u)};
+          else atomicOr(&B.ctr->err, 8u);
+        }
+        cbase[cc] += (uint32_t)__popcll(m);
+      }
+    }
+  }
+  __syncthreads();  // wtot/wbase are reused by the next batch
+}
+
+// One workgroup per 4 x kWaveItems rows: on large inputs eight rows a wavefront
+// overlap their loads and share the list atomics.
+constexpr int kWaveItems = 8;
+template <int MODE>
+__global__ __launch_bounds__(256, 5) void k_wave_sort(SortBufs B, int cur, RankOut R, int last_level, uint8_t *keep) {
+  __shared__ WaveLds<256> S;
+  const WaveList W = wave_list(B, cur);
+  constexpr uint32_t kBatch = 4 * kWaveItems;
+  uint32_t deferred = 0;
+  for (uint64_t b0 = (uint64_t)blockIdx.x * kBatch; b0 < W.total(); b0 += (uint64_t)gridDim.x * kBatch)
+    wave_rows<MODE, 256, kWaveItems>(B, cur, R, last_level, keep, W, (uint32_t)b0, S, deferred);
+  flush_counts(B, cur ^ 1, deferred);
 }
 
 // ------------------------------------------------- LDS grouping (large units)
@@ -715,257 +751,317 @@ __global__ __launch_bounds__(256, 5) void k_wave_sort(SortBufs B, int cur, RankO
 constexpr int kGroupMinCi = 6;  // 0-based class 6 = lengths 65..128
 constexpr int kGroupThreads = 512;
 
+
+// Ascending sort of D[0, m) (m <= NT * E) by the workgroup: a bitonic network
+// over E consecutive values a thread.  Distances inside a thread and a wavefront
+// are register moves; only those of 64 E and more (3 of 55 steps at m = 1024,
+// E = 4) go through LDS with its barriers.  Every step through LDS took 22 us
+// at m = 2048 and 8.5 us at 512.
+template <int E, int J>
+__device__ __forceinline__ void tile_merge(uint64_t (&r)[E], uint32_t base, uint32_t k) {
+  if (k > (uint32_t)J) {  // uniform
+    if constexpr (J >= E) {
+      const bool low = ((base & (uint32_t)J) == 0) == ((base & k) == 0);
+#pragma unroll
+      for (int e = 0; e < E; e++) r[e] = lane_step<J / E>(r[e], low);
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        if (e & J) continue;
+        const bool asc = ((base + e) & k) == 0;
+        const uint64_t a = r[e], b = r[e | J];
+        const bool swap = (a > b) == asc;
+        r[e] = swap ? b : a;
+        r[e | J] = swap ? a : b;
+      }
+    }
+  }
+  if constexpr (J > 1) tile_merge<E, J / 2>(r, base, k);
+}
+template <int NT, int E>
+__device__ __forceinline__ void sort_tile(uint64_t *D, uint32_t m) {
+  uint32_t m2 = 1;
+  while (m2 < m) m2 <<= 1;
+  const uint32_t base = threadIdx.x * E;
+  const bool mine = (threadIdx.x & ~63u) * E < m2;  // uniform in a wavefront
+  uint64_t r[E];
+#pragma unroll
+  for (int e = 0; e < E; e++) r[e] = base + e < m ? D[base + e] : ~0ull;
+  __syncthreads();
+  for (uint32_t k = 2; k <= m2; k <<= 1) {
+    for (uint32_t j = k >> 1; j >= 64 * E; j >>= 1) {
+      if (mine)
+#pragma unroll
+        for (int e = 0; e < E; e++) D[base + e] = r[e];
+      __syncthreads();
+      if (mine) {
+        const bool low = ((base & j) == 0) == ((base & k) == 0);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+          const uint64_t o = D[(base ^ j) + e];
+          r[e] = (o < r[e]) == low ? o : r[e];
+        }
+      }
+      __syncthreads();
+    }
+    if (mine) tile_merge<E, 32 * E>(r, base, k);
+  }
+  if (mine)
+#pragma unroll
+    for (int e = 0; e < E; e++) D[base + e] = r[e];
+  __syncthreads();
+}
+
+template <int TLG>
+struct GroupLds {
+  static constexpr int T = 1 << TLG;
+  uint64_t D[T];            // distinct (unit, key, slot); after scan: fill cursors (u32[2 T])
+  uint32_t K[T], V[T];
+  uint32_t tab[2 * T];      // hash slots (load <= 1/2).  Insert: (count << 16) | (entry + 1); after scan: (count << 16) | base
+  uint16_t EJ[T];           // unit of each entry
+  Unit ud[T >> (kGroupMinCi + 1)];  // units per tile of the smallest handled class
+  uint32_t uoff[(T >> (kGroupMinCi + 1)) + 1];
+  uint32_t sh[kGroupThreads / 64];
+  uint32_t nd, act_base, item_c, item_b;
+  uint32_t cls_loc[kClasses], cls_base[kClasses], cnt_c[kClasses];
+};
+
+// Tiles of the unit classes of a list, whose counts S.cnt_c gets.
+template <int TLG>
+__device__ __forceinline__ uint32_t group_tiles(const SortBufs &B, int cur, GroupLds<TLG> &S) {
+  const int ci_hi = min((int)B.tile_log, TLG);
+  if (threadIdx.x < kClasses) S.cnt_c[threadIdx.x] = B.ctr->cls_cnt[cur][threadIdx.x];
+  __syncthreads();
+  uint32_t tot = 0;
+  for (int ci = kGroupMinCi; ci < ci_hi; ci++) {
+    const uint32_t per = (1u << TLG) >> (ci + 1);
+    tot += (S.cnt_c[ci] + per - 1) / per;
+  }
+  return tot;
+}
+
+// One tile by one workgroup.
 template <int MODE, int TLG>
-__global__ __launch_bounds__(kGroupThreads, TLG == 11 ? 6 : 2) void k_lds_group(SortBufs B, int cur, RankOut R, int last_level,
-                                                            uint8_t *keep) {
+__device__ __forceinline__ void group_tile(const SortBufs &B, int cur, const RankOut &R, int last_level, uint8_t *keep,
+                                           uint32_t item, GroupLds<TLG> &S, uint32_t &deferred) {
   constexpr int NT = kGroupThreads;
   constexpr int T = 1 << TLG;
-  constexpr int HT = 2 * T;            // hash slots (load <= 1/2)
+  constexpr int HT = 2 * T;
   constexpr int PER = T / NT;
-  constexpr int MAXU = T >> (kGroupMinCi + 1);  // units per tile of the smallest handled class
-  __shared__ uint32_t K[T], V[T];
-  __shared__ uint16_t EJ[T];           // unit of each entry
-  __shared__ uint32_t tab[HT];         // insert: (count << 16) | (entry + 1); after scan: (count << 16) | base
-  __shared__ uint64_t D[T];            // distinct (unit, key, slot); after scan: fill cursors (u32[HT])
-  __shared__ Unit ud[MAXU];
-  __shared__ uint32_t uoff[MAXU + 1];
-  __shared__ uint32_t sh[NT / 64];
-  __shared__ uint32_t nd, act_base, items_total, item_c, item_b;
-  __shared__ uint32_t cls_loc[kClasses], cls_base[kClasses], cnt_c[kClasses];
-  uint32_t *cursor = reinterpret_cast<uint32_t *>(D);
+  uint32_t *cursor = reinterpret_cast<uint32_t *>(S.D);
   const int nxt = cur ^ 1;
   const int tid = threadIdx.x;
   const int ci_hi = min((int)B.tile_log, TLG);
-  if (tid < kClasses) cnt_c[tid] = B.ctr->cls_cnt[cur][tid];
-  __syncthreads();
   if (tid == 0) {
-    uint32_t tot = 0;
-    for (int ci = kGroupMinCi; ci < ci_hi; ci++) {
+    uint32_t it = item;
+    int ci = kGroupMinCi;
+    for (; ci < ci_hi; ci++) {
       const uint32_t per = (uint32_t)T >> (ci + 1);
-      tot += (cnt_c[ci] + per - 1) / per;
+      const uint32_t ni = (S.cnt_c[ci] + per - 1) / per;
+      if (it < ni) break;
+      it -= ni;
     }
-    items_total = tot;
+    S.item_c = (uint32_t)ci;
+    S.item_b = it;
+    S.nd = 0;
+  }
+  if (tid < kClasses) S.cls_loc[tid] = 0;
+  for (int h = tid; h < HT; h += NT) S.tab[h] = 0;
+  __syncthreads();
+  const int ci = (int)S.item_c;
+  const uint32_t per = (uint32_t)T >> (ci + 1);
+  const uint32_t first = S.item_b * per;
+  const uint32_t nb = min(per, S.cnt_c[ci] - first);
+  const Unit *src = B.cls[cur] + B.cls_off[ci] + first;
+  // unit descriptors and compact offsets (nb <= MAXU <= NT)
+  {
+    uint32_t len = 0;
+    if (tid < (int)nb) {
+      S.ud[tid] = src[tid];
+      len = src[tid].len & kLenMask;
+    }
+    uint32_t tot;
+    const uint32_t ex = block_excl_sum<NT>(len, S.sh, &tot);
+    if (tid < (int)nb) S.uoff[tid] = ex;
+    if (tid == 0) S.uoff[nb] = tot;
+    if (tid == kElemThread) deferred += tot;
   }
   __syncthreads();
-  const uint32_t total_items = items_total;
-  uint32_t elems = 0, act_deferred = 0;
+  const uint32_t total = S.uoff[nb];
+  // load entries: all of a thread's global loads are issued before the
+  // first is waited for
+  {
+    uint32_t kq[PER], vq[PER], jq[PER];
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+      const uint32_t p = tid + q * NT;
+      jq[q] = 0;
+      if (p < total) {
+        uint32_t lo = 0, hi = nb;  // unit j: S.uoff[j] <= p < S.uoff[j+1]
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (S.uoff[mid] <= p) lo = mid; else hi = mid;
+        }
+        const Unit u = S.ud[lo];
+        const int b = (u.len & kBufBit) ? 1 : 0;
+        const uint32_t g = u.start + (p - S.uoff[lo]);
+        kq[q] = key_buf(B, b)[g];
+        vq[q] = val_buf(B, b)[g];
+        jq[q] = lo;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+      const uint32_t p = tid + q * NT;
+      if (p < total) {
+        S.K[p] = kq[q];
+        S.V[p] = vq[q];
+        S.EJ[p] = (uint16_t)jq[q];
+      }
+    }
+  }
+  __syncthreads();
+  // insert into the hash table
+  uint32_t eslot[PER];
+  for (int q = 0; q < PER; q++) {
+    const uint32_t p = tid + q * NT;
+    eslot[q] = 0;
+    if (p < total) {
+      const uint32_t key = S.K[p], j = S.EJ[p];
+      uint32_t h = (uint32_t)(mix64(((uint64_t)j << 32) | key) >> 20) & (HT - 1);
+      while (true) {
+        uint32_t prev = S.tab[h];
+        if (prev == 0u) prev = atomicCAS(&S.tab[h], 0u, (1u << 16) | (p + 1));
+        if (prev == 0u) {
+          const uint32_t d = atomicAdd(&S.nd, 1u);
+          S.D[d] = ((uint64_t)j << 46) | ((uint64_t)key << 14) | h;
+          break;
+        }
+        const uint32_t e = (prev & 0xFFFFu) - 1;
+        if (S.K[e] == key && S.EJ[e] == j) {
+          agg_add(&S.tab[h], 1u << 16);
+          break;
+        }
+        h = (h + 1) & (HT - 1);
+      }
+      eslot[q] = h;
+    }
+  }
+  __syncthreads();
+  const uint32_t m = S.nd;
+  sort_tile<NT, PER>(S.D, m);
+  // offsets: exclusive scan of counts in (unit, key) order
+  {
+    const uint32_t chunk = (m + NT - 1) / NT;
+    const uint32_t d0 = tid * chunk, d1 = min(d0 + chunk, m);
+    uint32_t loc = 0;
+    for (uint32_t d = d0; d < d1; d++) loc += S.tab[(uint32_t)S.D[d] & (HT - 1)] >> 16;
+    uint32_t tot;
+    uint32_t ex = block_excl_sum<NT>(loc, S.sh, &tot);
+    uint32_t slots[8];
+    uint32_t bases[8];
+    int nsl = 0;
+    for (uint32_t d = d0; d < d1; d++) {
+      const uint32_t h = (uint32_t)S.D[d] & (HT - 1);
+      const uint32_t c = S.tab[h] >> 16;
+      if (nsl < 8) { slots[nsl] = h; bases[nsl] = ex; nsl++; }
+      else { S.tab[h] = (c << 16) | ex; }  // only when chunk > 8 (m > 8 * NT): never for T <= 4096
+      ex += c;
+    }
+    __syncthreads();  // every D read done before D is reused as cursors
+    for (int z = 0; z < nsl; z++) {
+      const uint32_t c = S.tab[slots[z]] >> 16;
+      S.tab[slots[z]] = (c << 16) | bases[z];
+      cursor[slots[z]] = bases[z];
+    }
+  }
+  __syncthreads();
+  // place entries and regroup
+  uint32_t my_act = 0;
+  uint32_t pos_q[PER];
+  for (int q = 0; q < PER; q++) {
+    const uint32_t p = tid + q * NT;
+    pos_q[q] = 0;
+    if (p < total) {
+      const uint32_t h = eslot[q];
+      const uint32_t info = S.tab[h];
+      const uint32_t gbase = info & 0xFFFFu, gcnt = info >> 16;
+      const uint32_t pos = agg_inc(&cursor[h]);
+      pos_q[q] = pos;
+      const uint32_t j = S.EJ[p];
+      const Unit u = S.ud[j];
+      const uint32_t slot = u.start + (pos - S.uoff[j]);
+      const uint32_t head = u.start + (gbase - S.uoff[j]);
+      const uint32_t v = S.V[p];
+      B.val[0][slot] = v;
+      if (MODE == MODE_SA) {
+        if (!((u.len & kHeadBit) && head == u.start)) R.rank[v] = head + 1;  // else unchanged
+        if (R.aflag) R.aflag[slot] = gcnt >= 2 ? 1 : 0;
+      }
+      if (last_level) {
+        keep[slot] = (pos == gbase) ? 1 : 0;
+      } else if (gcnt >= 2) {
+        my_act++;
+        if (pos == gbase) atomicAdd(&S.cls_loc[class_of(gcnt)], 1u);
+      }
+    }
+  }
+  if (!last_level) {
+    uint32_t tot;
+    const uint32_t off = block_excl_sum<NT>(my_act, S.sh, &tot);
+    if (R.aflag) {
+      if (tid == kActThread) deferred += tot;
+    } else if (tid == 0) {
+      S.act_base = tot ? atomicAdd(&B.ctr->act_cnt[nxt], tot) : 0u;
+    }
+    if (tid < kClasses) {
+      const uint32_t mm = S.cls_loc[tid];
+      S.cls_base[tid] = mm ? atomicAdd(&B.ctr->cls_cnt[nxt][tid], mm) : 0u;
+      S.cls_loc[tid] = 0;
+    }
+    __syncthreads();
+    uint32_t w = S.act_base + off;
+    for (int q = 0; q < PER; q++) {
+      const uint32_t p = tid + q * NT;
+      if (p >= total) continue;
+      const uint32_t info = S.tab[eslot[q]];
+      const uint32_t gbase = info & 0xFFFFu, gcnt = info >> 16;
+      if (gcnt < 2) continue;
+      const uint32_t j = S.EJ[p];
+      const Unit u = S.ud[j];
+      const uint32_t slot = u.start + (pos_q[q] - S.uoff[j]);
+      if (!R.aflag) {
+        if (w < B.cap) B.act[nxt][w] = slot;
+        else atomicOr(&B.ctr->err, 4u);
+        w++;
+      }
+      if (pos_q[q] == gbase) {
+        const int cc = class_of(gcnt);
+        const uint32_t k = S.cls_base[cc] + atomicAdd(&S.cls_loc[cc], 1u);
+        const uint32_t capc = B.cls_off[cc + 1] - B.cls_off[cc];
+        if (k < capc)
+          B.cls[nxt][B.cls_off[cc] + k] = Unit{u.start + (gbase - S.uoff[j]), gcnt | (MODE == MODE_SA ? kHeadBit : 0u)};
+        else atomicOr(&B.ctr->err, 8u);
+      }
+    }
+  }
+  __syncthreads();
+}
+
+template <int MODE, int TLG>
+__global__ __launch_bounds__(kGroupThreads, TLG == 11 ? 6 : 2) void k_lds_group(SortBufs B, int cur, RankOut R,
+                                                                               int last_level, uint8_t *keep) {
+  __shared__ GroupLds<TLG> S;
+  const uint32_t total = group_tiles<TLG>(B, cur, S);
+  uint32_t deferred = 0;
   // items are handed out XCD by XCD: neighbouring tiles hold units of
   // neighbouring windows, whose scattered rank writes then merge in one L2
-  for (uint32_t base = 0; base < total_items; base += gridDim.x) {
-    const uint32_t item = (uint32_t)xcd_item(base, total_items, blockIdx.x, gridDim.x);
-    if (item >= total_items) break;
-    if (tid == 0) {
-      uint32_t it = item;
-      int ci = kGroupMinCi;
-      for (; ci < ci_hi; ci++) {
-        const uint32_t per = (uint32_t)T >> (ci + 1);
-        const uint32_t ni = (cnt_c[ci] + per - 1) / per;
-        if (it < ni) break;
-        it -= ni;
-      }
-      item_c = (uint32_t)ci;
-      item_b = it;
-      nd = 0;
-    }
-    if (tid < kClasses) cls_loc[tid] = 0;
-    for (int h = tid; h < HT; h += NT) tab[h] = 0;
-    __syncthreads();
-    const int ci = (int)item_c;
-    const uint32_t per = (uint32_t)T >> (ci + 1);
-    const uint32_t first = item_b * per;
-    const uint32_t nb = min(per, cnt_c[ci] - first);
-    const Unit *src = B.cls[cur] + B.cls_off[ci] + first;
-    // unit descriptors and compact offsets (nb <= MAXU <= NT)
-    {
-      uint32_t len = 0;
-      if (tid < (int)nb) {
-        ud[tid] = src[tid];
-        len = src[tid].len & kLenMask;
-      }
-      uint32_t tot;
-      const uint32_t ex = block_excl_sum<NT>(len, sh, &tot);
-      if (tid < (int)nb) uoff[tid] = ex;
-      if (tid == 0) uoff[nb] = tot;
-      elems += tot;  // statistics: one atomic per workgroup at the end
-    }
-    __syncthreads();
-    const uint32_t total = uoff[nb];
-    // load entries: all of a thread's global loads are issued before the
-    // first is waited for
-    {
-      uint32_t kq[PER], vq[PER], jq[PER];
-#pragma unroll
-      for (int q = 0; q < PER; q++) {
-        const uint32_t p = tid + q * NT;
-        jq[q] = 0;
-        if (p < total) {
-          uint32_t lo = 0, hi = nb;  // unit j: uoff[j] <= p < uoff[j+1]
-          while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (uoff[mid] <= p) lo = mid; else hi = mid;
-          }
-          const Unit u = ud[lo];
-          const int b = (u.len & kBufBit) ? 1 : 0;
-          const uint32_t g = u.start + (p - uoff[lo]);
-          kq[q] = key_buf(B, b)[g];
-          vq[q] = val_buf(B, b)[g];
-          jq[q] = lo;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < PER; q++) {
-        const uint32_t p = tid + q * NT;
-        if (p < total) {
-          K[p] = kq[q];
-          V[p] = vq[q];
-          EJ[p] = (uint16_t)jq[q];
-        }
-      }
-    }
-    __syncthreads();
-    // insert into the hash table
-    uint32_t eslot[PER];
-    for (int q = 0; q < PER; q++) {
-      const uint32_t p = tid + q * NT;
-      eslot[q] = 0;
-      if (p < total) {
-        const uint32_t key = K[p], j = EJ[p];
-        uint32_t h = (uint32_t)(mix64(((uint64_t)j << 32) | key) >> 20) & (HT - 1);
-        while (true) {
-          uint32_t prev = tab[h];
-          if (prev == 0u) prev = atomicCAS(&tab[h], 0u, (1u << 16) | (p + 1));
-          if (prev == 0u) {
-            const uint32_t d = atomicAdd(&nd, 1u);
-            D[d] = ((uint64_t)j << 46) | ((uint64_t)key << 14) | h;
-            break;
-          }
-          const uint32_t e = (prev & 0xFFFFu) - 1;
-          if (K[e] == key && EJ[e] == j) {
-            agg_add(&tab[h], 1u << 16);
-            break;
-          }
-          h = (h + 1) & (HT - 1);
-        }
-        eslot[q] = h;
-      }
-    }
-    __syncthreads();
-    // sort the distinct pairs (bitonic over the next power of two)
-    const uint32_t m = nd;
-    uint32_t m2 = 1;
-    while (m2 < m) m2 <<= 1;
-    for (uint32_t i = m + tid; i < m2; i += NT) D[i] = ~0ull;
-    __syncthreads();
-    for (uint32_t k = 2; k <= m2; k <<= 1) {
-      for (uint32_t jj = k >> 1; jj > 0; jj >>= 1) {
-        for (uint32_t t = tid; t < m2 / 2; t += NT) {
-          const uint32_t i = ((t & ~(jj - 1)) << 1) | (t & (jj - 1));
-          const uint32_t l = i | jj;
-          const bool asc = (i & k) == 0;
-          const uint64_t a = D[i], b = D[l];
-          if ((a > b) == asc) { D[i] = b; D[l] = a; }
-        }
-        __syncthreads();
-      }
-    }
-    // offsets: exclusive scan of counts in (unit, key) order
-    {
-      const uint32_t chunk = (m + NT - 1) / NT;
-      const uint32_t d0 = tid * chunk, d1 = min(d0 + chunk, m);
-      uint32_t loc = 0;
-      for (uint32_t d = d0; d < d1; d++) loc += tab[(uint32_t)D[d] & (HT - 1)] >> 16;
-      uint32_t tot;
-      uint32_t ex = block_excl_sum<NT>(loc, sh, &tot);
-      uint32_t slots[8];
-      uint32_t bases[8];
-      int nsl = 0;
-      for (uint32_t d = d0; d < d1; d++) {
-        const uint32_t h = (uint32_t)D[d] & (HT - 1);
-        const uint32_t c = tab[h] >> 16;
-        if (nsl < 8) { slots[nsl] = h; bases[nsl] = ex; nsl++; }
-        else { tab[h] = (c << 16) | ex; }  // only when chunk > 8 (m > 8 * NT): never for T <= 4096
-        ex += c;
-      }
-      __syncthreads();  // every D read done before D is reused as cursors
-      for (int z = 0; z < nsl; z++) {
-        const uint32_t c = tab[slots[z]] >> 16;
-        tab[slots[z]] = (c << 16) | bases[z];
-        cursor[slots[z]] = bases[z];
-      }
-    }
-    __syncthreads();
-    // place entries and regroup
-    uint32_t my_act = 0;
-    uint32_t pos_q[PER];
-    for (int q = 0; q < PER; q++) {
-      const uint32_t p = tid + q * NT;
-      pos_q[q] = 0;
-      if (p < total) {
-        const uint32_t h = eslot[q];
-        const uint32_t info = tab[h];
-        const uint32_t gbase = info & 0xFFFFu, gcnt = info >> 16;
-        const uint32_t pos = agg_inc(&cursor[h]);
-        pos_q[q] = pos;
-        const uint32_t j = EJ[p];
-        const Unit u = ud[j];
-        const uint32_t slot = u.start + (pos - uoff[j]);
-        const uint32_t head = u.start + (gbase - uoff[j]);
-        const uint32_t v = V[p];
-        B.val[0][slot] = v;
-        if (MODE == MODE_SA) {
-          if (!((u.len & kHeadBit) && head == u.start)) R.rank[v] = head + 1;  // else unchanged
-          if (R.aflag) R.aflag[slot] = gcnt >= 2 ? 1 : 0;
-        }
-        if (last_level) {
-          keep[slot] = (pos == gbase) ? 1 : 0;
-        } else if (gcnt >= 2) {
-          my_act++;
-          if (pos == gbase) atomicAdd(&cls_loc[class_of(gcnt)], 1u);
-        }
-      }
-    }
-    if (!last_level) {
-      uint32_t tot;
-      const uint32_t off = block_excl_sum<NT>(my_act, sh, &tot);
-      if (tid == 0) {
-        if (R.aflag) act_deferred += tot;  // SA rounds keep flags: the count only, once per workgroup
-        else act_base = tot ? atomicAdd(&B.ctr->act_cnt[nxt], tot) : 0u;
-      }
-      if (tid < kClasses) {
-        const uint32_t mm = cls_loc[tid];
-        cls_base[tid] = mm ? atomicAdd(&B.ctr->cls_cnt[nxt][tid], mm) : 0u;
-        cls_loc[tid] = 0;
-      }
-      __syncthreads();
-      uint32_t w = act_base + off;
-      for (int q = 0; q < PER; q++) {
-        const uint32_t p = tid + q * NT;
-        if (p >= total) continue;
-        const uint32_t info = tab[eslot[q]];
-        const uint32_t gbase = info & 0xFFFFu, gcnt = info >> 16;
-        if (gcnt < 2) continue;
-        const uint32_t j = EJ[p];
-        const Unit u = ud[j];
-        const uint32_t slot = u.start + (pos_q[q] - uoff[j]);
-        if (!R.aflag) {
-          if (w < B.cap) B.act[nxt][w] = slot;
-          else atomicOr(&B.ctr->err, 4u);
-          w++;
-        }
-        if (pos_q[q] == gbase) {
-          const int cc = class_of(gcnt);
-          const uint32_t k = cls_base[cc] + atomicAdd(&cls_loc[cc], 1u);
-          const uint32_t capc = B.cls_off[cc + 1] - B.cls_off[cc];
-          if (k < capc)
-            B.cls[nxt][B.cls_off[cc] + k] = Unit{u.start + (gbase - uoff[j]), gcnt | (MODE == MODE_SA ? kHeadBit : 0u)};
-          else atomicOr(&B.ctr->err, 8u);
-        }
-      }
-    }
-    __syncthreads();
+  for (uint32_t base = 0; base < total; base += gridDim.x) {
+    const uint32_t item = (uint32_t)xcd_item(base, total, blockIdx.x, gridDim.x);
+    if (item >= total) break;
+    group_tile<MODE, TLG>(B, cur, R, last_level, keep, item, S, deferred);
   }
-  if (tid == 0 && elems) atomicAdd(&B.ctr->lds_elems, elems);
-  if (tid == 0 && act_deferred) atomicAdd(&B.ctr->act_cnt[nxt], act_deferred);
+  flush_counts(B, cur ^ 1, deferred);
 }
 
 // ----------------------------------------------------------- MSD bucketing
@@ -1162,50 +1258,88 @@ __global__ __launch_bounds__(256) void k_msd_scatter(SortBufs B, int cur, int le
 // chunk: SA-mode ranks and grouped-slot flags, copy-back from the
 // alternate buffer, the next level's active slots (plain mode), and (by the
 // unit's first chunk) the unit itself as a large unit of the next level.
+template <int MODE, int NT, int CL>
+__device__ __forceinline__ void bulk_chunk(const SortBufs &B, int cur, const RankOut &R, uint32_t next_bits,
+                                           int last_level, uint8_t *keep, uint32_t units, uint32_t ch, uint32_t &base,
+                                           uint32_t &deferred) {
+  constexpr int PER = (1 << CL) / NT;
+  const int nxt = cur ^ 1;
+  const uint32_t u = find_unit(B.bulk, units, ch);
+  const BigUnit bu = B.bulk[u];
+  const bool alt = (bu.meta & kMetaAlt) != 0;
+  const uint32_t lo = bu.start + ((ch - bu.cbase) << CL);
+  const uint32_t hi = min(lo + (1u << CL), bu.start + bu.len);
+  if (threadIdx.x == 0 && !last_level && ch == bu.cbase)
+    append_big(B.big[nxt][0], &B.ctr->big_pk[nxt][0], B.big_cap, bu.start, bu.len, next_bits, &B.ctr->err,
+               CL);
+  for (int q = 0; q < PER; q++) {
+    const uint32_t p = lo + threadIdx.x + q * NT;
+    if (p < hi) {
+      const uint32_t v = val_buf(B, alt ? 1 : 0)[p];
+      if (alt) B.val[0][p] = v;
+      if (MODE == MODE_SA) {
+        R.rank[v] = bu.start + 1;
+        if (R.aflag) R.aflag[p] = 1;
+      }
+      if (last_level) keep[p] = (p == bu.start) ? 1 : 0;
+    }
+  }
+  if (!last_level) {
+    const uint32_t cnt = hi - lo;
+    if (R.aflag) {
+      if (threadIdx.x == kActThread) deferred += cnt;
+      return;
+    }
+    if (threadIdx.x == 0) base = atomicAdd(&B.ctr->act_cnt[nxt], cnt);
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < cnt; e += NT) {
+      const uint32_t w = base + e;
+      if (w < B.cap) B.act[nxt][w] = lo + e;
+      else atomicOr(&B.ctr->err, 256u);
+    }
+    __syncthreads();
+  }
+}
+
 template <int MODE, int CL>
 __global__ __launch_bounds__(256) void k_bulk(SortBufs B, int cur, RankOut R, uint32_t next_bits,
                                               int last_level, uint8_t *keep) {
-  constexpr int NT = 256;
-  constexpr int PER = (1 << CL) / NT;
-  __shared__ uint32_t sh[NT / 64];
   __shared__ uint32_t base;
-  const int nxt = cur ^ 1;
-  uint32_t units, total;
+  uint32_t units, total, deferred = 0;
   list_size(B.ctr->bulk_pk, B.big_cap, units, total);
-  for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
-    const uint32_t u = find_unit(B.bulk, units, ch);
-    const BigUnit bu = B.bulk[u];
-    const bool alt = (bu.meta & kMetaAlt) != 0;
-    const uint32_t lo = bu.start + ((ch - bu.cbase) << CL);
-    const uint32_t hi = min(lo + (1u << CL), bu.start + bu.len);
-    if (threadIdx.x == 0 && !last_level && ch == bu.cbase)
-      append_big(B.big[nxt][0], &B.ctr->big_pk[nxt][0], B.big_cap, bu.start, bu.len, next_bits, &B.ctr->err,
-                 CL);
-    for (int q = 0; q < PER; q++) {
-      const uint32_t p = lo + threadIdx.x + q * NT;
-      if (p < hi) {
-        const uint32_t v = val_buf(B, alt ? 1 : 0)[p];
-        if (alt) B.val[0][p] = v;
-        if (MODE == MODE_SA) {
-          R.rank[v] = bu.start + 1;
-          if (R.aflag) R.aflag[p] = 1;
-        }
-        if (last_level) keep[p] = (p == bu.start) ? 1 : 0;
-      }
-    }
-    if (!last_level) {
-      const uint32_t cnt = hi - lo;
-      if (threadIdx.x == 0) base = atomicAdd(&B.ctr->act_cnt[nxt], cnt);
-      __syncthreads();
-      for (uint32_t e = threadIdx.x; e < cnt && !R.aflag; e += NT) {
-        const uint32_t w = base + e;
-        if (w < B.cap) B.act[nxt][w] = lo + e;
-        else atomicOr(&B.ctr->err, 256u);
-      }
-      __syncthreads();
-    }
+  for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x)
+    bulk_chunk<MODE, 256, CL>(B, cur, R, next_bits, last_level, keep, units, ch, base, deferred);
+  flush_counts(B, cur ^ 1, deferred);
+}
+
+// ------------------------------------------------- all of a small round's units
+// Analyses of up to 2^22 tokens leave each kind of unit's kernel a fraction of
+// the chip, each at the length of its one tile or row (n = 131071: 18 us for the
+// rows, 20 us for the tiles, 5 us for the chunks of a round, one after another):
+// here one launch takes them all, the tiles, which take longest, first.
+template <int MODE>
+__global__ __launch_bounds__(kGroupThreads, 4) void k_sort_units(SortBufs B, int cur, RankOut R, uint32_t next_bits,
+                                                                 int last_level, uint8_t *keep) {
+  constexpr int NT = kGroupThreads, ITEMS = 4;
+  constexpr uint32_t kBatch = NT / 64 * ITEMS;
+  __shared__ GroupLds<11> S;
+  __shared__ WaveLds<NT> SW;
+  __shared__ uint32_t bulk_base;
+  uint32_t bulk_units, bulk_chunks, deferred = 0;
+  list_size(B.ctr->bulk_pk, B.big_cap, bulk_units, bulk_chunks);
+  const WaveList W = wave_list(B, cur);
+  const uint32_t tiles = group_tiles<11>(B, cur, S);
+  const uint32_t total = tiles + bulk_chunks + (W.total() + kBatch - 1) / kBatch;
+  for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
+    if (i < tiles)
+      group_tile<MODE, 11>(B, cur, R, last_level, keep, i, S, deferred);
+    else if (i < tiles + bulk_chunks)
+      bulk_chunk<MODE, NT, kChunkLogSmall>(B, cur, R, next_bits, last_level, keep, bulk_units, i - tiles, bulk_base,
+                                           deferred);
+    else
+      wave_rows<MODE, NT, ITEMS>(B, cur, R, last_level, keep, W, (i - tiles - bulk_chunks) * kBatch, SW, deferred);
   }
-  (void)sh;
+  flush_counts(B, cur ^ 1, deferred);
 }
 
 // =================================================================== host
@@ -1351,26 +1485,35 @@ void SortEngine::msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, c
 }
 
 template <int MODE>
-static void launch_lds(const SortBufs &b, int cur, RankOut R, uint32_t next_bits, int last_level, uint8_t *keep,
-                       uint64_t work_hint, hipStream_t s) {
+static void launch_units(const SortBufs &b, int cur, RankOut R, uint32_t next_bits, int last_level, uint8_t *keep,
+                         uint64_t work_hint, hipStream_t s) {
+  const int tl = (int)b.tile_log;
+  if (b.chunk_log == kChunkLogSmall && tl == 11) {
+    const unsigned g = (unsigned)std::min<uint64_t>(2048, work_hint / 512 + 16);
+    hipLaunchKernelGGL(k_sort_units<MODE>, dim3(g), dim3(kGroupThreads), 0, s, b, cur, R, next_bits, last_level, keep);
+    return;
+  }
   const uint64_t tile = 1ull << b.tile_log;
   const unsigned g = (unsigned)std::min<uint64_t>(2048, std::max<uint64_t>(64, 2 * work_hint / tile + 16));
-  const int tl = (int)b.tile_log;
   // classes below kGroupMinCi: wavefront sort; kGroupMinCi..min(tl,12)-1:
   // hash grouping; class 13 (tile 2^13 only): LDS bitonic
-  const int grp_hi = std::min(tl, 12);
   // units of <= 64 entries: one wavefront each row
   const unsigned gw = (unsigned)std::min<uint64_t>(4096, std::max<uint64_t>(64, work_hint / 256 + 1));
   hipLaunchKernelGGL(k_wave_sort<MODE>, dim3(gw), dim3(256), 0, s, b, cur, R, last_level, keep);
   if (tl == 13)
     hipLaunchKernelGGL((k_lds_sort<MODE, 13>), dim3(g), dim3(kLdsThreads), 0, s, b, cur, R, next_bits, last_level,
                        keep, 12, 13);
-  if (grp_hi > kGroupMinCi) {
-    if (tl == 11)
-      hipLaunchKernelGGL((k_lds_group<MODE, 11>), dim3(g), dim3(kGroupThreads), 0, s, b, cur, R, last_level, keep);
-    else
-      hipLaunchKernelGGL((k_lds_group<MODE, 12>), dim3(g), dim3(kGroupThreads), 0, s, b, cur, R, last_level, keep);
-  }
+  if (tl == 11)
+    hipLaunchKernelGGL((k_lds_group<MODE, 11>), dim3(g), dim3(kGroupThreads), 0, s, b, cur, R, last_level, keep);
+  else
+    hipLaunchKernelGGL((k_lds_group<MODE, 12>), dim3(g), dim3(kGroupThreads), 0, s, b, cur, R, last_level, keep);
+  const unsigned gb = (unsigned)std::min<uint64_t>(2048, std::max<uint64_t>(64, (work_hint >> b.chunk_log) + 1));
+  if (b.chunk_log == kChunkLogSmall)
+    hipLaunchKernelGGL((k_bulk<MODE, kChunkLogSmall>), dim3(gb), dim3(256), 0, s, b, cur, R, next_bits, last_level,
+                       keep);
+  else
+    hipLaunchKernelGGL((k_bulk<MODE, kChunkLogLarge>), dim3(gb), dim3(256), 0, s, b, cur, R, next_bits, last_level,
+                       keep);
 }
 
 void SortEngine::set_params(int tile_log, int digit_bits) {
@@ -1385,36 +1528,14 @@ void SortEngine::set_chunk_for(uint64_t n) {
   b_.chunk_log = n <= kSmallChunkMaxN ? (uint32_t)kChunkLogSmall : (uint32_t)kChunkLogLarge;
 }
 
-void SortEngine::lds_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s) {
-  launch_lds<MODE_SA>(b_, cur, R, next_bits, 0, nullptr, work_hint, s);
+void SortEngine::units_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s) {
+  launch_units<MODE_SA>(b_, cur, R, next_bits, 0, nullptr, work_hint, s);
 }
 
-void SortEngine::lds_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep,
-                           uint64_t work_hint, hipStream_t s) {
+void SortEngine::units_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep, uint64_t work_hint,
+                             hipStream_t s) {
   RankOut R{};
-  launch_lds<MODE_PLAIN>(b_, cur, R, next_bits, last_level, keep, work_hint, s);
-}
-
-void SortEngine::bulk_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s) {
-  const unsigned g = (unsigned)std::min<uint64_t>(2048, std::max<uint64_t>(64, (work_hint >> b_.chunk_log) + 1));
-  if (b_.chunk_log == kChunkLogSmall)
-    hipLaunchKernelGGL((k_bulk<MODE_SA, kChunkLogSmall>), dim3(g), dim3(256), 0, s, b_, cur, R, next_bits, 0,
-                       (uint8_t *)nullptr);
-  else
-    hipLaunchKernelGGL((k_bulk<MODE_SA, kChunkLogLarge>), dim3(g), dim3(256), 0, s, b_, cur, R, next_bits, 0,
-                       (uint8_t *)nullptr);
-}
-
-void SortEngine::bulk_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep,
-                            uint64_t work_hint, hipStream_t s) {
-  RankOut R{};
-  const unsigned g = (unsigned)std::min<uint64_t>(2048, std::max<uint64_t>(64, (work_hint >> b_.chunk_log) + 1));
-  if (b_.chunk_log == kChunkLogSmall)
-    hipLaunchKernelGGL((k_bulk<MODE_PLAIN, kChunkLogSmall>), dim3(g), dim3(256), 0, s, b_, cur, R, next_bits,
-                       last_level, keep);
-  else
-    hipLaunchKernelGGL((k_bulk<MODE_PLAIN, kChunkLogLarge>), dim3(g), dim3(256), 0, s, b_, cur, R, next_bits,
-                       last_level, keep);
+  launch_units<MODE_PLAIN>(b_, cur, R, next_bits, last_level, keep, work_hint, s);
 }
 
 }  // namespace apo
