@@ -24,6 +24,8 @@ constexpr int kMsdLists = kMaxMsdLevels + 1;
 // 2^22 tokens (more workgroups than CUs on small inputs), 2^13 above.
 constexpr int kChunkLogSmall = 12, kChunkLogLarge = 13;
 constexpr uint64_t kSmallChunkMaxN = 1ull << 22;
+// Longest large unit that one workgroup splits on its own (see k_msd_unit).
+constexpr uint32_t kMsdUnitMax = 1u << 16;
 constexpr int kMaxRounds = 32;              // doubling rounds (n <= 2^26 needs <= 28)
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kBufBit = 0x80000000u;   // unit data lives in the alternate buffer
@@ -57,6 +59,7 @@ struct SortCounters {
   uint32_t act_cnt[2];              // active slot list lengths
   uint32_t err;                     // nonzero: capacity overflow detected on device
   uint32_t lds_elems;               // entries sorted by the LDS path this round
+  uint32_t huge[2];                 // units longer than kMsdUnitMax, [list]
 };
 
 // Pointers of one segmented-sort "engine" (arrays of capacity cap elements).

@@ -282,7 +282,8 @@ static void sort_plain(Workspace &w, const uint32_t *count_dev, uint64_t bound, 
   for (int L = 0; L < nlevels; L++) {
     const int last = (L == nlevels - 1);
     const uint32_t nb = last ? 0u : (uint32_t)bits[L + 1];
-    if (bound > (1u << E.tile_log())) E.msd(cur, bound, bits[L], s);
+    if (bound > kMsdUnitMax) E.msd(cur, bound, bits[L], s);
+    else if (bound > (1u << E.tile_log())) E.msd_units(cur, bound, s);
     E.units_plain(cur, nb, last, keep ? keep : w.keep, bound, s);
     if (!last) {
       cur ^= 1;
@@ -512,14 +513,19 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       E.gather_identity(key0, (uint32_t)N, s);
     E.init_units(cur, w.d_off, W, 0, bits0, s);
   }
-  bool big = maxwin > (1ull << E.tile_log());
+  // units too long for a tile are left; and units too long for one workgroup to
+  // split (only single windows count those: other runs go by their longest window)
+  const bool wide = maxwin > kMsdUnitMax;
+  bool big = maxwin > (1ull << E.tile_log()), huge = wide && !batch;
   uint64_t act = N;
   int r = pair0 ? 2 : pack, done_round = -1;
   w.kev_n = 0;
   const uint32_t seq = ++w.report_seq;
-  auto round = [&]() -> int {  // launches round r
-    if (r > pack) E.gather_sa(cur, w.rank, w.aflag, wend, (uint32_t)N, 1u << (r - 1), w.rhist, r, s, host ? w.hrhist : nullptr,
-                               seq);
+  auto gather = [&] {  // closes round r - 1, opens round r
+    if (r > pack)
+      E.gather_sa(cur, w.rank, w.aflag, wend, (uint32_t)N, 1u << (r - 1), w.rhist, r, s, host ? w.hrhist : nullptr, seq);
+  };
+  auto round = [&]() -> int {  // launches the rest of round r
     // sync-free runs with pair ranks: the second round's state from them,
     // after that round's gather (which found nothing grouped and cleared
     // the lists it fills), so the round's sort launches find no work
@@ -529,7 +535,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     RankOut R{w.rank, (uint32_t)r, w.aflag};
     if (r > 0 || !skip0) {
       const bool first = r == pack;  // keys are tokens, not ranks
-      if (big) E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg);
+      if (big && (huge || !host || (batch && wide))) E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg);
+      else if (big) E.msd_units(cur, act, s, first ? nullptr : wbeg);
       const bool timed = w.ktag == KT_LDS_SA && w.kev_n < kMaxTimed;
       if (timed) APO_HIP_TRY(hipEventRecord(w.kev[2 * w.kev_n], s));
       E.units_sa(cur, R, rel_bits, act, s);
@@ -544,28 +551,45 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     r++;
     return 0;
   };
+  auto outcome = [&](int k) -> int {  // waits for round k's
+    uint64_t got = 0;
+    auto there = [&] {
+      got = __atomic_load_n(reinterpret_cast<const uint64_t *>(w.hrhist + 4 * k), __ATOMIC_ACQUIRE);
+      return got >> 34 == (seq & 0x3FFFFFFFu);
+    };
+    if ((rc = wait_report(there, s))) return rc;
+    act = got & 0xFFFFFFFFu;
+    big = (got >> 32) & 1u;
+    huge = (got >> 33) & 1u;
+    if (act == 0) done_round = k;
+    return 0;
+  };
   if (!host) {
     while (r < r_max) {
       if (r >= w.nsnap) return -4;
+      gather();
       if ((rc = round())) return rc;
     }
     E.round_end(cur ^ 1, r - 1, w.rhist, s);
     done_round = r - 1;  // an upper bound of the last round that did work
   }
   for (int k = r; done_round < 0; k++) {  // k: the round whose outcome is next
-    while (r <= k + 1 && r < w.nsnap)
-      if ((rc = round())) return rc;
     if (k >= w.nsnap) return -4;
+    bool known = false;
+    while (r <= k + 1 && r < w.nsnap) {
+      gather();
+      // how round k + 1 is sorted depends on what round k left, where that may
+      // still be a unit too long for one workgroup: wait while its gather runs
+      if (r == k + 1 && huge) {
+        if ((rc = outcome(k))) return rc;
+        known = true;
+        if (done_round >= 0) break;
+      }
+      if ((rc = round())) return rc;
+    }
+    if (known) continue;
     if (r == k + 1) E.round_end(cur ^ 1, k, w.rhist, s, w.hrhist, seq);  // no round is left to close it
-    uint64_t got = 0;
-    auto there = [&] {
-      got = __atomic_load_n(reinterpret_cast<const uint64_t *>(w.hrhist + 4 * k), __ATOMIC_ACQUIRE);
-      return got >> 33 == (seq & 0x7FFFFFFFu);
-    };
-    if ((rc = wait_report(there, s))) return rc;
-    act = got & 0xFFFFFFFFu;
-    big = (got >> 32) & 1u;
-    if (act == 0) done_round = k;
+    if ((rc = outcome(k))) return rc;
   }
   if (w.fail_after >= 0 && w.fail_after-- == 0) {  // test hook, as in read_counters
     fprintf(stderr, "[apo] injected device error\n");
@@ -634,7 +658,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     flag_positions(w.keep, dc + CNT_C, c_bound, w.tmp_d, dc + CNT_AUX, w.tile_tmp, s);
     E.init_runs(0, w.tmp_d, dc + CNT_AUX, dc + CNT_C, c_bound, rank_bits, s);
     fill_u8_dev(w.keep, dc + CNT_C, c_bound, 1, s);
-    if (c_bound > (1ull << E.tile_log())) E.msd(0, c_bound, (int)rank_bits, s);
+    if (c_bound > kMsdUnitMax) E.msd(0, c_bound, (int)rank_bits, s);
+    else if (c_bound > (1ull << E.tile_log())) E.msd_units(0, c_bound, s);
     E.units_plain(0, 0, 1, w.keep, c_bound, s);
     compact_sorted_runs(B.val[0], w.keep, dc + CNT_C, c_bound, w.tmp_a, w.tmp_b, w.tmp_c, dc + CNT_MAXL, w.s_len,
                         w.s_start, w.s_id, w.tile_tmp, dc + CNT_M, s,

@@ -23,7 +23,7 @@ class SortEngine {
   int tile_log() const { return (int)b_.tile_log; }
   int digit_bits() const { return (int)b_.digit_bits; }
   void round_begin(int cur, hipStream_t s);
-  // mirror (nullable, pinned, 8-byte words): at word 2 r the active slots, above them 2 * seq + (large units left)
+  // mirror (nullable, pinned, 8-byte words): at word 2 r the active slots, above them 4 * seq + 2 * (a unit longer than kMsdUnitMax left) + (large units left)
   void round_end(int cur, int r, uint32_t *hist, hipStream_t s, uint32_t *mirror = nullptr, uint32_t seq = 0);
   // only (nullable): just the ranges w with only[w] != 0
   void init_units(int cur, const uint64_t *d_off, uint32_t nranges, uint32_t base, uint32_t key_bits,
@@ -47,6 +47,8 @@ class SortEngine {
   // stays 0), so keys that are ranks inside a window need only the window's
   // bits; max_bits counts those bits.
   void msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base = nullptr);
+  // the same in one launch, where no unit is longer than kMsdUnitMax (work_hint: at least the entries in units)
+  void msd_units(int cur, uint64_t work_hint, hipStream_t s, const uint32_t *slot_base = nullptr);
   // sorts and regroups the units the msd passes (or the list itself) left: rows, tiles, one-group chunks
   void units_sa(int cur, RankOut R, uint32_t next_bits, uint64_t work_hint, hipStream_t s);
   void units_plain(int cur, uint32_t next_bits, int last_level, uint8_t *keep, uint64_t work_hint, hipStream_t s);

@@ -42,13 +42,15 @@ __global__ void k_round_begin(SortCounters *c, int cur) {
     c->bulk_pk = 0;
     c->act_cnt[nxt] = 0;
     c->lds_elems = 0;
+    c->huge[nxt] = 0;
   }
 }
 
 // Records the outcome of round r - active slots and large units handed to
 // the next round, entries sorted in LDS - in hist and, for a host that polls,
-// the first two in its pinned mirror: one 64-bit store (nothing to order) of the
-// active slots below 2 * seq + (large units left).
+// what it goes by in its pinned mirror: one 64-bit store (nothing to order) of the
+// active slots below 4 * seq + 2 * (a unit too long for one workgroup left) +
+// (large units left).
 __device__ __forceinline__ void record_round(const SortCounters *c, int nxt, int r, uint32_t *hist, uint32_t *mirror,
                                              uint32_t seq) {
   const uint32_t act = c->act_cnt[nxt], big = (uint32_t)(c->big_pk[nxt][0] >> 32);
@@ -57,7 +59,7 @@ __device__ __forceinline__ void record_round(const SortCounters *c, int nxt, int
   hist[4 * r + 2] = c->lds_elems;
   if (mirror)
     __hip_atomic_store(reinterpret_cast<unsigned long long *>(mirror + 4 * r),
-                       ((unsigned long long)(2 * seq + (big ? 1u : 0u)) << 32) | act, __ATOMIC_RELAXED,
+                       ((unsigned long long)(4 * seq + (c->huge[nxt] ? 2u : 0u) + (big ? 1u : 0u)) << 32) | act, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -237,6 +239,7 @@ __global__ void k_gather_sa(SortBufs B, int cur, const uint32_t *rank, const uin
     c->bulk_pk = 0;
     c->act_cnt[nxt] = 0;
     c->lds_elems = 0;
+    c->huge[nxt] = 0;
   }
   if (B.ctr->act_cnt[cur] == 0) return;  // nothing grouped: a round launched past the last one
   // four consecutive slots per thread: flags, suffixes and window ends are
@@ -1253,6 +1256,126 @@ __global__ __launch_bounds__(256) void k_msd_scatter(SortBufs B, int cur, int le
   }
 }
 
+// All levels of one large unit by one workgroup, for units of up to kMsdUnitMax
+// entries: count digits, scan, scatter, route the buckets, and go on with those
+// still too long for a tile.  Bound by its own latency (one workgroup streams
+// some 60 GB/s); but a small round's units are few thousand entries each, for
+// which the three launches a level above took 30 us (n = 131071; two levels,
+// 60 us of a round's 90).
+constexpr int kUnitThreads = 1024, kUnitStack = 2 * (kMsdUnitMax >> kMinTileLog);  // pending buckets: disjoint, > a tile
+
+__global__ __launch_bounds__(kUnitThreads) void k_msd_unit(SortBufs B, int cur, const uint32_t *slot_base) {
+  constexpr int NT = kUnitThreads, PER = kBins / NT, LOADS = 4;
+  __shared__ uint32_t h[kBins];
+  __shared__ uint32_t sh[NT / 64];
+  __shared__ BigUnit todo[kUnitStack];
+  __shared__ uint32_t n_todo, one;
+  __shared__ uint32_t cls_n[kClasses], cls_at[kClasses];
+  uint32_t units, chunks;
+  list_size(B.ctr->big_pk[cur][0], B.big_cap, units, chunks);
+  const int tid = threadIdx.x;
+  for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+    if (tid == 0) {
+      todo[0] = B.big[cur][0][u];
+      n_todo = 1;
+    }
+    __syncthreads();
+    const uint32_t base = slot_base ? slot_base[todo[0].start] : 0u;
+    while (true) {  // each turn uses up key bits of one pending piece: it ends
+      const uint32_t left = n_todo;
+      if (left == 0) break;  // uniform
+      const BigUnit bu = todo[left - 1];
+      uint32_t shift, mask;
+      digit_params(bu.meta & 0xFFu, B.digit_bits, shift, mask);
+      const int sb = (bu.meta & kMetaAlt) ? 1 : 0;
+      const uint32_t *key = key_buf(B, sb) + bu.start, *val = val_buf(B, sb) + bu.start;
+      for (uint32_t b = tid; b <= mask; b += NT) h[b] = 0;
+      if (tid < kClasses) cls_n[tid] = 0;
+      __syncthreads();
+      if (tid == 0) {
+        n_todo = left - 1;
+        one = 0;
+      }
+      for (uint32_t p0 = tid; p0 < bu.len; p0 += NT * LOADS) {
+        uint32_t k[LOADS];
+#pragma unroll
+        for (int q = 0; q < LOADS; q++) k[q] = p0 + q * NT < bu.len ? key[p0 + q * NT] : 0u;
+#pragma unroll
+        for (int q = 0; q < LOADS; q++)
+          if (p0 + q * NT < bu.len) agg_add(&h[(rel_key(k[q], base) >> shift) & mask], 1u);
+      }
+      __syncthreads();
+      uint32_t v[PER], at[PER], loc = 0;
+#pragma unroll
+      for (int q = 0; q < PER; q++) {
+        const uint32_t b = tid * PER + q;
+        v[q] = b <= mask ? h[b] : 0u;
+        loc += v[q];
+        if (v[q] == bu.len) one = 1;
+      }
+      uint32_t tot;
+      uint32_t ex = block_excl_sum<NT>(loc, sh, &tot);  // (has barriers)
+      // everything in one bucket: goes on in place
+      const bool single = one != 0;
+      const uint32_t piece_meta = shift | ((sb ^ (single ? 0 : 1)) ? kMetaAlt : 0u);
+#pragma unroll
+      for (int q = 0; q < PER; q++) {
+        const uint32_t b = tid * PER + q;
+        at[q] = 0;
+        if (v[q]) {
+          h[b] = ex;
+          const uint32_t start = bu.start + ex;
+          if (v[q] <= (1u << B.tile_log)) {
+            at[q] = atomicAdd(&cls_n[class_of(v[q])], 1u);
+          } else if (shift == 0) {
+            append_big(B.bulk, &B.ctr->bulk_pk, B.big_cap, start, v[q], piece_meta, &B.ctr->err, B.chunk_log);
+          } else {
+            const uint32_t t = atomicAdd(&n_todo, 1u);
+            if (t < (uint32_t)kUnitStack) todo[t] = BigUnit{start, v[q], 0, piece_meta};
+            else atomicOr(&B.ctr->err, 512u);
+          }
+        }
+        ex += v[q];
+      }
+      __syncthreads();
+      if (tid < kClasses) cls_at[tid] = cls_n[tid] ? atomicAdd(&B.ctr->cls_cnt[cur][tid], cls_n[tid]) : 0u;
+      if (tid == 0 && n_todo > (uint32_t)kUnitStack) n_todo = kUnitStack;  // (err is set)
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < PER; q++) {
+        if (!v[q] || v[q] > (1u << B.tile_log)) continue;
+        const int d = class_of(v[q]);
+        const uint32_t k = cls_at[d] + at[q];
+        if (k < B.cls_off[d + 1] - B.cls_off[d])
+          B.cls[cur][B.cls_off[d] + k] = Unit{bu.start + h[tid * PER + q], v[q] | ((piece_meta & kMetaAlt) ? kBufBit : 0u)};
+        else atomicOr(&B.ctr->err, 16u);
+      }
+      __syncthreads();  // h: offsets read, cursors from here on
+      if (!single) {
+        uint32_t *dk = key_buf(B, sb ^ 1) + bu.start, *dv = val_buf(B, sb ^ 1) + bu.start;
+        for (uint32_t p0 = tid; p0 < bu.len; p0 += NT * LOADS) {
+          uint32_t k[LOADS], w[LOADS];
+#pragma unroll
+          for (int q = 0; q < LOADS; q++) {
+            const bool in = p0 + q * NT < bu.len;
+            k[q] = in ? key[p0 + q * NT] : 0u;
+            w[q] = in ? val[p0 + q * NT] : 0u;
+          }
+#pragma unroll
+          for (int q = 0; q < LOADS; q++)
+            if (p0 + q * NT < bu.len) {
+              const uint32_t o = agg_inc(&h[(rel_key(k[q], base) >> shift) & mask]);
+              dk[o] = k[q];
+              dv[o] = w[q];
+            }
+        }
+      }
+      __syncthreads();
+    }
+    __syncthreads();
+  }
+}
+
 // --------------------------------------------------- bulk (one-group) units
 // Pieces whose key bits are used up are one group each.  Processed chunk by
 // chunk: SA-mode ranks and grouped-slot flags, copy-back from the
@@ -1269,9 +1392,11 @@ __device__ __forceinline__ void bulk_chunk(const SortBufs &B, int cur, const Ran
   const bool alt = (bu.meta & kMetaAlt) != 0;
   const uint32_t lo = bu.start + ((ch - bu.cbase) << CL);
   const uint32_t hi = min(lo + (1u << CL), bu.start + bu.len);
-  if (threadIdx.x == 0 && !last_level && ch == bu.cbase)
+  if (threadIdx.x == 0 && !last_level && ch == bu.cbase) {
+    if (bu.len > kMsdUnitMax) atomicAdd(&B.ctr->huge[nxt], 1u);
     append_big(B.big[nxt][0], &B.ctr->big_pk[nxt][0], B.big_cap, bu.start, bu.len, next_bits, &B.ctr->err,
                CL);
+  }
   for (int q = 0; q < PER; q++) {
     const uint32_t p = lo + threadIdx.x + q * NT;
     if (p < hi) {
@@ -1469,6 +1594,11 @@ void SortEngine::gather_field(int cur, const uint32_t *field, int stride, const 
 
 void SortEngine::iota_val(const uint32_t *n_dev, uint64_t bound, hipStream_t s) {
   hipLaunchKernelGGL(k_iota_val, grid_for(bound, 256, 4096), dim3(256), 0, s, b_, n_dev);
+}
+
+void SortEngine::msd_units(int cur, uint64_t work_hint, hipStream_t s, const uint32_t *slot_base) {
+  const unsigned g = (unsigned)std::min<uint64_t>(512, (work_hint >> b_.tile_log) + 1);
+  hipLaunchKernelGGL(k_msd_unit, dim3(g), dim3(kUnitThreads), 0, s, b_, cur, slot_base);
 }
 
 void SortEngine::msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base) {
