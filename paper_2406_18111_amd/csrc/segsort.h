@@ -38,8 +38,10 @@ class SortEngine {
   // keys of k tokens of one window (src + add in 1 .. 2^b - 1, k * b <= 32); hist: the replaced rounds' counts, set to n
   void gather_packed(const uint32_t *src, uint32_t n, uint32_t add, int k, int b, uint32_t *hist, int skipped,
                      hipStream_t s);
+  // snap (nullable): gets the ranks after round r - 1 if round r has work, and *snaps = r
   void gather_sa(int cur, const uint32_t *rank, const uint8_t *aflag, const uint32_t *slot_wend, uint32_t n,
-                 uint32_t h, uint32_t *hist, int r, hipStream_t s, uint32_t *mirror = nullptr, uint32_t seq = 0);
+                 uint32_t h, uint32_t *hist, int r, uint32_t *snap, uint32_t *snaps, hipStream_t s,
+                 uint32_t *mirror = nullptr, uint32_t seq = 0);
   void gather_field(int cur, const uint32_t *field, int stride, const uint32_t *all_dev, int sub,
                     const uint32_t *c_dev, uint32_t c, uint64_t bound, hipStream_t s);
   void iota_val(const uint32_t *n_dev, uint64_t bound, hipStream_t s);

@@ -228,7 +228,7 @@ __global__ void k_gather_packed(SortBufs B, const uint32_t *src, uint32_t n, uin
 // slots (the grouped-slot flags are sequential) instead of an active list.
 __global__ void k_gather_sa(SortBufs B, int cur, const uint32_t *rank, const uint8_t *aflag,
                             const uint32_t *slot_wend, uint32_t n, uint32_t h, uint32_t *hist, int r,
-                            uint32_t *mirror, uint32_t seq) {
+                            uint32_t *mirror, uint32_t seq, uint32_t *snap, uint32_t *snaps) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     SortCounters *c = B.ctr;
     const int nxt = cur ^ 1;
@@ -242,6 +242,24 @@ __global__ void k_gather_sa(SortBufs B, int cur, const uint32_t *rank, const uin
     c->huge[nxt] = 0;
   }
   if (B.ctr->act_cnt[cur] == 0) return;  // nothing grouped: a round launched past the last one
+  // the ranks after round r - 1, for the LCP walk (the last round's are the final ones)
+  if (snap) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *snaps = (uint32_t)r;
+    const uint64_t step = (uint64_t)gridDim.x * blockDim.x * 4;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * blockDim.x * 4; b0 < n; b0 += step) {
+      uint32_t v[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const uint64_t i = b0 + (uint64_t)u * blockDim.x + threadIdx.x;  // coalesced for each u
+        v[u] = i < n ? rank[i] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const uint64_t i = b0 + (uint64_t)u * blockDim.x + threadIdx.x;
+        if (i < n) snap[i] = v[u];
+      }
+    }
+  }
   // four consecutive slots per thread: flags, suffixes and window ends are
   // single 4- and 16-byte loads and the four partner-rank reads are issued
   // together.  Keys of slots no longer grouped are never read (only units
@@ -1580,10 +1598,10 @@ void SortEngine::gather_packed(const uint32_t *src, uint32_t n, uint32_t add, in
 }
 
 void SortEngine::gather_sa(int cur, const uint32_t *rank, const uint8_t *aflag, const uint32_t *slot_wend,
-                           uint32_t n, uint32_t h, uint32_t *hist, int r, hipStream_t s, uint32_t *mirror,
-                           uint32_t seq) {
+                           uint32_t n, uint32_t h, uint32_t *hist, int r, uint32_t *snap, uint32_t *snaps,
+                           hipStream_t s, uint32_t *mirror, uint32_t seq) {
   hipLaunchKernelGGL(k_gather_sa, dim3(4096), dim3(256), 0, s, b_, cur, rank, aflag, slot_wend, n, h, hist, r, mirror,
-                     seq);
+                     seq, snap, snaps);
 }
 
 void SortEngine::gather_field(int cur, const uint32_t *field, int stride, const uint32_t *all_dev, int sub,

@@ -30,6 +30,10 @@ void hash_fields(const uint64_t *tok, const uint32_t *dist_idx, const uint32_t *
                  uint32_t *lo, uint64_t hint, hipStream_t s);
 void hash_assign(const uint32_t *sorted_d, const uint32_t *nd, const uint32_t *dist_slot,
                  uint32_t *slot_rank, uint64_t hint, hipStream_t s);
+// slot_rank[dist_slot[i]] = 1-based rank of token dist_idx[i] among the nd
+// distinct ones (nd^2 comparisons).
+void rank_distinct(const uint64_t *tok, const uint32_t *dist_idx, uint64_t nd, const uint32_t *dist_slot,
+                   uint32_t *slot_rank, hipStream_t s);
 // out[i] = slot_rank[tok_slot[i]] (out may be tok_slot), for the tokens of
 // flagged windows only when wflag is set; nothing unless *gate > 0 when set.
 void hash_rank(const uint32_t *tok_slot, uint64_t n, const uint32_t *slot_rank, uint32_t *out, hipStream_t s,
@@ -68,20 +72,15 @@ void win_round0(const SortBufs &B, const uint64_t *off, const uint32_t *order, u
 void window_bounds(const uint64_t *off, uint32_t nw, uint32_t *wbeg, uint32_t *wend, uint32_t *wid,
                    hipStream_t s);
 
-// Copy of the rank array after doubling round r into its snapshot level,
-// taken only when the round sorted something (*act_dev: slots that entered
-// it); *snaps then becomes r + 1.
-void snapshot_ranks(const uint32_t *rank, uint32_t *snap_r, uint64_t n, const uint32_t *act_dev, uint32_t *snaps,
-                    int r, hipStream_t s);
 // LCP of adjacent suffixes.  rank: final ranks of the suffix sort (1 + slot);
 // snap: level j at snap + j * n for kSnapFrom <= j < *snaps (and j <= top).
+void build_lcp(const uint32_t *sa, const uint32_t *rank, uint64_t n, const uint32_t *wbeg, const uint32_t *wend,
+               const uint32_t *snap, const uint32_t *snaps, const uint32_t *key0, int top, uint32_t *lcp,
+               hipStream_t s);
 // *out = max(*out, largest of the n tokens)
 void max_token(const uint32_t *tok, uint64_t n, uint32_t *out, hipStream_t s);
 // hist[4 r] = slots whose suffix shares its first 2^r tokens with a neighbour (r < rounds <= 4)
 void short_rounds(const uint32_t *lcp, uint64_t n, int rounds, uint32_t *hist, hipStream_t s);
-void build_lcp(const uint32_t *sa, const uint32_t *rank, uint64_t n, const uint32_t *wbeg, const uint32_t *wend,
-               const uint32_t *snap, const uint32_t *snaps, const uint32_t *key0, int top, uint32_t *lcp,
-               hipStream_t s);
 
 // Candidates are written as records of kCandWords words: length, start, ID.
 // *cnt counts the records written; a candidate that exactly repeats one of

@@ -334,6 +334,40 @@ __global__ void k_hash_assign(const uint32_t *sorted_d, const uint32_t *nd, cons
   GRID_STRIDE(q, m) slot_rank[dist_slot[sorted_d[q]]] = (uint32_t)q + 1u;
 }
 
+// Ranks of nd distinct tokens by counting the smaller ones: a wavefront's lanes
+// each hold one token, the 16 wavefronts take the nd tokens in turn, 64 loaded
+// side by side and then passed round as scalars.  nd^2 / 2^14 comparisons a SIMD
+// at the largest nd; sorting them (two levels of the sort engine) is some 20
+// launches, 100 us and more, whatever nd is.  nd = 2201: token ranks of 131071
+// tokens 165 -> 62 us; nd = 15705: of 2^20 tokens 213 -> 128 us.
+__global__ __launch_bounds__(1024) void k_rank_distinct(const uint64_t *tok, const uint32_t *dist_idx, uint32_t nd,
+                                                        const uint32_t *dist_slot, uint32_t *slot_rank) {
+  __shared__ uint32_t part[16][64];
+  const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const uint32_t i = blockIdx.x * 64 + lane;
+  const uint64_t mine = i < nd ? tok[dist_idx[i]] : 0;
+  auto load = [&](uint32_t j) { return j < nd ? tok[dist_idx[j]] : ~0ull; };  // ~0: below nothing
+  uint64_t t = load(wv * 64 + lane);
+  uint32_t below = 0;
+  for (uint32_t j0 = wv * 64; j0 < nd; j0 += 1024) {
+    const uint64_t tn = load(j0 + 1024 + lane);
+#pragma unroll
+    for (int l = 0; l < 64; l++) {
+      const uint64_t o = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(t >> 32), l) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)t, l);
+      below += o < mine ? 1u : 0u;
+    }
+    t = tn;
+  }
+  part[wv][lane] = below;
+  __syncthreads();
+  if (wv == 0 && i < nd) {
+    uint32_t r = 1;
+    for (int w = 0; w < 16; w++) r += part[w][lane];
+    slot_rank[dist_slot[i]] = r;
+  }
+}
+
 // rank of every token from its slot (in place: out may be tok_slot); four
 // tokens per thread with the loads issued together.
 __global__ void k_hash_rank(const uint32_t *tok_slot, uint64_t n, const uint32_t *slot_rank, uint32_t *out,
@@ -388,6 +422,12 @@ void hash_assign(const uint32_t *sorted_d, const uint32_t *nd, const uint32_t *d
                  uint64_t hint, hipStream_t s) {
   hipLaunchKernelGGL(k_hash_assign, grid_for(hint, 256, 8192), dim3(256), 0, s, sorted_d, nd, dist_slot,
                      slot_rank);
+}
+void rank_distinct(const uint64_t *tok, const uint32_t *dist_idx, uint64_t nd, const uint32_t *dist_slot,
+                   uint32_t *slot_rank, hipStream_t s) {
+  if (nd)
+    hipLaunchKernelGGL(k_rank_distinct, dim3((unsigned)((nd + 63) / 64)), dim3(1024), 0, s, tok, dist_idx, (uint32_t)nd,
+                       dist_slot, slot_rank);
 }
 void hash_rank(const uint32_t *tok_slot, uint64_t n, const uint32_t *slot_rank, uint32_t *out, hipStream_t s,
                const uint32_t *wid, const uint8_t *wflag, const uint32_t *gate) {
@@ -1038,34 +1078,8 @@ void window_bounds(const uint64_t *off, uint32_t nw, uint32_t *wbeg, uint32_t *w
 // Snapshot level j is the whole rank array after doubling round j: two
 // suffixes of one window carry equal ranks there iff their 2^j-prefixes are
 // equal (a suffix alone in its group has a rank no other suffix has).  It is
-// a coalesced copy taken once per round instead of a scattered write of every
-// grouped suffix's rank by the sort kernels.
-__global__ void k_snapshot(const uint32_t *rank, uint32_t *snap_r, uint64_t n, const uint32_t *act_dev,
-                           uint32_t *snaps, int r) {
-  if (*act_dev == 0) return;  // nothing was sorted: no later level is read
-  if (blockIdx.x == 0 && threadIdx.x == 0) *snaps = (uint32_t)r + 1;
-  const uint64_t step = (uint64_t)gridDim.x * blockDim.x * 4;
-  for (uint64_t b0 = (uint64_t)blockIdx.x * blockDim.x * 4; b0 < n; b0 += step) {
-    uint32_t v[4];
-#pragma unroll
-    for (int u = 0; u < 4; u++) {
-      const uint64_t i = b0 + (uint64_t)u * blockDim.x + threadIdx.x;  // coalesced for each u
-      v[u] = i < n ? rank[i] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; u++) {
-      const uint64_t i = b0 + (uint64_t)u * blockDim.x + threadIdx.x;
-      if (i < n) snap_r[i] = v[u];
-    }
-  }
-}
-
-void snapshot_ranks(const uint32_t *rank, uint32_t *snap_r, uint64_t n, const uint32_t *act_dev, uint32_t *snaps,
-                    int r, hipStream_t s) {
-  hipLaunchKernelGGL(k_snapshot, grid_for((n + 3) / 4, 256, 8192), dim3(256), 0, s, rank, snap_r, n, act_dev, snaps,
-                     r);
-}
-
+// a coalesced copy taken once per round, by the next round's gather, instead
+// of a scattered write of every grouped suffix's rank by the sort kernels.
 // lcp(x, y) >= acc known; extend by binary lifting over the per-round rank
 // snapshots: 2^j-prefixes at x+acc and y+acc are equal iff their ranks after
 // round j are equal.  Snapshots exist for rounds >= kSnapFrom only; the last
