@@ -520,15 +520,16 @@ __device__ __forceinline__ void window_short(const FusedArgs &a, ShortLds<NT, IP
     __syncthreads();
   }
   const uint32_t D = s_nd;
-  {
+  auto rank_by = [&](auto each) {
+    constexpr int R = decltype(each)::value;
     uint64_t *sorted = reinterpret_cast<uint64_t *>(lds + CAP * 8);
-    uint64_t x[IPT];
+    uint64_t x[R];
 #pragma unroll
-    for (int i = 0; i < IPT; i++) {
-      const uint32_t q = tid * IPT + i;
+    for (int i = 0; i < R; i++) {
+      const uint32_t q = tid * R + i;
       x[i] = q < D ? tokl[rc[min(q, D - 1)]] : ~0ull;
     }
-    merge_sort<NT, IPT>(x, sorted, D);  // the table's last reads are a barrier behind
+    merge_sort<NT, R>(x, sorted, D);  // the table's last reads are a barrier behind
 #pragma unroll 1
     for (uint32_t q = tid; q < D; q += NT) {
       const uint32_t k = rc[q];
@@ -536,13 +537,16 @@ __device__ __forceinline__ void window_short(const FusedArgs &a, ShortLds<NT, IP
       uint32_t lo = 0, hi = D - 1;  // sorted[lo .. hi] holds it
       while (lo < hi) {
         const uint32_t mid = (lo + hi) / 2;
-        if (sorted[spread<IPT>(mid)] < key) lo = mid + 1;
+        if (sorted[spread<R>(mid)] < key) lo = mid + 1;
         else hi = mid;
       }
       tokl[k] = (1ull << 63) | (lo + 1);
     }
     __syncthreads();
-  }
+  };
+  // one a thread where that holds them all: a merge's steps are one thread's outputs after another
+  if (D <= NT) rank_by(std::integral_constant<int, 1>{});
+  else rank_by(std::integral_constant<int, IPT>{});
   uint16_t *txt = reinterpret_cast<uint16_t *>(lds + CAP * 8);  // token ranks 1..D
   uint16_t *rank = txt + CAP + 32, *sa = rank + CAP, *lcp = sa + CAP;
   uint32_t *exch = reinterpret_cast<uint32_t *>(lds);
@@ -1141,6 +1145,17 @@ __device__ __forceinline__ void byte_move(const uint32_t *my, uint32_t beg, uint
   }
 }
 
+// c[r]++; its value before.  The lanes of a run of one token all meet on one
+// word: one of them adds for all.
+__device__ __forceinline__ uint32_t count_in(uint32_t *c, uint32_t r) {
+  const uint64_t act = __ballot(1);
+  if (__ballot(r != (uint32_t)__builtin_amdgcn_readfirstlane((int)r)) != 0) return atomicAdd(&c[r], 1u);
+  const uint32_t mine = lanes_below(act);
+  uint32_t old = 0;
+  if (mine == 0) old = atomicAdd(&c[r], (uint32_t)__popcll(act));
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)old) + mine;
+}
+
 // LDS of a longer window.  big holds, one after the other: the distinct tokens'
 // table, their sorted list (64 KB) and ranks by slot; token ranks; suffix ranks;
 // token ranks; LCP values; the survivors of a chunk of candidates.
@@ -1189,16 +1204,82 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     wave_order();
   };
 
-  // ---- token ranks: distinct values through an LDS hash table of the values
-  // (the largest one, which marks free slots, aside), sorted in LDS
-  {
-    unsigned long long *tab = reinterpret_cast<unsigned long long *>(big);
-    uint16_t *const slot = reinterpret_cast<uint16_t *>(e0);      // of every token
-    uint16_t *const dslot = reinterpret_cast<uint16_t *>(e1 + n);  // of every distinct value
-    if (tid == 0) s_nd = s_top = s_over = s_skip = s_max = s_c = s_acc = s_dup = s_pairs = 0;
-    if (tid < kLongRounds) s_hist[tid] = 0;
+  // An LDS hash table of distinct words, listed in e1 as they turn up, each with
+  // its slot; kFree marks free slots.
+  unsigned long long *const tab = reinterpret_cast<unsigned long long *>(big);
+  uint16_t *const slot = reinterpret_cast<uint16_t *>(e0);      // of every token
+  uint16_t *const dslot = reinterpret_cast<uint16_t *>(e1 + n);  // of every distinct word
+  auto clear_table = [&] {
+    if (tid == 0) s_nd = s_over = 0;
     for (uint32_t k = 2 * tid; k < kLongSlots; k += 2 * NT) *reinterpret_cast<ulonglong2 *>(tab + k) = make_ulonglong2(kFree, kFree);
     __syncthreads();
+  };
+  auto insert = [&](uint64_t key) -> uint32_t {
+    uint32_t at = (uint32_t)(mix64(key) >> 40) & (kLongSlots - 1);
+    for (int probe = 0;; probe++) {
+      if (probe == (int)kLongSlots) {  // full (only past the limit)
+        s_over = 1;
+        break;
+      }
+      unsigned long long cur = tab[at];
+      if (cur == kFree) {
+        cur = atomicCAS(&tab[at], (unsigned long long)kFree, (unsigned long long)key);
+        if (cur == kFree) {
+          const uint32_t q = atomicAdd(&s_nd, 1u);
+          if (q < kLongDistinct) {
+            e1[q] = key;
+            dslot[q] = (uint16_t)at;
+          } else {
+            s_over = 1;
+          }
+          break;
+        }
+      }
+      if (cur == key) break;
+      at = (at + 1) & (kLongSlots - 1);
+    }
+    return at;
+  };
+  // Sorts the table's d words; srank: their ranks from 1, by slot.
+  uint16_t *const srank = reinterpret_cast<uint16_t *>(big + kLongDistinct * 8);
+  auto rank_by = [&](auto per, uint32_t d) {
+    constexpr int R = decltype(per)::value;
+    uint64_t *sorted = reinterpret_cast<uint64_t *>(big);
+    uint64_t x[R];
+#pragma unroll
+    for (int i = 0; i < R; i++) {
+      const uint32_t q = tid * R + i;
+      x[i] = q < d ? e1[q] : ~0ull;
+    }
+    merge_sort<NT, R>(x, sorted, d);  // the table's last reads are a barrier behind
+#pragma unroll 1
+    for (uint32_t q = tid; q < d; q += NT) {
+      const uint64_t key = e1[q];
+      uint32_t lo = 0, hi = d - 1;  // sorted[lo .. hi] holds it
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (sorted[spread<R>(mid)] < key) lo = mid + 1;
+        else hi = mid;
+      }
+      srank[dslot[q]] = (uint16_t)(lo + 1);
+    }
+    __syncthreads();
+  };
+  // as few words a thread as hold them all: a merge's steps are one thread's
+  // outputs after another (1112 words: 25 us eight a thread, 13 two a thread)
+  auto rank_table = [&](uint32_t d) {
+    if (d <= NT) rank_by(std::integral_constant<int, 1>{}, d);
+    else if (d <= 2 * NT) rank_by(std::integral_constant<int, 2>{}, d);
+    else if (d <= 4 * NT) rank_by(std::integral_constant<int, 4>{}, d);
+    else rank_by(std::integral_constant<int, kLongDistinct / NT>{}, d);
+  };
+
+  // ---- token ranks: the distinct values through the table (the largest value
+  // a token can have, which marks free slots, aside)
+  {
+    if (tid == 0) s_top = s_skip = s_max = s_c = s_acc = s_dup = s_pairs = 0;
+    if (tid < kLongRounds) s_hist[tid] = 0;
+    clear_table();
 #pragma unroll 1
     for (uint32_t k0 = tid; k0 < n; k0 += 8 * NT) {
       uint64_t v[8];
@@ -1211,35 +1292,9 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
 #pragma unroll
       for (int u = 0; u < 8; u++) {
         if (k0 + u * NT >= n) break;
-        const uint64_t key = v[u];
-        uint32_t at = (uint32_t)(mix64(key) >> 40) & (kLongSlots - 1);
-        if (key == kFree) {
-          s_top = 1;
-          at = kLongSlots;
-        } else {
-          for (int probe = 0;; probe++) {
-            if (probe == (int)kLongSlots) {  // full (only past the limit)
-              s_over = 1;
-              break;
-            }
-            unsigned long long cur = tab[at];
-            if (cur == kFree) {
-              cur = atomicCAS(&tab[at], (unsigned long long)kFree, (unsigned long long)key);
-              if (cur == kFree) {
-                const uint32_t q = atomicAdd(&s_nd, 1u);
-                if (q < kLongDistinct) {
-                  e1[q] = key;
-                  dslot[q] = (uint16_t)at;
-                } else {
-                  s_over = 1;
-                }
-                break;
-              }
-            }
-            if (cur == key) break;
-            at = (at + 1) & (kLongSlots - 1);
-          }
-        }
+        uint32_t at = kLongSlots;
+        if (v[u] == kFree) s_top = 1;
+        else at = insert(v[u]);
         slot[k0 + u * NT] = (uint16_t)at;
       }
     }
@@ -1256,37 +1311,13 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     }
   }
   const uint32_t nd = s_nd, top = s_top, D = nd + top;
-  {
-    uint64_t *sorted = reinterpret_cast<uint64_t *>(big);
-    uint16_t *srank = reinterpret_cast<uint16_t *>(big + kLongDistinct * 8);  // by slot
-    uint16_t *const slot = reinterpret_cast<uint16_t *>(e0), *const dslot = reinterpret_cast<uint16_t *>(e1 + n);
-    constexpr int R = kLongDistinct / NT;
-    uint64_t x[R];
-#pragma unroll
-    for (int i = 0; i < R; i++) {
-      const uint32_t q = tid * R + i;
-      x[i] = q < nd ? e1[q] : ~0ull;
-    }
-    merge_sort<NT, R>(x, sorted, nd);  // the table's last reads are a barrier behind
-#pragma unroll 1
-    for (uint32_t q = tid; q < nd; q += NT) {
-      const uint64_t key = e1[q];
-      uint32_t lo = 0, hi = nd - 1;  // sorted[lo .. hi] holds it
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) / 2;
-        if (sorted[spread<R>(mid)] < key) lo = mid + 1;
-        else hi = mid;
-      }
-      srank[dslot[q]] = (uint16_t)(lo + 1);
-    }
-    __syncthreads();
+  rank_table(nd);
 #pragma unroll 4
-    for (uint32_t k = tid; k < n; k += NT) {
-      const uint32_t at = slot[k];
-      gtxt[k] = (uint16_t)(at == kLongSlots ? D : srank[at]);
-    }
-    __syncthreads();
+  for (uint32_t k = tid; k < n; k += NT) {
+    const uint32_t at = slot[k];
+    gtxt[k] = (uint16_t)(at == kLongSlots ? D : srank[at]);
   }
+  __syncthreads();
   auto load_lds = [&](const uint16_t *from) {  // n words, four a lane (windows start 4-byte aligned: two 4-byte loads)
     uint32_t *to = reinterpret_cast<uint32_t *>(big);
     const uint32_t *g = reinterpret_cast<const uint32_t *>(from);
@@ -1295,15 +1326,114 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     __syncthreads();
   };
   uint16_t *const txt = reinterpret_cast<uint16_t *>(big);
-  load_lds(gtxt);
+  uint16_t *const rank = reinterpret_cast<uint16_t *>(big);  // rank[j]: the first slot of j's group
   stamp(1);
 
-  // ---- suffix array: every suffix sorted by its first h tokens, as many as fit
-  // above its position in a 64-bit word (kLongPack at most), by a radix sort
+  // ---- suffix array: every suffix first sorted by its first h tokens.  A
+  // repetitive window holds few distinct words of h tokens (up to 63 bits;
+  // kLongPack tokens at most): those go through the table as the tokens did, and
+  // the suffixes are counted into their places (20000 tokens of a loop with 5 %
+  // substitutions, 4725 words of 5: 68 us against 122 for six radix passes).  How
+  // many there will be is told from the first 2048 positions and then from the second 8192
+  // against the first: too many, h is lowered in proportion; mostly new ones, or
+  // too many after all, and a radix sort takes as many tokens as fit above the
+  // position in a 64-bit word.  So it does at once where that is three passes or
+  // fewer (windows over a handful of tokens).
   const int tbits = bits_of(D);
-  uint32_t h = min((uint32_t)(48 / tbits), kLongPack);
+  uint32_t h = min((uint32_t)(63 / tbits), kLongPack);
   const uint32_t wbeg = min(wv * seg(n), n), wtop = min(wbeg + seg(n), n);  // the wavefront's tokens and slots
-  {
+  bool named = h >= 2 && min(48 / tbits, (int)kLongPack) * tbits > 24;
+  bool lowered = false;
+  while (named) {  // uniform; at most twice
+    clear_table();
+    uint32_t seen = 0, lower = 0;
+#pragma unroll 1
+    for (uint32_t t0 = 0; t0 < n;) {
+      const uint32_t t1 = min(t0 ? t0 + 8 * NT : 2 * NT, n);
+      uint64_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+      for (uint32_t q = 0; q < h; q++)
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const uint32_t k = t0 + u * NT + tid;
+          v[u] = (v[u] << tbits) | (k < t1 && k + q < n ? gtxt[k + q] : 0u);
+        }
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const uint32_t k = t0 + u * NT + tid;
+        if (k < t1) slot[k] = (uint16_t)insert(v[u]);
+      }
+      __syncthreads();
+      const uint32_t now = s_nd;
+      if (now > (t0 ? kLongDistinct : NT + NT / 4)) {
+        named = false;
+        break;
+      }
+      if (t0 == 2 * NT && !lowered) {
+        const uint64_t end = now + (uint64_t)(now - seen) * (n - t1) / (t1 - t0);
+        if (end > kLongDistinct) {
+          lower = (uint32_t)(h * (uint64_t)(kLongDistinct - kLongDistinct / 8) / end);
+          named = lower >= 2;
+          break;
+        }
+      }
+      __syncthreads();  // s_nd is read before it grows
+      seen = now;
+      t0 = t1;
+    }
+    __syncthreads();
+    if (!lower) break;
+    h = lower;
+    lowered = true;
+  }
+  if (named) {
+    const uint32_t d = s_nd;
+    rank_table(d);
+    uint32_t *const cnt = reinterpret_cast<uint32_t *>(big);  // the sorted list is done with
+    uint32_t *const cur = reinterpret_cast<uint32_t *>(big + kLongDistinct * 8 + kLongSlots * 2);
+    static_assert(kLongDistinct * 12 + kLongSlots * 2 <= sizeof(L.big), "list or counts, ranks, cursors");
+    for (uint32_t q = tid; q < kLongDistinct; q += NT) cnt[q] = 0;
+    for (uint32_t x = tid; x <= n / 32 + 1; x += NT) bitmap[x] = 0;
+    __syncthreads();
+#pragma unroll 4
+    for (uint32_t k = tid; k < n; k += NT) (void)count_in(cnt, srank[slot[k]] - 1u);
+    __syncthreads();
+    {
+      constexpr int R = kLongDistinct / NT;
+      uint32_t c[R], tot = 0, all;
+#pragma unroll
+      for (int i = 0; i < R; i++) tot += c[i] = cnt[tid * R + i];
+      const uint32_t inc = lane_incl_sum(tot);
+      if (lane == 63) wsum[wv] = inc;
+      __syncthreads();
+      uint32_t base = words_before<NW>(wsum, wv, all) + inc - tot;
+#pragma unroll
+      for (int i = 0; i < R; i++) {
+        cnt[tid * R + i] = cur[tid * R + i] = base;
+        if (c[i]) atomicOr(&bitmap[base >> 5], 1u << (base & 31));
+        base += c[i];
+      }
+    }
+    // the slots from n to the end of its 64 (slot n itself at least) count as openings
+    if (tid == 0) {
+      const uint64_t up = ~0ull << (n & 63);
+      atomicOr(&bitmap[(n >> 6) * 2], n % 64 == 0 ? 1u : (uint32_t)up);
+      if (n % 64) atomicOr(&bitmap[(n >> 6) * 2 + 1], (uint32_t)(up >> 32));
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (uint32_t k = tid; k < n; k += NT) {
+      const uint32_t r = srank[slot[k]] - 1u;
+      const uint32_t at = count_in(cur, r);
+      grank[k] = (uint16_t)cnt[r];
+      gsa[at] = (uint16_t)k;
+      if (k == 0) s_zero = at;
+    }
+    __syncthreads();
+    load_lds(grank);
+  } else {
+    load_lds(gtxt);
+    h = min((uint32_t)(48 / tbits), kLongPack);
     auto key_of = [&](uint32_t j) {
       uint64_t key = 0;
 #pragma unroll 1
@@ -1343,14 +1473,14 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     }
     if (tid == 0 && n % 64 == 0) bitmap[n >> 5] = 1;
     __syncthreads();
-  }
-  uint16_t *const rank = reinterpret_cast<uint16_t *>(big);  // rank[j]: the first slot of j's group
 #pragma unroll 4
-  for (uint32_t k = tid; k < n; k += NT) {
-    uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
-    while (!w) w = bitmap[--x];  // slot 0 opens a group
-    rank[gsa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
+    for (uint32_t k = tid; k < n; k += NT) {
+      uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
+      while (!w) w = bitmap[--x];  // slot 0 opens a group
+      rank[gsa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
+    }
   }
+  if (tid == 0) s_nd = nd;  // (the rows are counted from there)
   uint32_t active;
   auto survey = [&] {
     if (tid == 0) s_active = 0;
