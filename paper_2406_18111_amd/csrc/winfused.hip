@@ -1610,30 +1610,36 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
   }
   stamp(2);
 
-  // ---- LCP: Kasai's walk as in k_window, over the token ranks
+  // ---- LCP: Kasai's walk as in k_window, over the token ranks; the next
+  // position's predecessor is read ahead (two dependent reads a position)
   load_lds(gtxt);
   {
     const uint32_t per = (n + NT - 1) / NT;
-    uint32_t l = 0;
+    const uint32_t x0 = min(tid * per, n), x1 = min(x0 + per, n);
+    auto rank_at = [=](uint32_t x) { return (uint32_t)grank[min(x, n - 1)]; };
+    auto before = [=](uint32_t r) { return (uint32_t)gsa[r ? r - 1 : 0]; };
+    uint32_t l = 0, r = rank_at(x0), rn = rank_at(x0 + 1), y = before(r), yn, rnn;
 #pragma unroll 1
-    for (uint32_t x = tid * per; x < tid * per + per && x < n; x++) {
-      const uint32_t r = grank[x];
+    for (uint32_t x = x0; x < x1; x++, r = rn, y = yn, rn = rnn) {
+      yn = before(rn);
+      rnn = rank_at(x + 2);
       if (r == 0) {
         l = 0;
         continue;
       }
-      const uint32_t y = gsa[r - 1], lim = n - (x > y ? x : y);
-      while (l + 8 <= lim) {
+      const uint32_t lim = n - (x > y ? x : y);
+      bool differ = false;
+      while (!differ && l + 8 <= lim) {
         uint64_t p0, p1, q0, q1;
         __builtin_memcpy(&p0, txt + x + l, 8);
         __builtin_memcpy(&q0, txt + y + l, 8);
         __builtin_memcpy(&p1, txt + x + l + 4, 8);
         __builtin_memcpy(&q1, txt + y + l + 4, 8);
         const uint64_t d0 = p0 ^ q0, d1 = p1 ^ q1;
-        if (d0 | d1) break;
-        l += 8;
+        differ = (d0 | d1) != 0;
+        l += d0 ? (uint32_t)__builtin_ctzll(d0) / 16 : d1 ? 4 + (uint32_t)__builtin_ctzll(d1) / 16 : 8;
       }
-      while (l < lim && txt[x + l] == txt[y + l]) l++;  // at most 7 equal ones
+      while (!differ && l < lim && txt[x + l] == txt[y + l]) l++;  // fewer than 8 are left
       glcp[r - 1] = (uint16_t)l;
       l = l ? l - 1 : 0;
     }
@@ -1660,14 +1666,21 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
   __syncthreads();
   uint32_t mine = 0;  // the wavefront's records, in suffix-array order from 2 * wbeg on
   {
-    uint32_t mx = 0, pairs = 0, skipped = 0;
+    uint32_t mx = 0, pairs = 0, skipped = 0, hist = 0;  // hist: lane r's for round r
+    // suffixes of 64 slots, read once and one step ahead; the neighbours' from the other lanes
+    uint32_t xs = gsa[min(wbeg + lane, n - 1)], wlast = gsa[wbeg ? min(wbeg, n) - 1 : 0], xn;
 #pragma unroll 1
-    for (uint32_t k0 = wbeg; k0 < wtop; k0 += 64) {  // scalar
+    for (uint32_t k0 = wbeg; k0 < wtop; k0 += 64, wlast = (uint32_t)__builtin_amdgcn_readlane((int)xs, 63), xs = xn) {  // scalar
       const uint32_t k = k0 + lane;
+      xn = gsa[min(k + 64, n - 1)];
+      uint32_t ys = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)xs, 0x130, 0xF, 0xF, false), ws = lane_prev(xs);
+      const uint32_t next = (uint32_t)__builtin_amdgcn_readlane((int)xn, 0);
+      if (lane == 63) ys = next;
+      if (lane == 0) ws = wlast;
       uint32_t l = 0, s1 = 0, s2 = 0, both = 0, pp = 0;
       bool rep = false;
       if (k < n) {
-        const uint32_t x = gsa[k], y = k + 1 < n ? gsa[k + 1] : x, p = lcp[k], w = k ? gsa[k - 1] : x;
+        const uint32_t x = xs, y = k + 1 < n ? ys : x, p = lcp[k], w = k ? ws : x;
         pp = k ? lcp[k - 1] : 0u;
         both = max(p, pp);
         const uint32_t lo = min(x, y), d = max(x, y) - lo;
@@ -1689,7 +1702,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
       for (int r = 0; r < kLongRounds; r++) {
         const uint64_t g = __ballot(both >> r);
         if (!g) break;  // scalar
-        if (lane == 0) atomicAdd(&s_hist[r], (uint32_t)__popcll(g));
+        hist += lane == (uint32_t)r ? (uint32_t)__popcll(g) : 0u;
       }
       pairs += (uint32_t)__popcll(__ballot(k < n && pp < 2));  // first of its two-token prefix
       const uint64_t m2 = __ballot(l != 0), m1 = __ballot(l != 0 && !rep);
@@ -1707,6 +1720,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     }
     mx = lane_max(mx);
     if (lane == 63 && mx) atomicMax(&s_max, mx);
+    if (hist) atomicAdd(&s_hist[lane], hist);  // lanes below kLongRounds
     if (lane == 0) {
       atomicAdd(&s_pairs, pairs);
       atomicAdd(&s_skip, skipped);
