@@ -709,13 +709,20 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
 static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off, uint32_t W, uint32_t min_len,
                         hipStream_t s, uint64_t total) {
   int L = std::min<int>(ctx->lanes, (int)(W / 2));
-  // a batch of short windows is one launch with a workgroup per window, which
-  // lanes have nothing to add to
+  // windows analysed by a workgroup each are a launch or two, which lanes have
+  // nothing to add to (4096 windows of 256 to 65536 tokens: 5.7 ms, on three lanes 6.4)
   uint64_t longest = 0;
   for (uint32_t w = 0; w < W; w++) longest = std::max<uint64_t>(longest, off[w + 1] - off[w]);
-  if (longest <= kFusedMax && ctx->win_greedy && ctx->ws.ktag == KT_NONE &&
-      (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx)))
+  Workspace &w0 = ctx->ws;
+  std::fill(w0.lane_end, w0.lane_end + 3, kNone);
+  if (L >= 2 && longest <= kFusedLongMax && ctx->win_greedy && w0.ktag == KT_NONE && w0.fail_after < 0 &&
+      (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx))) {
+    // (what is counted by lane still is)
+    std::vector<uint32_t> ends;
+    lane_groups(off, W, total, L, ends);
+    for (int g = 0; g < 3 && g + 1 < L; g++) w0.lane_end[g] = ends[g + 1];
     L = 1;
+  }
   if (ctx->budget && L >= 2) {
     // fewer lanes when their workspaces would not fit the budget; lane
     // workspaces left idle by the smaller count give their memory back
@@ -727,6 +734,7 @@ static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   }
   if (L >= 2) return batch_lanes(ctx, d_tok, off, W, min_len, s, total, L);
   const int rc = batch_single(ctx, d_tok, off, W, min_len, s, total);
+  std::fill(w0.lane_end, w0.lane_end + 3, kNone);
   ctx->louts.assign(1, {&ctx->ws, W, ctx->info.rows});
   return rc;
 }

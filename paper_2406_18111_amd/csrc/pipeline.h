@@ -20,7 +20,7 @@ constexpr int kSelFreeRounds = 12;
 enum Cnt {
   CNT_ND = 0, CNT_C, CNT_MAXL, CNT_M, CNT_NLIVE0, CNT_NLIVE1, CNT_UNDEC, CNT_A, CNT_NROWS,
   CNT_CSKIP,       // candidates not written because they repeat the previous pair's (counted in the total)
-  CNT_RANGE = 10,  // two 64-bit words, 8-byte aligned
+  CNT_RANGE = 10,  // two 64-bit words, 8-byte aligned (one-workgroup analyses: CNT_PFLAG by lane)
   CNT_AUX = 14,    // scratch count of a stage (tile counts, histogram size, runs)
   CNT_SNAPS = 15,  // 1 + last doubling round with a rank snapshot (0: none)
   CNT_NDSUM = 16,  // batches: distinct tokens summed over the windows ranked on their own
@@ -121,6 +121,7 @@ struct Workspace {
   int kev_n = 0;
   int sel_cap = kSelRoundCap;      // host-driven selection rounds before the sequential completion
   int sel_prefix = -1;             // exact prefix walk before the rounds: -1 automatic, 0 never, k > 0 k candidates
+  uint32_t lane_end[3] = {kNone, kNone, kNone};  // one-workgroup analyses: windows of what would be the first three lanes
   uint32_t pair_w = 0;             // windows of the run when it ranked their token pairs (else 0)
   int fail_after = -1;             // test hook: host syncs before one reports a device error (-1: never)
   bool fuse_one = false;           // a lone short window takes the one-workgroup analysis in run_pipeline too

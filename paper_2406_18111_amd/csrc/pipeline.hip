@@ -108,7 +108,7 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
          o_hrank = L.take((hcap + 1) * 4);
   size_t o_di = L.take(N_ * 4), o_ds = L.take(N_ * 4), o_dhi = L.take(N_ * 4), o_dlo = L.take(N_ * 4);
   size_t o_off = L.take((wantW + 1) * 8), o_wb = L.take(N_ * 4), o_we = L.take(N_ * 4), o_wid = L.take(N_ * 4);
-  size_t o_wr = L.take((wantW + 1) * 4), o_ord = L.take((wantW + 1) * 4);
+  size_t o_wr = L.take((wantW + 1) * 4), o_ord = L.take((wantW + 4) * 4);
   size_t o_wf = L.take(wantW + 1);
   size_t o_rank = L.take(N_ * 4), o_snap = L.take((size_t)nsnap * N_ * 4), o_sa = L.take(N_ * 4);
   size_t o_lcp = L.take(N_ * 4);
@@ -199,9 +199,9 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
   hsel = hcnt + (o_sc - o_cnt) / 4;
   hflag = hcnt + mirror / 4;
   hctr = reinterpret_cast<SortCounters *>(reinterpret_cast<char *>(hcnt) + mirror + 64);
-  APO_HIP_TRY(hipHostMalloc((void **)&hoff, (size_t)(wantW + 1) * 16, hipHostMallocDefault));
+  APO_HIP_TRY(hipHostMalloc((void **)&hoff, (size_t)(wantW + 2) * 16, hipHostMallocDefault));
   horder = reinterpret_cast<uint32_t *>(hoff + wantW + 1);
-  hwin = horder + wantW + 1;
+  hwin = horder + wantW + 4;
   for (auto &ev_ : ev) APO_HIP_TRY(hipEventCreate(&ev_));
   for (auto &ev_ : kev) APO_HIP_TRY(hipEventCreate(&ev_));
   APO_HIP_TRY(hipMemset(dcnt, 0, CNT_COUNT * 4));
@@ -302,6 +302,15 @@ static void fill_info(Workspace &w, uint64_t N, RunInfo &info) {
   info.n = N;
   info.sigma = w.hcnt[CNT_ND] + w.hcnt[CNT_NDSUM];  // shared table + windows ranked on their own
   info.pair_windows = (w.pair_w && w.hcnt[CNT_PFLAG] == 0) ? w.pair_w : 0;
+  if (w.pair_w && w.hcnt[CNT_FUSED]) {  // lane by lane
+    info.pair_windows = 0;
+    uint32_t beg = 0;
+    for (int g = 0; g < 4; g++) {
+      const uint32_t end = g < 3 ? std::min(w.lane_end[g], w.pair_w) : w.pair_w;
+      if (end - beg >= 2 && w.hcnt[CNT_RANGE + g] == 0) info.pair_windows += end - beg;
+      beg = end;
+    }
+  }
   info.cands = w.hcnt[CNT_C] + w.hcnt[CNT_CSKIP];
   info.maxl = w.hcnt[CNT_MAXL];
   info.cands_dedup = w.hcnt[CNT_M];
@@ -331,8 +340,11 @@ int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t 
   };
   for (uint32_t k = 0; k < W; k++) cnt[bucket(k) + 1]++;
   for (int b = 1; b < 66; b++) cnt[b] += cnt[b - 1];
+  const uint32_t longer = cnt[64 - bit_length_u64(kFusedMidMax - 1)];
   for (uint32_t k = 0; k < W; k++) w.horder[cnt[bucket(k)]++] = k;
-  APO_HIP_TRY(hipMemcpyAsync(w.d_order, w.horder, W * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+  w.horder[W] = longer;  // windows of more than kFusedMidMax tokens: the first of the order
+  for (int g = 0; g < 3; g++) w.horder[W + 1 + g] = w.lane_end[g];
+  APO_HIP_TRY(hipMemcpyAsync(w.d_order, w.horder, (W + 4) * sizeof(uint32_t), hipMemcpyHostToDevice, s));
   return 0;
 }
 

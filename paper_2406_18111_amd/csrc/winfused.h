@@ -11,6 +11,7 @@ constexpr uint32_t kFusedMax = 8192;
 // Longest window one workgroup takes with its arrays in the workspace (positions
 // and ranks in 16 bits, one array of them in LDS at a time).
 constexpr uint32_t kFusedLongMax = 65536;
+constexpr uint32_t kFusedMidMax = 32768;  // and longest of a large batch that share a compute unit in twos
 
 // What one window's analysis reports to the host (pinned memory).
 struct FusedInfo {

@@ -370,7 +370,8 @@ struct FusedArgs {
   const void *tok;
   int bits;
   const uint64_t *off;     // batch: window offsets; null: one window of n tokens
-  const uint32_t *order;   // batch: block b takes window order[b]
+  const uint32_t *order;   // batch: block b takes window order[b] (what is behind the windows': upload_windows)
+  uint32_t windows;        // batch
   uint32_t n, min_len;
   Row *rows;               // one window: final; batch: window w's rows start at off[w] / min_len
   Occ *occ;
@@ -410,7 +411,11 @@ __device__ __forceinline__ void report(const FusedArgs &a, uint32_t win, const R
   atomicAdd(&a.dcnt[CNT_A], r.accepted);
   atomicAdd(&a.dcnt[CNT_NROWS], r.rows);
   // past the bounds of the stage-by-stage batch's per-window ranks and pair ranks
-  if (r.own > kOwnRanks || r.pairs > kOwnPairs) atomicAdd(&a.dcnt[CNT_PFLAG], 1u);
+  if (r.own > kOwnRanks || r.pairs > kOwnPairs) {
+    uint32_t g = 0;  // the window's lane
+    while (g < 3 && win >= a.order[a.windows + 1 + g]) g++;
+    atomicAdd(&a.dcnt[CNT_RANGE + g], 1u);
+  }
   for (uint32_t k = 0; k < r.nhist; k++)
     if (hist[k]) atomicAdd(&a.rhist[4 * k], hist[k]);
   for (int k = 0; k < kStages; k++) atomicMax(&a.dcnt[CNT_STAGE + k], (uint32_t)(stamp[k + 1] - stamp[k]));
@@ -1053,8 +1058,6 @@ __device__ __forceinline__ void window_short(const FusedArgs &a, ShortLds<NT, IP
 // L2 holds.
 constexpr int kLongNT = 1024, kLongNW = kLongNT / 64;
 constexpr int kByte = 256;                    // radix digits of 8 bits
-constexpr uint32_t kLongSlots = 16384;        // hash table of the distinct tokens
-constexpr uint32_t kLongDistinct = 8192;      // most distinct tokens (the largest value aside)
 constexpr uint64_t kFree = ~0ull;
 
 struct LongArgs {
@@ -1062,16 +1065,18 @@ struct LongArgs {
   uint16_t *txt, *sa, *rank, *lcp;  // two bytes per token, four bytes apart per window: base + 2 * offset
   uint64_t *e0, *e1;                // two words per token
   uint64_t *flags;                  // one word per token (n / 32 of them used)
+  uint8_t *again;                   // batches in two launches (else null): the windows that the first one left
 };
 
 // Rank of each lane among the items of its digit d < 256 that the wavefront has
 // met, `my` counting them (in: the lanes that hold an item).
-__device__ __forceinline__ uint32_t rank_lanes(uint32_t *my, uint32_t d, uint64_t in) {
+template <class Cnt>
+__device__ __forceinline__ uint32_t rank_lanes(Cnt *my, uint32_t d, uint64_t in) {
   const uint64_t same = equal_lanes<8>(d, in);
   const uint32_t before = lanes_below(same);
   const uint32_t prev = my[d];
   wave_order();  // every lane has read before the first one of each digit writes
-  if (before == 0 && ((in >> (threadIdx.x & 63)) & 1ull)) my[d] = prev + (uint32_t)__popcll(same);
+  if (before == 0 && ((in >> (threadIdx.x & 63)) & 1ull)) my[d] = (Cnt)(prev + (uint32_t)__popcll(same));
   wave_order();
   return prev + before;
 }
@@ -1081,8 +1086,8 @@ __device__ __forceinline__ uint32_t rank_lanes(uint32_t *my, uint32_t d, uint64_
 // wavefront's row of ctr): park(k, rank).  One LDS atomic per item took longer
 // than this, 22 us against 10 for 30011 items, since most lanes meet on a few
 // digits of a repetitive window.
-template <class Get, class Digit, class Park>
-__device__ __forceinline__ void byte_rank(uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit, Park park) {
+template <class Cnt, class Get, class Digit, class Park>
+__device__ __forceinline__ void byte_rank(Cnt *my, uint32_t beg, uint32_t end, Get get, Digit digit, Park park) {
   const uint32_t lane = threadIdx.x & 63;
 #pragma unroll 1
   for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
@@ -1100,7 +1105,8 @@ __device__ __forceinline__ void byte_rank(uint32_t *my, uint32_t beg, uint32_t e
 }
 
 // Rows of counts into first places: digit by digit, wavefront by wavefront.
-__device__ __forceinline__ void byte_scan(uint32_t *ctr, uint32_t *wsum) {
+template <class Cnt>
+__device__ __forceinline__ void byte_scan(Cnt *ctr, uint32_t *wsum) {
   const uint32_t tid = threadIdx.x, wv = wave_id();
   __syncthreads();
   uint32_t tot = 0, inc = 0;
@@ -1117,7 +1123,7 @@ __device__ __forceinline__ void byte_scan(uint32_t *ctr, uint32_t *wsum) {
 #pragma unroll 4
     for (int w = 0; w < kLongNW; w++) {
       const uint32_t c = ctr[w * kByte + tid];
-      ctr[w * kByte + tid] = base;
+      ctr[w * kByte + tid] = (Cnt)base;
       base += c;
     }
   }
@@ -1125,8 +1131,8 @@ __device__ __forceinline__ void byte_scan(uint32_t *ctr, uint32_t *wsum) {
 }
 
 // Moves a wavefront's items to their places: put(place, item).
-template <class Get, class Digit, class Parked, class Put>
-__device__ __forceinline__ void byte_move(const uint32_t *my, uint32_t beg, uint32_t end, Get get, Digit digit,
+template <class Cnt, class Get, class Digit, class Parked, class Put>
+__device__ __forceinline__ void byte_move(const Cnt *my, uint32_t beg, uint32_t end, Get get, Digit digit,
                                           Parked parked, Put put) {
   const uint32_t lane = threadIdx.x & 63;
 #pragma unroll 1
@@ -1159,19 +1165,26 @@ __device__ __forceinline__ uint32_t count_in(uint32_t *c, uint32_t r) {
 // LDS of a longer window.  big holds, one after the other: the distinct tokens'
 // table, their sorted list (64 KB) and ranks by slot; token ranks; suffix ranks;
 // token ranks; LCP values; the survivors of a chunk of candidates.
+template <uint32_t CAP>
 struct LongLds {
-  alignas(16) unsigned char big[kFusedLongMax * 2];
-  alignas(16) uint32_t ctr[kLongNW * kByte];                // radix counters; LCP minima of 8; run openings
-  alignas(16) uint32_t bitmap[kFusedLongMax / 32 + 2];      // as in ShortLds; LCP minima of 64 and 512
+  static constexpr uint32_t kSlots = CAP / 4;  // hash table of the distinct tokens
+  static constexpr uint32_t kDistinct = CAP == kFusedLongMax ? 8192 : CAP / 16 * 3;  // most of them (the largest value aside)
+  // a radix counter counts 2 * (CAP - 1) records at most
+  using Cnt = std::conditional_t<(CAP > 32768), uint32_t, uint16_t>;
+  alignas(16) unsigned char big[CAP * 2];
+  alignas(16) Cnt ctr[kLongNW * kByte];           // radix counters; LCP minima of 8; run openings
+  alignas(16) uint32_t bitmap[CAP / 32 + 2];      // as in ShortLds; LCP minima of 64 and 512
   uint32_t wsum[kLongNW], wsum2[kLongNW];
   uint32_t s_nd, s_top, s_over, s_zero, s_active, s_max, s_skip, s_c, s_acc, s_dup, s_pairs;
   uint32_t s_hist[kLongRounds];
   uint64_t s_stamp[kStages + 1];
+  unsigned long long s_differ;
 };
 
-__device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint32_t win, uint64_t tb, uint32_t n) {
+template <uint32_t CAP, bool FIRST>
+__device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L, uint32_t win, uint64_t tb, uint32_t n) {
   constexpr int NT = kLongNT, NW = kLongNW;
-  constexpr uint32_t CAP = kFusedLongMax;
+  constexpr uint32_t kSlots = LongLds<CAP>::kSlots, kDistinct = LongLds<CAP>::kDistinct;
   const FusedArgs &a = la.f;
   auto &big = L.big;
   auto &ctr = L.ctr;
@@ -1193,14 +1206,15 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
   stamp(0);
   // a wavefront's share of m items, in order
   auto seg = [](uint32_t m) { return ((m + 64 * kLongNW - 1) / (64 * kLongNW)) * 64; };
-  uint32_t *const my = ctr + wv * kByte;
+  typename LongLds<CAP>::Cnt *const my = ctr + wv * kByte;
   // ranks parked between the two halves of a radix pass (the LCP values come
   // later, and are in LDS when the candidates are sorted)
   uint16_t *const rel = glcp;
   auto park = [=](uint32_t k, uint32_t r) { rel[k] = (uint16_t)r; };
   auto parked = [=](uint32_t k) { return (uint32_t)rel[k]; };
   auto clear_row = [&] {
-    *reinterpret_cast<uint4 *>(my + 4 * lane) = make_uint4(0, 0, 0, 0);
+    if constexpr (sizeof(*my) == 4) *reinterpret_cast<uint4 *>(my + 4 * lane) = make_uint4(0, 0, 0, 0);
+    else *reinterpret_cast<uint2 *>(my + 4 * lane) = make_uint2(0, 0);
     wave_order();
   };
 
@@ -1211,13 +1225,13 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
   uint16_t *const dslot = reinterpret_cast<uint16_t *>(e1 + n);  // of every distinct word
   auto clear_table = [&] {
     if (tid == 0) s_nd = s_over = 0;
-    for (uint32_t k = 2 * tid; k < kLongSlots; k += 2 * NT) *reinterpret_cast<ulonglong2 *>(tab + k) = make_ulonglong2(kFree, kFree);
+    for (uint32_t k = 2 * tid; k < kSlots; k += 2 * NT) *reinterpret_cast<ulonglong2 *>(tab + k) = make_ulonglong2(kFree, kFree);
     __syncthreads();
   };
   auto insert = [&](uint64_t key) -> uint32_t {
-    uint32_t at = (uint32_t)(mix64(key) >> 40) & (kLongSlots - 1);
+    uint32_t at = (uint32_t)(mix64(key) >> 40) & (kSlots - 1);
     for (int probe = 0;; probe++) {
-      if (probe == (int)kLongSlots) {  // full (only past the limit)
+      if (probe == (int)kSlots) {  // full (only past the limit)
         s_over = 1;
         break;
       }
@@ -1226,7 +1240,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
         cur = atomicCAS(&tab[at], (unsigned long long)kFree, (unsigned long long)key);
         if (cur == kFree) {
           const uint32_t q = atomicAdd(&s_nd, 1u);
-          if (q < kLongDistinct) {
+          if (q < kDistinct) {
             e1[q] = key;
             dslot[q] = (uint16_t)at;
           } else {
@@ -1236,12 +1250,12 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
         }
       }
       if (cur == key) break;
-      at = (at + 1) & (kLongSlots - 1);
+      at = (at + 1) & (kSlots - 1);
     }
     return at;
   };
   // Sorts the table's d words; srank: their ranks from 1, by slot.
-  uint16_t *const srank = reinterpret_cast<uint16_t *>(big + kLongDistinct * 8);
+  uint16_t *const srank = reinterpret_cast<uint16_t *>(big + kDistinct * 8);
   auto rank_by = [&](auto per, uint32_t d) {
     constexpr int R = decltype(per)::value;
     uint64_t *sorted = reinterpret_cast<uint64_t *>(big);
@@ -1271,7 +1285,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     if (d <= NT) rank_by(std::integral_constant<int, 1>{}, d);
     else if (d <= 2 * NT) rank_by(std::integral_constant<int, 2>{}, d);
     else if (d <= 4 * NT) rank_by(std::integral_constant<int, 4>{}, d);
-    else rank_by(std::integral_constant<int, kLongDistinct / NT>{}, d);
+    else rank_by(std::integral_constant<int, 8>{}, d);
   };
 
   // ---- token ranks: the distinct values through the table (the largest value
@@ -1292,14 +1306,81 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
 #pragma unroll
       for (int u = 0; u < 8; u++) {
         if (k0 + u * NT >= n) break;
-        uint32_t at = kLongSlots;
+        uint32_t at = kSlots;
         if (v[u] == kFree) s_top = 1;
         else at = insert(v[u]);
         slot[k0 + u * NT] = (uint16_t)at;
       }
     }
     __syncthreads();
-    if (s_over) {  // uniform: left to the stage-by-stage analysis
+    if constexpr (FIRST) {
+      if (tid == 0) la.again[win] = s_over ? 1 : 0;
+      if (s_over) return;  // uniform: left to the larger table
+    }
+  }
+  uint32_t nd, D;
+  const bool by_table = !s_over;  // uniform
+  if (by_table) {
+    nd = s_nd;
+    D = nd + s_top;
+    rank_table(nd);
+#pragma unroll 4
+    for (uint32_t k = tid; k < n; k += NT) {
+      const uint32_t at = slot[k];
+      gtxt[k] = (uint16_t)(at == kSlots ? D : srank[at]);
+    }
+    __syncthreads();
+  } else {
+    // More distinct tokens than the table takes: positions sorted by token, a
+    // radix pass for every byte in which the tokens differ, ranks counted over
+    // the sorted positions.  (65536 distinct ones, whose ranks would not fit 16
+    // bits, are left to the stage-by-stage analysis.)
+    auto token = [=](uint32_t j) {
+      return a.bits == 64 ? static_cast<const uint64_t *>(a.tok)[tb + j] : (uint64_t) static_cast<const uint32_t *>(a.tok)[tb + j];
+    };
+    uint32_t *src = reinterpret_cast<uint32_t *>(e0), *dst = reinterpret_cast<uint32_t *>(e1);
+    const uint32_t kbeg = min(wv * seg(n), n), ktop = min(kbeg + seg(n), n);
+    uint64_t differ = 0;
+    for (uint32_t k = kbeg + lane; k < ktop; k += 64) {
+      differ |= token(k) ^ token(0);
+      src[k] = k;
+    }
+    if (tid == 0) L.s_differ = 0;
+    __syncthreads();
+    if (differ) atomicOr(&L.s_differ, (unsigned long long)differ);
+    __syncthreads();
+    differ = L.s_differ;
+#pragma unroll 1
+    for (int sh = 0; sh < a.bits; sh += 8) {
+      if (!((differ >> sh) & 255u)) continue;  // uniform
+      const uint32_t *from = src;
+      uint32_t *to = dst;
+      auto get = [=](uint32_t k) {
+        const uint32_t j = from[k];
+        return j | ((uint32_t)(token(j) >> sh) & 255u) << 16;
+      };
+      auto dig = [](uint32_t v) { return v >> 16; };
+      clear_row();
+      byte_rank(my, kbeg, ktop, get, dig, park);
+      byte_scan(ctr, wsum);
+      byte_move(my, kbeg, ktop, get, dig, parked, [=](uint32_t at, uint32_t v) { to[at] = v & 0xFFFFu; });
+      __syncthreads();
+      dst = src;
+      src = to;
+    }
+    uint32_t opened = 0;
+#pragma unroll 1
+    for (uint32_t k0 = kbeg; k0 < ktop; k0 += 64) {  // scalar
+      const uint32_t k = min(k0 + lane, n - 1);
+      const uint64_t open = __ballot(k0 + lane < ktop && (k == 0 || token(src[k]) != token(src[k - 1])));
+      if (lane == 0) fl[k0 >> 6] = open;
+      opened += (uint32_t)__popcll(open);
+    }
+    if (lane == 0) wsum[wv] = opened;
+    __syncthreads();
+    uint32_t at = words_before<NW>(wsum, wv, D);
+    nd = D;
+    if (D > 65535) {  // uniform
       if (tid == 0) {
         if (a.info) a.info->over = 1;
         else {
@@ -1309,15 +1390,14 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
       }
       return;
     }
+#pragma unroll 1
+    for (uint32_t k0 = kbeg; k0 < ktop; k0 += 64) {  // scalar
+      const uint64_t open = fl[k0 >> 6];
+      if (k0 + lane < ktop) gtxt[src[k0 + lane]] = (uint16_t)(at + (uint32_t)__popcll(open & (below | (1ull << lane))));
+      at += (uint32_t)__popcll(open);
+    }
+    __syncthreads();
   }
-  const uint32_t nd = s_nd, top = s_top, D = nd + top;
-  rank_table(nd);
-#pragma unroll 4
-  for (uint32_t k = tid; k < n; k += NT) {
-    const uint32_t at = slot[k];
-    gtxt[k] = (uint16_t)(at == kLongSlots ? D : srank[at]);
-  }
-  __syncthreads();
   auto load_lds = [&](const uint16_t *from) {  // n words, four a lane (windows start 4-byte aligned: two 4-byte loads)
     uint32_t *to = reinterpret_cast<uint32_t *>(big);
     const uint32_t *g = reinterpret_cast<const uint32_t *>(from);
@@ -1365,14 +1445,14 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
       }
       __syncthreads();
       const uint32_t now = s_nd;
-      if (now > (t0 ? kLongDistinct : NT + NT / 4)) {
+      if (now > (t0 ? kDistinct : NT + NT / 4)) {
         named = false;
         break;
       }
       if (t0 == 2 * NT && !lowered) {
         const uint64_t end = now + (uint64_t)(now - seen) * (n - t1) / (t1 - t0);
-        if (end > kLongDistinct) {
-          lower = (uint32_t)(h * (uint64_t)(kLongDistinct - kLongDistinct / 8) / end);
+        if (end > kDistinct) {
+          lower = (uint32_t)(h * (uint64_t)(kDistinct - kDistinct / 8) / end);
           named = lower >= 2;
           break;
         }
@@ -1390,16 +1470,16 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
     const uint32_t d = s_nd;
     rank_table(d);
     uint32_t *const cnt = reinterpret_cast<uint32_t *>(big);  // the sorted list is done with
-    uint32_t *const cur = reinterpret_cast<uint32_t *>(big + kLongDistinct * 8 + kLongSlots * 2);
-    static_assert(kLongDistinct * 12 + kLongSlots * 2 <= sizeof(L.big), "list or counts, ranks, cursors");
-    for (uint32_t q = tid; q < kLongDistinct; q += NT) cnt[q] = 0;
+    uint32_t *const cur = cnt + kDistinct;
+    static_assert(kDistinct * 8 + kSlots * 2 <= sizeof(L.big), "sorted list, or counts and cursors; ranks");
+    for (uint32_t q = tid; q < kDistinct; q += NT) cnt[q] = 0;
     for (uint32_t x = tid; x <= n / 32 + 1; x += NT) bitmap[x] = 0;
     __syncthreads();
 #pragma unroll 4
     for (uint32_t k = tid; k < n; k += NT) (void)count_in(cnt, srank[slot[k]] - 1u);
     __syncthreads();
     {
-      constexpr int R = kLongDistinct / NT;
+      constexpr int R = kDistinct / NT;
       uint32_t c[R], tot = 0, all;
 #pragma unroll
       for (int i = 0; i < R; i++) tot += c[i] = cnt[tid * R + i];
@@ -1760,19 +1840,21 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
       pass(sh ? cbeg : 2 * wbeg, sh ? ctop : 2 * wbeg + mine,
            [=](uint64_t v) { return ((maxl - (uint32_t)(v >> 32)) >> sh) & 255u; });
     // a bitmap of the records that open a run
+    uint32_t *const runs = reinterpret_cast<uint32_t *>(ctr);
+    static_assert(CAP / 16 * 4 <= sizeof(ctr), "two records a token");
     if (tid == 0) s_active = 0;
 #pragma unroll 1
     for (uint32_t q0 = cbeg; q0 < ctop; q0 += 64) {  // scalar
       const uint32_t k = min(q0 + lane, C - 1);
       const uint64_t open = __ballot(q0 + lane == 0 || q0 + lane >= C || (src[k] >> 16) != (src[k ? k - 1 : 0] >> 16));
       if (lane == 0) {
-        ctr[q0 >> 5] = (uint32_t)open;
-        ctr[(q0 >> 5) + 1] = (uint32_t)(open >> 32);
+        runs[q0 >> 5] = (uint32_t)open;
+        runs[(q0 >> 5) + 1] = (uint32_t)(open >> 32);
       }
     }
     __syncthreads();
     for (uint32_t x = tid; 32 * x + 128 <= C; x += NT)
-      if (!(ctr[x] | ctr[x + 1] | ctr[x + 2] | ctr[x + 3])) s_active = 1;  // 128 records without an opening
+      if (!(runs[x] | runs[x + 1] | runs[x + 2] | runs[x + 3])) s_active = 1;  // 128 records without an opening
     __syncthreads();
     if (s_active) {  // uniform
       __syncthreads();  // ... before the counters are used again
@@ -1790,12 +1872,12 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds &L, uint
       for (uint32_t k = cbeg + lane; k < ctop; k += 64) {
         const uint64_t v = from[k];
         const uint32_t s = (uint32_t)v & 0xFFFFu;
-        uint32_t x = k >> 5, w = ctr[x] & ((2u << (k & 31)) - 1u);
-        while (!w) w = ctr[--x];  // record 0 opens a run
+        uint32_t x = k >> 5, w = runs[x] & ((2u << (k & 31)) - 1u);
+        while (!w) w = runs[--x];  // record 0 opens a run
         const uint32_t b = 32 * x + 31u - (uint32_t)__clz((int)w);
         x = k >> 5;
-        w = ctr[x] & ~((2u << (k & 31)) - 1u);
-        while (!w && 32 * (x + 1) < C) w = ctr[++x];
+        w = runs[x] & ~((2u << (k & 31)) - 1u);
+        while (!w && 32 * (x + 1) < C) w = runs[++x];
         const uint32_t e = w ? min(32 * x + (uint32_t)__ffs((int)w) - 1u, C) : C;
         uint32_t at = b;
         if (e - b > 1)
@@ -1942,13 +2024,51 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
 __global__ __launch_bounds__(kLongNT) void k_window_any(LongArgs la) {
   __shared__ union Lds {
     ShortLds<kLongNT, kFusedMax / kLongNT> s;
-    LongLds l;
+    LongLds<kFusedLongMax> l;
   } L;
   uint32_t win;
   uint64_t tb;
   const uint32_t n = window_of(la.f, win, tb);
-  if (n > kFusedMax) window_long(la, L.l, win, tb, n);  // uniform
+  if (n > kFusedMax) window_long<kFusedLongMax, false>(la, L.l, win, tb, n);  // uniform
   else if (n >= 2) window_short<kLongNT, kFusedMax / kLongNT>(la.f, L.s, win, tb, n);
+}
+
+// Batches of more windows than compute units, in two launches.  These analyses
+// wait for memory, LDS and barriers 60 % of the time and issue vector
+// instructions a third of it, so the windows of up to kFusedMidMax tokens run
+// two to a compute unit, with half the LDS and the registers of 64 wavefronts;
+// the longer ones, and those with more distinct tokens than half the table
+// takes, by themselves.
+__global__ __launch_bounds__(kLongNT, 8) void k_window_mid(LongArgs la) {
+  __shared__ union Lds {
+    ShortLds<kLongNT, 4> s;
+    LongLds<kFusedMidMax> l;
+  } L;
+  static_assert(sizeof(Lds) <= 80 * 1024, "two workgroups in 160 KB");
+  const uint32_t at = blockIdx.x + la.f.order[la.f.windows];  // behind the longer windows
+  if (at >= la.f.windows) return;
+  const uint32_t win = la.f.order[at];
+  const uint64_t tb = la.f.off[win] - la.f.off[0];
+  const uint32_t n = (uint32_t)(la.f.off[win + 1] - la.f.off[win]);
+  if (n > 4 * kLongNT) {  // uniform
+    window_long<kFusedMidMax, true>(la, L.l, win, tb, n);
+    return;
+  }
+  if (threadIdx.x == 0) {
+    la.again[win] = 0;
+    if (n < 2) {
+      la.f.win_rows[win] = 0;
+      atomicAdd(&la.f.dcnt[CNT_NDSUM], n);
+    }
+  }
+  if (n >= 2) window_short<kLongNT, 4>(la.f, L.s, win, tb, n);
+}
+__global__ __launch_bounds__(kLongNT) void k_window_rest(LongArgs la) {
+  __shared__ LongLds<kFusedLongMax> L;
+  const uint32_t win = la.f.order[blockIdx.x];
+  if (blockIdx.x >= la.f.order[la.f.windows] && !la.again[win]) return;  // uniform
+  const uint64_t tb = la.f.off[win] - la.f.off[0];
+  window_long<kFusedLongMax, false>(la, L, win, tb, (uint32_t)(la.f.off[win + 1] - la.f.off[win]));
 }
 
 // Packs the windows' rows, each window's at row off[w] / min_len of `src`,
@@ -1975,7 +2095,10 @@ void launch(const LongArgs &la, uint32_t blocks, uint64_t longest, hipStream_t s
   else if (longest <= 2048) hipLaunchKernelGGL((k_window<512, 4>), dim3(blocks), dim3(512), 0, s, a);
   else if (longest <= 4096) hipLaunchKernelGGL((k_window<1024, 4>), dim3(blocks), dim3(1024), 0, s, a);
   else if (longest <= kFusedMax) hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL(k_window_any, dim3(blocks), dim3(kLongNT), 0, s, la);
+  else if (la.again) {
+    hipLaunchKernelGGL(k_window_mid, dim3(blocks), dim3(kLongNT), 0, s, la);
+    hipLaunchKernelGGL(k_window_rest, dim3(blocks), dim3(kLongNT), 0, s, la);
+  } else hipLaunchKernelGGL(k_window_any, dim3(blocks), dim3(kLongNT), 0, s, la);
 }
 
 LongArgs args_of(const Workspace &w) {
@@ -2040,12 +2163,14 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, ui
   a.bits = 64;
   a.off = w.d_off;
   a.order = w.d_order;
+  a.windows = W;
   a.min_len = min_len;
   a.rows = static_cast<Row *>(w.occ);  // a batch reports no occurrences: their array stages the rows
   a.row_cap = kNone;
   a.dcnt = w.dcnt;
   a.rhist = w.rhist;
   a.win_rows = w.win_rows;
+  if (W > 256) la.again = w.wflag;
   launch(la, W, longest, s);
   hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, W,
                      min_len, static_cast<Row *>(w.rows));
