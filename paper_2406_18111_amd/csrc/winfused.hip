@@ -1320,6 +1320,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   }
   uint32_t nd, D;
   const bool by_table = !s_over;  // uniform
+  bool by_first = false;          // uniform: sorted by one token already
   if (by_table) {
     nd = s_nd;
     D = nd + s_top;
@@ -1332,9 +1333,10 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     __syncthreads();
   } else {
     // More distinct tokens than the table takes: positions sorted by token, a
-    // radix pass for every byte in which the tokens differ, ranks counted over
-    // the sorted positions.  (65536 distinct ones, whose ranks would not fit 16
-    // bits, are left to the stage-by-stage analysis.)
+    // radix pass for each of the four highest bytes in which the tokens differ
+    // (then for all of them, should that not have put them in order), ranks
+    // counted over the sorted positions.  (65536 distinct ones, whose ranks would
+    // not fit 16 bits, are left to the stage-by-stage analysis.)
     auto token = [=](uint32_t j) {
       return a.bits == 64 ? static_cast<const uint64_t *>(a.tok)[tb + j] : (uint64_t) static_cast<const uint32_t *>(a.tok)[tb + j];
     };
@@ -1350,34 +1352,47 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     if (differ) atomicOr(&L.s_differ, (unsigned long long)differ);
     __syncthreads();
     differ = L.s_differ;
+    int low = 0;  // the lowest byte sorted by
+    for (int sh = a.bits - 8, many = 0; sh >= 0; sh -= 8)
+      if ((differ >> sh) & 255u)
+        if (++many == 4) low = sh;
+    uint32_t opened;
+    for (;;) {  // uniform; twice at most
 #pragma unroll 1
-    for (int sh = 0; sh < a.bits; sh += 8) {
-      if (!((differ >> sh) & 255u)) continue;  // uniform
-      const uint32_t *from = src;
-      uint32_t *to = dst;
-      auto get = [=](uint32_t k) {
-        const uint32_t j = from[k];
-        return j | ((uint32_t)(token(j) >> sh) & 255u) << 16;
-      };
-      auto dig = [](uint32_t v) { return v >> 16; };
-      clear_row();
-      byte_rank(my, kbeg, ktop, get, dig, park);
-      byte_scan(ctr, wsum);
-      byte_move(my, kbeg, ktop, get, dig, parked, [=](uint32_t at, uint32_t v) { to[at] = v & 0xFFFFu; });
+      for (int sh = low; sh < a.bits; sh += 8) {
+        if (!((differ >> sh) & 255u)) continue;  // uniform
+        const uint32_t *from = src;
+        uint32_t *to = dst;
+        auto get = [=](uint32_t k) {
+          const uint32_t j = from[k];
+          return j | ((uint32_t)(token(j) >> sh) & 255u) << 16;
+        };
+        auto dig = [](uint32_t v) { return v >> 16; };
+        clear_row();
+        byte_rank(my, kbeg, ktop, get, dig, park);
+        byte_scan(ctr, wsum);
+        byte_move(my, kbeg, ktop, get, dig, parked, [=](uint32_t at, uint32_t v) { to[at] = v & 0xFFFFu; });
+        __syncthreads();
+        dst = src;
+        src = to;
+      }
+      if (tid == 0) s_active = 0;
       __syncthreads();
-      dst = src;
-      src = to;
-    }
-    uint32_t opened = 0;
+      opened = 0;
 #pragma unroll 1
-    for (uint32_t k0 = kbeg; k0 < ktop; k0 += 64) {  // scalar
-      const uint32_t k = min(k0 + lane, n - 1);
-      const uint64_t open = __ballot(k0 + lane < ktop && (k == 0 || token(src[k]) != token(src[k - 1])));
-      if (lane == 0) fl[k0 >> 6] = open;
-      opened += (uint32_t)__popcll(open);
+      for (uint32_t k0 = kbeg; k0 < ktop; k0 += 64) {  // scalar
+        const uint32_t k = min(k0 + lane, n - 1);
+        const uint64_t t = token(src[k]), pt = token(src[k ? k - 1 : 0]);
+        if (pt > t) s_active = 1;
+        const uint64_t open = __ballot(k0 + lane < ktop && (k == 0 || pt != t));
+        if (lane == 0) fl[k0 >> 6] = open;
+        opened += (uint32_t)__popcll(open);
+      }
+      if (lane == 0) wsum[wv] = opened;
+      __syncthreads();
+      if (!s_active || low == 0) break;  // uniform
+      low = 0;
     }
-    if (lane == 0) wsum[wv] = opened;
-    __syncthreads();
     uint32_t at = words_before<NW>(wsum, wv, D);
     nd = D;
     if (D > 65535) {  // uniform
@@ -1390,12 +1405,27 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
       }
       return;
     }
+    // mostly distinct ones: the positions are as good as sorted, groups of one token in them
+    by_first = 2 * D >= n;
 #pragma unroll 1
     for (uint32_t k0 = kbeg; k0 < ktop; k0 += 64) {  // scalar
       const uint64_t open = fl[k0 >> 6];
-      if (k0 + lane < ktop) gtxt[src[k0 + lane]] = (uint16_t)(at + (uint32_t)__popcll(open & (below | (1ull << lane))));
+      const uint32_t j = src[min(k0 + lane, n - 1)];
+      if (k0 + lane < ktop) {
+        gtxt[j] = (uint16_t)(at + (uint32_t)__popcll(open & (below | (1ull << lane))));
+        if (by_first) {
+          gsa[k0 + lane] = (uint16_t)j;
+          if (j == 0) s_zero = k0 + lane;
+        }
+      }
       at += (uint32_t)__popcll(open);
+      if (lane == 0) {
+        const uint64_t hd = open | ~first_lanes(n - k0);  // as below
+        bitmap[k0 >> 5] = (uint32_t)hd;
+        bitmap[(k0 >> 5) + 1] = (uint32_t)(hd >> 32);
+      }
     }
+    if (tid == 0 && n % 64 == 0) bitmap[n >> 5] = 1;
     __syncthreads();
   }
   auto load_lds = [&](const uint16_t *from) {  // n words, four a lane (windows start 4-byte aligned: two 4-byte loads)
@@ -1422,7 +1452,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   const int tbits = bits_of(D);
   uint32_t h = min((uint32_t)(63 / tbits), kLongPack);
   const uint32_t wbeg = min(wv * seg(n), n), wtop = min(wbeg + seg(n), n);  // the wavefront's tokens and slots
-  bool named = h >= 2 && min(48 / tbits, (int)kLongPack) * tbits > 24;
+  bool named = !by_first && h >= 2 && min(48 / tbits, (int)kLongPack) * tbits > 24;
   bool lowered = false;
   while (named) {  // uniform; at most twice
     clear_table();
@@ -1511,7 +1541,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     }
     __syncthreads();
     load_lds(grank);
-  } else {
+  } else if (!by_first) {
     load_lds(gtxt);
     h = min((uint32_t)(48 / tbits), kLongPack);
     auto key_of = [&](uint32_t j) {
@@ -1553,13 +1583,16 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     }
     if (tid == 0 && n % 64 == 0) bitmap[n >> 5] = 1;
     __syncthreads();
+  } else {
+    h = 1;
+  }
+  if (!named)
 #pragma unroll 4
     for (uint32_t k = tid; k < n; k += NT) {
       uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
       while (!w) w = bitmap[--x];  // slot 0 opens a group
       rank[gsa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
     }
-  }
   if (tid == 0) s_nd = nd;  // (the rows are counted from there)
   uint32_t active;
   auto survey = [&] {

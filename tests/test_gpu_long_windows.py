@@ -1,0 +1,100 @@
+"""Windows at the edges of the longer analyses: batches of more windows than
+compute units (those of up to 32768 tokens two to a unit, the rest after them),
+token ranks by radix sort, and single windows whose stages are separate kernels
+(first sort by several tokens at once, large units split by one workgroup or
+many).  Rows against the oracle, active suffix counts against its rounds."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2406_18111_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(r):
+    return np.stack([r["row_start"], r["row_len"], r["row_count"]], 1).astype(np.int64).reshape(-1, 3)
+
+
+def _as3(rows):
+    return np.stack([rows[k] for k in rows.dtype.names], 1).astype(np.int64).reshape(-1, 3)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2406_18111_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def _active(t):
+    return int(oracle.suffix_array(t, return_active=True)[1].sum()) if len(t) > 1 else 0
+
+
+def _distinct(rng, n, d):
+    """n tokens, d distinct."""
+    return np.concatenate([rng.permutation(d), rng.integers(0, d, n - d)]).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+
+
+def test_large_batch(ctx):
+    rng = np.random.default_rng(11)
+    low = rng.integers(0, 2, (4, 12000)).astype(np.uint64)  # four high bytes that tie, low ones that differ
+    tied = (low[0] << np.uint64(56)) | (low[1] << np.uint64(48)) | (low[2] << np.uint64(40)) | (low[3] << np.uint64(32))
+    wins = [synth.loop_stream(k, int(rng.integers(0, 400)), 20, 64, 0.05) for k in range(300)]
+    wins += [synth.loop_stream(k, n, 60, 500, 0.05) for k, n in enumerate((4096, 4097, 8193, 32767, 32768, 32769, 50000, 65536))]
+    wins += [_distinct(rng, n, d) for n, d in ((20000, 6144), (20000, 6145), (32768, 12000), (33000, 8193), (40000, 39000), (4097, 4097))]
+    wins += [tied | rng.permutation(12000).astype(np.uint64), np.full(32768, 3, np.uint64), rng.integers(0, 2, 30000).astype(np.uint64)]
+    order = rng.permutation(len(wins))
+    wins = [wins[k] for k in order]
+    toks = np.concatenate(wins)
+    off = np.zeros(len(wins) + 1, dtype=np.uint64)
+    off[1:] = np.cumsum([len(w) for w in wins])
+    refs = [_rows(oracle.find_repeats(w, 3)) for w in wins]
+    act = sum(_active(w) for w in wins)
+    for graphs in (True, False):
+        try:
+            ctx.set_graphs(graphs)
+            for rep in range(2):
+                print("graphs", graphs, "rep", rep, flush=True)
+                rows, oo = ctx.analyze_batch(toks, off, 3)
+                for w in range(len(wins)):
+                    assert np.array_equal(_as3(rows[int(oo[w]):int(oo[w + 1])]), refs[w]), (rep, w, len(wins[w]))
+                c = ctx.counters()
+                assert c["active_sum"] - len(toks) == act and c["sigma"] == sum(len(np.unique(w)) for w in wins)
+        finally:
+            ctx.set_graphs(True)
+
+
+def test_batch_of_all_distinct_tokens(ctx):
+    """65536 distinct tokens in one window: ranks that 16 bits do not hold."""
+    rng = np.random.default_rng(12)
+    wins = [rng.permutation(65536).astype(np.uint64), np.resize(np.arange(9, dtype=np.uint64), 5000), rng.permutation(65535).astype(np.uint64)]
+    toks = np.concatenate(wins)
+    off = np.array([0, 65536, 70536, 136071], dtype=np.uint64)
+    rows, oo = ctx.analyze_batch(toks, off, 2)
+    for w in range(3):
+        assert np.array_equal(_as3(rows[int(oo[w]):int(oo[w + 1])]), _rows(oracle.find_repeats(wins[w], 2)))
+
+
+@pytest.mark.parametrize("n,values", [(32769, 2), (40000, 1), (65536, 3), (65537, 15), (65537, 16), (70000, 255), (90001, 256),
+                                      (131072, 65535), (131075, 16385), (140000, 70000)])
+@pytest.mark.parametrize("bits", (32, 64))
+def test_long_single_window(ctx, n, values, bits):
+    """Alphabets around the widths at which 16, 8, 4, 2 or 1 tokens fit the
+    first key, random with a run and a repeated part (units on both sides of
+    what one workgroup splits)."""
+    rng = np.random.default_rng(n + values)
+    t = rng.integers(0, values, n).astype(np.uint64)
+    t[n // 5: n // 5 + n // 9] = values - 1
+    t[n // 2: n // 2 + n // 7] = t[:n // 7]
+    t = t * np.uint64(0x9E3779B97F4A7C15) if bits == 64 else t.astype(np.uint32)
+    rows, occ = ctx.analyze(t, 6, occurrences=True)
+    ref = oracle.find_repeats(t.astype(np.uint64), 6)
+    assert np.array_equal(_as3(rows), _rows(ref)) and len(occ) == int(ref["row_count"].sum())
+    act = oracle.suffix_array(t.astype(np.uint64), return_active=True)[1]
+    c, r = ctx.counters(), ctx.rounds()
+    assert c["active_sum"] - n == int(act.sum())
+    assert c["sigma"] == (len(np.unique(t)) if bits == 64 else 0)

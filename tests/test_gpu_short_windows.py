@@ -131,9 +131,8 @@ def test_short_window_batch(ctx, longest):
 
 def test_long_window_batch(ctx):
     """Windows of up to 65536 tokens beside short ones, at the largest sizes
-    and the least and most repetitive inputs; then with a window over the
-    distinct-token limit (8192, the largest value aside), which sends the batch
-    through the stage-by-stage analysis."""
+    and the least and most repetitive inputs; then with a window of more
+    distinct tokens than the hash table takes (8192, the largest value aside)."""
     rng = np.random.default_rng(7)
     many = synth.loop_stream(5, 20000, 300, 4096, 0.05)
     at = np.concatenate([rng.permutation(8192).astype(np.uint64), rng.integers(0, 8192, 3000).astype(np.uint64), [TOP]])
@@ -163,7 +162,7 @@ def test_long_window_batch(ctx):
 
 
 def test_window_over_the_distinct_limit(ctx):
-    """A lone window of more than 8192 distinct tokens is analysed stage by stage."""
+    """A lone window of more than 8192 distinct tokens."""
     t = np.concatenate([np.arange(8193, dtype=np.uint64) << np.uint64(33)] * 2)
     rows, occ = ctx.analyze(t, 3, occurrences=True)
     assert np.array_equal(_as3(rows), _rows(oracle.find_repeats(t, 3))) and len(occ) == 2
