@@ -89,6 +89,31 @@ __device__ __forceinline__ uint64_t lane_step(uint64_t v, bool low) {
   return (o < v) == low ? o : v;
 }
 
+// The steps of a bitonic network's merge of k values that have distances J, J / 2,
+// .., 1, over E consecutive values a lane (the lane's first has index base):
+// register moves all of them.  Runs of k alternate in direction, or all ascend (up).
+template <int E, int J>
+__device__ __forceinline__ void lanes_merge(uint64_t (&r)[E], uint32_t base, uint32_t k, bool up) {
+  if (k > (uint32_t)J) {  // uniform
+    if constexpr (J >= E) {
+      const bool low = ((base & (uint32_t)J) == 0) == (up || (base & k) == 0);
+#pragma unroll
+      for (int e = 0; e < E; e++) r[e] = lane_step<J / E>(r[e], low);
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        if (e & J) continue;
+        const bool asc = up || ((base + e) & k) == 0;
+        const uint64_t a = r[e], b = r[e | J];
+        const bool swap = (a > b) == asc;
+        r[e] = swap ? b : a;
+        r[e | J] = swap ? a : b;
+      }
+    }
+  }
+  if constexpr (J > 1) lanes_merge<E, J / 2>(r, base, k, up);
+}
+
 // Block-wide exclusive sum over NT threads.  `sh` needs NT/64 words.  Returns
 // the exclusive prefix of the calling thread; *total receives the block sum.
 template <int NT>

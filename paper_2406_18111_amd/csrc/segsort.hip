@@ -778,27 +778,6 @@ constexpr int kGroupThreads = 512;
 // are register moves; only those of 64 E and more (3 of 55 steps at m = 1024,
 // E = 4) go through LDS with its barriers.  Every step through LDS took 22 us
 // at m = 2048 and 8.5 us at 512.
-template <int E, int J>
-__device__ __forceinline__ void tile_merge(uint64_t (&r)[E], uint32_t base, uint32_t k) {
-  if (k > (uint32_t)J) {  // uniform
-    if constexpr (J >= E) {
-      const bool low = ((base & (uint32_t)J) == 0) == ((base & k) == 0);
-#pragma unroll
-      for (int e = 0; e < E; e++) r[e] = lane_step<J / E>(r[e], low);
-    } else {
-#pragma unroll
-      for (int e = 0; e < E; e++) {
-        if (e & J) continue;
-        const bool asc = ((base + e) & k) == 0;
-        const uint64_t a = r[e], b = r[e | J];
-        const bool swap = (a > b) == asc;
-        r[e] = swap ? b : a;
-        r[e | J] = swap ? a : b;
-      }
-    }
-  }
-  if constexpr (J > 1) tile_merge<E, J / 2>(r, base, k);
-}
 template <int NT, int E>
 __device__ __forceinline__ void sort_tile(uint64_t *D, uint32_t m) {
   uint32_t m2 = 1;
@@ -825,7 +804,7 @@ __device__ __forceinline__ void sort_tile(uint64_t *D, uint32_t m) {
       }
       __syncthreads();
     }
-    if (mine) tile_merge<E, 32 * E>(r, base, k);
+    if (mine) lanes_merge<E, 32 * E>(r, base, k, false);
   }
   if (mine)
 #pragma unroll
