@@ -46,9 +46,10 @@ struct BigUnit {
   uint32_t len;
   uint32_t cbase;   // index of the unit's first chunk (2^chunk_log entries) in its list
   uint32_t meta;    // bits 0-7: key bits still unsorted (from the top);
-                    // bit 8: data in the alternate buffer; bit 9: skip scatter
+                    // bit 8: data in the alternate buffer; bit 9: skip scatter;
+                    // bit 10: taken apart around its most frequent key
 };
-constexpr uint32_t kMetaAlt = 1u << 8, kMetaSkip = 1u << 9;
+constexpr uint32_t kMetaAlt = 1u << 8, kMetaSkip = 1u << 9, kMetaDone = 1u << 10;
 
 // Device-side counters of one segmented-sort level/round.  Lives in device
 // memory; the host reads it back between rounds.

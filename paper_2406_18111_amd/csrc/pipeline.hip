@@ -555,7 +555,10 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     RankOut R{w.rank, (uint32_t)r, w.aflag};
     if (r > 0 || !skip0) {
       const bool first = r == pack;  // keys are tokens, not ranks
-      if (big && (huge || !host || (batch && wide))) E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg);
+      // up to kSmallChunkMaxN tokens the launches cost more than the moves they save
+      const bool pivot = !first && huge && host && !batch && N > kSmallChunkMaxN;
+      if (big && (huge || !host || (batch && wide)))
+        E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg, pivot ? &R : nullptr);
       else if (big) E.msd_units(cur, act, s, first ? nullptr : wbeg);
       const bool timed = w.ktag == KT_LDS_SA && w.kev_n < kMaxTimed;
       if (timed) APO_HIP_TRY(hipEventRecord(w.kev[2 * w.kev_n], s));

@@ -48,7 +48,9 @@ class SortEngine {
   // slot_base (nullable): digits come from key - slot_base[unit start] (key 0
   // stays 0), so keys that are ranks inside a window need only the window's
   // bits; max_bits counts those bits.
-  void msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base = nullptr);
+  // pivot (nullable): a doubling round, whose units of mostly one key are taken apart around it first.
+  void msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base = nullptr,
+           const RankOut *pivot = nullptr);
   // the same in one launch, where no unit is longer than kMsdUnitMax (work_hint: at least the entries in units)
   void msd_units(int cur, uint64_t work_hint, hipStream_t s, const uint32_t *slot_base = nullptr);
   // sorts and regroups the units the msd passes (or the list itself) left: rows, tiles, one-group chunks

@@ -1074,6 +1074,8 @@ __device__ __forceinline__ void digit_params(uint32_t bits, uint32_t dbits, uint
 // Digit of a key relative to its unit's base (0 stays 0: past the window end).
 __device__ __forceinline__ uint32_t rel_key(uint32_t k, uint32_t base) { return k ? k - base : 0u; }
 
+constexpr uint32_t kPivotWords = 6;  // hist words the pivot kernels below use
+
 __global__ __launch_bounds__(256) void k_msd_hist(SortBufs B, int cur, int level, const uint32_t *slot_base) {
   __shared__ uint32_t h[kBins];
   uint32_t units, total;
@@ -1084,6 +1086,11 @@ __global__ __launch_bounds__(256) void k_msd_hist(SortBufs B, int cur, int level
     __syncthreads();
     const uint32_t u = find_unit(U, units, ch);
     const BigUnit bu = U[u];
+    if (bu.meta & kMetaDone) {  // uniform across the block
+      if (ch == bu.cbase && threadIdx.x < kPivotWords) B.hist[(size_t)u * kBins + threadIdx.x] = 0;
+      __syncthreads();
+      continue;
+    }
     uint32_t shift, mask;
     digit_params(bu.meta & 0xFFu, B.digit_bits, shift, mask);
     const uint32_t lo = bu.start + ((ch - bu.cbase) << B.chunk_log);
@@ -1127,6 +1134,7 @@ __global__ __launch_bounds__(256) void k_msd_scan(SortBufs B, int cur, int level
   BigUnit *U = B.big[cur][level];
   for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
     const BigUnit bu = U[u];
+    if (bu.meta & kMetaDone) continue;  // uniform across the block
     const uint32_t buf = (bu.meta & kMetaAlt) ? 1u : 0u;
     uint32_t shift, mask;
     digit_params(bu.meta & 0xFFu, B.digit_bits, shift, mask);
@@ -1216,7 +1224,7 @@ __global__ __launch_bounds__(256) void k_msd_scatter(SortBufs B, int cur, int le
   for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
     const uint32_t u = find_unit(U, units, ch);
     const BigUnit bu = U[u];
-    if (bu.meta & kMetaSkip) continue;  // uniform across the block
+    if (bu.meta & (kMetaSkip | kMetaDone)) continue;  // uniform across the block
     for (int b = threadIdx.x; b < (1 << B.digit_bits); b += NT) cnt[b] = 0;
     __syncthreads();
     uint32_t shift, mask;
@@ -1250,6 +1258,159 @@ __global__ __launch_bounds__(256) void k_msd_scatter(SortBufs B, int cur, int le
       }
     }
     __syncthreads();
+  }
+}
+
+// Units longer than kMsdUnitMax of which three entries in four or more have one
+// key, as a long run's or loop's have in every round (their second halves are
+// in one group too): taken apart around that key (the middle entry's), in place.
+// Entries of smaller and larger keys go to the alternate buffer as pieces for
+// the passes below; of the others only those move that lie where the
+// pieces will be, into the places those entries leave; the group stays a large unit
+// of the next round and, unless smaller keys moved its start, keeps its ranks.
+// Bound by reading the keys twice.  The passes moved all 8.4 M entries of a run
+// in every one of 20 rounds, 310 us a round; with these 150 to 250 (2^24 tokens, half of
+// them one run: 10.2 -> 8.5 ms).
+// hist words of a unit: entries below the key and equal to it; then places
+// taken by the smaller, the larger, the gaps they leave and the displaced.
+__device__ __forceinline__ bool pivoted(const uint32_t *ph, uint32_t len) {
+  return len > kMsdUnitMax && 4ull * ph[1] >= 3ull * len;
+}
+
+__global__ __launch_bounds__(256) void k_pivot_count(SortBufs B, int cur) {
+  __shared__ uint32_t sh[2][4];
+  uint32_t units, total;
+  list_size(B.ctr->big_pk[cur][0], B.big_cap, units, total);
+  const BigUnit *U = B.big[cur][0];
+  for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
+    const uint32_t u = find_unit(U, units, ch);
+    const BigUnit bu = U[u];
+    if (bu.len <= kMsdUnitMax) continue;  // uniform
+    const uint32_t pivot = B.key[0][bu.start + bu.len / 2];
+    const uint32_t lo = bu.start + ((ch - bu.cbase) << B.chunk_log);
+    const uint32_t hi = min(lo + (1u << B.chunk_log), bu.start + bu.len);
+    uint32_t lt = 0, eq = 0;
+#pragma unroll 4
+    for (uint32_t p = lo + threadIdx.x; p < hi; p += 256) {
+      const uint32_t k = B.key[0][p];
+      lt += k < pivot ? 1u : 0u;
+      eq += k == pivot ? 1u : 0u;
+    }
+    lt = wave_incl_sum(lt);
+    eq = wave_incl_sum(eq);
+    if ((threadIdx.x & 63) == 63) {
+      sh[0][threadIdx.x >> 6] = lt;
+      sh[1][threadIdx.x >> 6] = eq;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+      const uint32_t *w = sh[threadIdx.x];
+      const uint32_t sum = w[0] + w[1] + w[2] + w[3];
+      if (sum) atomicAdd(&B.hist[(size_t)u * kBins + threadIdx.x], sum);
+    }
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void k_pivot_move(SortBufs B, int cur) {
+  __shared__ uint32_t at[4];
+  uint32_t units, total;
+  list_size(B.ctr->big_pk[cur][0], B.big_cap, units, total);
+  const BigUnit *U = B.big[cur][0];
+  for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
+    const uint32_t u = find_unit(U, units, ch);
+    const BigUnit bu = U[u];
+    uint32_t *ph = B.hist + (size_t)u * kBins;
+    if (!pivoted(ph, bu.len)) continue;  // uniform
+    const uint32_t pivot = B.key[0][bu.start + bu.len / 2];
+    const uint32_t mid = bu.start + ph[0], top = mid + ph[1];  // the group's slots: [mid, top)
+    const uint32_t lo = bu.start + ((ch - bu.cbase) << B.chunk_log);
+    const uint32_t hi = min(lo + (1u << B.chunk_log), bu.start + bu.len);
+    if (threadIdx.x < 4) at[threadIdx.x] = 0;
+    __syncthreads();
+    // count, take places for the whole chunk, then move
+    for (int move = 0; move < 2; move++) {
+#pragma unroll 4
+      for (uint32_t p = lo + threadIdx.x; p < hi; p += 256) {
+        const uint32_t k = B.key[0][p];
+        const bool in = p >= mid && p < top;
+        if ((k == pivot) == in) {
+          if (in) continue;
+          // a larger or smaller key, outside the group's slots
+          const uint32_t c = k < pivot ? 0 : 1, o = agg_inc(&at[c]);
+          if (move) {
+            const uint32_t q = (c ? top : bu.start) + o;
+            B.key[1][q] = k;
+            B.val[1][q] = B.val[0][p];
+          }
+        } else if (in) {  // leaves a gap
+          const uint32_t c = k < pivot ? 0 : 1, o = agg_inc(&at[c]), g = agg_inc(&at[2]);
+          if (move) {
+            const uint32_t q = (c ? top : bu.start) + o;
+            B.key[1][q] = k;
+            B.val[1][q] = B.val[0][p];
+            B.val[1][mid + g] = p;
+          }
+        } else {  // displaced
+          const uint32_t d = agg_inc(&at[3]);
+          if (move) B.key[1][mid + d] = B.val[0][p];
+        }
+      }
+      __syncthreads();
+      if (!move && threadIdx.x < 4) {
+        const uint32_t c = at[threadIdx.x];
+        at[threadIdx.x] = c ? atomicAdd(&ph[2 + threadIdx.x], c) : 0u;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_pivot_fix(SortBufs B, int cur, RankOut R, uint32_t next_bits) {
+  const int nxt = cur ^ 1;
+  uint32_t units, total;
+  list_size(B.ctr->big_pk[cur][0], B.big_cap, units, total);
+  BigUnit *U = B.big[cur][0];
+  for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
+    const uint32_t u = find_unit(U, units, ch);
+    const BigUnit bu = U[u];
+    uint32_t *ph = B.hist + (size_t)u * kBins;
+    const bool first = ch == bu.cbase;
+    if (!pivoted(ph, bu.len)) {  // uniform; the passes below count anew
+      __syncthreads();
+      if (first && threadIdx.x < kPivotWords) ph[threadIdx.x] = 0;
+      continue;
+    }
+    const uint32_t below = ph[0], same = ph[1], gaps = ph[4], mid = bu.start + below;
+    const uint32_t lo = (ch - bu.cbase) << B.chunk_log, hi = min(lo + (1u << B.chunk_log), bu.len);
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
+      if (i < gaps) {
+        const uint32_t v = B.key[1][mid + i];
+        B.val[0][B.val[1][mid + i]] = v;
+        if (below) R.rank[v] = mid + 1;
+      }
+      // (an entry that leaves is still read here or not: its rank comes with its piece)
+      if (below && i < same) R.rank[B.val[0][mid + i]] = mid + 1;
+    }
+    if (first && threadIdx.x == 0) {
+      if (same > kMsdUnitMax) atomicAdd(&B.ctr->huge[nxt], 1u);
+      append_big(B.big[nxt][0], &B.ctr->big_pk[nxt][0], B.big_cap, mid, same, next_bits, &B.ctr->err, B.chunk_log);
+      atomicAdd(&B.ctr->act_cnt[nxt], same);
+      U[u].meta = bu.meta | kMetaDone;
+      for (int side = 0; side < 2; side++) {
+        const uint32_t start = side ? mid + same : bu.start, len = side ? bu.len - below - same : below;
+        if (len == 0) continue;
+        if (len <= (1u << B.tile_log)) {
+          const int ci = class_of(len);
+          const uint32_t k = atomicAdd(&B.ctr->cls_cnt[cur][ci], 1u);
+          if (k < B.cls_off[ci + 1] - B.cls_off[ci]) B.cls[cur][B.cls_off[ci] + k] = Unit{start, len | kBufBit};
+          else atomicOr(&B.ctr->err, 1024u);
+        } else {
+          append_big(B.big[cur][1], &B.ctr->big_pk[cur][1], B.big_cap, start, len, (bu.meta & 0xFFu) | kMetaAlt,
+                     &B.ctr->err, B.chunk_log);
+        }
+      }
+    }
   }
 }
 
@@ -1598,9 +1759,16 @@ void SortEngine::msd_units(int cur, uint64_t work_hint, hipStream_t s, const uin
   hipLaunchKernelGGL(k_msd_unit, dim3(g), dim3(kUnitThreads), 0, s, b_, cur, slot_base);
 }
 
-void SortEngine::msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base) {
+void SortEngine::msd(int cur, uint64_t work_hint, int max_bits, hipStream_t s, const uint32_t *slot_base,
+                     const RankOut *pivot) {
   const unsigned g = (unsigned)std::min<uint64_t>(4096, std::max<uint64_t>(256, (work_hint >> b_.chunk_log) + 1));
-  const int levels = std::min(kMaxMsdLevels, (max_bits + (int)b_.digit_bits - 1) / (int)b_.digit_bits);
+  int levels = std::min(kMaxMsdLevels, (max_bits + (int)b_.digit_bits - 1) / (int)b_.digit_bits);
+  if (pivot && levels < kMaxMsdLevels) {
+    hipLaunchKernelGGL(k_pivot_count, dim3(g), dim3(256), 0, s, b_, cur);
+    hipLaunchKernelGGL(k_pivot_move, dim3(g), dim3(256), 0, s, b_, cur);
+    hipLaunchKernelGGL(k_pivot_fix, dim3(g), dim3(256), 0, s, b_, cur, *pivot, (uint32_t)max_bits);
+    levels++;  // their pieces start a level below
+  }
   for (int level = 0; level < levels; level++) {
     hipLaunchKernelGGL(k_msd_hist, dim3(g), dim3(256), 0, s, b_, cur, level, slot_base);
     hipLaunchKernelGGL(k_msd_scan, dim3(256), dim3(256), 0, s, b_, cur, level);

@@ -98,3 +98,24 @@ def test_long_single_window(ctx, n, values, bits):
     c, r = ctx.counters(), ctx.rounds()
     assert c["active_sum"] - n == int(act.sum())
     assert c["sigma"] == (len(np.unique(t)) if bits == 64 else 0)
+
+
+@pytest.mark.parametrize("kind", ("runs", "period"))
+def test_units_of_mostly_one_key(ctx, kind):
+    """Above 2^22 tokens, where a unit of mostly one key is taken apart around
+    it: runs of the smallest, a middle and the largest value (entries leave on
+    either side), a loop of period 3 (the key is another group's)."""
+    n = (1 << 22) + 4097
+    rng = np.random.default_rng(5)
+    t = rng.integers(0, 4, n).astype(np.uint32)
+    if kind == "runs":
+        for at, length, value in ((7, 200000, 0), (300000, n // 2, 2), (3000000, 400000, 3), (3500000, 100000, 2)):
+            t[at: at + length] = value
+    else:
+        t[100000: 100000 + n // 2] = np.resize(np.array([1, 0, 2], np.uint32), n // 2)
+        t[n - 300000:] = 1
+    rows = ctx.analyze(t, 64)
+    ref = oracle.find_repeats(t.astype(np.uint64), 64)
+    assert np.array_equal(_as3(rows), _rows(ref))
+    act = oracle.suffix_array(t.astype(np.uint64), return_active=True)[1]
+    assert ctx.counters()["active_sum"] - n == int(act.sum())
