@@ -739,7 +739,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     // test lowers it) and finish with the sequential completion
     const int cap = host ? std::max(0, std::min(w.sel_cap, kSelRoundCap)) : kSelRoundCap;
     while (sel_done < 0 && q0 < cap) {
-      const int lo = q0, hi = std::min(q0 + ahead, cap);
+      // (few are left after the first two rounds: then one at a time)
+      const int lo = q0, hi = std::min(q0 + (q0 >= 2 && host ? 1 : ahead), cap);
       for (int q = lo; q < hi; q++)
         sel_round(w.s_len, w.s_start, (q & 1) ? Tb : Ta, (q & 1) ? Ta : Tb, top, N, w.state, w.live[0],
                   w.live[1], nlive, nwork, undec, q, hint, dc + CNT_MAXL, w.ctree, npad, w.mark, s);

@@ -91,9 +91,44 @@ __global__ __launch_bounds__(kScanNT) void k_scan_apply(const uint32_t *in, cons
   }
 }
 
+// The same by one workgroup, for up to kScanSmall elements: three launches of
+// some 4 us each did little but start there.
+constexpr uint64_t kScanSmall = 32768;
+
+__global__ __launch_bounds__(1024) void k_scan_small(const uint32_t *in, const uint32_t *n_dev, uint32_t *out,
+                                                     uint32_t *total) {
+  __shared__ uint32_t sh[1024 / 64];
+  const uint32_t n = *n_dev;
+  uint32_t carry = 0;
+  for (uint32_t b0 = 0; b0 < n; b0 += 1024 * kScanPer) {
+    const uint32_t base = b0 + threadIdx.x * kScanPer;
+    uint32_t v[kScanPer];
+    uint32_t loc = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; q++) {
+      v[q] = base + q < n ? in[base + q] : 0u;
+      loc += v[q];
+    }
+    uint32_t tot;
+    uint32_t ex = carry + block_excl_sum<1024>(loc, sh, &tot);
+#pragma unroll
+    for (int q = 0; q < kScanPer; q++) {
+      if (base + q < n) out[base + q] = ex;
+      ex += v[q];
+    }
+    carry += tot;
+    __syncthreads();  // sh is used again
+  }
+  if (threadIdx.x == 0 && total) *total = carry;
+}
+
 // n_dev: element count in device memory; bound: host upper bound (grid size).
 void scan_excl(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint64_t bound, uint32_t *tile_tmp,
                uint32_t *total, hipStream_t s) {
+  if (bound <= kScanSmall) {
+    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, in, n_dev, out, total);
+    return;
+  }
   const uint32_t tiles = (uint32_t)std::max<uint64_t>((bound + kScanTile - 1) / kScanTile, 1);
   hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(kScanNT), 0, s, in, n_dev, tile_tmp);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, tile_tmp, n_dev, total);
@@ -1743,11 +1778,7 @@ __global__ __launch_bounds__(64) void k_lsd_segments(const uint32_t *rec, const 
                                                      uint32_t nseg, uint32_t *off, uint32_t *nt) {
   const uint32_t g = blockIdx.x;
   const uint32_t n = *n_dev;
-  uint32_t lo = 0, hi = n;
-  if (wid) {
-    lo = rec_window_bound(rec, wid, n, g);
-    hi = rec_window_bound(rec, wid, n, g + 1);
-  }
+  const uint32_t lo = rec_window_bound(rec, wid, n, g), hi = rec_window_bound(rec, wid, n, g + 1);
   if (threadIdx.x == 0) {
     off[g] = lo;
     nt[g] = (hi - lo + kLsdTile - 1) / kLsdTile;
@@ -1764,6 +1795,19 @@ __global__ __launch_bounds__(64) void k_lsd_seg_fill(const uint32_t *tb, uint32_
   const uint32_t g = blockIdx.x;
   for (uint32_t t = tb[g] + threadIdx.x; t < tb[g + 1]; t += 64) tseg[t] = g;
   if (g == 0 && threadIdx.x == 0) *hist_words = tb[nseg] * kLsdBins;
+}
+
+// Both for records that are not in segments: one segment, its tiles from 0 on.
+__global__ void k_lsd_one_segment(const uint32_t *n_dev, uint32_t *off, uint32_t *tb, uint32_t *tseg,
+                                  uint32_t *hist_words) {
+  const uint32_t n = *n_dev, tiles = (n + kLsdTile - 1) / kLsdTile;
+  GRID_STRIDE(t, tiles) tseg[t] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    off[0] = tb[0] = 0;
+    off[1] = n;
+    tb[1] = tiles;
+    *hist_words = tiles * kLsdBins;
+  }
 }
 
 __global__ __launch_bounds__(kLsdNT) void k_lsd_hist(LsdSrc in, int shift, uint32_t *hist, LsdTiles T) {
@@ -1902,10 +1946,14 @@ void lsd_sort_candidates(const uint32_t *crec, const uint32_t *maxl_dev, const u
   const uint64_t tiles_bound = (bound + kLsdTile - 1) / kLsdTile + nseg;
   const unsigned grid = (unsigned)std::min<uint64_t>(std::max<uint64_t>(tiles_bound, 1), 8192);
   uint32_t *off = seg, *nt = seg + (nseg + 1), *tb = seg + 2 * (nseg + 1), *tseg = seg + 3 * (nseg + 1);
-  hipLaunchKernelGGL(k_lsd_segments, dim3(nseg), dim3(64), 0, s, crec, n_dev, seg_wid, nseg, off, nt);
-  fill_u32(hist_n, 1, nseg + 1, s);
-  scan_excl(nt, tb, hist_n, nseg + 1, tile_tmp, nullptr, s);
-  hipLaunchKernelGGL(k_lsd_seg_fill, dim3(nseg), dim3(64), 0, s, tb, nseg, tseg, hist_n);
+  if (!seg_wid) {
+    hipLaunchKernelGGL(k_lsd_one_segment, grid_for(tiles_bound, 256, 64), dim3(256), 0, s, n_dev, off, tb, tseg, hist_n);
+  } else {
+    hipLaunchKernelGGL(k_lsd_segments, dim3(nseg), dim3(64), 0, s, crec, n_dev, seg_wid, nseg, off, nt);
+    fill_u32(hist_n, 1, nseg + 1, s);
+    scan_excl(nt, tb, hist_n, nseg + 1, tile_tmp, nullptr, s);
+    hipLaunchKernelGGL(k_lsd_seg_fill, dim3(nseg), dim3(64), 0, s, tb, nseg, tseg, hist_n);
+  }
   const LsdTiles T{off, tb, tseg, nseg};
   LsdSrc in{crec, maxl_dev, nullptr, nullptr, nullptr, wid, wshift};
   for (int ps = 0; ps < passes; ps++) {
