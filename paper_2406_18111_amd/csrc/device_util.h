@@ -176,21 +176,22 @@ namespace apo {
 // of active lanes and the others derive their slot from their rank; otherwise
 // each lane increments on its own.  Returns the counter value before this
 // lane's increment (a unique slot among all callers).
-__device__ __forceinline__ uint32_t agg_inc(uint32_t *ctr) {
-  const uint64_t active = __ballot(1);
-  const int lane = __lane_id();
-  const int leader = __ffsll((unsigned long long)active) - 1;
+// Whether they do is told by scalar reads of the first lane's address (lane
+// reads through LDS took longer than the atomics).
+__device__ __forceinline__ bool one_counter(const uint32_t *ctr) {
   const uintptr_t mine = reinterpret_cast<uintptr_t>(ctr);
   const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
-  const bool same = __all(lo == (uint32_t)__shfl((int)lo, leader, 64) && hi == (uint32_t)__shfl((int)hi, leader, 64));
-  if (same) {
-    const uint32_t rank = (uint32_t)__popcll(active & ((1ull << lane) - 1ull));
-    uint32_t old = 0;
-    if (lane == leader) old = atomicAdd(ctr, (uint32_t)__popcll(active));
-    old = (uint32_t)__shfl((int)old, leader, 64);
-    return old + rank;
-  }
-  return atomicAdd(ctr, 1u);
+  return __all(lo == (uint32_t)__builtin_amdgcn_readfirstlane((int)lo) &&
+               hi == (uint32_t)__builtin_amdgcn_readfirstlane((int)hi));
+}
+__device__ __forceinline__ uint32_t agg_inc(uint32_t *ctr) {
+  if (!one_counter(ctr)) return atomicAdd(ctr, 1u);
+  const uint64_t active = __ballot(1);
+  const uint32_t rank =
+      __builtin_amdgcn_mbcnt_hi((uint32_t)(active >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)active, 0u));
+  uint32_t old = 0;
+  if (rank == 0) old = atomicAdd(ctr, (uint32_t)__popcll(active));
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)old) + rank;  // the first active lane's
 }
 
 // Same, when only the total matters.
@@ -212,18 +213,14 @@ __device__ __forceinline__ void agg_add_any(uint32_t *ctr, uint32_t v) {
 }
 
 __device__ __forceinline__ void agg_add(uint32_t *ctr, uint32_t v) {
-  const uint64_t active = __ballot(1);
-  const int lane = __lane_id();
-  const int leader = __ffsll((unsigned long long)active) - 1;
-  const uintptr_t mine = reinterpret_cast<uintptr_t>(ctr);
-  const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
-  const bool same = __all(lo == (uint32_t)__shfl((int)lo, leader, 64) && hi == (uint32_t)__shfl((int)hi, leader, 64));
-  if (same) {
-    // every lane adds the same v in all call sites
-    if (lane == leader) atomicAdd(ctr, v * (uint32_t)__popcll(active));
+  if (!one_counter(ctr)) {
+    atomicAdd(ctr, v);
     return;
   }
-  atomicAdd(ctr, v);
+  // every lane adds the same v in all call sites
+  const uint64_t active = __ballot(1);
+  if (__builtin_amdgcn_mbcnt_hi((uint32_t)(active >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)active, 0u)) == 0)
+    atomicAdd(ctr, v * (uint32_t)__popcll(active));
 }
 
 }  // namespace apo

@@ -1423,7 +1423,7 @@ __global__ __launch_bounds__(256) void k_pivot_fix(SortBufs B, int cur, RankOut 
 constexpr int kUnitThreads = 1024, kUnitStack = 2 * (kMsdUnitMax >> kMinTileLog);  // pending buckets: disjoint, > a tile
 
 __global__ __launch_bounds__(kUnitThreads) void k_msd_unit(SortBufs B, int cur, const uint32_t *slot_base) {
-  constexpr int NT = kUnitThreads, PER = kBins / NT, LOADS = 4;
+  constexpr int NT = kUnitThreads, PER = kBins / NT, LOADS = 8;
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t sh[NT / 64];
   __shared__ BigUnit todo[kUnitStack];
