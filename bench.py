@@ -5,11 +5,11 @@ Default workload (batched): 4096 independent windows, lengths log-uniform in
 [256, 65536] (48.8 M tokens in total), each a loop stream (body length
 uniform in [10, 500] from an alphabet of 2^12 hashes, 5% substitutions), min
 repeat length 8.  One step = one complete analysis of every window (rank
-compression, suffix array, LCP, candidates, sort, greedy selection, output)
-split into concurrent window groups (lanes), each run host-driven on its own
-stream, tokens resident in device memory.  Reported beside it: the same step
-captured once as a HIP graph and replayed (the lanes as branches of one
-graph, and one stream), the same windows
+compression, suffix array, LCP, candidates, sort, greedy selection, output),
+each by one workgroup, captured once as a HIP graph and replayed, tokens
+resident in device memory.  Reported beside it: the same step enqueued
+without a graph, the stage-by-stage kernels on the same batch (what longer
+windows take) with their sort family timed, the same windows
 through one plain per-window analysis each, the single-window n = 2^20
 nested-loop workload, the continuous-batching server against a plain FIFO on
 a Poisson trace (p50/p99 latency), the C oracle on the host's cores, and the
@@ -168,8 +168,8 @@ def cpu_baseline_single(t, m, seconds):
 
 
 def timed_steps(ctx, step, steps):
-    """Runs `steps` steps with live kernel timing; returns seconds/step, kernel
-    totals, per-stage device ms and the last step's output."""
+    """Runs `steps` steps; returns seconds/step, the totals of a kernel timed
+    meanwhile (profile_kernel), per-stage device ms and the last step's output."""
     import torch
     kprof = {"launches": 0, "ms": 0.0, "elems": 0}
     stage_tot = None
@@ -187,8 +187,8 @@ def timed_steps(ctx, step, steps):
     return el, kprof, {k: v / steps for k, v in stage_tot.items()}, out
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "findrepeats_batched_lds_family_traffic.md")
-FAMILY_SOURCE = os.path.join(ROOT, "paper_2406_18111_amd", "csrc", "segsort.hip")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "findrepeats_batched_traffic.md")
+FAMILY_SOURCE = os.path.join(ROOT, "paper_2406_18111_amd", "csrc", "winfused.hip")
 
 
 def code_hash(path):
@@ -203,11 +203,10 @@ def code_hash(path):
     return hashlib.sha256(text.encode()).hexdigest()
 
 
-def measured_traffic(workload, lanes=1):
-    """HBM bytes per launch of the timed kernel family from the committed
+def measured_traffic(workload):
+    """HBM bytes per step of the one-workgroup analyses from the committed
     rocprofv3 FETCH_SIZE/WRITE_SIZE summary, or None when it does not exist,
     covers another workload, or the kernels' source changed since."""
-    import hashlib
     try:
         recs = [json.loads(line[len("TRAFFIC_RECORD "):]) for line in open(TRAFFIC_FILE)
                 if line.startswith("TRAFFIC_RECORD ")]
@@ -215,26 +214,34 @@ def measured_traffic(workload, lanes=1):
     except OSError:
         return None
     for rec in recs:
-        if (rec.get("workload") == workload and rec.get("lanes", 1) == lanes
-                and rec.get("kernel_source_sha256") == src):
-            return float(rec["traffic_bytes_per_launch"])
+        if rec.get("workload") == workload and rec.get("kernel_source_sha256") == src:
+            return float(rec["traffic_bytes_per_step"])
     return None
 
 
-def roofline(kprof, steps, workload=None, lanes=1, copy_gbs=None):
+def batch_roofline(path, workload):
+    """The timed step is the one-workgroup analyses and little else: their
+    roof is the whole step's."""
+    out = dict(path, kernel="k_window_mid (windows of up to 32768 tokens, two to a compute unit) + k_window_rest "
+                            "(the longer ones): every stage of a window by one workgroup",
+               traffic=measured_traffic(workload),
+               traffic_unit="bytes per step (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)")
+    return out
+
+
+def roofline(kprof, steps, lanes=1, copy_gbs=None):
+    """The stage-by-stage kernels' sort family, timed with events."""
     if not kprof["launches"]:
         return None
     avg_ms = kprof["ms"] / kprof["launches"]
     entries = kprof["elems"] / kprof["launches"]
     bytes_per_launch = entries * LDS_SA_BYTES_PER_ENTRY
     achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9
-    traffic = measured_traffic(workload, lanes) if workload else None
     out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-           "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-           "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-           "kernel": "per doubling round, the LDS sort family in SA mode: k_wave_sort<0> (units <= 64) + "
-                     "k_lds_group<0> (65..4096) [+ k_lds_sort<0,13> with 8192-entry tiles], one event pair "
-                     "around the family",
+           "frac": achieved / HBM_PEAK_GBS, "traffic": None,
+           "kernel": "per doubling round, the units' sort family in SA mode: k_sort_units<0>, or above 2^22 tokens "
+                     "k_wave_sort<0> (units <= 64) + k_lds_group<0> (65..4096) [+ k_lds_sort<0,13> with 8192-entry "
+                     "tiles] + k_bulk<0>, one event pair around the family",
            "bytes_per_entry": LDS_SA_BYTES_PER_ENTRY, "entries_per_launch": entries,
            "avg_launch_us": avg_ms * 1e3, "bytes_per_launch": bytes_per_launch,
            "kernel_local_bytes_per_launch": entries * LDS_SA_LOCAL_BYTES_PER_ENTRY,
@@ -441,53 +448,39 @@ def main():
             # untimed: the project's autotuner picks the LDS tile and MSD digit width on this batch
             tl, db, tms = ctx.tune_batch(dev, off, m, reps=1)
             tuned = {"tile_log": tl, "digit_bits": db, "tuning_ms_at_best": tms}
-        # timed region: one batch call per step (lanes run host-driven, one
-        # lane runs the sync-free sequence) with the dominant kernel family
-        # bracketed by events on its stream (kernel timing is not taken inside
-        # captured graphs)
-        ctx.profile_kernel(LDS_SA_TAG)
+        # timed region: one batch call per step
         for _ in range(warm):
             ctx.analyze_batch_dev(dev, off, m)
-        sec, kprof, stages, res = timed_steps(ctx, lambda: ctx.analyze_batch_dev(dev, off, m), steps)
-        ctx.profile_kernel(0)
+        sec, _, stages, res = timed_steps(ctx, lambda: ctx.analyze_batch_dev(dev, off, m), steps)
         out.update({"value": total / sec, "ms_per_step": sec * 1e3, "dtype": "u64",
                     "config": {"workload": "config3", "windows": len(wins), "tokens": total, "min_len": m,
                                "description": ("4096 windows, lengths log-uniform 256..65536, loop bodies 10..500, "
-                                               "alphabet 2^12, 5 percent substitutions; per step the windows are "
-                                               "split into {} groups of about equal tokens, each analysed "
-                                               "on its own stream").format(args.lanes),
+                                               "alphabet 2^12, 5 percent substitutions; per step every window is "
+                                               "analysed by one workgroup"),
                                "lanes": args.lanes},
-                    "counters": ctx.counters(), "rows": int(res[1][-1]), "tuned": tuned})
-        rf = roofline(kprof, steps, "config3", args.lanes, copy_gbs)
-        if rf:
-            out["roofline"] = rf
+                    "counters": ctx.counters(), "rows": int(res[1][-1]), "tuned": tuned, "graph": ctx.graph_stats()})
         out["path_roofline"] = path_roofline(out["counters"], total, 8, res[0], sec, copy_gbs)
-        if not args.profile_steps and not args.no_extras and args.lanes > 1:
-            # the same kernel family timed with one stream only (no other lane
-            # sharing the GPU while an event pair is open)
+        out["roofline"] = batch_roofline(out["path_roofline"], "config3")
+        if not args.profile_steps and not args.no_extras:
+            # the stage-by-stage kernels on the same batch, their sort family
+            # timed with events (one stream: nothing else runs inside a pair)
             ctx.set_lanes(1)
             ctx.profile_kernel(LDS_SA_TAG)
             ctx.analyze_batch_dev(dev, off, m)
-            _, kp1, _, _ = timed_steps(ctx, lambda: ctx.analyze_batch_dev(dev, off, m), 3)
+            ssec, kp1, _, sres = timed_steps(ctx, lambda: ctx.analyze_batch_dev(dev, off, m), 3)
             ctx.profile_kernel(0)
             ctx.set_lanes(args.lanes)
-            out["roofline_one_lane"] = roofline(kp1, 3, "config3", 1, copy_gbs)
-        if not args.profile_steps and not args.no_graphs and args.lanes > 1:
-            # the same lanes, each lane's sync-free sequence a branch of one
-            # graph captured once and replayed
-            ctx.analyze_batch_dev(dev, off, m)
-            gsec, _, _, gres = timed_steps(ctx, lambda: ctx.analyze_batch_dev(dev, off, m), steps)
-            out["graph_replay_lanes"] = {
-                "tokens_per_s": total / gsec, "ms": gsec * 1e3, "lanes": args.lanes, "graph": ctx.graph_stats(),
-                "same_rows": bool(np.array_equal(gres[1], res[1]) and torch.equal(gres[0], res[0]))}
+            out["stage_by_stage"] = {"tokens_per_s": total / ssec, "ms": ssec * 1e3,
+                                     "roofline": roofline(kp1, 3, 1, copy_gbs),
+                                     "same_rows": bool(np.array_equal(sres[1], res[1]) and torch.equal(sres[0], res[0]))}
         if not args.profile_steps and not args.no_graphs:
-            # one stream: the step captured once as a HIP graph and replayed
-            ctx.set_lanes(1)
+            # the same launches enqueued step by step
+            ctx.set_graphs(False)
             ctx.analyze_batch_dev(dev, off, m)
             gsec, _, _, gres = timed_steps(ctx, lambda: ctx.analyze_batch_dev(dev, off, m), steps)
-            ctx.set_lanes(args.lanes)
-            out["graph_replay_one_lane"] = {
-                "tokens_per_s": total / gsec, "ms": gsec * 1e3, "graph": ctx.graph_stats(),
+            ctx.set_graphs(True)
+            out["without_graph"] = {
+                "tokens_per_s": total / gsec, "ms": gsec * 1e3,
                 "same_rows": bool(np.array_equal(gres[1], res[1]) and torch.equal(gres[0], res[0]))}
         if not args.profile_steps and not args.no_extras:
             tw, nrows = per_window_leg(ctx, dev, off, m)
@@ -520,16 +513,16 @@ def main():
             tuned = {"tile_log": tl, "digit_bits": db, "tuning_ms_at_best": tms}
         for _ in range(warm):
             ctx.analyze_dev(dev, m)
-        ctx.profile_kernel(LDS_SA_TAG)
-        sec, kprof, stages, res = timed_steps(ctx, lambda: ctx.analyze_dev(dev, m), steps)
-        ctx.profile_kernel(0)
+        sec, _, stages, res = timed_steps(ctx, lambda: ctx.analyze_dev(dev, m), steps)
         out.update({"value": n / sec, "ms_per_step": sec * 1e3, "dtype": "u32" if t.dtype == np.uint32 else "u64",
                     "config": {"workload": args.workload, "description": desc, "n": n, "min_len": m, "windows": 1},
                     "stage_ms": stages, "counters": ctx.counters(), "rows": int(res[0].shape[0]), "tuned": tuned})
-        rf = roofline(kprof, steps, copy_gbs=copy_gbs)
-        if rf:
-            out["roofline"] = rf
         out["path_roofline"] = path_roofline(out["counters"], n, t.dtype.itemsize, res[0], sec, copy_gbs)
+        if not args.profile_steps and not args.no_extras:
+            ctx.profile_kernel(LDS_SA_TAG)
+            _, kprof, _, _ = timed_steps(ctx, lambda: ctx.analyze_dev(dev, m), 3)
+            ctx.profile_kernel(0)
+            out["roofline"] = roofline(kprof, 3, copy_gbs=copy_gbs)
         if not args.profile_steps and not args.no_cpu_baseline:
             out["cpu_baseline"] = cpu_baseline_single(t, m, args.cpu_seconds)
     print(json.dumps(out), flush=True)

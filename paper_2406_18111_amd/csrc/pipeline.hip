@@ -532,10 +532,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       E.gather_identity(key0, (uint32_t)N, s);
     E.init_units(cur, w.d_off, W, 0, bits0, s);
   }
-  // units too long for a tile are left; and units too long for one workgroup to
-  // split (only single windows count those: other runs go by their longest window)
-  const bool wide = maxwin > kMsdUnitMax;
-  bool big = maxwin > (1ull << E.tile_log()), huge = wide && !batch;
+  // units too long for a tile are left; and units too long for one workgroup to split
+  bool big = maxwin > (1ull << E.tile_log()), huge = maxwin > kMsdUnitMax;
   uint64_t act = N;
   int r = pair0 ? 2 : pack, done_round = -1;
   w.kev_n = 0;
@@ -557,7 +555,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       const bool first = r == pack;  // keys are tokens, not ranks
       // up to kSmallChunkMaxN tokens the launches cost more than the moves they save
       const bool pivot = !first && huge && host && !batch && N > kSmallChunkMaxN;
-      if (big && (huge || !host || (batch && wide)))
+      if (big && (huge || !host))
         E.msd(cur, act, first ? (int)bits0 : (int)rel_bits, s, first ? nullptr : wbeg, pivot ? &R : nullptr);
       else if (big) E.msd_units(cur, act, s, first ? nullptr : wbeg);
       const bool timed = w.ktag == KT_LDS_SA && w.kev_n < kMaxTimed;

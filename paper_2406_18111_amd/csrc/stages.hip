@@ -1012,8 +1012,11 @@ __global__ __launch_bounds__(kWinRankThreads) void k_win_round0(SortBufs B, cons
       act += c;
       ur[q] = r;
       if (c <= tile) ui[q] = atomicAdd(&cls_loc[class_of(c)], 1u);
-      else append_big_unit(B.big[LIST][0], &B.ctr->big_pk[LIST][0], B.big_cap, (uint32_t)b + gst[r], c, next_bits,
-                           &B.ctr->err, B.chunk_log);
+      else {
+        if (c > kMsdUnitMax) atomicAdd(&B.ctr->huge[LIST], 1u);
+        append_big_unit(B.big[LIST][0], &B.ctr->big_pk[LIST][0], B.big_cap, (uint32_t)b + gst[r], c, next_bits,
+                             &B.ctr->err, B.chunk_log);
+      }
     }
     {
       uint32_t tot;
