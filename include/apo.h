@@ -151,12 +151,13 @@ int apo_analyze_batch_dev(apo_ctx *ctx, const uint64_t *d_tokens, const uint64_t
                           uint32_t num_windows, uint32_t min_len, apo_candidate *d_out,
                           uint64_t out_cap, uint64_t *h_out_offsets, void *hip_stream);
 
-/* Batches with a window of more than 8192 tokens are split into `lanes` (1..4, default 3) groups of consecutive
- * windows with about equal token counts, analysed concurrently on separate
- * streams, workspaces and host threads (lane 0 uses the caller's stream),
- * each lane host-driven (launches sized from device counts read between
- * stages); results are identical for every value.  With more than one lane,
- * batch calls do not use graph capture.  APO_EINVAL outside 1..4. */
+/* Batches that go stage by stage (a window of more than 2^16 tokens, or the
+ * per-window selection off) are split into `lanes` (1..4, default 3) groups of
+ * consecutive windows with about equal token counts, analysed concurrently on
+ * separate streams and workspaces (lane 0 uses the caller's stream): as branches
+ * of one captured graph, or, with graphs off or a kernel being timed, each lane
+ * host-driven on its own host thread.  Results are identical for every value.
+ * APO_EINVAL outside 1..4. */
 int apo_set_lanes(apo_ctx *ctx, int lanes);
 
 /* Batches on one lane enqueue their whole launch sequence without host
@@ -249,9 +250,8 @@ int apo_inject_device_error(apo_ctx *ctx, int after_syncs);
  * window's candidates in priority order over an on-chip bitmap; longer
  * windows use the round-based evaluation.  Such single windows, and batches
  * whose windows all have at most 2^16 tokens, go through all stages in one
- * workgroup per window, unless a window over 8192 tokens has more than 8192
- * distinct ones, a kernel is being timed (apo_profile_kernel) or an error is to
- * be injected.  on = 0 sends every analysis stage by stage through the
+ * workgroup per window, unless a window holds 2^16 distinct tokens, a kernel is
+ * being timed (apo_profile_kernel) or an error is to be injected.  on = 0 sends every analysis stage by stage through the
  * rounds.  Results are identical either way.  APO_EINVAL
  * unless on is 0 or 1. */
 int apo_set_window_greedy(apo_ctx *ctx, int on);

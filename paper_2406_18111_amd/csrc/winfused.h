@@ -11,12 +11,13 @@ constexpr uint32_t kFusedMax = 8192;
 // Longest window one workgroup takes with its arrays in the workspace (positions
 // and ranks in 16 bits, one array of them in LDS at a time).
 constexpr uint32_t kFusedLongMax = 65536;
-constexpr uint32_t kFusedMidMax = 32768;  // and longest of a large batch that share a compute unit in twos
+// Longest window of a large batch that shares a compute unit with another.
+constexpr uint32_t kFusedMidMax = 32768;
 
 // What one window's analysis reports to the host (pinned memory).
 struct FusedInfo {
   uint32_t sigma, cands, maxl, m, accepted, rows, nhist;
-  uint32_t over;              // 1: too many distinct tokens for one workgroup, nothing else is set
+  uint32_t over;              // 1: 65536 distinct tokens, whose ranks 16 bits do not hold; nothing else is set
   uint32_t hist[kMaxRounds];  // suffixes still grouped after each doubling round
   uint64_t stamp[kStages + 1];
 };
@@ -35,7 +36,11 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info);
 // Batch of windows of at most kFusedLongMax 64-bit tokens each (offsets and
 // order in w.d_off and w.d_order): rows of all windows packed in window order
 // into w.rows, counts into w.win_rows, counters where finish_run reads them.
-// Windows with too many distinct tokens are left out and counted in CNT_WFLAG.
-void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, uint32_t min_len, hipStream_t s);
+// Windows of 65536 distinct tokens are left out and counted in CNT_WFLAG.  Uses w.wflag.
+// two: in two launches, where fused_in_two says so; either form is right for any
+// windows.
+bool fused_in_two(const uint64_t *off, uint32_t W);
+void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bool two, uint32_t min_len,
+                 hipStream_t s);
 
 }  // namespace apo

@@ -6,12 +6,13 @@
 // and 7 host synchronisations around a few microseconds of work each.  Here it
 // is one launch: the window's tokens are read once and its rows written once,
 // and the steps in between are separated by workgroup barriers.  Measured on
-// MI355X, whole calls: 250 tokens 748 -> 48 us, 4096 tokens 976 -> 190 us, 5000
-// tokens with occurrences 1191 -> 227 us, a batch of 64 windows of 250 to 5000
-// tokens 4.0 ms -> 329 us.  What bounds it now is the issue rate of one compute
-// unit (64 lanes per cycle): 4096 tokens take 138 us of kernel time, the token
-// ranks 11, the suffix sort 55, LCP 9, candidates 12, their sort 24, the greedy
-// 25.  A first form, radix passes over every suffix in every round, took 162.
+// MI355X, whole calls: 250 tokens 740 -> 45 us, 4096 tokens 960 -> 170 us, 5000
+// tokens with occurrences 1181 -> 204 us, a batch of 64 windows of 250 to 5000
+// tokens 4.1 ms -> 271 us.  What bounds it now is the issue rate of one compute
+// unit (64 lanes per cycle) and the steps' own latency: 4096 tokens take 118 us
+// of kernel time, the token ranks 8, the suffix sort 51, LCP 9, candidates 12,
+// their sort 19, the greedy 19.  A first form, radix passes over every suffix in
+// every round, took 162.
 #include "winfused.h"
 #include "device_util.h"
 #include "stages.h"
@@ -2058,12 +2059,13 @@ __global__ __launch_bounds__(kLongNT) void k_window_any(LongArgs la) {
   else if (n >= 2) window_short<kLongNT, kFusedMax / kLongNT>(la.f, L.s, win, tb, n);
 }
 
-// Batches of more windows than compute units, in two launches.  These analyses
+// Batches that keep the chip busy for long (fused_in_two), in two launches.  These analyses
 // wait for memory, LDS and barriers 60 % of the time and issue vector
 // instructions a third of it, so the windows of up to kFusedMidMax tokens run
 // two to a compute unit, with half the LDS and the registers of 64 wavefronts;
 // the longer ones, and those with more distinct tokens than half the table
-// takes, by themselves.
+// takes, by themselves (4096 windows of 256 to 65536 tokens: 2.1 ms of the one,
+// 3.8 of the other half of the tokens).
 __global__ __launch_bounds__(kLongNT, 8) void k_window_mid(LongArgs la) {
   __shared__ union Lds {
     ShortLds<kLongNT, 4> s;
@@ -2177,7 +2179,28 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
   for (int k = 0; k < kStages; k++) info.stage_ms[k] = (double)(f.stamp[k + 1] - f.stamp[k]) * 1e-5;  // 100 MHz
 }
 
-void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, uint32_t min_len, hipStream_t s) {
+// The two launches run one after the other, so each takes its longest window's
+// time at least; one launch fills the chip to its end.  Nanoseconds as measured:
+// a window alone 23 a token (30 with another on its compute unit), many of them
+// 34 a token and compute unit, in twos 22.  (Windows of 256 to 65536 tokens,
+// one launch and two: 1200 of them 1.98 and 2.87 ms, 4096 6.5 and 5.9; of 5000 to
+// 20000: 300 0.60 and 0.65, 600 0.98 and 0.78.)
+bool fused_in_two(const uint64_t *off, uint32_t W) {
+  uint64_t n[2] = {0, 0}, longest[2] = {0, 0};  // windows that share a compute unit, longer ones
+  for (uint32_t k = 0; k < W; k++) {
+    const uint64_t len = off[k + 1] - off[k];
+    const int side = len > kFusedMidMax;
+    n[side] += len;
+    longest[side] = std::max(longest[side], len);
+  }
+  if (std::max(longest[0], longest[1]) <= kFusedMax) return false;
+  const uint64_t one = std::max(23 * std::max(longest[0], longest[1]), 34 * (n[0] + n[1]) / 256);
+  const uint64_t two = std::max(23 * longest[1], 34 * n[1] / 256) + std::max(30 * longest[0], 22 * n[0] / 256);
+  return two < one;
+}
+
+void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bool two, uint32_t min_len,
+                 hipStream_t s) {
   fill_u32(w.dcnt, CNT_COUNT, 0, s);
   fill_u32(w.dcnt + CNT_FUSED, 1, 1, s);
   fill_u32(w.rhist, 4 * (uint64_t)w.nsnap, 0, s);
@@ -2195,7 +2218,7 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, ui
   a.dcnt = w.dcnt;
   a.rhist = w.rhist;
   a.win_rows = w.win_rows;
-  if (W > 256) la.again = w.wflag;
+  if (two) la.again = w.wflag;
   launch(la, W, longest, s);
   hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, W,
                      min_len, static_cast<Row *>(w.rows));

@@ -43,29 +43,31 @@ def test_large_batch(ctx):
     rng = np.random.default_rng(11)
     low = rng.integers(0, 2, (4, 12000)).astype(np.uint64)  # four high bytes that tie, low ones that differ
     tied = (low[0] << np.uint64(56)) | (low[1] << np.uint64(48)) | (low[2] << np.uint64(40)) | (low[3] << np.uint64(32))
-    wins = [synth.loop_stream(k, int(rng.integers(0, 400)), 20, 64, 0.05) for k in range(300)]
-    wins += [synth.loop_stream(k, n, 60, 500, 0.05) for k, n in enumerate((4096, 4097, 8193, 32767, 32768, 32769, 50000, 65536))]
-    wins += [_distinct(rng, n, d) for n, d in ((20000, 6144), (20000, 6145), (32768, 12000), (33000, 8193), (40000, 39000), (4097, 4097))]
-    wins += [tied | rng.permutation(12000).astype(np.uint64), np.full(32768, 3, np.uint64), rng.integers(0, 2, 30000).astype(np.uint64)]
-    order = rng.permutation(len(wins))
-    wins = [wins[k] for k in order]
-    toks = np.concatenate(wins)
-    off = np.zeros(len(wins) + 1, dtype=np.uint64)
-    off[1:] = np.cumsum([len(w) for w in wins])
-    refs = [_rows(oracle.find_repeats(w, 3)) for w in wins]
-    act = sum(_active(w) for w in wins)
-    for graphs in (True, False):
-        try:
-            ctx.set_graphs(graphs)
-            for rep in range(2):
-                print("graphs", graphs, "rep", rep, flush=True)
-                rows, oo = ctx.analyze_batch(toks, off, 3)
-                for w in range(len(wins)):
-                    assert np.array_equal(_as3(rows[int(oo[w]):int(oo[w + 1])]), refs[w]), (rep, w, len(wins[w]))
-                c = ctx.counters()
-                assert c["active_sum"] - len(toks) == act and c["sigma"] == sum(len(np.unique(w)) for w in wins)
-        finally:
-            ctx.set_graphs(True)
+    base = [synth.loop_stream(k, int(rng.integers(0, 400)), 20, 64, 0.05) for k in range(20)]
+    base += [synth.loop_stream(k, n, 60, 500, 0.05) for k, n in enumerate((4096, 4097, 8193, 32767, 32768, 32769, 50000, 65536))]
+    base += [_distinct(rng, n, d) for n, d in ((20000, 6144), (20000, 6145), (32768, 12000), (33000, 8193), (40000, 39000), (4097, 4097))]
+    base += [tied | rng.permutation(12000).astype(np.uint64), np.full(32768, 3, np.uint64), rng.integers(0, 2, 30000).astype(np.uint64)]
+    refs = [_rows(oracle.find_repeats(w, 3)) for w in base]
+    active = [_active(w) for w in base]
+    for times in (1, 44):  # one launch, and two (the sum of the windows keeps the chip busy long enough)
+        pick = rng.permutation(np.repeat(np.arange(len(base)), times))
+        toks = np.concatenate([base[k] for k in pick])
+        off = np.zeros(len(pick) + 1, dtype=np.uint64)
+        off[1:] = np.cumsum([len(base[k]) for k in pick])
+        for graphs in (True, False):
+            try:
+                ctx.set_graphs(graphs)
+                for rep in range(2):
+                    print("times", times, "graphs", graphs, "rep", rep, flush=True)
+                    rows, oo = ctx.analyze_batch(toks, off, 3)
+                    rows = _as3(rows)
+                    for w, k in enumerate(pick):
+                        assert np.array_equal(rows[int(oo[w]):int(oo[w + 1])], refs[k]), (rep, w, len(base[k]))
+                    c = ctx.counters()
+                    assert c["active_sum"] - len(toks) == sum(active[k] for k in pick)
+                    assert c["sigma"] == times * sum(len(np.unique(w)) for w in base)
+            finally:
+                ctx.set_graphs(True)
 
 
 def test_batch_of_all_distinct_tokens(ctx):
