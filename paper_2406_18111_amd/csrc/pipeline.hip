@@ -332,7 +332,7 @@ int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t 
   // longest first, in buckets of an eighth of a power of two (a counting sort): a long
   // window taken last would hold one workgroup while the others are idle
   // (with a bucket a power of two, 512 windows of 32769 to 65536 tokens took
-  // 3.8 ms on 256 compute units instead of 3.4).  Host-driven lanes keep the given
+  // 3.8 ms on 256 compute units instead of 3.5).  Host-driven lanes keep the given
   // order: there other lanes fill the idle compute units, and the step measured
   // slower with it
   constexpr uint32_t kBuckets = 65 * 8;

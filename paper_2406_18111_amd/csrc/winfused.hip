@@ -1079,16 +1079,16 @@ __device__ __forceinline__ uint32_t rank_lanes(Cnt *my, uint32_t d, uint64_t in)
 // wavefront's row of ctr): park(k, rank).  One LDS atomic per item took longer
 // than this, 22 us against 10 for 30011 items, since most lanes meet on a few
 // digits of a repetitive window.
-template <class Cnt, class Get, class Digit, class Park>
+template <int U, class Cnt, class Get, class Digit, class Park>
 __device__ __forceinline__ void byte_rank(Cnt *my, uint32_t beg, uint32_t end, Get get, Digit digit, Park park) {
   const uint32_t lane = threadIdx.x & 63;
 #pragma unroll 1
-  for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
-    decltype(get(0u)) v[4];
+  for (uint32_t q0 = beg; q0 < end; q0 += 64 * U) {  // scalar
+    decltype(get(0u)) v[U];
 #pragma unroll
-    for (int u = 0; u < 4; u++) v[u] = get(min(q0 + 64 * u + lane, end - 1));
+    for (int u = 0; u < U; u++) v[u] = get(min(q0 + 64 * u + lane, end - 1));
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
+    for (int u = 0; u < U; u++) {
       const uint32_t q = q0 + 64 * u;
       if (q >= end) continue;  // scalar
       const uint32_t r = rank_lanes(my, digit(v[u]), first_lanes(end - q));
@@ -1124,22 +1124,22 @@ __device__ __forceinline__ void byte_scan(Cnt *ctr, uint32_t *wsum) {
 }
 
 // Moves a wavefront's items to their places: put(place, item).
-template <class Cnt, class Get, class Digit, class Parked, class Put>
+template <int U, class Cnt, class Get, class Digit, class Parked, class Put>
 __device__ __forceinline__ void byte_move(const Cnt *my, uint32_t beg, uint32_t end, Get get, Digit digit,
                                           Parked parked, Put put) {
   const uint32_t lane = threadIdx.x & 63;
 #pragma unroll 1
-  for (uint32_t q0 = beg; q0 < end; q0 += 256) {  // scalar
-    decltype(get(0u)) v[4];
-    uint32_t r[4];
+  for (uint32_t q0 = beg; q0 < end; q0 += 64 * U) {  // scalar
+    decltype(get(0u)) v[U];
+    uint32_t r[U];
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
+    for (int u = 0; u < U; u++) {
       const uint32_t k = min(q0 + 64 * u + lane, end - 1);
       v[u] = get(k);
       r[u] = parked(k);
     }
 #pragma unroll
-    for (int u = 0; u < 4; u++)
+    for (int u = 0; u < U; u++)
       if (q0 + 64 * u + lane < end) put(my[digit(v[u])] + r[u], v[u]);
   }
 }
@@ -1177,6 +1177,7 @@ struct LongLds {
 template <uint32_t CAP, bool FIRST>
 __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L, uint32_t win, uint64_t tb, uint32_t n) {
   constexpr int NT = kLongNT, NW = kLongNW;
+  constexpr int U = CAP > kFusedMidMax ? 8 : 4;  // steps whose reads are issued together
   constexpr uint32_t kSlots = LongLds<CAP>::kSlots, kDistinct = LongLds<CAP>::kDistinct;
   const FusedArgs &a = la.f;
   auto &big = L.big;
@@ -1362,9 +1363,9 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
         };
         auto dig = [](uint32_t v) { return v >> 16; };
         clear_row();
-        byte_rank(my, kbeg, ktop, get, dig, park);
+        byte_rank<U>(my, kbeg, ktop, get, dig, park);
         byte_scan(ctr, wsum);
-        byte_move(my, kbeg, ktop, get, dig, parked, [=](uint32_t at, uint32_t v) { to[at] = v & 0xFFFFu; });
+        byte_move<U>(my, kbeg, ktop, get, dig, parked, [=](uint32_t at, uint32_t v) { to[at] = v & 0xFFFFu; });
         __syncthreads();
         dst = src;
         src = to;
@@ -1552,10 +1553,10 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
       auto get = [=](uint32_t k) { return src[k]; };
       auto dig = [=](uint64_t v) { return (uint32_t)(v >> sh) & 255u; };
       clear_row();
-      byte_rank(my, wbeg, wtop, get, dig, park);
+      byte_rank<U>(my, wbeg, wtop, get, dig, park);
       byte_scan(ctr, wsum);
       uint64_t *to = dst;
-      byte_move(my, wbeg, wtop, get, dig, parked, [=](uint32_t at, uint64_t v) { to[at] = v; });
+      byte_move<U>(my, wbeg, wtop, get, dig, parked, [=](uint32_t at, uint64_t v) { to[at] = v; });
       __syncthreads();
       dst = src;
       src = to;
@@ -1634,9 +1635,9 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
       // the wavefront's own entries first, then an even share of them all
       auto low = [](uint32_t e) { return (e >> 16) & 255u; };
       clear_row();
-      byte_rank(my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, low, park);
+      byte_rank<U>(my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, low, park);
       byte_scan(ctr, wsum);
-      byte_move(
+      byte_move<U>(
           my, wbeg, wbeg + mine, [=](uint32_t q) { return l0[q]; }, low, parked,
           [=](uint32_t at, uint32_t e) { l1[at] = e; });
       __syncthreads();
@@ -1644,9 +1645,9 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
       auto get = [=](uint32_t q) { return l1[q]; };
       auto dig = [](uint32_t e) { return e >> 24; };
       clear_row();
-      byte_rank(my, qbeg, qtop, get, dig, park);
+      byte_rank<U>(my, qbeg, qtop, get, dig, park);
       byte_scan(ctr, wsum);
-      byte_move(my, qbeg, qtop, get, dig, parked, [=](uint32_t at, uint32_t e) { l0[at] = e; });
+      byte_move<U>(my, qbeg, qtop, get, dig, parked, [=](uint32_t at, uint32_t e) { l0[at] = e; });
       __syncthreads();
       // openings of old and new groups among the sorted entries
       uint32_t lo = kNone, ln = kNone;
@@ -1854,9 +1855,9 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
       uint64_t *to = dst;
       auto get = [=](uint32_t k) { return from[k]; };
       clear_row();
-      byte_rank(my, beg, end, get, dig, park);
+      byte_rank<U>(my, beg, end, get, dig, park);
       byte_scan(ctr, wsum);
-      byte_move(my, beg, end, get, dig, parked, [=](uint32_t at, uint64_t v) { to[at] = v; });
+      byte_move<U>(my, beg, end, get, dig, parked, [=](uint32_t at, uint64_t v) { to[at] = v; });
       __syncthreads();
       dst = src;
       src = to;
