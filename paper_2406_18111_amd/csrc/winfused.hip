@@ -1444,7 +1444,8 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   // position in a 64-bit word.  So it does at once where that is three passes or
   // fewer (windows over a handful of tokens).
   const int tbits = bits_of(D);
-  uint32_t h = min((uint32_t)(63 / tbits), kLongPack);
+  // (a rare token spoils h words: with mostly rare ones there are some 0.75 h D)
+  uint32_t h = min(min((uint32_t)(63 / tbits), kLongPack), max(2u, kDistinct * 13 / (10 * D)));
   const uint32_t wbeg = min(wv * seg(n), n), wtop = min(wbeg + seg(n), n);  // the wavefront's tokens and slots
   bool named = !by_first && h >= 2 && min(48 / tbits, (int)kLongPack) * tbits > 24;
   bool lowered = false;
