@@ -822,22 +822,36 @@ struct GroupLds {
   Unit ud[T >> (kGroupMinCi + 1)];  // units per tile of the smallest handled class
   uint32_t uoff[(T >> (kGroupMinCi + 1)) + 1];
   uint32_t sh[kGroupThreads / 64];
-  uint32_t nd, act_base, item_c, item_b;
+  uint32_t nd, act_base, entries;
   uint32_t cls_loc[kClasses], cls_base[kClasses], cnt_c[kClasses];
 };
 
-// Tiles of the unit classes of a list, whose counts S.cnt_c gets.
-template <int TLG>
+// Units of a class in a tile of `entries` (a power of two).
+__device__ __forceinline__ uint32_t tile_units(uint32_t entries, int ci) { return max(entries >> (ci + 1), 1u); }
+
+// Tiles of the unit classes of a list, whose counts S.cnt_c gets.  A tile holds
+// 2^TLG entries, or kFewEntries while there are still no more of them than
+// kFewTiles (where the caller takes a round's units together): a round's last
+// tile is its latency, and with larger ones most of the chip would have none
+// (n = 131071: 50 tiles of 2048 entries; suffix array 426 us, with 512 entries
+// 382).  With 400 tiles and more of 512 the larger ones were faster again (n = 2^20:
+// 42 and 53 us a round instead of 33 and 35).
+constexpr uint32_t kFewEntries = 512, kFewTiles = 256;
+template <int TLG, bool FEW>
 __device__ __forceinline__ uint32_t group_tiles(const SortBufs &B, int cur, GroupLds<TLG> &S) {
   const int ci_hi = min((int)B.tile_log, TLG);
   if (threadIdx.x < kClasses) S.cnt_c[threadIdx.x] = B.ctr->cls_cnt[cur][threadIdx.x];
   __syncthreads();
-  uint32_t tot = 0;
+  uint32_t tot = 0, few = 0;
   for (int ci = kGroupMinCi; ci < ci_hi; ci++) {
-    const uint32_t per = (1u << TLG) >> (ci + 1);
-    tot += (S.cnt_c[ci] + per - 1) / per;
+    const uint32_t c = S.cnt_c[ci], per = tile_units(1u << TLG, ci), per_few = tile_units(kFewEntries, ci);
+    tot += (c + per - 1) / per;
+    few += (c + per_few - 1) / per_few;
   }
-  return tot;
+  const bool use_few = FEW && few <= kFewTiles;
+  if (threadIdx.x == 0) S.entries = use_few ? kFewEntries : 1u << TLG;
+  __syncthreads();
+  return use_few ? few : tot;
 }
 
 // One tile by one workgroup.
@@ -852,25 +866,21 @@ __device__ __forceinline__ void group_tile(const SortBufs &B, int cur, const Ran
   const int nxt = cur ^ 1;
   const int tid = threadIdx.x;
   const int ci_hi = min((int)B.tile_log, TLG);
-  if (tid == 0) {
-    uint32_t it = item;
-    int ci = kGroupMinCi;
-    for (; ci < ci_hi; ci++) {
-      const uint32_t per = (uint32_t)T >> (ci + 1);
-      const uint32_t ni = (S.cnt_c[ci] + per - 1) / per;
-      if (it < ni) break;
-      it -= ni;
-    }
-    S.item_c = (uint32_t)ci;
-    S.item_b = it;
-    S.nd = 0;
+  uint32_t it = item;
+  int ci = kGroupMinCi;
+  for (; ci < ci_hi; ci++) {  // uniform
+    const uint32_t per = tile_units(S.entries, ci);
+    const uint32_t ni = (S.cnt_c[ci] + per - 1) / per;
+    if (it < ni) break;
+    it -= ni;
   }
+  const uint32_t slots = 2 * max(S.entries, 2u << ci);  // of the table
+  if (tid == 0) S.nd = 0;
   if (tid < kClasses) S.cls_loc[tid] = 0;
-  for (int h = tid; h < HT; h += NT) S.tab[h] = 0;
+  for (uint32_t h = tid; h < slots; h += NT) S.tab[h] = 0;
   __syncthreads();
-  const int ci = (int)S.item_c;
-  const uint32_t per = (uint32_t)T >> (ci + 1);
-  const uint32_t first = S.item_b * per;
+  const uint32_t per = tile_units(S.entries, ci);
+  const uint32_t first = it * per;
   const uint32_t nb = min(per, S.cnt_c[ci] - first);
   const Unit *src = B.cls[cur] + B.cls_off[ci] + first;
   // unit descriptors and compact offsets (nb <= MAXU <= NT)
@@ -928,7 +938,7 @@ __device__ __forceinline__ void group_tile(const SortBufs &B, int cur, const Ran
     eslot[q] = 0;
     if (p < total) {
       const uint32_t key = S.K[p], j = S.EJ[p];
-      uint32_t h = (uint32_t)(mix64(((uint64_t)j << 32) | key) >> 20) & (HT - 1);
+      uint32_t h = (uint32_t)(mix64(((uint64_t)j << 32) | key) >> 20) & (slots - 1);
       while (true) {
         uint32_t prev = S.tab[h];
         if (prev == 0u) prev = atomicCAS(&S.tab[h], 0u, (1u << 16) | (p + 1));
@@ -942,7 +952,7 @@ __device__ __forceinline__ void group_tile(const SortBufs &B, int cur, const Ran
           agg_add(&S.tab[h], 1u << 16);
           break;
         }
-        h = (h + 1) & (HT - 1);
+        h = (h + 1) & (slots - 1);
       }
       eslot[q] = h;
     }
@@ -1052,7 +1062,7 @@ template <int MODE, int TLG>
 __global__ __launch_bounds__(kGroupThreads, TLG == 11 ? 6 : 2) void k_lds_group(SortBufs B, int cur, RankOut R,
                                                                                int last_level, uint8_t *keep) {
   __shared__ GroupLds<TLG> S;
-  const uint32_t total = group_tiles<TLG>(B, cur, S);
+  const uint32_t total = group_tiles<TLG, false>(B, cur, S);
   uint32_t deferred = 0;
   // items are handed out XCD by XCD: neighbouring tiles hold units of
   // neighbouring windows, whose scattered rank writes then merge in one L2
@@ -1611,7 +1621,7 @@ __global__ __launch_bounds__(kGroupThreads, 4) void k_sort_units(SortBufs B, int
   uint32_t bulk_units, bulk_chunks, deferred = 0;
   list_size(B.ctr->bulk_pk, B.big_cap, bulk_units, bulk_chunks);
   const WaveList W = wave_list(B, cur);
-  const uint32_t tiles = group_tiles<11>(B, cur, S);
+  const uint32_t tiles = group_tiles<11, true>(B, cur, S);
   const uint32_t total = tiles + bulk_chunks + (W.total() + kBatch - 1) / kBatch;
   for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
     if (i < tiles)
