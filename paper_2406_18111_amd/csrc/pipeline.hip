@@ -271,8 +271,7 @@ static void sort_plain(Workspace &w, const uint32_t *count_dev, uint64_t bound, 
                        int nlevels, uint8_t *keep, hipStream_t s) {
   SortEngine &E = w.eng;
   int cur = 0;
-  E.reset_counters(s);
-  E.round_begin(cur, s);
+  E.reset_counters(s);  // opens the first round too
   E.iota_val(count_dev, bound, s);
   E.gather_field(cur, fields[0], strides[0], count_dev, subs[0], c_devs[0], 0, bound, s);
   uint64_t *rng = reinterpret_cast<uint64_t *>(w.dcnt + CNT_RANGE);
@@ -374,7 +373,6 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       if ((rc = upload_windows(w, h_off, W, s, true))) return rc;
     w.pair_w = W > 1 ? W : 0;
     w.kev_n = 0;
-    E.reset_counters(s);
     fused_batch(w, d_tok, W, maxwin, fused_in_two(h_off, W), min_len, s);
     if (mode == Mode::CAPTURE) return 0;
     rc = finish_run(w, N, W, N, 1, info, s, false);
@@ -396,11 +394,8 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     wend = w.wend;
     wid = w.wid;
   }
-  fill_u32(dc, CNT_RANGE, 0, s);
-  fill_u32(dc + CNT_NDSUM, 8, 0, s);
-  fill_u32(dc + CNT_SNAPS, 1, 0, s);
-  fill_u32(dc + CNT_FUSED, 1, 0, s);
-  fill_u32(w.rhist, 4 * (uint64_t)w.nsnap, 0, s);
+  const uint32_t zeroed = ((1u << CNT_RANGE) - 1) | (0xFFu << CNT_NDSUM) | (1u << CNT_SNAPS) | (1u << CNT_FUSED);
+  clear_run(dc, zeroed, CNT_COUNT, w.rhist, 4 * (uint32_t)w.nsnap, nullptr, 0, nullptr, 0, s);
 
   // ---- order-preserving token ranks
   const uint32_t *key0;
@@ -515,8 +510,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   const uint32_t rel_bits = (uint32_t)bit_length_u64(std::max<uint64_t>(maxwin, 1));
   const int r_max = ceil_log2_u64(std::max<uint64_t>(maxwin, 2)) + 1;  // rounds 0..r_max-1 suffice
   int cur = 0;
-  E.reset_counters(s);
-  E.round_begin(cur, s);
+  E.reset_counters(s);  // opens the first round too
   if (win_r0) {
     if (!skip0) {
       E.gather_identity(key0, (uint32_t)N, s, wid, w.wflag, dc + CNT_WFLAG);
@@ -676,12 +670,9 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
                         w.tmp_d, dc + CNT_AUX, w.tile_tmp, s, wkey ? wid : nullptr, lbits, wseg ? wid : nullptr, W,
                         w.o_len);
     E.reset_counters(s);
-    E.round_begin(0, s);
-    E.iota_val(dc + CNT_C, c_bound, s);
-    run_flags(w.tmp_a, w.tmp_c, dc + CNT_C, c_bound, w.keep, s);
-    flag_positions(w.keep, dc + CNT_C, c_bound, w.tmp_d, dc + CNT_AUX, w.tile_tmp, s);
+    run_setup(w.tmp_a, w.tmp_c, dc + CNT_C, c_bound, w.state, B.val[0], w.keep, s);
+    flag_positions(w.state, dc + CNT_C, c_bound, w.tmp_d, dc + CNT_AUX, w.tile_tmp, s);
     E.init_runs(0, w.tmp_d, dc + CNT_AUX, dc + CNT_C, c_bound, rank_bits, s);
-    fill_u8_dev(w.keep, dc + CNT_C, c_bound, 1, s);
     if (c_bound > kMsdUnitMax) E.msd(0, c_bound, (int)rank_bits, s);
     else if (c_bound > (1ull << E.tile_log())) E.msd_units(0, c_bound, s);
     E.units_plain(0, 0, 1, w.keep, c_bound, s);
@@ -720,13 +711,9 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     if (host && w.sel_prefix > 0) kpre = (uint32_t)std::min<uint64_t>((uint64_t)w.sel_prefix, m_bound);
     if (host && w.sel_prefix < 0 && maxl_bound * kSelPrefixDiv >= N)
       kpre = (uint32_t)std::min<uint64_t>(kSelPrefixAuto, m_bound);
-    if (!kpre) sel_table_init(Ta, N, dc + CNT_MAXL, top, s);
-    fill_u32(w.selcnt, 3 * (kSelRoundCap + 2), 0, s);
     const uint64_t npad = pow2_at_least(N);
-    fill_u32(w.ctree, 2 * npad, 0xFFFFFFFFu, s);
-    fill_u8(w.mark, N, 0, s);
-    copy_u32(nlive, dc + CNT_M, s);
-    sel_init(w.live[1], nlive, w.state, m_bound, s);
+    sel_init({kpre ? nullptr : Ta, N, dc + CNT_MAXL, dc + CNT_M, top, w.ctree, npad, w.mark, w.live[1], w.state,
+              w.selcnt, 3 * (kSelRoundCap + 2)}, m_bound, s);
     const int ahead = host ? 2 : kSelFreeRounds;
     int q0 = 0;
     uint64_t hint = m_bound;
@@ -782,8 +769,8 @@ int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t
   SortBufs &B = w.eng.bufs();
   uint32_t *dc = w.dcnt;
   int rc;
-  fill_u32(dc + CNT_A, 1, 0, s);
-  fill_u32(dc + CNT_NROWS, 1, 0, s);
+  static_assert(CNT_NROWS == CNT_A + 1, "cleared together");
+  fill_u32(dc + CNT_A, 2, 0, s);
   if (batch) fill_u32(w.win_rows, W + 1, 0, s);
   if (m_bound == 0) return 0;
   gather_accepted(w.state, dc + CNT_M, m_bound, w.s_len, w.s_start, w.s_id, w.o_len, w.o_start, w.o_id, w.tile_tmp,

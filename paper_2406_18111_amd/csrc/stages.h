@@ -13,6 +13,8 @@ void fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 void fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s);
 void fill_u8_dev(uint8_t *p, const uint32_t *n_dev, uint64_t bound, uint8_t v, hipStream_t s);
 void copy_u32(uint32_t *dst, const uint32_t *src, hipStream_t s);
+void clear_run(uint32_t *cnt, uint32_t mask, uint32_t set, uint32_t *a, uint32_t na, uint32_t *b, uint32_t nb,
+               uint32_t *c, uint32_t nc, hipStream_t s);
 void copy_n_u32(uint32_t *dst, const uint32_t *src, uint64_t n, hipStream_t s);
 void scan_excl(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint64_t bound, uint32_t *tile_tmp,
                uint32_t *total, hipStream_t s);
@@ -111,8 +113,8 @@ void lsd_sort_candidates(const uint32_t *crec, const uint32_t *maxl_dev, const u
                          int wshift, const uint32_t *seg_wid, uint32_t nseg, uint32_t *seg);
 constexpr uint64_t kLsdTileRecords = 4096;
 // flag[i] = 1 where (key, p2) differs from position i - 1.
-void run_flags(const uint32_t *key, const uint32_t *p2, const uint32_t *n_dev, uint64_t bound, uint8_t *flag,
-               hipStream_t s);
+void run_setup(const uint32_t *key, const uint32_t *p2, const uint32_t *n_dev, uint64_t bound, uint8_t *flag,
+               uint32_t *val, uint8_t *keep, hipStream_t s);
 // Positions of the set flags, in order; *count receives their number.
 void flag_positions(const uint8_t *flag, const uint32_t *n_dev, uint64_t bound, uint32_t *out, uint32_t *count,
                     uint32_t *tile_tmp, hipStream_t s);
@@ -128,8 +130,19 @@ void compact_sorted(const uint32_t *order, const uint8_t *keep, const uint32_t *
                     uint32_t *total, hipStream_t s);
 
 // Empties the levels of a selection sparse table that a run can use.
-void sel_table_init(uint32_t *T, uint64_t n, const uint32_t *maxl, int top, hipStream_t s);
-void sel_init(uint32_t *work, const uint32_t *nlive_dev, uint8_t *state, uint64_t bound, hipStream_t s);
+struct SelInit {
+  uint32_t *T;  // first round's sparse table, null where that round is skipped
+  uint64_t n;
+  const uint32_t *maxl, *m_dev;
+  int top;
+  uint32_t *ctree;
+  uint64_t npad;
+  uint8_t *mark;
+  uint32_t *work;
+  uint8_t *state;
+  uint32_t *selcnt, nselcnt;  // selcnt[0]: the candidates, the rest 0
+};
+void sel_init(const SelInit &a, uint64_t bound, hipStream_t s);
 // One selection round: filter by painted positions (r >= 1), then dense
 // (sparse table over all positions) or sparse (canonical blocks of the
 // working list) evaluation, chosen on the device.  Round 0 works on `work`

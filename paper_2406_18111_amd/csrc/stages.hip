@@ -29,6 +29,24 @@ void fill_u8(uint8_t *p, uint64_t n, uint8_t v, hipStream_t s) {
   if (n) hipLaunchKernelGGL(k_fill_u8, grid_for(n, 256, 8192), dim3(256), 0, s, p, n, v);
 }
 
+// A run's counters in one launch: the words of `cnt` named by `mask` become 0,
+// word `set` 1 if it is below 32, and three ranges 0.  A launch that follows
+// another costs some 4.5 us however little it does.  With this, the set-ups of the
+// candidate sort and of the selection and the upper block minima in one launch
+// each, 18 fewer: one window of 131071 tokens 1058 -> 1001 us, of 2^20 1758 -> 1722.
+__global__ __launch_bounds__(256) void k_clear_run(uint32_t *cnt, uint32_t mask, uint32_t set, uint32_t *a,
+                                                   uint32_t na, uint32_t *b, uint32_t nb, uint32_t *c, uint32_t nc) {
+  const uint32_t t = threadIdx.x;
+  if (t < 32 && (mask >> t & 1)) cnt[t] = t == set;
+  for (uint32_t i = t; i < na; i += blockDim.x) a[i] = 0;
+  for (uint32_t i = t; i < nb; i += blockDim.x) b[i] = 0;
+  for (uint32_t i = t; i < nc; i += blockDim.x) c[i] = 0;
+}
+void clear_run(uint32_t *cnt, uint32_t mask, uint32_t set, uint32_t *a, uint32_t na, uint32_t *b, uint32_t nb,
+               uint32_t *c, uint32_t nc, hipStream_t s) {
+  hipLaunchKernelGGL(k_clear_run, dim3(1), dim3(256), 0, s, cnt, mask, set, a, na, b, nb, c, nc);
+}
+
 // ------------------------------------------------------ device-wide scan
 // Exclusive prefix sum of u32 values (sums fit in u32).  Three phases:
 // per-tile sums, one-workgroup scan of the tile sums, per-tile rescan.
@@ -1388,6 +1406,37 @@ __global__ void k_blockmin(const uint32_t *src, uint64_t nsrc, uint32_t *dst, ui
   }
 }
 
+// The further levels by one workgroup, a level's writes read by the next: they are
+// launches of 4.5 us otherwise, three of them at 2^20 tokens.  Up to 65536 entries below
+// the first: four results a thread, each one round of loads.
+constexpr uint64_t kUpperMax = 65536;  // entries below the first of them
+struct MinUpper {
+  uint32_t *lv[kMinLevels];
+  uint64_t sz[kMinLevels];
+  int from, to;  // levels [from, to), level from - 1 is there
+};
+__global__ __launch_bounds__(1024) void k_blockmin_upper(MinUpper M) {
+  for (int k = M.from; k < M.to; k++) {
+    const uint32_t *src = M.lv[k - 1];
+    const uint64_t nsrc = M.sz[k - 1];
+    for (uint64_t j = threadIdx.x; j < M.sz[k]; j += blockDim.x) {
+      uint32_t m = 0xFFFFFFFFu;
+      if ((j + 1) * kMinFan <= nsrc) {
+        const uint4 *q = reinterpret_cast<const uint4 *>(src + j * kMinFan);
+#pragma unroll
+        for (int u = 0; u < kMinFan / 4; u++) {
+          const uint4 v = q[u];
+          m = min(min(m, min(v.x, v.y)), min(v.z, v.w));
+        }
+      } else {
+        for (uint64_t i = j * kMinFan; i < nsrc; i++) m = min(m, src[i]);
+      }
+      M.lv[k][j] = m;
+    }
+    __syncthreads();
+  }
+}
+
 struct MinLevels {
   const uint32_t *lv[kMinLevels];
   uint64_t sz[kMinLevels];
@@ -1611,7 +1660,7 @@ __global__ __launch_bounds__(256, 6) void k_candidates(const uint32_t *sa, const
 
 // Sum of the tiles' skipped repeats and maximum of their longest lengths.
 __global__ __launch_bounds__(1024) void k_tile_totals(const uint32_t *skip, const uint32_t *mx, uint32_t ntiles,
-                                                      uint32_t *skipped, uint32_t *maxl) {
+                                                      uint32_t *skipped, uint32_t *maxl, uint32_t *ntiles_out) {
   __shared__ uint32_t ssum, smax;
   if (threadIdx.x == 0) ssum = smax = 0;
   __syncthreads();
@@ -1629,6 +1678,7 @@ __global__ __launch_bounds__(1024) void k_tile_totals(const uint32_t *skip, cons
   if (threadIdx.x == 0) {
     *skipped = ssum;
     *maxl = smax;
+    *ntiles_out = max(ntiles, 1u);
   }
 }
 
@@ -1640,21 +1690,28 @@ void gen_candidates(const uint32_t *sa, const uint32_t *lcp, uint64_t n, const u
   M.lv[0] = lcp;
   M.sz[0] = n;
   M.nlev = 1;
+  MinUpper U{};
   for (int k = 1; k < nlev && k < kMinLevels && sz > (uint64_t)kMinFan; k++) {
     const uint64_t nd = (sz + kMinFan - 1) / kMinFan;
-    hipLaunchKernelGGL(k_blockmin, grid_for(nd, 256, 8192), dim3(256), 0, s, M.lv[k - 1], sz, levels[k], nd);
-    M.lv[k] = levels[k];
-    M.sz[k] = nd;
+    if (sz > kUpperMax || k == 1)
+      hipLaunchKernelGGL(k_blockmin, grid_for(nd, 256, 8192), dim3(256), 0, s, M.lv[k - 1], sz, levels[k], nd);
+    else if (!U.from)
+      U.from = k;
+    M.lv[k] = U.lv[k] = levels[k];
+    M.sz[k] = U.sz[k] = nd;
     M.nlev = k + 1;
     sz = nd;
+  }
+  if (U.from) {
+    U.to = M.nlev;
+    hipLaunchKernelGGL(k_blockmin_upper, dim3(1), dim3(1024), 0, s, U);
   }
   const uint64_t span = 256 * kCandItems;
   const uint64_t ntiles = std::max<uint64_t>((n + span - 1) / span, 1);
   const dim3 grid((unsigned)std::min<uint64_t>(ntiles, 8192));
   hipLaunchKernelGGL((k_candidates<false>), grid, dim3(256), 0, s, sa, lcp, n, wend, min_len, M, tile_val, crec);
   hipLaunchKernelGGL(k_tile_totals, dim3(1), dim3(1024), 0, s, tile_val + ntiles, tile_val + 2 * ntiles,
-                     (uint32_t)((n + span - 1) / span), skipped, maxl);
-  fill_u32(ntiles_dev, 1, (uint32_t)ntiles, s);
+                     (uint32_t)((n + span - 1) / span), skipped, maxl, ntiles_dev);
   scan_excl(tile_val, tile_val, ntiles_dev, ntiles, tile_tmp, cnt, s);  // tile offsets; *cnt = records
   hipLaunchKernelGGL((k_candidates<true>), grid, dim3(256), 0, s, sa, lcp, n, wend, min_len, M, tile_val, crec);
 }
@@ -1969,14 +2026,20 @@ void lsd_sort_candidates(const uint32_t *crec, const uint32_t *maxl_dev, const u
   }
 }
 
-// Run starts of equal (key, p2) in the sorted order, as byte flags.
-__global__ void k_run_flags(const uint32_t *key, const uint32_t *p2, const uint32_t *n_dev, uint8_t *flag) {
+// Run starts of equal (key, p2) in the sorted order, as byte flags; the
+// entries in order and the kept flags for the sort of the runs.
+__global__ void k_run_setup(const uint32_t *key, const uint32_t *p2, const uint32_t *n_dev, uint8_t *flag,
+                            uint32_t *val, uint8_t *keep) {
   const uint64_t n = *n_dev;
-  GRID_STRIDE(i, n) flag[i] = (i == 0 || key[i] != key[i - 1] || p2[i] != p2[i - 1]) ? 1 : 0;
+  GRID_STRIDE(i, n) {
+    flag[i] = (i == 0 || key[i] != key[i - 1] || p2[i] != p2[i - 1]) ? 1 : 0;
+    val[i] = (uint32_t)i;
+    keep[i] = 1;
+  }
 }
-void run_flags(const uint32_t *key, const uint32_t *p2, const uint32_t *n_dev, uint64_t bound, uint8_t *flag,
-               hipStream_t s) {
-  hipLaunchKernelGGL(k_run_flags, grid_for(bound, 256, 8192), dim3(256), 0, s, key, p2, n_dev, flag);
+void run_setup(const uint32_t *key, const uint32_t *p2, const uint32_t *n_dev, uint64_t bound, uint8_t *flag,
+               uint32_t *val, uint8_t *keep, hipStream_t s) {
+  hipLaunchKernelGGL(k_run_setup, grid_for(bound, 256, 8192), dim3(256), 0, s, key, p2, n_dev, flag, val, keep);
 }
 
 struct StoreIndex {
@@ -2362,28 +2425,31 @@ __global__ void k_sel_sparse_cover(SelArgs a) {
   }
 }
 
-__global__ void k_iota(uint32_t *p, const uint32_t *n) {
-  const uint32_t m = *n;
-  GRID_STRIDE(i, m) p[i] = (uint32_t)i;
+// Everything the rounds start from, in one launch instead of seven: levels
+// 0..min(top, log2 maxl) of the sparse table (the only ones a run touches;
+// T null: none), the cover tree, the marks, the list of all candidates, their
+// states and the rounds' counters.
+__global__ __launch_bounds__(256) void k_sel_init(SelInit a) {
+  const uint32_t m = *a.m_dev;
+  const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+  if (a.T) {
+    const uint32_t ml = *a.maxl;
+    const int lv = ml ? 32 - __clz((int)ml) : 1;
+    const uint64_t lim = (uint64_t)min(lv, a.top + 1) * a.n;
+    for (uint64_t i = t0; i < lim; i += step) a.T[i] = kInf;
+  }
+  for (uint64_t i = t0; i < 2 * a.npad; i += step) a.ctree[i] = 0xFFFFFFFFu;
+  for (uint64_t i = t0; i < a.n; i += step) a.mark[i] = 0;
+  for (uint64_t i = t0; i < m; i += step) {
+    a.work[i] = (uint32_t)i;
+    a.state[i] = 0;
+  }
+  for (uint64_t i = t0; i < a.nselcnt; i += step) a.selcnt[i] = i ? 0 : m;
 }
 
-// Fills levels 0..min(top, log2 maxl) of a sparse table (the only ones a
-// run touches).
-__global__ void k_fill_levels(uint32_t *p, uint64_t n, const uint32_t *maxl, int top, uint32_t v) {
-  const uint32_t ml = *maxl;
-  const int lv = ml ? 32 - __clz((int)ml) : 1;
-  const uint64_t lim = (uint64_t)min(lv, top + 1) * n;
-  GRID_STRIDE(i, lim) p[i] = v;
-}
-
-void sel_table_init(uint32_t *T, uint64_t n, const uint32_t *maxl, int top, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_levels, grid_for((uint64_t)(top + 1) * n, 256, 8192), dim3(256), 0, s, T, n, maxl, top,
-                     kInf);
-}
-
-void sel_init(uint32_t *work, const uint32_t *nlive_dev, uint8_t *state, uint64_t bound, hipStream_t s) {
-  hipLaunchKernelGGL(k_iota, grid_for(bound, 256, 8192), dim3(256), 0, s, work, nlive_dev);
-  fill_u8_dev(state, nlive_dev, bound, 0, s);
+void sel_init(const SelInit &a, uint64_t bound, hipStream_t s) {
+  const uint64_t most = std::max(std::max(2 * a.npad, bound), a.T ? (uint64_t)(a.top + 1) * a.n : 0);
+  hipLaunchKernelGGL(k_sel_init, grid_for(most, 256, 8192), dim3(256), 0, s, a);
 }
 
 void sel_round(const uint32_t *len, const uint32_t *start, uint32_t *Tc, uint32_t *To, int top, uint64_t n,

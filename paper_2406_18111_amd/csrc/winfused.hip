@@ -2203,10 +2203,9 @@ bool fused_in_two(const uint64_t *off, uint32_t W) {
 
 void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bool two, uint32_t min_len,
                  hipStream_t s) {
-  fill_u32(w.dcnt, CNT_COUNT, 0, s);
-  fill_u32(w.dcnt + CNT_FUSED, 1, 1, s);
-  fill_u32(w.rhist, 4 * (uint64_t)w.nsnap, 0, s);
-  fill_u32(w.selcnt, 3 * (kSelRoundCap + 2), 0, s);
+  static_assert(CNT_COUNT == 32, "one bit a word");
+  clear_run(w.dcnt, ~0u, CNT_FUSED, w.rhist, 4 * (uint32_t)w.nsnap, w.selcnt, 3 * (kSelRoundCap + 2),
+            reinterpret_cast<uint32_t *>(w.eng.bufs().ctr), sizeof(SortCounters) / 4, s);
   LongArgs la = args_of(w);
   FusedArgs &a = la.f;
   a.tok = tok;

@@ -121,3 +121,17 @@ def test_units_of_mostly_one_key(ctx, kind):
     assert np.array_equal(_as3(rows), _rows(ref))
     act = oracle.suffix_array(t.astype(np.uint64), return_active=True)[1]
     assert ctx.counters()["active_sum"] - n == int(act.sum())
+
+
+@pytest.mark.parametrize("n", (1 << 20, (1 << 20) + 1, (1 << 20) + 273))
+def test_block_minima_over_several_levels(ctx, n):
+    """Either side of the size up to which one workgroup takes every level of
+    block minima above the first: repeats from a few tokens that occur in every
+    block to one half of the window, so that the walks use all levels."""
+    rng = np.random.default_rng(n)
+    t = rng.integers(0, 1 << 14, n).astype(np.uint32)
+    t[n // 2: n // 2 + n // 3] = t[: n // 3]
+    t[rng.integers(0, n - 4, 50000)[:, None] + np.arange(4)] = np.array([5, 6, 7, 8], np.uint32)
+    rows = ctx.analyze(t, 3)
+    ref = oracle.find_repeats(t.astype(np.uint64), 3)
+    assert np.array_equal(_as3(rows), _rows(ref))
