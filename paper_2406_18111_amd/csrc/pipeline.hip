@@ -737,9 +737,16 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       q0 = hi;
       sel_launched = hi;
       if (!host) break;  // checked after the output stage
+      sel_tail(w.s_len, w.s_start, w.state, w.live[0], nlive, hi, cap, N, dc + CNT_MAXL, w.ctree, npad, w.mark, s);
       if ((rc = read_counters(w, s))) return rc;
-      for (int q = lo; q < hi; q++)
-        if (w.hsel[q + 1] == 0) { sel_done = q; break; }  // nlive[q + 1]: undecided after round q
+      // nlive[q + 1]: undecided after round q
+      for (int q = lo; q < hi && sel_done < 0; q++)
+        if (w.hsel[q + 1] == 0) sel_done = q;
+      if (sel_done < 0 && w.hsel[hi] <= kSelTail) {  // then the rest is done too, up to the cap
+        for (q0 = hi; q0 < cap && sel_done < 0; q0++)
+          if (w.hsel[q0 + 1] == 0) sel_done = q0;
+        sel_launched = q0;
+      }
       if (sel_done < 0) hint = w.hsel[hi];
     }
     if (host && sel_done < 0) {

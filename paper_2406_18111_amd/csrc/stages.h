@@ -143,6 +143,12 @@ struct SelInit {
   uint32_t *selcnt, nselcnt;  // selcnt[0]: the candidates, the rest 0
 };
 void sel_init(const SelInit &a, uint64_t bound, hipStream_t s);
+// Rounds r..cap-1 at once where at most kSelTail candidates are undecided before
+// round r (1 to kSelTail; nothing otherwise).  More threads do not fit a workgroup.
+constexpr uint32_t kSelTail = 1024;
+void sel_tail(const uint32_t *len, const uint32_t *start, uint8_t *state, uint32_t *pend, uint32_t *nlive, int r,
+              int cap, uint64_t n, const uint32_t *maxl, uint32_t *ctree, uint64_t npad, uint8_t *mark,
+              hipStream_t s);
 // One selection round: filter by painted positions (r >= 1), then dense
 // (sparse table over all positions) or sparse (canonical blocks of the
 // working list) evaluation, chosen on the device.  Round 0 works on `work`

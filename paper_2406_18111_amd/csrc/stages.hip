@@ -2425,6 +2425,40 @@ __global__ void k_sel_sparse_cover(SelArgs a) {
   }
 }
 
+// The rounds from a.r on by one workgroup, an undecided candidate a thread, once
+// that few are left: the same rounds by the same tree, their phases parted by fences and
+// barriers.  As launches a round is nine and a report the host waits for.  Windows of
+// nested loops leave 17 to 300 candidates after two rounds: n = 131071 1001 -> 962 us in
+// all (selection now 124), 2^20 1722 -> 1690 (216).
+__global__ __launch_bounds__(kSelTail) void k_sel_tail(SelArgs a, int cap) {
+  const uint32_t m = a.nlive[a.r];
+  if (m == 0 || m > kSelTail) return;
+  const uint32_t ml = *a.maxl;
+  const int levels = ml ? 32 - __clz((int)ml) : 1;
+  bool on = threadIdx.x < m;
+  const uint32_t k = on ? a.pend[threadIdx.x] : 0u;
+  const uint32_t s = on ? a.start[k] : 0u, l = on ? a.len[k] : 1u, e = s + l - 1;
+  for (int r = a.r; r < cap; r++) {
+    if (on && (a.mark[s] || a.mark[e])) {
+      a.state[k] = 2;
+      on = false;
+    }
+    if (on) ctree_cover<false>(a, s, l, k);
+    __threadfence();
+    __syncthreads();
+    const bool acc = on && ctree_point(a, s, levels) >= k && ctree_point(a, e, levels) >= k;
+    __syncthreads();  // the tree has been read
+    if (on) ctree_cover<true>(a, s, l, k);
+    if (acc) a.state[k] = 1;
+    paint_wave(a.mark, acc, s, l);
+    on = on && !acc;
+    __threadfence();
+    const int left = __syncthreads_count(on);
+    if (threadIdx.x == 0) a.nlive[r + 1] = (uint32_t)left;
+    if (!left) break;
+  }
+}
+
 // Everything the rounds start from, in one launch instead of seven: levels
 // 0..min(top, log2 maxl) of the sparse table (the only ones a run touches;
 // T null: none), the cover tree, the marks, the list of all candidates, their
@@ -2473,6 +2507,14 @@ void sel_round(const uint32_t *len, const uint32_t *start, uint32_t *Tc, uint32_
     hipLaunchKernelGGL(k_sel_decide<false>, g, dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_sel_sparse_cover<true>, g, dim3(256), 0, s, a);
   }
+}
+
+void sel_tail(const uint32_t *len, const uint32_t *start, uint8_t *state, uint32_t *pend, uint32_t *nlive, int r,
+              int cap, uint64_t n, const uint32_t *maxl, uint32_t *ctree, uint64_t npad, uint8_t *mark,
+              hipStream_t s) {
+  SelArgs a{len, start, nullptr, nullptr, n, 0, state, pend, nullptr, nlive, nullptr, nullptr, r, maxl, ctree, npad,
+            mark};
+  hipLaunchKernelGGL(k_sel_tail, dim3(1), dim3(kSelTail), 0, s, a, cap);
 }
 
 // Exact sequential completion for whatever is still undecided after the

@@ -135,3 +135,28 @@ def test_block_minima_over_several_levels(ctx, n):
     rows = ctx.analyze(t, 3)
     ref = oracle.find_repeats(t.astype(np.uint64), 3)
     assert np.array_equal(_as3(rows), _rows(ref))
+
+
+@pytest.mark.parametrize("cap", (64, 2, 3, 4, 5))
+@pytest.mark.parametrize("half", (False, True))
+@pytest.mark.parametrize("n", (33000, 60001, 131071))
+def test_last_selection_rounds(ctx, n, half, cap):
+    """Few symbols, so that some thousands of candidates stay undecided for
+    several rounds: the rounds of the whole chip, those of one workgroup from 1024
+    candidates on, and the round cap before, at and inside these."""
+    rng = np.random.default_rng(n)
+    t = rng.integers(0, 4, n).astype(np.uint32)
+    if half:
+        t[n // 3: n // 3 + n // 2] = 0
+    ref = oracle.find_repeats(t.astype(np.uint64), 4)
+    rows = ctx.analyze(t, 4)
+    full = ctx.rounds()["sel_live"]
+    try:
+        ctx.set_selection_round_cap(cap)
+        rows2 = ctx.analyze(t, 4)
+        live = ctx.rounds()["sel_live"]
+    finally:
+        ctx.set_selection_round_cap(64)
+    assert np.array_equal(_as3(rows), _rows(ref)) and np.array_equal(_as3(rows2), _rows(ref))
+    assert len(full) > 3 and all(a > b for a, b in zip(full[1:], full[2:]))
+    assert live[:cap] == full[:cap]
