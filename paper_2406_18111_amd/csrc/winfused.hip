@@ -272,6 +272,72 @@ __device__ __forceinline__ int below8(const uint16_t *p, uint32_t c, uint32_t l)
   return f ? 31 - __clz((int)f) : -1;
 }
 
+// Tokens that the suffixes at x and y share, known to share `from`, `lim` being
+// left of the shorter one; by a whole wavefront, 512 tokens a step.
+__device__ __forceinline__ uint32_t wave_match(const uint16_t *txt, uint32_t x, uint32_t y, uint32_t lim,
+                                               uint32_t from) {
+  const uint32_t lane = threadIdx.x & 63;
+  for (;; from += 512) {
+    const uint32_t o = from + 8 * lane;
+    uint32_t c = 0;
+    bool stop = true;
+    if (o + 8 <= lim) {
+      uint64_t p0, p1, q0, q1;
+      __builtin_memcpy(&p0, txt + x + o, 8);
+      __builtin_memcpy(&q0, txt + y + o, 8);
+      __builtin_memcpy(&p1, txt + x + o + 4, 8);
+      __builtin_memcpy(&q1, txt + y + o + 4, 8);
+      const uint64_t d0 = p0 ^ q0, d1 = p1 ^ q1;
+      stop = (d0 | d1) != 0;
+      c = d0 ? (uint32_t)__builtin_ctzll(d0) / 16 : d1 ? 4 + (uint32_t)__builtin_ctzll(d1) / 16 : 8;
+    } else {
+      while (o + c < lim && txt[x + o + c] == txt[y + o + c]) c++;  // fewer than 8 are left
+    }
+    const uint64_t b = __ballot(stop);  // the lanes before the first of them matched 8 each
+    if (b) return (uint32_t)__shfl((int)(o + c), __ffsll((long long)b) - 1, 64);
+  }
+}
+
+// A lower bound of the LCP at the first of a thread's `per` positions, x, with
+// its predecessor y (`on`: it has one), within 8 tokens of the LCP or its end where
+// that is below kAlone, the LCP itself otherwise.  Kasai's walk from zero is its
+// long one: in a periodic window every thread's took up to n tokens.  A lane
+// gives up after kAlone; its wavefront goes on, lane by lane from the bound that the lane
+// before leaves (an LCP falls by at most one a position), so that the wavefront walks
+// its span's length once.  LCP of a loop of 100 tokens over 3000, 8192, 20000 and 32768:
+// 156, 257, 1106 and 1213 us before, 48, 40, 70 and 85 so.  kAlone 64: 29, 30, 50, 72, but
+// a lane's turn costs more than a short walk (nested loops of 5000, the whole
+// call: 229 us instead of 207); 1024: 105, 80, 144, 133.
+constexpr uint32_t kAlone = 256;
+__device__ __forceinline__ uint32_t first_lcp(const uint16_t *txt, bool on, uint32_t x, uint32_t y, uint32_t lim,
+                                              uint32_t per) {
+  uint32_t l = 0;
+  bool open = on;
+  while (open && l < kAlone) {
+    if (l + 8 > lim) {
+      open = false;
+      break;
+    }
+    uint64_t p0, p1, q0, q1;
+    __builtin_memcpy(&p0, txt + x + l, 8);
+    __builtin_memcpy(&q0, txt + y + l, 8);
+    __builtin_memcpy(&p1, txt + x + l + 4, 8);
+    __builtin_memcpy(&q1, txt + y + l + 4, 8);
+    if ((p0 ^ q0) | (p1 ^ q1)) open = false;
+    else l += 8;
+  }
+  for (uint64_t m = __ballot(open); m; m &= m - 1) {
+    const int src = __ffsll((long long)m) - 1;
+    const uint32_t before = (uint32_t)__shfl((int)l, src ? src - 1 : 0, 64);
+    uint32_t from = (uint32_t)__shfl((int)l, src, 64);
+    if (src && before > per) from = max(from, before - per);
+    const uint32_t v = wave_match(txt, (uint32_t)__shfl((int)x, src, 64), (uint32_t)__shfl((int)y, src, 64),
+                                  (uint32_t)__shfl((int)lim, src, 64), from);
+    if ((int)(threadIdx.x & 63) == src) l = v;
+  }
+  return l;
+}
+
 // Last i < k with lcp[i] < l, or -1: climbs the levels of minima of 8 until a
 // block left of k holds one, then descends to it.  Windows of up to CAP tokens.
 template <uint32_t CAP>
@@ -807,9 +873,10 @@ __device__ __forceinline__ void window_short(const FusedArgs &a, ShortLds<NT, IP
   // ---- LCP: Kasai's walk over ipt consecutive positions per thread, eight
   // tokens per step; suffixes are all alone, so rank is the inverse of sa
   {
-    uint32_t h = 0;
+    const uint32_t x0 = tid * ipt, r0 = x0 < n ? rank[x0] : 0u, y0 = r0 ? sa[r0 - 1] : 0u;
+    uint32_t h = first_lcp(txt, r0 != 0, x0, y0, n - (x0 > y0 ? x0 : y0), ipt);
     for (int i = 0; i < ipt; i++) {
-      const uint32_t x = tid * ipt + i;
+      const uint32_t x = x0 + i;
       if (x >= n) break;
       const uint32_t r = rank[x];
       if (r == 0) {
@@ -1726,7 +1793,8 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     const uint32_t x0 = min(tid * per, n), x1 = min(x0 + per, n);
     auto rank_at = [=](uint32_t x) { return (uint32_t)grank[min(x, n - 1)]; };
     auto before = [=](uint32_t r) { return (uint32_t)gsa[r ? r - 1 : 0]; };
-    uint32_t l = 0, r = rank_at(x0), rn = rank_at(x0 + 1), y = before(r), yn, rnn;
+    uint32_t r = rank_at(x0), rn = rank_at(x0 + 1), y = before(r), yn, rnn;
+    uint32_t l = first_lcp(txt, x0 < n && r != 0, x0, y, n - (x0 > y ? x0 : y), per);
 #pragma unroll 1
     for (uint32_t x = x0; x < x1; x++, r = rn, y = yn, rn = rnn) {
       yn = before(rn);

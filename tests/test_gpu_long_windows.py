@@ -160,3 +160,33 @@ def test_last_selection_rounds(ctx, n, half, cap):
     assert np.array_equal(_as3(rows), _rows(ref)) and np.array_equal(_as3(rows2), _rows(ref))
     assert len(full) > 3 and all(a > b for a, b in zip(full[1:], full[2:]))
     assert live[:cap] == full[:cap]
+
+
+@pytest.mark.parametrize("n", (270, 777, 4095, 5000, 8192, 8193, 20011, 32768))
+@pytest.mark.parametrize("period", (1, 7, 500))
+@pytest.mark.parametrize("bits", (32, 64))
+def test_periodic_windows(ctx, n, period, bits):
+    """LCPs of up to the whole window at every position: a loop without a
+    substitution, and with two that part it."""
+    t = np.resize(np.random.default_rng(period).permutation(500)[:period].astype(np.uint32), n)
+    parted = t.copy()
+    parted[n // 3] += 1
+    parted[n - n // 5] += 1
+    for u in (t, parted):
+        rows, occ = ctx.analyze(u.astype(np.uint64) if bits == 64 else u, 5, occurrences=True)
+        ref = oracle.find_repeats(u.astype(np.uint64), 5)
+        assert np.array_equal(_as3(rows), _rows(ref)) and len(occ) == int(ref["row_count"].sum())
+
+
+def test_batch_of_periodic_windows(ctx):
+    wins = []
+    for k, n in enumerate((65536, 65535, 50001, 32769, 32768, 9000, 3000, 300, 40) * 2):
+        t = np.resize(np.arange(1 + 37 * k, dtype=np.uint64), n)
+        if k % 2:
+            t[n // 2] = np.uint64(1 << 40)
+        wins.append(t)
+    off = np.zeros(len(wins) + 1, np.uint64)
+    off[1:] = np.cumsum([len(t) for t in wins])
+    rows, oo = ctx.analyze_batch(np.concatenate(wins), off, 5)
+    for w, t in enumerate(wins):
+        assert np.array_equal(_as3(rows[int(oo[w]):int(oo[w + 1])]), _rows(oracle.find_repeats(t, 5))), len(t)
