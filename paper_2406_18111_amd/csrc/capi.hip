@@ -288,11 +288,13 @@ static int run_ctx(apo_ctx *c, const void *d_tok, int bits, uint32_t n, uint32_t
   return map_rc(rc);
 }
 
-// Whether a lone window of n tokens is analysed by one workgroup.  At the limit
-// most windows are still better off there (32768 tokens there against 33001 stage
-// by stage: a loop with 5 % substitutions 690 and 900 us, a nested loop 870 and
-// 980, random symbols 330 and 400; half the window one run 1780 and 1200); from some
-// 40000 tokens on none is.  Kernel
+// Whether a lone window of n tokens is analysed by one workgroup.  Below the limit
+// windows that settle in a few rounds are better off there (28000 tokens, there and
+// stage by stage: a loop with 5 % substitutions 590 and 700 us, a nested loop 752
+// and 761, random symbols 262 and 272), at 32768 the loop still is (658 and 720; the
+// others 852 and 752, 300 and 291); those that keep most suffixes to the last round
+// are not from some 20000 tokens on (a loop without substitutions 922 and 822, half the
+// window one run 922 and 928; at 32768 1426 and 945, 1479 and 1035).  Kernel
 // timing and the injected errors are those of the stage-by-stage analysis.
 static bool fused_one(const apo_ctx *c, uint32_t n) {
   return n <= kWinSelSingle && c->win_greedy && c->ws.ktag == KT_NONE && c->ws.fail_after < 0;
