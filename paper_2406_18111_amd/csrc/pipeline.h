@@ -113,6 +113,10 @@ struct Workspace {
   uint32_t *hcnt = nullptr;        // pinned host mirror of dcnt; rhist and selcnt follow it here and on the device
   SortCounters *hctr = nullptr;    // pinned: the engine counters' error word
   uint32_t *hflag = nullptr;       // pinned: report_seq of the last report that is there
+  // pinned: the outcome of each doubling round, which the host polls.  Nothing but
+  // a round's own store goes there: a word that holds anything else could pass for
+  // the outcome of a later run (the counts that k_report copies did, at hrhist).
+  uint32_t *hround = nullptr;
   uint32_t report_seq = 0;         // reports asked for
   hipEvent_t ev[kStages + 1] = {};
   int ktag = KT_NONE;              // kernel family timed with events around each launch

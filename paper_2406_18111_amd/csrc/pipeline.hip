@@ -54,8 +54,8 @@ void Workspace::release() {
   if (mem && !external) (void)hipFree(mem);
   mem = nullptr;
   external = false;
-  if (hcnt) (void)hipHostFree(hcnt);  // holds hrhist, hsel, hflag and hctr too
-  hcnt = hrhist = hsel = hflag = nullptr;
+  if (hcnt) (void)hipHostFree(hcnt);  // holds hrhist, hsel, hflag, hround and hctr too
+  hcnt = hrhist = hsel = hflag = hround = nullptr;
   hctr = nullptr;
   if (hoff) (void)hipHostFree(hoff);  // holds horder and hwin too
   hoff = nullptr;
@@ -193,12 +193,14 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
   if (rc) { release(); return rc; }
   // the mirrors of dcnt, rhist and selcnt lie as those do, so that one pass takes all three
   const size_t mirror = o_sc + 2 * (kSelRoundCap + 2) * 4 - o_cnt;
-  APO_HIP_TRY(hipHostMalloc((void **)&hcnt, mirror + 64 + sizeof(SortCounters), hipHostMallocCoherent));
-  memset(hcnt, 0, mirror + 64 + sizeof(SortCounters));
+  const size_t polled = 4 * 64 * 4;  // one polled word per round, at the stride of rhist
+  APO_HIP_TRY(hipHostMalloc((void **)&hcnt, mirror + 64 + polled + sizeof(SortCounters), hipHostMallocCoherent));
+  memset(hcnt, 0, mirror + 64 + polled + sizeof(SortCounters));
   hrhist = hcnt + (o_rh - o_cnt) / 4;
   hsel = hcnt + (o_sc - o_cnt) / 4;
   hflag = hcnt + mirror / 4;
-  hctr = reinterpret_cast<SortCounters *>(reinterpret_cast<char *>(hcnt) + mirror + 64);
+  hround = hcnt + (mirror + 64) / 4;
+  hctr = reinterpret_cast<SortCounters *>(reinterpret_cast<char *>(hcnt) + mirror + 64 + polled);
   APO_HIP_TRY(hipHostMalloc((void **)&hoff, (size_t)(wantW + 2) * 16, hipHostMallocDefault));
   horder = reinterpret_cast<uint32_t *>(hoff + wantW + 1);
   hwin = horder + wantW + 4;
@@ -536,11 +538,14 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   uint64_t act = N;
   int r = pair0 ? 2 : pack, done_round = -1;
   w.kev_n = 0;
-  const uint32_t seq = ++w.report_seq;
+  // 30 bits of it tag the outcomes; 0 is what the words hold before a run's first
+  if ((++w.report_seq & 0x3FFFFFFFu) == 0) w.report_seq++;
+  const uint32_t seq = w.report_seq;
+  if (host) memset(w.hround, 0, 4 * (size_t)w.nsnap * 4);
   auto gather = [&] {  // closes round r - 1, opens round r
     if (r > pack)
       E.gather_sa(cur, w.rank, w.aflag, wend, (uint32_t)N, 1u << (r - 1), w.rhist, r,
-                  r > kSnapFrom ? w.snap + (size_t)(r - 1) * N : nullptr, dc + CNT_SNAPS, s, host ? w.hrhist : nullptr, seq);
+                  r > kSnapFrom ? w.snap + (size_t)(r - 1) * N : nullptr, dc + CNT_SNAPS, s, host ? w.hround : nullptr, seq);
   };
   auto round = [&]() -> int {  // launches the rest of round r
     // sync-free runs with pair ranks: the second round's state from them,
@@ -572,7 +577,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   auto outcome = [&](int k) -> int {  // waits for round k's
     uint64_t got = 0;
     auto there = [&] {
-      got = __atomic_load_n(reinterpret_cast<const uint64_t *>(w.hrhist + 4 * k), __ATOMIC_ACQUIRE);
+      got = __atomic_load_n(reinterpret_cast<const uint64_t *>(w.hround + 4 * k), __ATOMIC_ACQUIRE);
       return got >> 34 == (seq & 0x3FFFFFFFu);
     };
     if ((rc = wait_report(there, s))) return rc;
@@ -606,7 +611,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
       if ((rc = round())) return rc;
     }
     if (known) continue;
-    if (r == k + 1) E.round_end(cur ^ 1, k, w.rhist, s, w.hrhist, seq);  // no round is left to close it
+    if (r == k + 1) E.round_end(cur ^ 1, k, w.rhist, s, w.hround, seq);  // no round is left to close it
     if ((rc = outcome(k))) return rc;
   }
   if (w.fail_after >= 0 && w.fail_after-- == 0) {  // test hook, as in read_counters

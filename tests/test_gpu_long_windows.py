@@ -190,3 +190,20 @@ def test_batch_of_periodic_windows(ctx):
     rows, oo = ctx.analyze_batch(np.concatenate(wins), off, 5)
     for w, t in enumerate(wins):
         assert np.array_equal(_as3(rows[int(oo[w]):int(oo[w + 1])]), _rows(oracle.find_repeats(t, 5))), len(t)
+
+
+@pytest.mark.parametrize("values", [12, 14, 20, 22, 28, 44, 60])
+def test_repeated_calls_of_one_context(values):
+    """Each round's outcome is the host's to read once the round has written it,
+    whatever the calls before it left behind: a few tokens' worth of groups longer
+    than a tile, whose count earlier calls report, over enough calls for the runs'
+    numbers to come past a quarter of it."""
+    import torch
+    from paper_2406_18111_amd import Context
+    t = np.random.default_rng(values).integers(0, values, 1 << 17).astype(np.uint32)
+    ref = oracle.suffix_array(t.astype(np.uint64))
+    dev = torch.from_numpy(t.view(np.int32)).cuda()
+    with Context(0) as c:
+        for call in range(10):
+            sa, _ = c.suffix_array_dev(dev)
+            assert np.array_equal(sa.cpu().numpy().astype(np.int64), ref), (values, call)
