@@ -378,10 +378,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     fused_batch(w, d_tok, W, maxwin, fused_in_two(h_off, W), min_len, s);
     if (mode == Mode::CAPTURE) return 0;
     rc = finish_run(w, N, W, N, 1, info, s, false);
-    if (rc != 1) {
-      for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;
-      return rc;
-    }
+    if (rc != 1) return rc;
     info = RunInfo{};
   }
   stamp(w, 0, s, stamps);
@@ -818,7 +815,10 @@ int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_l
   if (W > 1) APO_HIP_TRY(hipMemcpyAsync(w.hwin, w.win_rows, W * 4, hipMemcpyDeviceToHost, s));
   if ((rc = read_counters(w, s, true))) return rc;
   fill_info(w, N, info);
-  if (w.hcnt[CNT_FUSED] && w.hcnt[CNT_WFLAG]) return 1;
+  if (w.hcnt[CNT_FUSED]) {
+    if (w.hcnt[CNT_WFLAG]) return 1;
+    for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;  // (10 ns)
+  }
   info.sel_rounds = 0;
   const int qmax = sel_launched < 0 ? kSelRoundCap : sel_launched;
   for (int q = 0; q < qmax; q++)

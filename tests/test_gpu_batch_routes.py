@@ -1,0 +1,58 @@
+"""The routes that a batch can take: a workgroup per window, or stage by stage where
+a window is longer than 65536 tokens (in lanes, captured or host-driven).  Rows
+against the oracle; what else a call reports, against what it did."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2406_18111_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def ctx():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2406_18111_amd import Context
+    with Context(0) as c:
+        yield c
+
+
+def _pack(wins):
+    import torch
+    off = np.zeros(len(wins) + 1, dtype=np.uint64)
+    off[1:] = np.cumsum([len(w) for w in wins])
+    return torch.from_numpy(np.concatenate(wins).astype(np.uint64).view(np.int64)).cuda(), off
+
+
+def _refs(wins, m):
+    out = []
+    for w in wins:
+        r = oracle.find_repeats(w, m)
+        out.append(np.stack([r["row_start"], r["row_len"], r["row_count"]], 1).astype(np.int64).reshape(-1, 3))
+    return out
+
+
+def _check(got, refs, what=None):
+    rows, off = got
+    rows = rows.cpu().numpy().astype(np.int64)
+    for w, ref in enumerate(refs):
+        assert np.array_equal(rows[int(off[w]):int(off[w + 1])], ref), (what, w)
+
+
+def _loops(lens, seed=0):
+    return [synth.loop_stream(seed + k, n, 10 + 7 * k, 64, 0.05).astype(np.uint64) for k, n in enumerate(lens)]
+
+
+def test_stage_times_of_a_workgroup_per_window(ctx):
+    """The longest time that a window took in each stage: of the first run of a
+    shape, of its replays, and of a run without graphs."""
+    wins = _loops([300, 5000, 20000, 9000])
+    dev, off = _pack(wins)
+    refs = _refs(wins, 4)
+    for graphs in (True, True, False):
+        ctx.set_graphs(graphs)
+        _check(ctx.analyze_batch_dev(dev, off, 4), refs)
+        ms = ctx.stage_ms()
+        assert all(0 < v < 100 for v in ms.values()), (graphs, ms)
