@@ -250,8 +250,8 @@ int apo_inject_device_error(apo_ctx *ctx, int after_syncs);
  * window's candidates in priority order over an on-chip bitmap; longer
  * windows use the round-based evaluation.  Such single windows, and batches
  * whose windows all have at most 2^16 tokens, go through all stages in one
- * workgroup per window, unless a window holds 2^16 distinct tokens, a kernel is
- * being timed (apo_profile_kernel) or an error is to be injected.  on = 0 sends every analysis stage by stage through the
+ * workgroup per window, unless a kernel is being timed (apo_profile_kernel) or an
+ * error is to be injected.  on = 0 sends every analysis stage by stage through the
  * rounds.  Results are identical either way.  APO_EINVAL
  * unless on is 0 or 1. */
 int apo_set_window_greedy(apo_ctx *ctx, int on);

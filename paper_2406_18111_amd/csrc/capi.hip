@@ -296,11 +296,10 @@ static int run_ctx(apo_ctx *c, const void *d_tok, int bits, uint32_t n, uint32_t
 // are not from some 20000 tokens on (a loop without substitutions 922 and 822, half the
 // window one run 922 and 928; at 32768 1426 and 945, 1479 and 1035).  Kernel
 // timing and the injected errors are those of the stage-by-stage analysis.
+static_assert(kWinSelSingle < kFusedLongMax, "16 bits hold their ranks");
 static bool fused_one(const apo_ctx *c, uint32_t n) {
   return n <= kWinSelSingle && c->win_greedy && c->ws.ktag == KT_NONE && c->ws.fail_after < 0;
 }
-
-constexpr int kOver = 1;  // too many distinct tokens for it
 
 // That analysis on stream s, through the pinned report; tokens and outputs in
 // device or pinned host memory.  Fills ctx->info; outputs are written only if
@@ -314,7 +313,6 @@ static int run_fused(apo_ctx *c, const void *tok, int bits, uint32_t n, uint32_t
     (void)hipGetLastError();
     return APO_EDEVICE;
   }
-  if (c->finfo->over) return kOver;
   fused_read(*c->finfo, n, c->ws, c->info);
   return APO_OK;
 }
@@ -354,16 +352,14 @@ static int analyze_host(apo_ctx *ctx, const void *tokens, int bits, uint32_t n, 
     memcpy(ctx->ftok, tokens, bytes);
     rc = run_fused(ctx, ctx->ftok, bits, n, min_len, ctx->frows, out_cap, occ ? ctx->focc : nullptr, occ_cap,
                    ctx->stream);
-    if (rc != kOver) {
-      if (rc) return rc;
-      const uint32_t rows = ctx->info.rows, acc = ctx->info.accepted;
-      *out_n = rows;
-      if (occ_n) *occ_n = acc;
-      if (rows > out_cap || (occ && acc > occ_cap)) return APO_ERANGE;
-      if (rows) memcpy(out, ctx->frows, (size_t)rows * sizeof(apo_candidate));
-      if (occ && acc) memcpy(occ, ctx->focc, (size_t)acc * sizeof(apo_occurrence));
-      return APO_OK;
-    }
+    if (rc) return rc;
+    const uint32_t rows = ctx->info.rows, acc = ctx->info.accepted;
+    *out_n = rows;
+    if (occ_n) *occ_n = acc;
+    if (rows > out_cap || (occ && acc > occ_cap)) return APO_ERANGE;
+    if (rows) memcpy(out, ctx->frows, (size_t)rows * sizeof(apo_candidate));
+    if (occ && acc) memcpy(occ, ctx->focc, (size_t)acc * sizeof(apo_occurrence));
+    return APO_OK;
   }
   int rc = ctx_ensure(ctx, ctx->ws, n, 1);
   if (rc) return map_rc(rc);
@@ -414,12 +410,10 @@ extern "C" int apo_analyze_window_dev(apo_ctx *ctx, const void *d_tokens, int to
   if (fused_one(ctx, n)) {
     int rc = fused_buffers(ctx);
     if (!rc) rc = run_fused(ctx, d_tokens, token_bits, n, min_len, d_out, out_cap, d_occ, occ_cap, s);
-    if (rc != kOver) {
-      if (rc) return rc;
-      *h_out_n = ctx->info.rows;
-      if (h_occ_n) *h_occ_n = ctx->info.accepted;
-      return ctx->info.rows > out_cap || (d_occ && ctx->info.accepted > occ_cap) ? APO_ERANGE : APO_OK;
-    }
+    if (rc) return rc;
+    *h_out_n = ctx->info.rows;
+    if (h_occ_n) *h_occ_n = ctx->info.accepted;
+    return ctx->info.rows > out_cap || (d_occ && ctx->info.accepted > occ_cap) ? APO_ERANGE : APO_OK;
   }
   int rc = run_ctx(ctx, d_tokens, token_bits, n, min_len, Stop::FULL, s);
   if (rc) return rc;

@@ -53,7 +53,7 @@ int noalloc_setup(int device) {
     }
     if (hipHostMalloc((void **)&D.finfo, sizeof(FusedInfo), hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
-      D.finfo = nullptr;  // short windows then take the stage-by-stage analysis too
+      D.finfo = nullptr;  // windows then go stage by stage
     }
     D.rc = APO_OK;
   });
@@ -69,18 +69,17 @@ int noalloc_run(int device, hipStream_t s, int tile_log, int digit_bits, const v
   if (n > APO_NOALLOC_MAX_N) return APO_ENOMEM;
   std::lock_guard<std::mutex> lk(D.mu);
   Workspace &w = D.ws;
+  static_assert(APO_NOALLOC_MAX_N < kFusedLongMax, "one workgroup takes every window");
   if (D.finfo) {
     fused_window(w, d_tok, bits, n, min_len, d_out, out_cap, d_occ, occ_cap, D.finfo, s);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
       (void)hipGetLastError();
       return APO_EDEVICE;
     }
-    if (!D.finfo->over) {
-      fused_read(*D.finfo, n, w, info);
-      *h_out_n = info.rows;
-      if (h_occ_n) *h_occ_n = info.accepted;
-      return info.rows > out_cap || (d_occ && info.accepted > occ_cap) ? APO_ERANGE : APO_OK;
-    }
+    fused_read(*D.finfo, n, w, info);
+    *h_out_n = info.rows;
+    if (h_occ_n) *h_occ_n = info.accepted;
+    return info.rows > out_cap || (d_occ && info.accepted > occ_cap) ? APO_ERANGE : APO_OK;
   }
   // The array keeps the previous call's contents: clear what the stages
   // expect to find zeroed (device counters, the sort engine's histograms and

@@ -168,8 +168,8 @@ int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t
                 uint64_t m_bound, bool host, hipStream_t s, bool window_major);
 // W > 1: the windows' row counts arrive in w.hwin.
 // sel_launched: selection rounds enqueued by a sync-free run (-1: host-driven).
-// Returns 1 when a sync-free run left candidates undecided, or one-workgroup
-// analyses left windows out (the caller then reruns host-driven).
+// Returns 1 when a sync-free run left candidates undecided (the caller then
+// reruns host-driven).
 int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
                bool stamps);
 

@@ -367,8 +367,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   uint64_t maxwin = 0;
   for (uint32_t k = 0; k < W; k++) maxwin = std::max<uint64_t>(maxwin, h_off[k + 1] - h_off[k]);
   // The whole analysis of each window by one workgroup, where every window is
-  // short enough; if some hold too many distinct tokens for that, stage by stage
-  // after all.
+  // short enough.
   if (stop == Stop::FULL && (W > 1 || w.fuse_one) && maxwin <= kFusedLongMax && bits == 64 && w.win_greedy &&
       w.ktag == KT_NONE && w.fail_after < 0) {
     if (mode != Mode::CAPTURE)
@@ -377,9 +376,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     w.kev_n = 0;
     fused_batch(w, d_tok, W, maxwin, fused_in_two(h_off, W), min_len, s);
     if (mode == Mode::CAPTURE) return 0;
-    rc = finish_run(w, N, W, N, 1, info, s, false);
-    if (rc != 1) return rc;
-    info = RunInfo{};
+    return finish_run(w, N, W, N, 1, info, s, false);
   }
   stamp(w, 0, s, stamps);
   if (mode != Mode::CAPTURE)  // a captured sequence expects d_off (and the order) to be uploaded already
@@ -815,10 +812,8 @@ int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_l
   if (W > 1) APO_HIP_TRY(hipMemcpyAsync(w.hwin, w.win_rows, W * 4, hipMemcpyDeviceToHost, s));
   if ((rc = read_counters(w, s, true))) return rc;
   fill_info(w, N, info);
-  if (w.hcnt[CNT_FUSED]) {
-    if (w.hcnt[CNT_WFLAG]) return 1;
+  if (w.hcnt[CNT_FUSED])
     for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;  // (10 ns)
-  }
   info.sel_rounds = 0;
   const int qmax = sel_launched < 0 ? kSelRoundCap : sel_launched;
   for (int q = 0; q < qmax; q++)

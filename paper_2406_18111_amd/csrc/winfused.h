@@ -17,12 +17,11 @@ constexpr uint32_t kFusedMidMax = 32768;
 // What one window's analysis reports to the host (pinned memory).
 struct FusedInfo {
   uint32_t sigma, cands, maxl, m, accepted, rows, nhist;
-  uint32_t over;              // 1: 65536 distinct tokens, whose ranks 16 bits do not hold; nothing else is set
   uint32_t hist[kMaxRounds];  // suffixes still grouped after each doubling round
   uint64_t stamp[kStages + 1];
 };
 
-// One window of n tokens (2 <= n <= kFusedLongMax, `bits` 32 or 64; device
+// One window of n tokens (2 <= n < kFusedLongMax, `bits` 32 or 64; device
 // memory or pinned host memory).  Rows and occurrences are written only when
 // both fit (row_cap; occ_cap unless occ is null); `info` always is.  w: scratch
 // arrays for n tokens.
@@ -36,7 +35,7 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info);
 // Batch of windows of at most kFusedLongMax 64-bit tokens each (offsets and
 // order in w.d_off and w.d_order): rows of all windows packed in window order
 // into w.rows, counts into w.win_rows, counters where finish_run reads them.
-// Windows of 65536 distinct tokens are left out and counted in CNT_WFLAG.  Uses w.wflag.
+// Uses w.wflag.
 // two: in two launches, where fused_in_two says so; either form is right for any
 // windows.
 bool fused_in_two(const uint64_t *off, uint32_t W);

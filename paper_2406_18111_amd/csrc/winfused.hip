@@ -455,7 +455,6 @@ __device__ __forceinline__ void report(const FusedArgs &a, uint32_t win, const R
     f.accepted = r.accepted;
     f.rows = r.rows;
     f.nhist = r.nhist;
-    f.over = 0;
     for (uint32_t k = 0; k < r.nhist; k++) f.hist[k] = hist[k];
     for (int k = 0; k <= kStages; k++) f.stamp[k] = stamp[k];
     return;
@@ -1396,8 +1395,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     // More distinct tokens than the table takes: positions sorted by token, a
     // radix pass for each of the four highest bytes in which the tokens differ
     // (then for all of them, should that not have put them in order), ranks
-    // counted over the sorted positions.  (65536 distinct ones, whose ranks would
-    // not fit 16 bits, are left to the stage-by-stage analysis.)
+    // counted over the sorted positions.
     auto token = [=](uint32_t j) {
       return a.bits == 64 ? static_cast<const uint64_t *>(a.tok)[tb + j] : (uint64_t) static_cast<const uint32_t *>(a.tok)[tb + j];
     };
@@ -1456,13 +1454,10 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     }
     uint32_t at = words_before<NW>(wsum, wv, D);
     nd = D;
-    if (D > 65535) {  // uniform
+    if (D > 65535) {  // uniform: kFusedLongMax distinct tokens, more ranks than 16 bits hold, and no repeats
       if (tid == 0) {
-        if (a.info) a.info->over = 1;
-        else {
-          a.win_rows[win] = 0;
-          atomicAdd(&a.dcnt[CNT_WFLAG], 1u);
-        }
+        for (int k = 1; k <= kStages; k++) stamp(k);
+        report(a, win, Report{D, D, 0, 0, 0, 0, 0, 0, n, 1}, s_hist, s_stamp);
       }
       return;
     }

@@ -56,3 +56,27 @@ def test_stage_times_of_a_workgroup_per_window(ctx):
         _check(ctx.analyze_batch_dev(dev, off, 4), refs)
         ms = ctx.stage_ms()
         assert all(0 < v < 100 for v in ms.values()), (graphs, ms)
+
+
+@pytest.mark.parametrize("windows", [1, 2, 5])
+def test_windows_of_65536_distinct_tokens(ctx, windows):
+    """More ranks than 16 bits hold, and nothing that repeats: no rows, beside
+    windows that have some, in one run (which reports its stage times)."""
+    rng = np.random.default_rng(9)
+    all_distinct = rng.permutation(1 << 16).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15)
+    top = all_distinct.copy()
+    top[77] = np.uint64(np.iinfo(np.uint64).max)
+    one_twice = all_distinct.copy()
+    one_twice[40000:40003] = one_twice[100:103]
+    wins = [all_distinct, one_twice, top, _loops([65536])[0], all_distinct][:windows]
+    dev, off = _pack(wins)
+    refs = _refs(wins, 3)
+    active = sum(int(oracle.suffix_array(w, return_active=True)[1].sum()) for w in wins)
+    for graphs in (True, True, False):
+        ctx.set_graphs(graphs)
+        _check(ctx.analyze_batch_dev(dev, off, 3), refs, graphs)
+        c = ctx.counters()
+        assert c["sigma"] == sum(len(np.unique(w)) for w in wins)
+        assert c["active_sum"] - int(off[-1]) == active, c
+        if windows > 1:
+            assert any(ctx.stage_ms().values())
