@@ -302,8 +302,9 @@ int apo_tune(apo_ctx *ctx, const void *d_tokens, int token_bits, uint32_t n, uin
              int *best_tile_log, int *best_digit_bits, double *best_ms);
 
 /* Tunes on a whole batch of device windows (offsets as in
- * apo_analyze_batch_dev), timing each pair as the batch call runs it
- * (lanes included), and keeps the fastest for the size of one lane's share.
+ * apo_analyze_batch_dev), timing each pair as the batch call runs it stage by
+ * stage (lanes included; the one-workgroup analyses have no such parameters),
+ * and keeps the fastest for the size of one lane's share.
  * Same outputs as apo_tune.  APO_EINVAL for fewer than 2 tokens. */
 int apo_tune_batch(apo_ctx *ctx, const uint64_t *d_tokens, const uint64_t *h_offsets, uint32_t num_windows,
                    uint32_t min_len, int reps, int *best_tile_log, int *best_digit_bits, double *best_ms);

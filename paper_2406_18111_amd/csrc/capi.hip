@@ -97,6 +97,7 @@ struct GraphCache {
   uint64_t total = 0, maxwin = 0;
   uint32_t W = 0, min_len = 0;
   int tile = 0, digit = 0;
+  bool greedy = false, fused = false;  // the selection path, and whether windows have a workgroup each
   void *mem = nullptr;
   hipStream_t stream = nullptr;
   void reset() {
@@ -578,6 +579,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
     ln.ws->sel_prefix = ctx->sel_prefix;
     ln.ws->win_greedy = ctx->win_greedy;
     ln.ws->fuse_one = true;
+    ln.ws->by_stage = ctx->ws.by_stage;
     if (ln.st != s && hipStreamWaitEvent(ln.st, ctx->lane_ready, 0) != hipSuccess) return APO_EDEVICE;
     lanes.push_back(std::move(ln));
   }
@@ -592,7 +594,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
       for (uint32_t w = 0; w < ln.W; w++) mw = std::max<uint64_t>(mw, ln.norm[w + 1] - ln.norm[w]);
       key.insert(key.end(), {ln.tok0, ln.total, ln.W, mw, (uint64_t)ln.ws->eng.tile_log(),
                              (uint64_t)ln.ws->eng.digit_bits(), (uint64_t)(uintptr_t)ln.ws->mem,
-                             (uint64_t)(uintptr_t)ln.st});
+                             (uint64_t)(uintptr_t)ln.st, (uint64_t)takes_fused(*ln.ws, ln.W, mw)});
     }
     LaneGraph &G = ctx->lg;
     // window offsets (and order) of every lane, ahead of the branches that read them
@@ -715,8 +717,8 @@ static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   for (uint32_t w = 0; w < W; w++) longest = std::max<uint64_t>(longest, off[w + 1] - off[w]);
   Workspace &w0 = ctx->ws;
   std::fill(w0.lane_end, w0.lane_end + 3, kNone);
-  if (L >= 2 && longest <= kFusedLongMax && ctx->win_greedy && w0.ktag == KT_NONE && w0.fail_after < 0 &&
-      (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx))) {
+  w0.win_greedy = ctx->win_greedy;
+  if (L >= 2 && takes_fused(w0, W, longest) && (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx))) {
     // (what is counted by lane still is)
     std::vector<uint32_t> ends;
     lane_groups(off, W, total, L, ends);
@@ -753,7 +755,6 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   Workspace &w = ctx->ws;
   w.sel_cap = ctx->sel_cap;
   w.sel_prefix = ctx->sel_prefix;
-  if (w.win_greedy != ctx->win_greedy) ctx->gc.reset();  // a captured sequence holds the other selection path
   w.win_greedy = ctx->win_greedy;
   w.fuse_one = true;
   // Timed kernel launches are bracketed by events on the stream, which is
@@ -765,12 +766,13 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
     return map_rc(rc);
   }
   GraphCache &G = ctx->gc;
-  const bool hit = G.exec && G.tok == d_tok && G.total == total && G.W == W && G.maxwin == maxwin &&
-                   G.min_len == min_len && G.tile == tl && G.digit == db && G.mem == w.mem && G.stream == s;
+  const bool fused = takes_fused(w, W, maxwin);
+  const bool hit = G.exec && G.tok == d_tok && G.total == total && G.W == W && G.maxwin == maxwin && G.fused == fused &&
+                   G.greedy == w.win_greedy && G.min_len == min_len && G.tile == tl && G.digit == db && G.mem == w.mem && G.stream == s;
   if (upload_windows(w, norm.data(), W, s, true)) return APO_EDEVICE;
   // Windows with a workgroup each: the first run of a shape is enqueued right
   // away, and its few launches are recorded while it is on the GPU.
-  const bool ahead = !hit && maxwin <= kFusedLongMax && w.win_greedy;
+  const bool ahead = !hit && fused;
   if (ahead) {
     rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::CAPTURE);
     if (rc) return map_rc(rc);
@@ -803,6 +805,8 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
     G.total = total;
     G.W = W;
     G.maxwin = maxwin;
+    G.fused = fused;
+    G.greedy = w.win_greedy;
     G.min_len = min_len;
     G.tile = tl;
     G.digit = db;
@@ -1085,7 +1089,8 @@ extern "C" int apo_last_rounds(apo_ctx *ctx, uint32_t *sa_active, uint32_t *n_sa
 // Times every (LDS tile, digit width) pair on the caller's window and keeps the
 // fastest for the window's size bucket.  Results never depend on the choice.
 // Batch tuning: times every pair on the caller's whole batch (as
-// apo_analyze_batch_dev runs it, lanes included) and keeps the fastest for the
+// apo_analyze_batch_dev runs it stage by stage, lanes included; windows that have a
+// workgroup each take no parameters) and keeps the fastest for the
 // size bucket of one lane's share.  Results never depend on the choice.
 static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off, uint32_t W, uint32_t min_len,
                         hipStream_t s, uint64_t total);
@@ -1102,6 +1107,7 @@ extern "C" int apo_tune_batch(apo_ctx *ctx, const uint64_t *d_tokens, const uint
   const int keep_t = ctx->tune.fixed_tile, keep_d = ctx->tune.fixed_digit;
   double best = 1e30;
   int bt = kDefaultTileLog, bd = kDefaultDigitBits;
+  ctx->ws.by_stage = true;  // what the parameters are for
   for (int tl = kMinTileLog; tl <= kMaxTileLog && rc == APO_OK; tl++) {
     for (int db : {8, 10, 11, 12}) {
       ctx->tune.fixed_tile = tl;
@@ -1122,6 +1128,7 @@ extern "C" int apo_tune_batch(apo_ctx *ctx, const uint64_t *d_tokens, const uint
   }
   ctx->tune.fixed_tile = keep_t;
   ctx->tune.fixed_digit = keep_d;
+  ctx->ws.by_stage = false;
   if (rc) return rc;
   const int L = std::max(1, std::min<int>(ctx->lanes, (int)(W / 2)));
   ctx->tune.best[ceil_log2_u64(std::max<uint64_t>(total / L, 2))] = {bt, bd};

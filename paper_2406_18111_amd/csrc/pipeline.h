@@ -129,6 +129,7 @@ struct Workspace {
   uint32_t pair_w = 0;             // windows of the run when it ranked their token pairs (else 0)
   int fail_after = -1;             // test hook: host syncs before one reports a device error (-1: never)
   bool fuse_one = false;           // a lone short window takes the one-workgroup analysis in run_pipeline too
+  bool by_stage = false;           // every analysis goes stage by stage
   bool win_greedy = true;          // one-wavefront-per-window greedy where windows are short enough
 
   // device bytes a workspace of capacity (N, W) holds (exact)
@@ -156,6 +157,10 @@ struct Workspace {
 // set the order in which the per-window kernels of sync-free and captured
 // runs take its windows (longest first, by bit length of the window's size).
 int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t s, bool order);
+
+// Whether a full analysis of W windows, the longest of maxwin 64-bit tokens, gives
+// each of them a workgroup.
+bool takes_fused(const Workspace &w, uint32_t W, uint64_t maxwin);
 
 // Runs the stages of one analysis on stream s.  d_tok: device tokens of
 // `bits` (32/64) bits, windows given by host offsets h_off[0..W] (global,

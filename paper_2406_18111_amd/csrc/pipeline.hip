@@ -354,6 +354,11 @@ int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t 
   return 0;
 }
 
+bool takes_fused(const Workspace &w, uint32_t W, uint64_t maxwin) {
+  return !w.by_stage && (W > 1 || w.fuse_one) && maxwin <= kFusedLongMax && w.win_greedy && w.ktag == KT_NONE &&
+         w.fail_after < 0;
+}
+
 int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const uint64_t *h_off, uint32_t W,
                  uint32_t min_len, Stop stop, hipStream_t s, RunInfo &info, Mode mode) {
   info = RunInfo{};
@@ -368,8 +373,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   for (uint32_t k = 0; k < W; k++) maxwin = std::max<uint64_t>(maxwin, h_off[k + 1] - h_off[k]);
   // The whole analysis of each window by one workgroup, where every window is
   // short enough.
-  if (stop == Stop::FULL && (W > 1 || w.fuse_one) && maxwin <= kFusedLongMax && bits == 64 && w.win_greedy &&
-      w.ktag == KT_NONE && w.fail_after < 0) {
+  if (stop == Stop::FULL && bits == 64 && takes_fused(w, W, maxwin)) {
     if (mode != Mode::CAPTURE)
       if ((rc = upload_windows(w, h_off, W, s, true))) return rc;
     w.pair_w = W > 1 ? W : 0;

@@ -58,6 +58,24 @@ def test_stage_times_of_a_workgroup_per_window(ctx):
         assert all(0 < v < 100 for v in ms.values()), (graphs, ms)
 
 
+def test_tuning_times_the_kernels_that_it_tunes(ctx):
+    """The tile and the digit width are the stage-by-stage kernels': a tuned batch
+    goes stage by stage while it is timed, whatever its windows' lengths (which a
+    captured run shows by reporting no stage times), and not afterwards."""
+    wins = _loops([3000, 5000, 20000, 9000])
+    dev, off = _pack(wins)
+    refs = _refs(wins, 4)
+    for lanes in (3, 1):
+        ctx.set_lanes(lanes)
+        _check(ctx.analyze_batch_dev(dev, off, 4), refs)
+        assert any(ctx.stage_ms().values())
+        ctx.tune_batch(dev, off, 4, reps=1)
+        assert not any(ctx.stage_ms().values()), lanes
+        for rep in range(2):  # and no graph of the timed form is left over
+            _check(ctx.analyze_batch_dev(dev, off, 4), refs)
+            assert any(ctx.stage_ms().values()), (lanes, rep)
+
+
 @pytest.mark.parametrize("windows", [1, 2, 5])
 def test_windows_of_65536_distinct_tokens(ctx, windows):
     """More ranks than 16 bits hold, and nothing that repeats: no rows, beside
