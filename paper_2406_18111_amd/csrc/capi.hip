@@ -710,6 +710,14 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
 
 static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off, uint32_t W, uint32_t min_len,
                         hipStream_t s, uint64_t total) {
+  // A batch waits for its counters, which a stream that its owner is capturing
+  // cannot: told before anything is enqueued there (and not from a failed capture
+  // of its own, after which the context would run without graphs).
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return APO_EDEVICE;
+  }
   int L = std::min<int>(ctx->lanes, (int)(W / 2));
   // windows analysed by a workgroup each are a launch or two, which lanes have
   // nothing to add to (4096 windows of 256 to 65536 tokens: 5.7 ms, on three lanes 6.4)

@@ -76,6 +76,36 @@ def test_tuning_times_the_kernels_that_it_tunes(ctx):
             assert any(ctx.stage_ms().values()), (lanes, rep)
 
 
+def test_a_capturing_stream_is_refused(ctx):
+    """A batch reads counters on the host, which a stream that the caller is
+    capturing cannot do: the call is refused before anything is enqueued, the
+    caller's capture goes on, and the context keeps its graphs."""
+    import torch
+    from paper_2406_18111_amd import ApoError, _lib
+    wins = _loops([3000, 5000, 700])
+    dev, off = _pack(wins)
+    refs = _refs(wins, 4)
+    _check(ctx.analyze_batch_dev(dev, off, 4), refs)
+    x = torch.zeros(8, device="cuda")
+    s = torch.cuda.Stream()
+    for lanes in (3, 1):
+        ctx.set_lanes(lanes)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s, capture_error_mode="thread_local"):
+            x += 1
+            with pytest.raises(ApoError) as e:
+                ctx.analyze_batch_dev(dev, off, 4, stream=s)
+            assert e.value.code == _lib.APO_EDEVICE
+        g.replay()
+        g.replay()
+        torch.cuda.synchronize()
+    assert x.tolist() == [4.0] * 8
+    before = ctx.graph_stats()["replays"]
+    for _ in range(3):
+        _check(ctx.analyze_batch_dev(dev, off, 4), refs)
+    assert ctx.graph_stats()["replays"] >= before + 2
+
+
 @pytest.mark.parametrize("windows", [1, 2, 5])
 def test_windows_of_65536_distinct_tokens(ctx, windows):
     """More ranks than 16 bits hold, and nothing that repeats: no rows, beside
