@@ -98,7 +98,7 @@ struct GraphCache {
   uint32_t W = 0, min_len = 0;
   int tile = 0, digit = 0;
   bool greedy = false, fused = false;  // the selection path, and whether windows have a workgroup each
-  void *mem = nullptr;
+  uint64_t laid = 0;  // Workspace::laid
   hipStream_t stream = nullptr;
   void reset() {
     if (exec) (void)hipGraphExecDestroy(exec);
@@ -593,7 +593,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
       uint64_t mw = 0;
       for (uint32_t w = 0; w < ln.W; w++) mw = std::max<uint64_t>(mw, ln.norm[w + 1] - ln.norm[w]);
       key.insert(key.end(), {ln.tok0, ln.total, ln.W, mw, (uint64_t)ln.ws->eng.tile_log(),
-                             (uint64_t)ln.ws->eng.digit_bits(), (uint64_t)(uintptr_t)ln.ws->mem,
+                             (uint64_t)ln.ws->eng.digit_bits(), ln.ws->laid,
                              (uint64_t)(uintptr_t)ln.st, (uint64_t)takes_fused(*ln.ws, ln.W, mw)});
     }
     LaneGraph &G = ctx->lg;
@@ -708,6 +708,14 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
 static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off, uint32_t W, uint32_t min_len,
                         hipStream_t s, uint64_t total);
 
+// Whether the device has the memory for w to hold the whole batch.  The lanes'
+// workspaces can fit where one, of the next power of two tokens, does not.
+static bool one_fits(const Workspace &w, uint64_t total, uint32_t W) {
+  const size_t after = w.bytes_after(std::max<uint64_t>(total, 2), W);
+  size_t avail = 0, all = 0;
+  return after <= w.held() || hipMemGetInfo(&avail, &all) != hipSuccess || after <= avail + w.held();
+}
+
 static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off, uint32_t W, uint32_t min_len,
                         hipStream_t s, uint64_t total) {
   // A batch waits for its counters, which a stream that its owner is capturing
@@ -726,12 +734,18 @@ static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   Workspace &w0 = ctx->ws;
   std::fill(w0.lane_end, w0.lane_end + 3, kNone);
   w0.win_greedy = ctx->win_greedy;
-  if (L >= 2 && takes_fused(w0, W, longest) && (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx))) {
+  if (L >= 2 && takes_fused(w0, W, longest) &&
+      (!ctx->budget || lanes_footprint(ctx, off, W, total, 1) <= ctx_limit(ctx)) && one_fits(w0, total, W)) {
     // (what is counted by lane still is)
     std::vector<uint32_t> ends;
     lane_groups(off, W, total, L, ends);
     for (int g = 0; g < 3 && g + 1 < L; g++) w0.lane_end[g] = ends[g + 1];
-    L = 1;
+    const int rc = batch_single(ctx, d_tok, off, W, min_len, s, total);
+    std::fill(w0.lane_end, w0.lane_end + 3, kNone);
+    if (rc != APO_ENOMEM) {  // (else something else took the memory meanwhile)
+      ctx->louts.assign(1, {&w0, W, ctx->info.rows});
+      return rc;
+    }
   }
   if (ctx->budget && L >= 2) {
     // fewer lanes when their workspaces would not fit the budget; lane
@@ -744,8 +758,7 @@ static int batch_common(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   }
   if (L >= 2) return batch_lanes(ctx, d_tok, off, W, min_len, s, total, L);
   const int rc = batch_single(ctx, d_tok, off, W, min_len, s, total);
-  std::fill(w0.lane_end, w0.lane_end + 3, kNone);
-  ctx->louts.assign(1, {&ctx->ws, W, ctx->info.rows});
+  ctx->louts.assign(1, {&w0, W, ctx->info.rows});
   return rc;
 }
 
@@ -776,7 +789,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   GraphCache &G = ctx->gc;
   const bool fused = takes_fused(w, W, maxwin);
   const bool hit = G.exec && G.tok == d_tok && G.total == total && G.W == W && G.maxwin == maxwin && G.fused == fused &&
-                   G.greedy == w.win_greedy && G.min_len == min_len && G.tile == tl && G.digit == db && G.mem == w.mem && G.stream == s;
+                   G.greedy == w.win_greedy && G.min_len == min_len && G.tile == tl && G.digit == db && G.laid == w.laid && G.stream == s;
   if (upload_windows(w, norm.data(), W, s, true)) return APO_EDEVICE;
   // Windows with a workgroup each: the first run of a shape is enqueued right
   // away, and its few launches are recorded while it is on the GPU.
@@ -818,7 +831,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
     G.min_len = min_len;
     G.tile = tl;
     G.digit = db;
-    G.mem = w.mem;
+    G.laid = w.laid;
     G.stream = s;
     ctx->graph_captures++;
   } else {

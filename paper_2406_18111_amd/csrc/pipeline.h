@@ -80,6 +80,7 @@ struct Workspace {
   void *mem = nullptr;
   bool external = false;  // device arrays live in caller-owned memory (attach)
   size_t bytes = 0;
+  uint64_t laid = 0;  // layouts so far: a captured sequence holds the pointers of one (the address alone can come back)
 
   uint64_t *tok64 = nullptr;
   uint32_t *tokrank = nullptr, *hrank = nullptr, *dist_idx = nullptr, *dist_slot = nullptr;

@@ -141,6 +141,7 @@ int Workspace::layout(uint64_t wantN, uint32_t wantW, size_t *dry_bytes, void *e
     if (e != hipSuccess) { mem = nullptr; (void)hipGetLastError(); return -2; }
   }
   bytes = L.total;
+  laid++;
   char *m = static_cast<char *>(mem);
   tok64 = (uint64_t *)(m + o_tok64);
   tokrank = (uint32_t *)(m + o_tokrank);

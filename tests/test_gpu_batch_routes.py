@@ -106,6 +106,38 @@ def test_a_capturing_stream_is_refused(ctx):
     assert ctx.graph_stats()["replays"] >= before + 2
 
 
+def test_lanes_where_one_workspace_does_not_fit(ctx):
+    """A batch whose one workspace (of the next power of two tokens) finds no
+    device memory is analysed in lanes, whose smaller ones do."""
+    import torch
+    total, lanes = 12_000_000, 3
+    lens = [20000] * (total // 20000)
+    base = _loops([20000] * 10)
+    wins = [base[k % 10] for k in range(len(lens))]
+    dev, off = _pack(wins)
+    refs10 = _refs(base, 25)
+    lib = ctx._lib
+    one = lib.apo_workspace_bytes(total, len(wins))
+    per_lane = lib.apo_workspace_bytes(1 << 22, len(wins))
+    room = (one + lanes * per_lane) // 2
+    assert lanes * per_lane + (1 << 30) < room < one - (1 << 30)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hog = []
+    try:
+        while torch.cuda.mem_get_info()[0] > room + (64 << 20):
+            hog.append(torch.empty(torch.cuda.mem_get_info()[0] - room, dtype=torch.uint8, device="cuda"))
+            assert len(hog) < 8
+        for rep in range(2):
+            got = ctx.analyze_batch_dev(dev, off, 25)
+            _check(got, [refs10[k % 10] for k in range(len(wins))], rep)
+    finally:
+        hog.clear()
+        torch.cuda.empty_cache()
+    _check(ctx.analyze_batch_dev(dev, off, 25), [refs10[k % 10] for k in range(len(wins))])
+    assert any(ctx.stage_ms().values())  # a workgroup per window again, now that there is room
+
+
 @pytest.mark.parametrize("windows", [1, 2, 5])
 def test_windows_of_65536_distinct_tokens(ctx, windows):
     """More ranks than 16 bits hold, and nothing that repeats: no rows, beside
