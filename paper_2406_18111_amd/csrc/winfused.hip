@@ -2163,18 +2163,48 @@ __global__ __launch_bounds__(kLongNT) void k_window_rest(LongArgs la) {
   window_long<kFusedLongMax, false>(la, L, win, tb, (uint32_t)(la.f.off[win + 1] - la.f.off[win]));
 }
 
+// Where each window's rows go, for batches of more than kOwnBase windows: the sums
+// of the counts before it, by one workgroup (2^20 windows: 128 steps).
+constexpr uint32_t kOwnBase = 4096;
+__global__ __launch_bounds__(1024) void k_row_bases(const uint32_t *win_rows, uint32_t W, uint32_t *base) {
+  constexpr uint32_t PER = 8;
+  __shared__ uint32_t sh[1024 / 64];
+  uint32_t carry = 0;
+  for (uint32_t b0 = 0; b0 < W; b0 += 1024 * PER) {
+    const uint32_t b = b0 + threadIdx.x * PER;
+    uint32_t v[PER], loc = 0, tot;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+      v[q] = b + q < W ? win_rows[b + q] : 0u;
+      loc += v[q];
+    }
+    uint32_t at = carry + block_excl_sum<1024>(loc, sh, &tot);
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+      if (b + q < W) base[b + q] = at;
+      at += v[q];
+    }
+    carry += tot;
+    __syncthreads();  // sh is used again
+  }
+}
+
 // Packs the windows' rows, each window's at row off[w] / min_len of `src`,
 // into dst in window order: window w's go to the sum of the counts before it,
-// which its workgroup adds up itself (a few thousand words at most).
+// which its workgroup adds up itself up to kOwnBase windows (bases null).
 __global__ __launch_bounds__(256) void k_pack_rows(const Row *src, const uint64_t *off, const uint32_t *win_rows,
-                                                   uint32_t W, uint32_t min_len, Row *dst) {
+                                                   const uint32_t *bases, uint32_t min_len, Row *dst) {
   __shared__ uint32_t sh[4];
   const uint32_t w = blockIdx.x, c = win_rows[w];
   if (c == 0) return;  // uniform
-  uint32_t part = 0;
-  for (uint32_t q = threadIdx.x; q < w; q += 256) part += win_rows[q];
   uint32_t base;
-  (void)block_excl_sum<256>(part, sh, &base);
+  if (bases) {
+    base = bases[w];
+  } else {
+    uint32_t part = 0;
+    for (uint32_t q = threadIdx.x; q < w; q += 256) part += win_rows[q];
+    (void)block_excl_sum<256>(part, sh, &base);
+  }
   const Row *from = src + (off[w] - off[0]) / min_len;
   for (uint32_t r = threadIdx.x; r < c; r += 256) dst[base + r] = from[r];
 }
@@ -2284,7 +2314,9 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bo
   a.win_rows = w.win_rows;
   if (two) la.again = w.wflag;
   launch(la, W, longest, s);
-  hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, W,
+  uint32_t *bases = W > kOwnBase ? w.d_order : nullptr;  // the order has been read, and comes with every run
+  if (bases) hipLaunchKernelGGL(k_row_bases, dim3(1), dim3(1024), 0, s, w.win_rows, W, bases);
+  hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, bases,
                      min_len, static_cast<Row *>(w.rows));
   copy_u32(w.selcnt, w.dcnt + CNT_M, s);
 }

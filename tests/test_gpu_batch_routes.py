@@ -160,3 +160,47 @@ def test_windows_of_65536_distinct_tokens(ctx, windows):
         assert c["active_sum"] - int(off[-1]) == active, c
         if windows > 1:
             assert any(ctx.stage_ms().values())
+
+
+@pytest.mark.parametrize("windows", [4096, 4097, 8193, 150000])
+def test_many_small_windows(ctx, windows):
+    """Rows packed in window order for any number of windows (up to 4096 each
+    finds its place on its own), and what is counted over all of them."""
+    rng = np.random.default_rng(windows)
+    base = _loops(rng.integers(0, 60, 40), seed=3) + [np.zeros(0, np.uint64), np.full(33, 7, np.uint64)]
+    refs, sigma = _refs(base, 3), [len(np.unique(w)) for w in base]
+    active = [int(oracle.suffix_array(w, return_active=True)[1].sum()) if len(w) > 1 else 0 for w in base]
+    pick = rng.integers(0, len(base), windows)
+    if windows == 8193:
+        pick[50:-50] = len(base) - 2  # more windows than tokens
+    dev, off = _pack([base[k] for k in pick])
+    want = np.concatenate([refs[k] for k in pick])
+    counts = np.cumsum([0] + [len(refs[k]) for k in pick])
+    for graphs in (True, True, False):
+        ctx.set_graphs(graphs)
+        rows, oo = ctx.analyze_batch_dev(dev, off, 3)
+        assert np.array_equal(oo.astype(np.int64), counts)
+        assert np.array_equal(rows.cpu().numpy().astype(np.int64), want)
+        c = ctx.counters()
+        assert c["rows"] == len(want) and c["sigma"] == sum(sigma[k] for k in pick)
+        assert c["active_sum"] - int(off[-1]) == sum(active[k] for k in pick)
+
+
+def test_time_grows_with_the_number_of_windows_only(ctx):
+    """Four times the windows take some four times as long (rows placed by adding up
+    all counts before each window's took 12 times), the shortest of three runs each."""
+    import time
+    import torch
+    took = []
+    for windows in (500000, 2000000):
+        dev = torch.tensor([1, 2, 3, 4], device="cuda").repeat(2 * windows)
+        off = np.arange(windows + 1, dtype=np.uint64) * np.uint64(8)
+        ts = []
+        for _ in range(4):
+            t0 = time.perf_counter()
+            rows, oo = ctx.analyze_batch_dev(dev, off, 2)
+            ts.append(time.perf_counter() - t0)
+        assert np.array_equal(oo, np.arange(windows + 1)) and torch.equal(rows[:2], rows[-2:])
+        assert rows[0].tolist() == [0, 4, 2]
+        took.append(min(ts[1:]))
+    assert took[1] < 7 * took[0], took
