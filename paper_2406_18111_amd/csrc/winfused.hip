@@ -437,8 +437,20 @@ struct FusedArgs {
   uint32_t row_cap, occ_cap;
   uint64_t *spill;         // two words per token: records that find no room in LDS yet
   FusedInfo *info;         // one window
-  uint32_t *dcnt, *rhist, *win_rows;  // batch: counters added up over the windows
+  uint32_t *win_rows;      // batch
+  uint32_t *parts;         // batch: copies of the counters, added up over a share of the windows each
+  uint32_t part_mask;      // their number, a power of two, - 1
 };
+
+// A batch's counters: in one copy for all its windows an atomic waits for another on
+// the same words, some 100 ns a window (10^5 windows of 250 tokens 12.7 ms, now
+// 4.0; 10^6 of 25 tokens 119 and 23).  A copy for 64 windows, up to kParts: the words
+// of dcnt, then a word per doubling round.
+constexpr uint32_t kParts = 64, kPartWords = 64;
+static_assert(CNT_COUNT + kLongRounds <= kPartWords, "a part");
+__device__ __forceinline__ uint32_t *part_of(const FusedArgs &a) {
+  return a.parts + (blockIdx.x & a.part_mask) * kPartWords;
+}
 
 // What a window's analysis found, to the host (one window) or added to the
 // batch's counters.  own: distinct tokens without the largest value.
@@ -460,23 +472,24 @@ __device__ __forceinline__ void report(const FusedArgs &a, uint32_t win, const R
     return;
   }
   a.win_rows[win] = r.rows;
-  atomicAdd(&a.dcnt[CNT_NDSUM], r.sigma);
-  atomicMax(&a.dcnt[CNT_NDMAX], r.sigma);
-  atomicAdd(&a.dcnt[CNT_C], r.cands);
-  atomicAdd(&a.dcnt[CNT_CSKIP], r.skipped);
-  atomicMax(&a.dcnt[CNT_MAXL], r.maxl);
-  atomicAdd(&a.dcnt[CNT_M], r.m);
-  atomicAdd(&a.dcnt[CNT_A], r.accepted);
-  atomicAdd(&a.dcnt[CNT_NROWS], r.rows);
+  uint32_t *const cnt = part_of(a);
+  atomicAdd(&cnt[CNT_NDSUM], r.sigma);
+  atomicMax(&cnt[CNT_NDMAX], r.sigma);
+  atomicAdd(&cnt[CNT_C], r.cands);
+  atomicAdd(&cnt[CNT_CSKIP], r.skipped);
+  atomicMax(&cnt[CNT_MAXL], r.maxl);
+  atomicAdd(&cnt[CNT_M], r.m);
+  atomicAdd(&cnt[CNT_A], r.accepted);
+  atomicAdd(&cnt[CNT_NROWS], r.rows);
   // past the bounds of the stage-by-stage batch's per-window ranks and pair ranks
   if (r.own > kOwnRanks || r.pairs > kOwnPairs) {
     uint32_t g = 0;  // the window's lane
     while (g < 3 && win >= a.order[a.windows + 1 + g]) g++;
-    atomicAdd(&a.dcnt[CNT_RANGE + g], 1u);
+    atomicAdd(&cnt[CNT_RANGE + g], 1u);
   }
   for (uint32_t k = 0; k < r.nhist; k++)
-    if (hist[k]) atomicAdd(&a.rhist[4 * k], hist[k]);
-  for (int k = 0; k < kStages; k++) atomicMax(&a.dcnt[CNT_STAGE + k], (uint32_t)(stamp[k + 1] - stamp[k]));
+    if (hist[k]) atomicAdd(&cnt[CNT_COUNT + k], hist[k]);
+  for (int k = 0; k < kStages; k++) atomicMax(&cnt[CNT_STAGE + k], (uint32_t)(stamp[k + 1] - stamp[k]));
 }
 
 // LDS of a window of up to NT * IPT tokens.  lds holds, one phase after the other:
@@ -2096,7 +2109,7 @@ __device__ __forceinline__ uint32_t window_of(const FusedArgs &a, uint32_t &win,
   const uint32_t n = (uint32_t)(a.off[win + 1] - a.off[win]);
   if (n < 2 && threadIdx.x == 0) {
     a.win_rows[win] = 0;
-    atomicAdd(&a.dcnt[CNT_NDSUM], n);
+    if (n) atomicAdd(&part_of(a)[CNT_NDSUM], n);
   }
   return n;
 }
@@ -2150,7 +2163,7 @@ __global__ __launch_bounds__(kLongNT, 8) void k_window_mid(LongArgs la) {
     la.again[win] = 0;
     if (n < 2) {
       la.f.win_rows[win] = 0;
-      atomicAdd(&la.f.dcnt[CNT_NDSUM], n);
+      if (n) atomicAdd(&part_of(la.f)[CNT_NDSUM], n);
     }
   }
   if (n >= 2) window_short<kLongNT, 4>(la.f, L.s, win, tb, n);
@@ -2161,6 +2174,23 @@ __global__ __launch_bounds__(kLongNT) void k_window_rest(LongArgs la) {
   if (blockIdx.x >= la.f.order[la.f.windows] && !la.again[win]) return;  // uniform
   const uint64_t tb = la.f.off[win] - la.f.off[0];
   window_long<kFusedLongMax, false>(la, L, win, tb, (uint32_t)(la.f.off[win + 1] - la.f.off[win]));
+}
+
+// The counters' copies into where finish_run reads them: dcnt, a word of rhist per
+// round, and the candidates as the selection's first count.
+__global__ __launch_bounds__(kPartWords) void k_sum_parts(const uint32_t *parts, uint32_t n, uint32_t *dcnt,
+                                                          uint32_t *rhist, uint32_t *selcnt) {
+  const uint32_t t = threadIdx.x;
+  const bool most = t == CNT_NDMAX || t == CNT_MAXL || (t >= CNT_STAGE && t < CNT_STAGE + kStages);
+  uint32_t v = 0;
+#pragma unroll 8
+  for (uint32_t p = 0; p < n; p++) {
+    const uint32_t x = parts[p * kPartWords + t];
+    v = most ? max(v, x) : v + x;
+  }
+  if (t < CNT_COUNT) dcnt[t] = t == CNT_FUSED ? 1u : v;
+  else if (t < CNT_COUNT + kLongRounds) rhist[4 * (t - CNT_COUNT)] = v;
+  if (t == CNT_M) selcnt[0] = v;
 }
 
 // Where each window's rows go, for batches of more than kOwnBase windows: the sums
@@ -2296,8 +2326,10 @@ bool fused_in_two(const uint64_t *off, uint32_t W) {
 
 void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bool two, uint32_t min_len,
                  hipStream_t s) {
-  static_assert(CNT_COUNT == 32, "one bit a word");
-  clear_run(w.dcnt, ~0u, CNT_FUSED, w.rhist, 4 * (uint32_t)w.nsnap, w.selcnt, 3 * (kSelRoundCap + 2),
+  uint32_t *const parts = w.snap;  // (a capacity of 1024 tokens holds 12 K words)
+  uint32_t nparts = 1;
+  while (nparts < kParts && 64 * nparts < W) nparts *= 2;
+  clear_run(nullptr, 0, CNT_COUNT, parts, nparts * kPartWords, w.selcnt, 3 * (kSelRoundCap + 2),
             reinterpret_cast<uint32_t *>(w.eng.bufs().ctr), sizeof(SortCounters) / 4, s);
   LongArgs la = args_of(w);
   FusedArgs &a = la.f;
@@ -2309,8 +2341,8 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bo
   a.min_len = min_len;
   a.rows = static_cast<Row *>(w.occ);  // a batch reports no occurrences: their array stages the rows
   a.row_cap = kNone;
-  a.dcnt = w.dcnt;
-  a.rhist = w.rhist;
+  a.parts = parts;
+  a.part_mask = nparts - 1;
   a.win_rows = w.win_rows;
   if (two) la.again = w.wflag;
   launch(la, W, longest, s);
@@ -2318,7 +2350,7 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bo
   if (bases) hipLaunchKernelGGL(k_row_bases, dim3(1), dim3(1024), 0, s, w.win_rows, W, bases);
   hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, bases,
                      min_len, static_cast<Row *>(w.rows));
-  copy_u32(w.selcnt, w.dcnt + CNT_M, s);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(kPartWords), 0, s, parts, nparts, w.dcnt, w.rhist, w.selcnt);
 }
 
 }  // namespace apo
