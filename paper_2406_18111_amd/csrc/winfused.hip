@@ -2109,7 +2109,7 @@ __device__ __forceinline__ uint32_t window_of(const FusedArgs &a, uint32_t &win,
   const uint32_t n = (uint32_t)(a.off[win + 1] - a.off[win]);
   if (n < 2 && threadIdx.x == 0) {
     a.win_rows[win] = 0;
-    if (n) atomicAdd(&part_of(a)[CNT_NDSUM], n);
+    atomicAdd(&part_of(a)[CNT_NDSUM], n);  // (0 too: the kernels took 18 registers more with a branch for it)
   }
   return n;
 }
@@ -2163,7 +2163,7 @@ __global__ __launch_bounds__(kLongNT, 8) void k_window_mid(LongArgs la) {
     la.again[win] = 0;
     if (n < 2) {
       la.f.win_rows[win] = 0;
-      if (n) atomicAdd(&part_of(la.f)[CNT_NDSUM], n);
+      atomicAdd(&part_of(la.f)[CNT_NDSUM], n);
     }
   }
   if (n >= 2) window_short<kLongNT, 4>(la.f, L.s, win, tb, n);
