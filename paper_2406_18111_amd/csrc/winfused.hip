@@ -2246,11 +2246,11 @@ void launch(const LongArgs &la, uint32_t blocks, uint64_t longest, hipStream_t s
   if (longest <= 1024) hipLaunchKernelGGL((k_window<256, 4>), dim3(blocks), dim3(256), 0, s, a);
   else if (longest <= 2048) hipLaunchKernelGGL((k_window<512, 4>), dim3(blocks), dim3(512), 0, s, a);
   else if (longest <= 4096) hipLaunchKernelGGL((k_window<1024, 4>), dim3(blocks), dim3(1024), 0, s, a);
-  else if (longest <= kFusedMax) hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a);
   else if (la.again) {
     hipLaunchKernelGGL(k_window_mid, dim3(blocks), dim3(kLongNT), 0, s, la);
     hipLaunchKernelGGL(k_window_rest, dim3(blocks), dim3(kLongNT), 0, s, la);
-  } else hipLaunchKernelGGL(k_window_any, dim3(blocks), dim3(kLongNT), 0, s, la);
+  } else if (longest <= kFusedMax) hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a);
+  else hipLaunchKernelGGL(k_window_any, dim3(blocks), dim3(kLongNT), 0, s, la);
 }
 
 LongArgs args_of(const Workspace &w) {
@@ -2307,20 +2307,26 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
 // The two launches run one after the other, so each takes its longest window's
 // time at least; one launch fills the chip to its end.  Nanoseconds as measured:
 // a window alone 23 a token (30 with another on its compute unit), many of them
-// 34 a token and compute unit, in twos 22.  (Windows of 256 to 65536 tokens,
-// one launch and two: 1200 of them 1.98 and 2.87 ms, 4096 6.5 and 5.9; of 5000 to
-// 20000: 300 0.60 and 0.65, 600 0.98 and 0.78.)
+// 34 a token and compute unit, in twos 22; and a window, however short, some 27000,
+// in twos 12000, since every workgroup of a launch is of the size that its longest
+// window needs.  (Windows of 256 to 65536 tokens, one launch and two: 1200 of them 1.98
+// and 2.87 ms, 4096 6.5 and 5.9; of 5000 to 20000: 300 0.60 and 0.65, 600 0.98 and
+// 0.78; of 250 to 8192: 1200 0.54 and 0.37, 2048 0.86 and 0.57; 200000 of 25 and one of
+// 6000: 28.7 and 13.4, stage by stage 23.)  Up to 4096 tokens the single launch has the
+// same workgroups.
 bool fused_in_two(const uint64_t *off, uint32_t W) {
-  uint64_t n[2] = {0, 0}, longest[2] = {0, 0};  // windows that share a compute unit, longer ones
+  uint64_t n[2] = {0, 0}, count[2] = {0, 0}, longest[2] = {0, 0};  // windows that share a compute unit, longer ones
   for (uint32_t k = 0; k < W; k++) {
     const uint64_t len = off[k + 1] - off[k];
     const int side = len > kFusedMidMax;
     n[side] += len;
+    count[side]++;
     longest[side] = std::max(longest[side], len);
   }
-  if (std::max(longest[0], longest[1]) <= kFusedMax) return false;
-  const uint64_t one = std::max(23 * std::max(longest[0], longest[1]), 34 * (n[0] + n[1]) / 256);
-  const uint64_t two = std::max(23 * longest[1], 34 * n[1] / 256) + std::max(30 * longest[0], 22 * n[0] / 256);
+  if (std::max(longest[0], longest[1]) <= 4096) return false;
+  const uint64_t one = std::max(23 * std::max(longest[0], longest[1]), (34 * (n[0] + n[1]) + 27000 * (count[0] + count[1])) / 256);
+  const uint64_t two = std::max(23 * longest[1], (34 * n[1] + 27000 * count[1]) / 256) +
+                       std::max(30 * longest[0], (22 * n[0] + 12000 * count[0]) / 256);
   return two < one;
 }
 

@@ -204,3 +204,25 @@ def test_time_grows_with_the_number_of_windows_only(ctx):
         assert rows[0].tolist() == [0, 4, 2]
         took.append(min(ts[1:]))
     assert took[1] < 7 * took[0], took
+
+
+@pytest.mark.parametrize("longest", [4096, 4097, 8192])
+def test_many_windows_beside_one_somewhat_longer(ctx, longest):
+    """Windows of up to 8192 tokens share compute units in twos where they are many:
+    at the edges of that form's two analyses, with as many distinct tokens as its
+    table takes and one more, and beside windows of a few tokens."""
+    rng = np.random.default_rng(longest)
+    mix = np.uint64(0x9E3779B97F4A7C15)
+    base = _loops([4095, longest - 1, longest, 300, 30, 1, 0, 2], seed=5)
+    base += [np.concatenate([rng.permutation(d), rng.integers(0, d, longest - d)]).astype(np.uint64) * mix
+             for d in (6144, 6145, longest) if d <= longest]
+    base += [np.full(longest, 3, np.uint64), np.tile(np.arange(7, dtype=np.uint64), longest)[:longest]]
+    refs = _refs(base, 2)
+    pick = np.concatenate([np.repeat(np.arange(len(base)), 100), rng.integers(4, 8, 3000)])
+    rng.shuffle(pick)
+    dev, off = _pack([base[k] for k in pick])
+    want = np.concatenate([refs[k] for k in pick])
+    for rep in range(3):
+        rows, oo = ctx.analyze_batch_dev(dev, off, 2)
+        assert np.array_equal(oo.astype(np.int64), np.cumsum([0] + [len(refs[k]) for k in pick]))
+        assert np.array_equal(rows.cpu().numpy().astype(np.int64), want), rep
