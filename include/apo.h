@@ -165,7 +165,9 @@ int apo_set_lanes(apo_ctx *ctx, int lanes);
  * enabled (default), record it as a HIP graph that is replayed for later
  * batches of the same shape (same token pointer, total length, window count,
  * longest window, min_len and kernel parameters); window offsets are uploaded
- * outside the graph.  on = 0 disables capture. */
+ * outside the graph.  A batch of one window of more than 25600 tokens goes
+ * host-driven, as that window does on its own, and is not captured.  on = 0
+ * disables capture. */
 int apo_set_graphs(apo_ctx *ctx, int on);
 
 /* Number of graph captures and replays made by this context. */
@@ -246,11 +248,12 @@ int apo_inject_device_error(apo_ctx *ctx, int after_syncs);
 
 /* Selection path (Section 4.2, the greedy walk of Algorithm 2): with on = 1
  * (default) windows of at most 2^17 tokens in a batch, and single windows of
- * at most 2^15 tokens, are decided by one wavefront per window walking the
+ * at most 2^15 tokens (25600 where the window is a batch's or the server's only
+ * one), are decided by one wavefront per window walking the
  * window's candidates in priority order over an on-chip bitmap; longer
  * windows use the round-based evaluation.  Such single windows, and batches
- * whose windows all have at most 2^16 tokens, go through all stages in one
- * workgroup per window, unless a kernel is being timed (apo_profile_kernel) or an
+ * of two windows or more that all have at most 2^16 tokens, go through all stages
+ * in one workgroup per window, unless a kernel is being timed (apo_profile_kernel) or an
  * error is to be injected.  on = 0 sends every analysis stage by stage through the
  * rounds.  Results are identical either way.  APO_EINVAL
  * unless on is 0 or 1. */

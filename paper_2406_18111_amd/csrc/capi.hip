@@ -778,6 +778,11 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   w.sel_prefix = ctx->sel_prefix;
   w.win_greedy = ctx->win_greedy;
   w.fuse_one = true;
+  const bool fused = takes_fused(w, W, maxwin);
+  // One window has no others to wait for on the device: stage by stage each round is
+  // sized by what the one before left.
+  if (W == 1 && !fused && w.ktag == KT_NONE)
+    return map_rc(run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::HOST));
   // Timed kernel launches are bracketed by events on the stream, which is
   // only reliable outside captured graphs: profiling runs the same sync-free
   // sequence without capture.
@@ -787,7 +792,6 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
     return map_rc(rc);
   }
   GraphCache &G = ctx->gc;
-  const bool fused = takes_fused(w, W, maxwin);
   const bool hit = G.exec && G.tok == d_tok && G.total == total && G.W == W && G.maxwin == maxwin && G.fused == fused &&
                    G.greedy == w.win_greedy && G.min_len == min_len && G.tile == tl && G.digit == db && G.laid == w.laid && G.stream == s;
   if (upload_windows(w, norm.data(), W, s, true)) return APO_EDEVICE;

@@ -356,8 +356,8 @@ int upload_windows(Workspace &w, const uint64_t *h_off, uint32_t W, hipStream_t 
 }
 
 bool takes_fused(const Workspace &w, uint32_t W, uint64_t maxwin) {
-  return !w.by_stage && (W > 1 || w.fuse_one) && maxwin <= kFusedLongMax && w.win_greedy && w.ktag == KT_NONE &&
-         w.fail_after < 0;
+  return !w.by_stage && (W > 1 ? maxwin <= kFusedLongMax : w.fuse_one && maxwin <= kFusedLone) && w.win_greedy &&
+         w.ktag == KT_NONE && w.fail_after < 0;
 }
 
 int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const uint64_t *h_off, uint32_t W,
@@ -651,7 +651,7 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
   const int lbits = bit_length_u64(maxl_bound);
   const int wbits = batch ? bit_length_u64(W - 1) : 0;
   const bool winsel =
-      w.win_greedy && (batch ? (maxwin <= kWinSelMax && lbits + wbits <= 32) : (N <= kWinSelSingle));
+      w.win_greedy && (batch ? (maxwin <= kWinSelMax && lbits + wbits <= 32) : (N <= kFusedLone));
   uint64_t m_bound = 0;
   if (c_bound > 0) {
     // Priority order (length desc, ID asc, start asc).  The records are in

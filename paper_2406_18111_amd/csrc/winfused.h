@@ -11,6 +11,13 @@ constexpr uint32_t kFusedMax = 8192;
 // Longest window one workgroup takes with its arrays in the workspace (positions
 // and ranks in 16 bits, one array of them in LDS at a time).
 constexpr uint32_t kFusedLongMax = 65536;
+// Longest window that takes one workgroup where it is a batch's or the server's only
+// one.  Up to here no content is slower than stage by stage before there was that
+// form (a loop without substitutions 1.16 ms at either; in most windows the one workgroup is
+// twice as fast); above, stage by stage, host-driven, is as fast for a loop with 5 %
+// substitutions (30000 tokens: 0.70 and 0.70 ms; 65536: 1.48 and 0.80) and faster for
+// one without (1.34 and 0.86; 2.85 and 0.96), 65536 random tokens 3.1 and 0.62.
+constexpr uint32_t kFusedLone = 25600;
 // Longest window of a large batch that shares a compute unit with another.
 constexpr uint32_t kFusedMidMax = 32768;
 

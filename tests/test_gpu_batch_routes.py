@@ -226,3 +226,36 @@ def test_many_windows_beside_one_somewhat_longer(ctx, longest):
         rows, oo = ctx.analyze_batch_dev(dev, off, 2)
         assert np.array_equal(oo.astype(np.int64), np.cumsum([0] + [len(refs[k]) for k in pick]))
         assert np.array_equal(rows.cpu().numpy().astype(np.int64), want), rep
+
+
+@pytest.mark.parametrize("n", [25600, 25601, 32768, 65536, 65537])
+def test_the_only_window_of_a_batch(ctx, n):
+    """One window in a batch, and one request at a time at the server, around the
+    length up to which it takes one workgroup: with and without graphs, from
+    device and host tokens."""
+    from paper_2406_18111_amd import Context
+    rng = np.random.default_rng(n)
+    wins = [_loops([n])[0], np.tile(np.arange(100, dtype=np.uint64), n // 100 + 1)[:n],
+            rng.integers(0, 1 << 40, n).astype(np.uint64),
+            np.concatenate([np.zeros(n // 2, np.uint64), rng.integers(0, 4, n - n // 2).astype(np.uint64)])]
+    refs = [_refs([w], 8) for w in wins]
+    active = [int(oracle.suffix_array(w, return_active=True)[1].sum()) for w in wins]
+    for k, w in enumerate(wins):
+        dev, off = _pack([w])
+        for graphs in (True, True, False):
+            ctx.set_graphs(graphs)
+            _check(ctx.analyze_batch_dev(dev, off, 8), refs[k], k)
+            c = ctx.counters()
+            assert c["active_sum"] - n == active[k] and c["rows"] == len(refs[k][0]), (k, c)
+            assert c["sigma"] == len(np.unique(w)), (k, c)
+        rows, _ = ctx.analyze_batch(w, off, 8)
+        assert np.array_equal(np.stack([rows[f] for f in rows.dtype.names], 1).astype(np.int64), refs[k][0]), k
+    with Context(0) as srv:
+        srv.server_start(slots=1)
+        for k, w in enumerate(wins):
+            ticket, got = srv.submit(w, 8), None
+            while got is None:
+                got = srv.fetch(ticket)
+            rows = got[0]
+            assert np.array_equal(np.stack([rows[f] for f in rows.dtype.names], 1).astype(np.int64), refs[k][0]), k
+        srv.server_stop()
