@@ -580,6 +580,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
     ln.ws->win_greedy = ctx->win_greedy;
     ln.ws->fuse_one = true;
     ln.ws->by_stage = ctx->ws.by_stage;
+    ln.ws->may_leave = false;  // (the other lanes would wait for its second run)
     if (ln.st != s && hipStreamWaitEvent(ln.st, ctx->lane_ready, 0) != hipSuccess) return APO_EDEVICE;
     lanes.push_back(std::move(ln));
   }
@@ -664,8 +665,7 @@ static int batch_lanes(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off,
         ln.ws->kev_n = 0;
         int rc = finish_run(*ln.ws, ln.total, ln.W, 2 * ln.total, kSelFreeRounds, ln.info, s, false);
         if (rc == 1)  // greedy rounds left candidates undecided: this lane again, host-driven
-          rc = run_pipeline(*ln.ws, d_tok + ln.tok0, 64, ln.total, ln.norm.data(), ln.W, min_len, Stop::FULL, s,
-                            ln.info, Mode::HOST);
+          rc = run_by_stage(*ln.ws, d_tok + ln.tok0, ln.total, ln.norm.data(), ln.W, min_len, s, ln.info);
         if (rc) return map_rc(rc);
         merge_info(ctx->info, ln.info);
         ctx->louts.push_back({ln.ws, ln.W, ln.info.rows});
@@ -778,6 +778,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   w.sel_prefix = ctx->sel_prefix;
   w.win_greedy = ctx->win_greedy;
   w.fuse_one = true;
+  w.may_leave = true;
   const bool fused = takes_fused(w, W, maxwin);
   // One window has no others to wait for on the device: stage by stage each round is
   // sized by what the one before left.
@@ -788,7 +789,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   // sequence without capture.
   if (!ctx->graphs || w.ktag != 0) {
     rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::FREE);
-    if (rc == 1) rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::HOST);
+    if (rc == 1) rc = run_by_stage(w, d_tok, total, norm.data(), W, min_len, s, ctx->info);
     return map_rc(rc);
   }
   GraphCache &G = ctx->gc;
@@ -822,7 +823,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
       fprintf(stderr, "[apo] graph capture failed; batches run without graphs\n");
       ctx->graphs = false;
       rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::FREE);
-      if (rc == 1) rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::HOST);
+      if (rc == 1) rc = run_by_stage(w, d_tok, total, norm.data(), W, min_len, s, ctx->info);
       return map_rc(rc);
     }
     G.graph = g;
@@ -845,7 +846,7 @@ static int batch_single(apo_ctx *ctx, const uint64_t *d_tok, const uint64_t *off
   if (!ahead && hipGraphLaunch(G.exec, s) != hipSuccess) return APO_EDEVICE;
   ctx->info = RunInfo{};
   rc = finish_run(w, total, W, 2 * total, kSelFreeRounds, ctx->info, s, false);
-  if (rc == 1) rc = run_pipeline(w, d_tok, 64, total, norm.data(), W, min_len, Stop::FULL, s, ctx->info, Mode::HOST);
+  if (rc == 1) rc = run_by_stage(w, d_tok, total, norm.data(), W, min_len, s, ctx->info);
   return map_rc(rc);
 }
 
@@ -1355,6 +1356,7 @@ static void slot_loop(Server *S, Slot *sl) {
         S->tune.pick(total, tl, db);
         sl->ws.eng.set_params(tl, db);
         sl->ws.fuse_one = true;
+        sl->ws.may_leave = true;
         rc = map_rc(run_pipeline(sl->ws, sl->ws.tok64, 64, total, off.data(), W, batch[0]->min_len, Stop::FULL,
                                  sl->stream, info));
       }

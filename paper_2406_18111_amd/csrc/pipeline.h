@@ -131,6 +131,7 @@ struct Workspace {
   int fail_after = -1;             // test hook: host syncs before one reports a device error (-1: never)
   bool fuse_one = false;           // a lone short window takes the one-workgroup analysis in run_pipeline too
   bool by_stage = false;           // every analysis goes stage by stage
+  bool may_leave = false;          // few windows may give up their workgroups (finish_run then returns 1)
   bool win_greedy = true;          // one-wavefront-per-window greedy where windows are short enough
 
   // device bytes a workspace of capacity (N, W) holds (exact)
@@ -168,14 +169,17 @@ bool takes_fused(const Workspace &w, uint32_t W, uint64_t maxwin);
 // ascending, h_off[0] == 0).  Results stay in the workspace.
 int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const uint64_t *h_off, uint32_t W,
                  uint32_t min_len, Stop stop, hipStream_t s, RunInfo &info, Mode mode = Mode::HOST);
+// The same host-driven and stage by stage, after a run that finish_run returned 1 for.
+int run_by_stage(Workspace &w, const void *d_tok, uint64_t N, const uint64_t *h_off, uint32_t W, uint32_t min_len,
+                 hipStream_t s, RunInfo &info);
 // window_major: the candidate list (and so the accepted occurrences) is
 // already ordered window by window.
 int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t *wid, const uint32_t *wbeg,
                 uint64_t m_bound, bool host, hipStream_t s, bool window_major);
 // W > 1: the windows' row counts arrive in w.hwin.
 // sel_launched: selection rounds enqueued by a sync-free run (-1: host-driven).
-// Returns 1 when a sync-free run left candidates undecided (the caller then
-// reruns host-driven).
+// Returns 1 when a sync-free run left candidates undecided, or windows their
+// workgroups (the caller then reruns host-driven, see run_by_stage).
 int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
                bool stamps);
 

@@ -381,7 +381,9 @@ int run_pipeline(Workspace &w, const void *d_tok, int bits, uint64_t N, const ui
     w.kev_n = 0;
     fused_batch(w, d_tok, W, maxwin, fused_in_two(h_off, W), min_len, s);
     if (mode == Mode::CAPTURE) return 0;
-    return finish_run(w, N, W, N, 1, info, s, false);
+    rc = finish_run(w, N, W, N, 1, info, s, false);
+    if (rc != 1 || !host) return rc;
+    info = RunInfo{};
   }
   stamp(w, 0, s, stamps);
   if (mode != Mode::CAPTURE)  // a captured sequence expects d_off (and the order) to be uploaded already
@@ -809,6 +811,15 @@ int emit_output(Workspace &w, uint64_t N, uint32_t W, bool batch, const uint32_t
   return 0;
 }
 
+int run_by_stage(Workspace &w, const void *d_tok, uint64_t N, const uint64_t *h_off, uint32_t W, uint32_t min_len,
+                 hipStream_t s, RunInfo &info) {
+  const bool keep = w.by_stage;
+  w.by_stage = true;
+  const int rc = run_pipeline(w, d_tok, 64, N, h_off, W, min_len, Stop::FULL, s, info, Mode::HOST);
+  w.by_stage = keep;
+  return rc;
+}
+
 // Final synchronisation of a run (or of a replayed graph): counters, the
 // rare selection completion for sync-free runs, stage and kernel timings.
 int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_launched, RunInfo &info, hipStream_t s,
@@ -817,6 +828,7 @@ int finish_run(Workspace &w, uint64_t N, uint32_t W, uint64_t m_bound, int sel_l
   if (W > 1) APO_HIP_TRY(hipMemcpyAsync(w.hwin, w.win_rows, W * 4, hipMemcpyDeviceToHost, s));
   if ((rc = read_counters(w, s, true))) return rc;
   fill_info(w, N, info);
+  if (w.hcnt[CNT_FUSED] && w.hcnt[CNT_WFLAG]) return 1;
   if (w.hcnt[CNT_FUSED])
     for (int k = 0; k < kStages; k++) info.stage_ms[k] = w.hcnt[CNT_STAGE + k] * 1e-5;  // (10 ns)
   info.sel_rounds = 0;

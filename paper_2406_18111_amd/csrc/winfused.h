@@ -42,7 +42,8 @@ void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info);
 // Batch of windows of at most kFusedLongMax 64-bit tokens each (offsets and
 // order in w.d_off and w.d_order): rows of all windows packed in window order
 // into w.rows, counts into w.win_rows, counters where finish_run reads them.
-// Uses w.wflag.
+// Uses w.wflag.  With w.may_leave, batches of two or three windows may come out
+// unfinished: CNT_WFLAG is then not 0.
 // two: in two launches, where fused_in_two says so; either form is right for any
 // windows.
 bool fused_in_two(const uint64_t *off, uint32_t W);

@@ -1247,13 +1247,15 @@ struct LongLds {
   alignas(16) Cnt ctr[kLongNW * kByte];           // radix counters; LCP minima of 8; run openings
   alignas(16) uint32_t bitmap[CAP / 32 + 2];      // as in ShortLds; LCP minima of 64 and 512
   uint32_t wsum[kLongNW], wsum2[kLongNW];
-  uint32_t s_nd, s_top, s_over, s_zero, s_active, s_max, s_skip, s_c, s_acc, s_dup, s_pairs;
+  uint32_t s_nd, s_top, s_over, s_zero, s_active, s_left, s_eighths, s_max, s_skip, s_c, s_acc, s_dup, s_pairs;
   uint32_t s_hist[kLongRounds];
   uint64_t s_stamp[kStages + 1];
   unsigned long long s_differ;
 };
 
-template <uint32_t CAP, bool FIRST>
+// FIRST: leaves a window of too many distinct tokens to the other launch.  LEAVE (see
+// k_window_any): gives up a window that keeps its suffixes grouped.
+template <uint32_t CAP, bool FIRST, bool LEAVE>
 __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L, uint32_t win, uint64_t tb, uint32_t n) {
   constexpr int NT = kLongNT, NW = kLongNW;
   constexpr int U = CAP > kFusedMidMax ? 8 : 4;  // steps whose reads are issued together
@@ -1656,17 +1658,15 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   } else {
     h = 1;
   }
-  if (!named)
-#pragma unroll 4
-    for (uint32_t k = tid; k < n; k += NT) {
-      uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
-      while (!w) w = bitmap[--x];  // slot 0 opens a group
-      rank[gsa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
-    }
-  if (tid == 0) s_nd = nd;  // (the rows are counted from there)
+  // (both are read into registers here: the first thread sets the words again at the next survey, which has to be
+  // behind a barrier of its own)
   uint32_t active;
+  bool left = false;  // another window has left
   auto survey = [&] {
-    if (tid == 0) s_active = 0;
+    if (tid == 0) {
+      s_active = 0;
+      if constexpr (LEAVE) L.s_left = __hip_atomic_load(part_of(a) + CNT_WFLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     uint32_t more = 0;
     for (uint32_t x = tid; 32 * x < n; x += NT) {
@@ -1677,11 +1677,41 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     if (lane == 63 && more) atomicAdd(&s_active, more);
     __syncthreads();
     active = s_active;
+    if constexpr (LEAVE) left = L.s_left != 0;
   };
+  auto leave = [&] {
+    if (tid == 0) {
+      a.win_rows[win] = 0;
+      atomicAdd(&part_of(a)[CNT_WFLAG], 1u);
+    }
+  };
+  if constexpr (LEAVE) {  // (before the loop below, which goes back to the opening of a group for each of its suffixes)
+    survey();
+    // the eighths of the slots in which some group opens
+    if (tid == 0) L.s_eighths = 0;
+    __syncthreads();
+    uint32_t m = 0;
+    for (uint32_t x = tid; 32 * x < n; x += NT)
+      if (bitmap[x]) m |= 1u << (256 * x / n);
+    if (m) atomicOr(&L.s_eighths, m);
+    __syncthreads();
+    if (left || (n > kFusedLone && (active > n - n / 256 * h || L.s_eighths != 0xFFu))) {  // uniform
+      leave();
+      return;
+    }
+  }
+  if (!named)
+#pragma unroll 4
+    for (uint32_t k = tid; k < n; k += NT) {
+      uint32_t x = k >> 5, w = bitmap[x] & ((2u << (k & 31)) - 1u);
+      while (!w) w = bitmap[--x];  // slot 0 opens a group
+      rank[gsa[k]] = (uint16_t)(32 * x + 31u - (uint32_t)__clz((int)w));
+    }
+  if (tid == 0) s_nd = nd;  // (the rows are counted from there)
   survey();
 
   // Prefix doubling of the suffixes still grouped, listed in the order of their
-  // second halves and sorted stably by the group of the first half (k_window's
+  // second halves and sorted stably by the group of the first half (window_short's
   // second form): j | group << 16
   {
     uint32_t *const l0 = reinterpret_cast<uint32_t *>(e0), *const l1 = reinterpret_cast<uint32_t *>(e1);
@@ -1783,6 +1813,11 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
       }
       h *= 2;
       survey();  // its first barrier ends the writes above
+      if constexpr (LEAVE)
+        if (left) {  // uniform
+          leave();
+          return;
+        }
     }
   }
   {
@@ -2125,6 +2160,17 @@ __global__ __launch_bounds__(NT) void k_window(FusedArgs a) {
 
 // Windows of any length up to kFusedLongMax in one launch: in launches of their
 // own the short windows of a batch would wait for its last long one.
+// LEAVE, for two or three windows, some longer than kFusedLone: there a workgroup each
+// is the better form for most (two of 40000 tokens, loops with 5 % substitutions, 0.93 ms,
+// stage by stage 1.06; random tokens 0.55 and 18), but not for a window that keeps its
+// suffixes grouped for many rounds (loops without substitutions 1.76 and 1.16, of 65536
+// tokens 2.88 and 1.36; half of it one run, 65536 tokens, 3.53 and 1.81).  The first sort, by
+// h <= 8 tokens, tells it: all but h in 256 suffixes are grouped (substitutions of 1 % leave
+// out 2 h or more), or one group fills an eighth of the slots.  Such a window gives up,
+// the others as soon as they see it, and the batch goes stage by stage, host-driven:
+// 1.32, 1.61 and 2.16 ms in all, no slower than before there was the one workgroup (1.42,
+// 1.65, 2.41).
+template <bool LEAVE>
 __global__ __launch_bounds__(kLongNT) void k_window_any(LongArgs la) {
   __shared__ union Lds {
     ShortLds<kLongNT, kFusedMax / kLongNT> s;
@@ -2133,7 +2179,7 @@ __global__ __launch_bounds__(kLongNT) void k_window_any(LongArgs la) {
   uint32_t win;
   uint64_t tb;
   const uint32_t n = window_of(la.f, win, tb);
-  if (n > kFusedMax) window_long<kFusedLongMax, false>(la, L.l, win, tb, n);  // uniform
+  if (n > kFusedMax) window_long<kFusedLongMax, false, LEAVE>(la, L.l, win, tb, n);  // uniform
   else if (n >= 2) window_short<kLongNT, kFusedMax / kLongNT>(la.f, L.s, win, tb, n);
 }
 
@@ -2156,7 +2202,7 @@ __global__ __launch_bounds__(kLongNT, 8) void k_window_mid(LongArgs la) {
   const uint64_t tb = la.f.off[win] - la.f.off[0];
   const uint32_t n = (uint32_t)(la.f.off[win + 1] - la.f.off[win]);
   if (n > 4 * kLongNT) {  // uniform
-    window_long<kFusedMidMax, true>(la, L.l, win, tb, n);
+    window_long<kFusedMidMax, true, false>(la, L.l, win, tb, n);
     return;
   }
   if (threadIdx.x == 0) {
@@ -2173,7 +2219,7 @@ __global__ __launch_bounds__(kLongNT) void k_window_rest(LongArgs la) {
   const uint32_t win = la.f.order[blockIdx.x];
   if (blockIdx.x >= la.f.order[la.f.windows] && !la.again[win]) return;  // uniform
   const uint64_t tb = la.f.off[win] - la.f.off[0];
-  window_long<kFusedLongMax, false>(la, L, win, tb, (uint32_t)(la.f.off[win + 1] - la.f.off[win]));
+  window_long<kFusedLongMax, false, false>(la, L, win, tb, (uint32_t)(la.f.off[win + 1] - la.f.off[win]));
 }
 
 // The counters' copies into where finish_run reads them: dcnt, a word of rhist per
@@ -2239,7 +2285,7 @@ __global__ __launch_bounds__(256) void k_pack_rows(const Row *src, const uint64_
   for (uint32_t r = threadIdx.x; r < c; r += 256) dst[base + r] = from[r];
 }
 
-void launch(const LongArgs &la, uint32_t blocks, uint64_t longest, hipStream_t s) {
+void launch(const LongArgs &la, uint32_t blocks, uint64_t longest, bool leave, hipStream_t s) {
   // the smallest workgroup that holds the longest window: fewer wavefronts per
   // barrier, and more windows per compute unit
   const FusedArgs &a = la.f;
@@ -2250,7 +2296,8 @@ void launch(const LongArgs &la, uint32_t blocks, uint64_t longest, hipStream_t s
     hipLaunchKernelGGL(k_window_mid, dim3(blocks), dim3(kLongNT), 0, s, la);
     hipLaunchKernelGGL(k_window_rest, dim3(blocks), dim3(kLongNT), 0, s, la);
   } else if (longest <= kFusedMax) hipLaunchKernelGGL((k_window<1024, 8>), dim3(blocks), dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL(k_window_any, dim3(blocks), dim3(kLongNT), 0, s, la);
+  else if (leave) hipLaunchKernelGGL(k_window_any<true>, dim3(blocks), dim3(kLongNT), 0, s, la);
+  else hipLaunchKernelGGL(k_window_any<false>, dim3(blocks), dim3(kLongNT), 0, s, la);
 }
 
 LongArgs args_of(const Workspace &w) {
@@ -2281,7 +2328,7 @@ void fused_window(const Workspace &w, const void *tok, int bits, uint32_t n, uin
   a.occ = static_cast<Occ *>(occ);
   a.occ_cap = occ_cap;
   a.info = info;
-  launch(la, 1, n, s);
+  launch(la, 1, n, false, s);
 }
 
 void fused_read(const FusedInfo &f, uint32_t n, Workspace &w, RunInfo &info) {
@@ -2351,7 +2398,7 @@ void fused_batch(Workspace &w, const void *tok, uint32_t W, uint64_t longest, bo
   a.part_mask = nparts - 1;
   a.win_rows = w.win_rows;
   if (two) la.again = w.wflag;
-  launch(la, W, longest, s);
+  launch(la, W, longest, w.may_leave && W <= 3 && longest > kFusedLone, s);
   uint32_t *bases = W > kOwnBase ? w.d_order : nullptr;  // the order has been read, and comes with every run
   if (bases) hipLaunchKernelGGL(k_row_bases, dim3(1), dim3(1024), 0, s, w.win_rows, W, bases);
   hipLaunchKernelGGL(k_pack_rows, dim3(W), dim3(256), 0, s, static_cast<const Row *>(w.occ), w.d_off, w.win_rows, bases,

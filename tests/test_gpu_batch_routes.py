@@ -259,3 +259,38 @@ def test_the_only_window_of_a_batch(ctx, n):
             rows = got[0]
             assert np.array_equal(np.stack([rows[f] for f in rows.dtype.names], 1).astype(np.int64), refs[k][0]), k
         srv.server_stop()
+
+
+@pytest.mark.parametrize("n", [25600, 25601, 50000, 65536])
+def test_few_long_windows_that_give_up_their_workgroups(ctx, n):
+    """Two or three windows, one of which keeps its suffixes grouped (alone, beside
+    others that would finish, and beside a short one): rows and counts whichever form
+    the batch ends up in, through a graph, its replays, no graph, and the server."""
+    from paper_2406_18111_amd import Context
+    rng = np.random.default_rng(n)
+    loop, other = _loops([n, n - 1000], seed=9)
+    periodic = np.tile(np.arange(100, dtype=np.uint64), n // 100 + 1)[:n]
+    run = np.concatenate([rng.integers(0, 4, n // 4), np.zeros(n // 2, np.int64), rng.integers(0, 4, n // 4)]).astype(np.uint64)
+    distinct = rng.permutation(n).astype(np.uint64)
+    short, none = _loops([3000])[0], np.zeros(0, np.uint64)
+    batches = [[periodic, loop], [loop, run, other], [short, periodic], [none, run, none], [distinct, periodic[:-7], distinct],
+               [loop, other, distinct], [np.full(n, 5, np.uint64), run]]
+    for wins in batches:
+        dev, off = _pack(wins)
+        refs = _refs(wins, 8)
+        active = sum(int(oracle.suffix_array(w, return_active=True)[1].sum()) for w in wins if len(w) > 1)
+        for graphs in (True, True, True, False):
+            ctx.set_graphs(graphs)
+            _check(ctx.analyze_batch_dev(dev, off, 8), refs, graphs)
+            c = ctx.counters()
+            assert c["active_sum"] - int(off[-1]) == active and c["rows"] == sum(len(r) for r in refs), c
+    with Context(0) as srv:
+        srv.server_start(slots=1)
+        for wins in batches:
+            tickets = [srv.submit(w, 8) for w in wins]
+            for ticket, ref in zip(tickets, _refs(wins, 8)):
+                got = None
+                while got is None:
+                    got = srv.fetch(ticket)
+                assert np.array_equal(np.stack([got[0][f] for f in got[0].dtype.names], 1).astype(np.int64), ref)
+        srv.server_stop()
