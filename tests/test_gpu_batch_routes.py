@@ -294,3 +294,133 @@ def test_few_long_windows_that_give_up_their_workgroups(ctx, n):
                     got = srv.fetch(ticket)
                 assert np.array_equal(np.stack([got[0][f] for f in got[0].dtype.names], 1).astype(np.int64), ref)
         srv.server_stop()
+
+
+# ---- stage by stage: batches with a window of more than 65536 tokens
+
+FORMS = [(3, False), (2, False), (1, False), (3, True), (2, True), (1, True)]  # lanes, graphs
+
+
+def _long(seed=1, n=66000):
+    """A window that sends its batch stage by stage: few distinct tokens and pairs."""
+    return synth.loop_stream(seed, n, 40, 64, 0.05).astype(np.uint64)
+
+
+def _each_form(ctx, wins, m, check=None, forms=FORMS):
+    dev, off = _pack(wins)
+    refs = _refs(wins, m)
+    for lanes, graphs in forms:
+        ctx.set_lanes(lanes)
+        ctx.set_graphs(graphs)
+        for rep in range(3 if graphs else 1):
+            _check(ctx.analyze_batch_dev(dev, off, m), refs, (lanes, graphs, rep))
+            if check:
+                check(ctx.counters(), lanes)
+
+
+@pytest.mark.parametrize("over", [(), (4097,), (6000, 4097)])
+def test_stage_batch_window_ranks(ctx, over):
+    """Windows at the bound of the per-window token ranks (4096 distinct tokens,
+    the largest value aside), and over it, where the shared table ranks them."""
+    from test_gpu_batch_serve import _distinct_window
+    rng = np.random.default_rng(22)
+    wins = [_distinct_window(rng, d, mx) for d, mx in ((1, False), (700, False), (4095, True), (4096, False), (4096, True))]
+    wins += [_long()] + [_distinct_window(rng, d, True) for d in over]
+    sigma = sum(len(np.unique(w)) for w in wins)
+
+    def check(c, lanes):
+        if not over:
+            assert c["sigma"] == sigma
+    _each_form(ctx, wins, 2, check)
+
+
+@pytest.mark.parametrize("order", range(3))
+def test_stage_batch_pair_ranks(ctx, order):
+    """The first two doubling rounds from the windows' own pair ranks, in the lanes
+    whose windows all have at most 8192 distinct adjacent pairs (picked by the host
+    in host-driven lanes, on the device in sync-free ones and graphs)."""
+    from test_gpu_batch_serve import _oracle_active, _pair_lane_windows, _pairs_window
+    rng = np.random.default_rng(34)
+    at, over = _pairs_window(rng, 8192), _pairs_window(rng, 8193)
+    loops = _loops([3000, 9000, 700, 5000], seed=50)
+    wins = [loops + [at, _long()], loops[:2] + [over, _long()] + loops[2:] + [at], [_long(2), over, at, _long()] + loops][order]
+    active = sum(_oracle_active(w) for w in wins)
+    total = sum(len(w) for w in wins)
+
+    def check(c, lanes):
+        assert c["active_sum"] - total == active
+        assert c["pair_windows"] == _pair_lane_windows(wins, lanes, over), (c, lanes)
+    _each_form(ctx, wins, 3, check)
+
+
+@pytest.mark.parametrize("seed", [8, 9])
+def test_stage_batch_random(ctx, seed):
+    """Random windows around those bounds, tiny ones and the largest token value among them."""
+    from test_gpu_batch_serve import _oracle_active, _pair_mix_windows
+    wins = _pair_mix_windows(seed, 14)
+    wins.insert(5, _long(seed))
+    active, total = sum(_oracle_active(w) for w in wins), sum(len(w) for w in wins)
+
+    def check(c, lanes):
+        assert c["active_sum"] - total == active
+    _each_form(ctx, wins, 3, check)
+
+
+def test_stage_lanes_never_get_only_empty_windows(ctx):
+    """Empty windows join a lane that has tokens: behind the long one, before it, and
+    where a lane's first boundary lands past it."""
+    e = np.zeros(0, np.uint64)
+    heads = _loops([17, 100, 2047], seed=70)
+    for wins in (heads + [_long(), e], [_long()] + [e] * 5, [e] * 3 + [_long()] + heads + [e] * 3,
+                 [heads[0][:5], heads[0][:3], heads[2], heads[0][:1], heads[1], _long(), e]):
+        _each_form(ctx, wins, 3)
+        stats = ctx.graph_stats()
+    assert stats["captures"] >= 8 and stats["replays"] >= 16  # none of them fell back to host-driven lanes
+
+
+def test_stage_lane_graph_replays(ctx):
+    """Three lanes as branches of one graph: replays on tokens rewritten in place,
+    on other window boundaries of the same shape, with eager work in between."""
+    import torch
+    ctx.set_lanes(3)
+    lens_a, lens_b = [70100, 100, 66000, 4200, 69000, 1200], [100, 70100, 4200, 66000, 1200, 69000]
+    a, b = _loops(lens_a, seed=80), _loops(lens_b, seed=90)
+    dev, off_a = _pack(a)
+    _, off_b = _pack(b)
+    refs = [_refs(w, 4) for w in (a, b)]
+    eager = _refs(a[3:4], 4)[0]
+    for rep, which in enumerate((0, 0, 1, 0, 1, 1)):
+        dev.copy_(torch.from_numpy(np.concatenate((a, b)[which]).view(np.int64)))
+        _check(ctx.analyze_batch_dev(dev, (off_a, off_b)[which], 4), refs[which], rep)
+        rows = ctx.analyze(a[3], 4)
+        assert np.array_equal(np.stack([rows[f] for f in rows.dtype.names], 1).astype(np.int64), eager)
+        torch.zeros(1 << 20, device="cuda").add_(1)
+    assert ctx.graph_stats() == {"captures": 1, "replays": 5}
+    c = _loops([66000, 300, 70000, 20], seed=100)
+    dev_c, off_c = _pack(c)
+    _check(ctx.analyze_batch_dev(dev_c, off_c, 4), _refs(c, 4), "another shape")
+    assert ctx.graph_stats()["captures"] == 2
+
+
+def test_stage_batch_of_the_batched_workload(ctx):
+    """Windows of the batched workload stage by stage: beside a long one, and without
+    it while a kernel is timed."""
+    wins, m = synth.config3(num_windows=40)
+    wins = [w.astype(np.uint64) for w in wins]
+    _each_form(ctx, wins[:20] + [_long()] + wins[20:], m)
+    ctx.profile_kernel(1)
+    _each_form(ctx, wins, m, forms=FORMS[:3])
+    assert ctx.kernel_profile()["launches"] > 0
+    ctx.profile_kernel(0)
+
+
+def test_stage_batch_needing_many_selection_rounds(ctx):
+    """Block families need more greedy rounds than a sync-free run enqueues (windows
+    past the per-window greedy's 2^17 tokens go through the rounds): such a run, or such
+    a lane, is finished host-driven."""
+    blocks = []
+    for k in range(1, 60):
+        blocks += [0] * k + [1]
+    blocks = np.array(blocks, dtype=np.uint64)
+    wins = [blocks, _long(3, 140000), synth.config0()[0].astype(np.uint64), _long(4, 132000), blocks]
+    _each_form(ctx, wins, 1)
