@@ -219,13 +219,19 @@ def measured_traffic(workload):
     return None
 
 
-def batch_roofline(path, workload):
-    """The timed step is the one-workgroup analyses and little else: their
-    roof is the whole step's."""
-    out = dict(path, kernel="k_window_mid (windows of up to 32768 tokens, two to a compute unit) + k_window_rest "
-                            "(the longer ones): every stage of a window by one workgroup",
-               traffic=measured_traffic(workload),
-               traffic_unit="bytes per step (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)")
+def batch_roofline(sec, workload, copy_gbs=None):
+    """The timed step is the one-workgroup analyses and little else: the bytes
+    that they move (the byte model of path_roofline is the method's, stage by
+    stage, of which they keep much in LDS) over the step's time."""
+    moved = measured_traffic(workload)
+    rate = moved / sec / 1e9 if moved else None
+    out = {"bound": "latency", "achieved": rate, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": rate / HBM_PEAK_GBS if moved else None,
+           "kernel": "k_window_mid (windows of up to 32768 tokens, two to a compute unit) + k_window_rest "
+                     "(the longer ones): every stage of a window by one workgroup",
+           "traffic": moved, "traffic_unit": "bytes per step (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)"}
+    if copy_gbs:
+        out["achievable_copy_GBps"] = copy_gbs
     return out
 
 
@@ -460,7 +466,7 @@ def main():
                                "lanes": args.lanes},
                     "counters": ctx.counters(), "rows": int(res[1][-1]), "tuned": tuned, "graph": ctx.graph_stats()})
         out["path_roofline"] = path_roofline(out["counters"], total, 8, res[0], sec, copy_gbs)
-        out["roofline"] = batch_roofline(out["path_roofline"], "config3")
+        out["roofline"] = batch_roofline(sec, "config3", copy_gbs)
         if not args.profile_steps and not args.no_extras:
             # the stage-by-stage kernels on the same batch, their sort family
             # timed with events (one stream: nothing else runs inside a pair)

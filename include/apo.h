@@ -151,8 +151,9 @@ int apo_analyze_batch_dev(apo_ctx *ctx, const uint64_t *d_tokens, const uint64_t
                           uint32_t num_windows, uint32_t min_len, apo_candidate *d_out,
                           uint64_t out_cap, uint64_t *h_out_offsets, void *hip_stream);
 
-/* Batches that go stage by stage (a window of more than 2^16 tokens, or the
- * per-window selection off) are split into `lanes` (1..4, default 3) groups of
+/* Batches that go stage by stage (a window of more than 2^16 tokens, the
+ * per-window selection off, or no device memory for one workspace that holds the
+ * batch) are split into `lanes` (1..4, default 3) groups of
  * consecutive windows with about equal token counts, analysed concurrently on
  * separate streams and workspaces (lane 0 uses the caller's stream): as branches
  * of one captured graph, or, with graphs off or a kernel being timed, each lane

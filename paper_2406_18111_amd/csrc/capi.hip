@@ -289,14 +289,14 @@ static int run_ctx(apo_ctx *c, const void *d_tok, int bits, uint32_t n, uint32_t
   return map_rc(rc);
 }
 
-// Whether a lone window of n tokens is analysed by one workgroup.  Below the limit
-// windows that settle in a few rounds are better off there (28000 tokens, there and
-// stage by stage: a loop with 5 % substitutions 590 and 700 us, a nested loop 752
-// and 761, random symbols 262 and 272), at 32768 the loop still is (658 and 720; the
-// others 852 and 752, 300 and 291); those that keep most suffixes to the last round
-// are not from some 20000 tokens on (a loop without substitutions 922 and 822, half the
-// window one run 922 and 928; at 32768 1426 and 945, 1479 and 1035).  Kernel
-// timing and the injected errors are those of the stage-by-stage analysis.
+// Whether a lone window of n tokens is analysed by one workgroup.  Up to the limit
+// most windows are better off there (28000 tokens, there and stage by stage: a loop
+// with 5 % substitutions 630 and 690 us, a nested loop 745 and 745, random
+// tokens 390 and 460, four symbols 450 and 550; 32768: 730 and 710, 840 and 735, 430 and
+// 505, 530 and 575).  Windows that keep their suffixes grouped are not, from some 20000
+// tokens on (32768: a loop without substitutions 1390 and 895 us, half of the window one run 1230
+// and 1060), but take no longer than they did before there was that form (1430, 1770).
+// Kernel timing and the injected errors are those of the stage-by-stage analysis.
 static_assert(kWinSelSingle < kFusedLongMax, "16 bits hold their ranks");
 static bool fused_one(const apo_ctx *c, uint32_t n) {
   return n <= kWinSelSingle && c->win_greedy && c->ws.ktag == KT_NONE && c->ws.fail_after < 0;

@@ -1828,7 +1828,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   }
   stamp(2);
 
-  // ---- LCP: Kasai's walk as in k_window, over the token ranks; the next
+  // ---- LCP: Kasai's walk as in window_short, over the token ranks; the next
   // position's predecessor is read ahead (two dependent reads a position)
   load_lds(gtxt);
   {
@@ -1876,7 +1876,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   __syncthreads();
   stamp(3);
 
-  // ---- candidates, as in k_window
+  // ---- candidates, as in window_short
   for (uint32_t b = tid; b < (n + 7) / 8; b += NT) min1[b] = (uint16_t)min8(lcp + 8 * b);
   __syncthreads();
   for (uint32_t b = tid; b < (n + 63) / 64; b += NT) min2[b] = (uint16_t)min8(min1 + 8 * b);
@@ -2039,7 +2039,7 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
   __syncthreads();
   stamp(5);
 
-  // ---- greedy selection, as in k_window; the survivors' intervals and numbers
+  // ---- greedy selection, as in window_short; the survivors' intervals and numbers
   // go to LDS
   {
     uint32_t *const item = reinterpret_cast<uint32_t *>(big), *const num = item + NT;
