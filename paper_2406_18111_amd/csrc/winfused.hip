@@ -1410,7 +1410,9 @@ __device__ __forceinline__ void window_long(const LongArgs &la, LongLds<CAP> &L,
     // More distinct tokens than the table takes: positions sorted by token, a
     // radix pass for each of the four highest bytes in which the tokens differ
     // (then for all of them, should that not have put them in order), ranks
-    // counted over the sorted positions.
+    // counted over the sorted positions.  A lone window's host tokens are read from
+    // pinned memory in every pass (32768 distinct ones: the call 510 us, from the device 440,
+    // stage by stage 620).
     auto token = [=](uint32_t j) {
       return a.bits == 64 ? static_cast<const uint64_t *>(a.tok)[tb + j] : (uint64_t) static_cast<const uint32_t *>(a.tok)[tb + j];
     };
